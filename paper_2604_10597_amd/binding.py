@@ -1,8 +1,10 @@
-"""ctypes binding of libcorey.so: argument marshalling only.
+"""Binding of libcorey.so: argument marshalling only.
 
 Functions carry the names of the C entry points (include/corey.h).  Device buffers are torch tensors
 (torch is used for GPU memory and streams, nothing else); every step of the path runs in the library's
-HIP kernels.  There is no fallback: if the library is missing or fails to load, calls raise.
+HIP kernels.  Calls on tensors go through the extension `_native` (csrc/corey_torch.cpp), which checks and converts their
+arguments in native code; the host functions and the raw C ABI (`lib()`) through ctypes.  There is no fallback: if the
+library or the extension is missing or fails to load, calls raise.
 """
 from __future__ import annotations
 
@@ -106,6 +108,20 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_ext = None
+
+
+def _native():
+    """The torch extension, on the library that lib() loads; raises if either is not there."""
+    global _ext
+    if _ext is None:
+        lib()
+        from . import _native as ext      # built in-tree by build.py
+        ext.attach(LIB_PATH, CoreyError, DeferredRoute)
+        _ext = ext
+    return _ext
+
+
 def _check(code: int):
     if code != 0:
         raise CoreyError(code, lib().corey_last_error().decode())
@@ -129,17 +145,6 @@ def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
-def _dev(t, name):
-    if t is not None and (not t.is_cuda or not t.is_contiguous()):
-        raise ValueError(f"{name} must be a contiguous GPU tensor")
-
-
-def _want(t, name, dtype, shape):
-    """Optional tensor `t` must have this dtype and shape (the library reads raw memory and cannot check either)."""
-    if t is not None and (t.dtype != dtype or tuple(t.shape) != tuple(shape)):
-        raise TypeError(f"{name} must be {dtype} of shape {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
-
-
 def policy_default() -> Policy:
     p = Policy()
     _check(lib().corey_policy_default(ctypes.byref(p)))
@@ -158,23 +163,7 @@ def selective_state_update(state: torch.Tensor, x: torch.Tensor, delta: torch.Te
                            Ct: torch.Tensor, Dv: torch.Tensor | None = None, z: torch.Tensor | None = None,
                            delta_bias: torch.Tensor | None = None, delta_softplus: bool = True, y: torch.Tensor | None = None):
     """One decode step: state float32 [B, D, N] is updated in place; x, delta, z [B, D]; Bt, Ct [B, N]; returns y [B, D]."""
-    for name, t in (("state", state), ("x", x), ("delta", delta), ("A", A), ("Bt", Bt), ("Ct", Ct), ("Dv", Dv), ("z", z),
-                    ("delta_bias", delta_bias), ("y", y)):
-        _dev(t, name)
-    B, D, N = state.shape
-    if state.dtype != torch.float32 or A.dtype != torch.float32 or A.shape != (D, N):
-        raise TypeError("state [B, D, N] and A [D, N] must be float32")
-    for name, t, shape in (("x", x, (B, D)), ("delta", delta, (B, D)), ("z", z, (B, D)), ("Bt", Bt, (B, N)), ("Ct", Ct, (B, N))):
-        if t is not None and (tuple(t.shape) != shape or t.dtype != x.dtype):
-            raise TypeError(f"{name} must be {shape} in the dtype of x")
-    for name, t in (("Dv", Dv), ("delta_bias", delta_bias)):
-        if t is not None and (t.dtype != torch.float32 or tuple(t.shape) != (D,)):
-            raise TypeError(f"{name} must be float32 [D]")
-    if y is None:
-        y = torch.empty_like(x)
-    _check(lib().selective_state_update(_ptr(state), _ptr(x), _ptr(delta), _ptr(A), _ptr(Bt), _ptr(Ct), _ptr(Dv), _ptr(z),
-                                        _ptr(delta_bias), 1 if delta_softplus else 0, _ptr(y), _dtype_code(x), B, D, N, _stream()))
-    return y
+    return (_ext or _native()).selective_state_update(state, x, delta, A, Bt, Ct, Dv, z, delta_bias, delta_softplus, y)
 
 
 HANDOFF_BYTES = 1024 * 16 + 16 * 4096 * 4      # COREY_HANDOFF_BYTES: partial ranges + partial histograms
@@ -190,24 +179,7 @@ def causal_conv1d_silu_fwd(x: torch.Tensor, weight: torch.Tensor, bias: torch.Te
     corey_entropy_hist / corey_route_device on this u, which then skip their range sweep.  pattern_table: uint8 GPU
     tensor of corey_pattern_table_workspace() bytes; the kernel then also fills the bit-pattern table of u for
     corey_entropy_hist_from_table."""
-    for name, t in (("x", x), ("weight", weight), ("bias", bias), ("state_in", state_in), ("u", u), ("range_parts", range_parts),
-                    ("pattern_table", pattern_table)):
-        _dev(t, name)
-    B, D, L = x.shape
-    W = weight.shape[1]
-    if weight.shape[0] != D or weight.dtype != torch.float32 or (bias is not None and bias.dtype != torch.float32):
-        raise TypeError("weight [D, W] and bias [D] must be float32")
-    if u is None:
-        u = torch.empty_like(x)
-    state_out = torch.empty((B, D, W - 1), dtype=x.dtype, device=x.device) if want_state else None
-    if range_parts is None:
-        range_parts = torch.empty(HANDOFF_BYTES, dtype=torch.uint8, device=x.device)
-    elif range_parts.numel() < HANDOFF_BYTES or range_parts.dtype != torch.uint8:
-        raise TypeError(f"range_parts must be a uint8 tensor of {HANDOFF_BYTES} bytes")
-    _check(lib().causal_conv1d_silu_fwd(_ptr(x), _ptr(weight), _ptr(bias), _ptr(state_in), _ptr(u), _ptr(state_out),
-                                        _ptr(range_parts), _ptr(pattern_table), 0 if pattern_table is None else pattern_table.numel(),
-                                        _dtype_code(x), B, D, L, W, _stream()))
-    return u, state_out, range_parts
+    return (_ext or _native()).causal_conv1d_silu_fwd(x, weight, bias, state_in, u, want_state, range_parts, pattern_table)
 
 
 def corey_entropy_hist(x: torch.Tensor, K: int, eps: float = 1e-8, stride: int = 1, seqlens: torch.Tensor | None = None,
@@ -215,68 +187,25 @@ def corey_entropy_hist(x: torch.Tensor, K: int, eps: float = 1e-8, stride: int =
                        range_parts: torch.Tensor | None = None):
     """x: [B, D, L] GPU tensor (float32 or bfloat16).  Returns dict(counts, H, r, range) of GPU tensors;
     nothing is copied to the host and the call does not synchronise."""
-    _dev(x, "x"), _dev(seqlens, "seqlens")
-    if x.dim() != 3:
-        raise ValueError("x must be [B, D, L]")
-    B, D, L = x.shape
-    nh = B if seqlens is not None else 1
-    _want(seqlens, "seqlens", torch.int32, (B,))
-    if out is None:
-        out = dict(counts=torch.empty((nh, K), dtype=torch.int32, device=x.device),   # uint32 bit patterns
-                   H=torch.empty(nh, dtype=torch.float64, device=x.device),
-                   r=torch.empty(nh, dtype=torch.float64, device=x.device),
-                   range=torch.empty((nh, 2), dtype=torch.float32, device=x.device))
-    need = corey_entropy_hist_workspace(B, K)
-    if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
-    _check(lib().corey_entropy_hist(_ptr(x), _dtype_code(x), B, D, L, _ptr(seqlens), K, eps, stride, block,
-                                    _ptr(out["counts"]), _ptr(out["H"]), _ptr(out["r"]), _ptr(out.get("range")),
-                                    _ptr(range_parts), _ptr(workspace), workspace.numel(), _stream()))
-    out["workspace"] = workspace
-    return out
+    return (_ext or _native()).corey_entropy_hist(x, K, eps, stride, seqlens, out, workspace, block, range_parts)
 
 
 def corey_pattern_table_workspace() -> int:
     return int(lib().corey_pattern_table_workspace())
 
 
-def _table_out(K, device, policy, out):
-    if out is None:
-        out = dict(counts=torch.empty((1, K), dtype=torch.int32, device=device), H=torch.empty(1, dtype=torch.float64, device=device),
-                   r=torch.empty(1, dtype=torch.float64, device=device), range=torch.empty((1, 2), dtype=torch.float32, device=device))
-    if policy is not None and out.get("chunks") is None:
-        out["chunks"] = torch.empty(1, dtype=torch.int32, device=device)
-    return out
-
-
 def corey_entropy_hist_onesweep(x: torch.Tensor, K: int, eps: float = 1e-8, policy: Policy | None = None, out: dict | None = None,
                                 table_ws: torch.Tensor | None = None):
     """The statistic of a bfloat16 / float16 tensor from one pass over it (bit-pattern table).  Returns the dict of
     corey_entropy_hist (plus `chunks` when a policy is given, as corey_route_device) and `table_ws`."""
-    _dev(x, "x"), _dev(table_ws, "table_ws")
-    if x.dim() != 3:
-        raise ValueError("x must be [B, D, L]")
-    B, D, L = x.shape
-    out = _table_out(K, x.device, policy, out)
-    if table_ws is None:
-        table_ws = torch.empty(corey_pattern_table_workspace(), dtype=torch.uint8, device=x.device)
-    _check(lib().corey_entropy_hist_onesweep(_ptr(x), _dtype_code(x), B, D, L, K, eps, ctypes.byref(policy) if policy is not None else None,
-                                             _ptr(out.get("chunks")) if policy is not None else None, _ptr(out["counts"]), _ptr(out["H"]),
-                                             _ptr(out["r"]), _ptr(out.get("range")), _ptr(table_ws), table_ws.numel(), _stream()))
-    out["table_ws"] = table_ws
-    return out
+    return (_ext or _native()).corey_entropy_hist_onesweep(x, K, eps, policy, out, table_ws)
 
 
 def corey_entropy_hist_from_table(table_ws: torch.Tensor, dtype: torch.dtype, L: int, K: int, eps: float = 1e-8,
                                   policy: Policy | None = None, out: dict | None = None):
     """The statistic of the tensor whose producer (causal_conv1d_silu_fwd with pattern_table=table_ws) filled the table."""
-    _dev(table_ws, "table_ws")
-    out = _table_out(K, table_ws.device, policy, out)
     code = {torch.bfloat16: COREY_BF16, torch.float16: COREY_F16, torch.float32: COREY_F32}[dtype]
-    _check(lib().corey_entropy_hist_from_table(code, L, K, eps, ctypes.byref(policy) if policy is not None else None,
-                                               _ptr(out.get("chunks")) if policy is not None else None, _ptr(out["counts"]), _ptr(out["H"]),
-                                               _ptr(out["r"]), _ptr(out.get("range")), _ptr(table_ws), table_ws.numel(), _stream()))
-    return out
+    return (_ext or _native()).corey_entropy_hist_from_table(table_ws, code, L, K, eps, policy, out)
 
 
 STATIC_SCRATCH_BYTES = 1 << 20     # COREY_STATIC_SCRATCH_BYTES
@@ -286,20 +215,7 @@ def corey_entropy_hist_static(x: torch.Tensor, K: int, out: dict, eps: float = 1
                               seqlens: torch.Tensor | None = None, block: int = 1, range_parts: torch.Tensor | None = None):
     """corey_entropy_hist on the library's built-in scratch buffer: nothing is allocated, here or in the library, so
     `out` (dict(counts, H, r[, range]) of GPU tensors, as corey_entropy_hist returns) must be given."""
-    _dev(x, "x"), _dev(seqlens, "seqlens")
-    if x.dim() != 3:
-        raise ValueError("x must be [B, D, L]")
-    B, D, L = x.shape
-    nh = B if seqlens is not None else 1
-    _want(seqlens, "seqlens", torch.int32, (B,))
-    _want(out["counts"], "counts", torch.int32, (nh, K))
-    _want(out["H"], "H", torch.float64, (nh,))
-    _want(out["r"], "r", torch.float64, (nh,))
-    _want(out.get("range"), "range", torch.float32, (nh, 2))
-    _check(lib().corey_entropy_hist_static(_ptr(x), _dtype_code(x), B, D, L, _ptr(seqlens), K, eps, stride, block,
-                                           _ptr(out["counts"]), _ptr(out["H"]), _ptr(out["r"]), _ptr(out.get("range")),
-                                           _ptr(range_parts), _stream()))
-    return out
+    return (_ext or _native()).corey_entropy_hist_static(x, K, out, eps, stride, seqlens, block, range_parts)
 
 
 def corey_ema_update(lam: float, state: float, H: float) -> float:
@@ -317,31 +233,8 @@ def corey_route_device(x: torch.Tensor, K: int, policy: Policy | None = None, ep
     (int32 GPU tensor [nh], directly usable as `chunks_dev` of selective_scan_fwd); no synchronisation.
     ema_state: float64 GPU tensor [nh] (NaN = no estimate yet), updated in place; chunk_calls: int32 GPU tensor
     [COREY_CHUNK_SLOTS] of counters the caller clears."""
-    _dev(ema_state, "ema_state"), _dev(chunk_calls, "chunk_calls")
-    _dev(x, "x"), _dev(seqlens, "seqlens")
-    if x.dim() != 3:
-        raise ValueError("x must be [B, D, L]")
-    B, D, L = x.shape
-    nh = B if seqlens is not None else 1
-    _want(seqlens, "seqlens", torch.int32, (B,))
-    _want(ema_state, "ema_state", torch.float64, (nh,))
-    _want(chunk_calls, "chunk_calls", torch.int32, (CHUNK_SLOTS,))
-    p = policy if policy is not None else policy_default()
-    if out is None:
-        out = dict(counts=torch.empty((nh, K), dtype=torch.int32, device=x.device),
-                   H=torch.empty(nh, dtype=torch.float64, device=x.device),
-                   r=torch.empty(nh, dtype=torch.float64, device=x.device),
-                   range=torch.empty((nh, 2), dtype=torch.float32, device=x.device),
-                   chunks=torch.empty(nh, dtype=torch.int32, device=x.device))
-    if workspace is None:
-        workspace = out.get("workspace")
-    if workspace is None:
-        workspace = torch.empty(max(corey_entropy_hist_workspace(B, K), 256), dtype=torch.uint8, device=x.device)
-    _check(lib().corey_route_device(_ptr(x), _dtype_code(x), B, D, L, _ptr(seqlens), K, eps, stride, block, ctypes.byref(p),
-                                    float(ema_lambda), _ptr(ema_state), _ptr(chunk_calls), _ptr(out["counts"]), _ptr(out["H"]), _ptr(out["r"]), _ptr(out.get("range")),
-                                    _ptr(range_parts), _ptr(out["chunks"]), _ptr(workspace), workspace.numel(), _stream()))
-    out["workspace"] = workspace
-    return out
+    return (_ext or _native()).corey_route_device(x, K, policy, eps, stride, block, seqlens, out, workspace, chunk_calls, range_parts,
+                                                  ema_lambda, ema_state)
 
 
 def corey_route_device_deferred(x: torch.Tensor, K: int, policy: Policy | None = None, eps: float = 1e-8, stride: int = 1, block: int = 1,
@@ -349,32 +242,8 @@ def corey_route_device_deferred(x: torch.Tensor, K: int, policy: Policy | None =
                                 chunk_calls: torch.Tensor | None = None, range_parts: torch.Tensor | None = None):
     """The sweeps of corey_route_device without its reduction: returns the same dict (its tensors are written by the
     selective_scan_fwd_routed call that follows) with `route`, the ticket that call takes."""
-    _dev(chunk_calls, "chunk_calls"), _dev(x, "x"), _dev(seqlens, "seqlens")
-    if x.dim() != 3:
-        raise ValueError("x must be [B, D, L]")
-    B, D, L = x.shape
-    nh = B if seqlens is not None else 1
-    _want(seqlens, "seqlens", torch.int32, (B,))
-    _want(chunk_calls, "chunk_calls", torch.int32, (CHUNK_SLOTS,))
-    p = policy if policy is not None else policy_default()
-    if out is None:
-        out = dict(counts=torch.empty((nh, K), dtype=torch.int32, device=x.device),
-                   H=torch.empty(nh, dtype=torch.float64, device=x.device),
-                   r=torch.empty(nh, dtype=torch.float64, device=x.device),
-                   range=torch.empty((nh, 2), dtype=torch.float32, device=x.device),
-                   chunks=torch.empty(nh, dtype=torch.int32, device=x.device))
-    if workspace is None:
-        workspace = out.get("workspace")
-    if workspace is None:
-        workspace = torch.empty(max(corey_entropy_hist_workspace(B, K), 256), dtype=torch.uint8, device=x.device)
-    route = out.get("route") or DeferredRoute()
-    _check(lib().corey_route_device_deferred(_ptr(x), _dtype_code(x), B, D, L, _ptr(seqlens), K, eps, stride, block, ctypes.byref(p),
-                                             _ptr(chunk_calls), _ptr(out["counts"]), _ptr(out["H"]), _ptr(out["r"]), _ptr(out.get("range")),
-                                             _ptr(range_parts), _ptr(out["chunks"]), _ptr(workspace), workspace.numel(),
-                                             ctypes.byref(route), _stream()))
-    out["workspace"] = workspace
-    out["route"] = route
-    return out
+    return (_ext or _native()).corey_route_device_deferred(x, K, policy, eps, stride, block, seqlens, out, workspace, chunk_calls,
+                                                           range_parts)
 
 
 def corey_select_chunk(r: float, L: int, policy: Policy | None = None) -> int:
@@ -387,16 +256,7 @@ def corey_select_chunk(r: float, L: int, policy: Policy | None = None) -> int:
 def corey_select_chunk_device(r_dev: torch.Tensor, L: int, policy: Policy | None = None, seqlens: torch.Tensor | None = None,
                               out: torch.Tensor | None = None) -> torch.Tensor:
     """r_dev: float64 GPU tensor [nh].  Returns an int32 GPU tensor [nh] of chunks (no synchronisation)."""
-    _dev(r_dev, "r_dev"), _dev(seqlens, "seqlens")
-    if r_dev.dtype != torch.float64:
-        raise TypeError("r_dev must be float64")
-    p = policy if policy is not None else policy_default()
-    nh = r_dev.numel()
-    _want(seqlens, "seqlens", torch.int32, (nh,))
-    if out is None:
-        out = torch.empty(nh, dtype=torch.int32, device=r_dev.device)
-    _check(lib().corey_select_chunk_device(_ptr(r_dev), _ptr(seqlens), int(L), nh, ctypes.byref(p), _ptr(out), _stream()))
-    return out
+    return (_ext or _native()).corey_select_chunk_device(r_dev, L, policy, seqlens, out)
 
 
 def selective_scan_fwd_plan(B: int, D: int, N: int, chunk: int) -> int:
@@ -429,46 +289,5 @@ def selective_scan_fwd(u, delta, A, Bm, Cm, Dv=None, z=None, delta_bias=None, de
     `chunks_dev` of one entry for a batch of several sequences is passed with COREY_SCAN_ONE_CHUNK.
     `whole_rows`: COREY_SCAN_WHOLE_ROWS, i.e. never share a channel's states between two rows of lanes.
     `route`: the ticket of corey_route_device_deferred; the call is then selective_scan_fwd_routed (no chunks_dev)."""
-    for name, t in (("u", u), ("delta", delta), ("A", A), ("Bm", Bm), ("Cm", Cm), ("Dv", Dv), ("z", z),
-                    ("delta_bias", delta_bias), ("h0", h0), ("seqlens", seqlens), ("chunks_dev", chunks_dev),
-                    ("y", y), ("last_state", last_state), ("workspace", workspace)):
-        _dev(t, name)
-    if u.dim() != 3 or A.dim() != 2:
-        raise ValueError("u must be [B, D, L] and A [D, N]")
-    B, D, L = u.shape
-    N = A.shape[1]
-    if A.shape != (D, N) or Bm.shape != (B, N, L) or Cm.shape != (B, N, L) or delta.shape != u.shape:
-        raise ValueError("inconsistent shapes")
-    for name, t in (("delta", delta), ("z", z), ("y", y)):
-        _want(t, name, u.dtype, (B, D, L))
-    for name, t in (("Bm", Bm), ("Cm", Cm)):
-        _want(t, name, u.dtype, (B, N, L))
-    _want(A, "A", torch.float32, (D, N))
-    for name, t in (("Dv", Dv), ("delta_bias", delta_bias)):
-        _want(t, name, torch.float32, (D,))
-    for name, t in (("h0", h0), ("last_state", last_state)):
-        _want(t, name, torch.float32, (B, D, N))
-    _want(seqlens, "seqlens", torch.int32, (B,))
-    # a single routed chunk (the whole-tensor statistic of a batch) applies to every sequence
-    one_chunk = chunks_dev is not None and B > 1 and tuple(chunks_dev.shape) == (1,)
-    _want(chunks_dev, "chunks_dev", torch.int32, (1,) if one_chunk else (B,))
-    if y is None:
-        y = torch.empty_like(u)
-    if last_state is None:
-        last_state = torch.empty((B, D, N), dtype=torch.float32, device=u.device)
-    if workspace is None:
-        workspace = torch.empty(selective_scan_fwd_workspace(B, N, L), dtype=torch.uint8, device=u.device)
-    flags = (COREY_SCAN_GENERAL_A if general_a else 0) | (COREY_SCAN_WHOLE_ROWS if whole_rows else 0)
-    if route is not None:
-        if chunks_dev is not None:
-            raise ValueError("a route brings its own chunks")
-        _check(lib().selective_scan_fwd_routed(_ptr(u), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dv), _ptr(z),
-                                               _ptr(delta_bias), 1 if delta_softplus else 0, _ptr(h0), _ptr(seqlens), int(chunk),
-                                               ctypes.byref(route), _ptr(y), _ptr(last_state), _dtype_code(u), B, D, N, L,
-                                               flags, _ptr(workspace), workspace.numel(), _stream()))
-        return y, last_state
-    _check(lib().selective_scan_fwd(_ptr(u), _ptr(delta), _ptr(A), _ptr(Bm), _ptr(Cm), _ptr(Dv), _ptr(z),
-                                    _ptr(delta_bias), 1 if delta_softplus else 0, _ptr(h0), _ptr(seqlens), int(chunk),
-                                    _ptr(chunks_dev), _ptr(y), _ptr(last_state), _dtype_code(u), B, D, N, L,
-                                    flags | (COREY_SCAN_ONE_CHUNK if one_chunk else 0), _ptr(workspace), workspace.numel(), _stream()))
-    return y, last_state
+    return (_ext or _native()).selective_scan_fwd(u, delta, A, Bm, Cm, Dv, z, delta_bias, delta_softplus, h0, seqlens, chunk, chunks_dev, y,
+                                                  last_state, workspace, general_a, route, whole_rows)

@@ -1,8 +1,9 @@
-"""Compile libcorey.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Compile libcorey.so for gfx950 and its torch extension (hipcc cross-compiles without a GPU)."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -10,6 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcorey.so")
+NATIVE = os.path.join(HERE, "_native.so")          # Python extension: marshals torch tensors into libcorey
 # one translation unit per storage type of the scan: they compile side by side
 SOURCES = ["corey_host.cpp", "corey_entropy.hip", "corey_table.hip", "corey_conv.hip", "corey_decode.hip", "corey_scan.hip", "corey_scan_bf16.hip", "corey_scan_f16.hip",
            "corey_scan_f32.hip"]
@@ -29,8 +31,24 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def build_native(verbose: bool = False) -> str:
+    """The torch extension: host code only, by the host compiler against torch's headers."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), os.path.join(ROOT, "include"),
+           sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+           *(a for i in inc[:2] for a in ("-isystem", i)), *(f"-I{i}" for i in inc[2:]), "-isystem", "/opt/rocm/include",
+           os.path.join(CSRC, "corey_torch.cpp"), f"-L{os.path.join(t, 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip",
+           "-ltorch_python", "-o", NATIVE]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return NATIVE
+
+
 def build_lib(verbose: bool = False, extra: list[str] | None = None, jobs: int = 6) -> str:
-    """Always recompiles; returns the path of the shared library."""
+    """Always recompiles the library and the torch extension; returns the path of the library."""
     cc = hipcc()
     inc = [f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
     with tempfile.TemporaryDirectory(prefix="corey_build_") as tmp:
@@ -43,7 +61,9 @@ def build_lib(verbose: bool = False, extra: list[str] | None = None, jobs: int =
             return obj
 
         with ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
+            native = pool.submit(build_native, verbose)
             objs = list(pool.map(compile_one, SOURCES))
+            native.result()
         link = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-Wno-unused-command-line-argument", *objs,
                 "-o", LIB]
         if verbose:
