@@ -40,30 +40,9 @@ namespace corey_scan {
 using corey::bf16_to_f32;
 using corey::f32_to_bf16;
 
-#ifndef COREY_BLOCK
-#define COREY_BLOCK 256
-#endif
-constexpr int kBlock = COREY_BLOCK;   // lanes per workgroup: four waves, one per SIMD of a compute unit
+constexpr int kBlock = 256;   // lanes per workgroup: four waves, one per SIMD of a compute unit
 constexpr int kWaves = kBlock / 64;
-// Build-time tuning knobs (defaults are the measured best on MI355X).
-#ifndef COREY_STAGE_FLOATS_K16
-#define COREY_STAGE_FLOATS_K16 2048   // fp32 values of B (and of C) per LDS staging buffer (two buffers), 16 steps per lane
-#endif
-#ifndef COREY_STAGE_FLOATS_K8
-#define COREY_STAGE_FLOATS_K8 2048    // the same for 8 or 4 steps per lane
-#endif
-#ifndef COREY_WAVES_K16
-#define COREY_WAVES_K16 4             // waves per SIMD the register allocation of the 16-step kernels leaves room for
-#endif
-#ifndef COREY_WAVES_K8
-#define COREY_WAVES_K8 4              // the same for 8 or 4 steps per lane (the spare registers hold the tile fetched ahead)
-#endif
-#ifndef COREY_CPREFETCH_MAXK
-#define COREY_CPREFETCH_MAXK 8        // geometries with at most this many steps per lane fetch C before the lane scan
-#endif
-#ifndef COREY_SPLIT_WAVES
-#define COREY_SPLIT_WAVES 1536        // a launch with at most this many waves splits the states of a row between two rows
-#endif
+constexpr int kStageFloats = 2048;    // fp32 values of B (and of C) per LDS staging buffer (two buffers)
 constexpr int kMaxGroup = 4;          // most states staged (and unrolled) per group
 constexpr int kPad = COREY_MAX_CHUNK; // the relaid-out time axis is padded to whole tiles
 constexpr float kLog2e = 1.4426950408889634f;
@@ -75,14 +54,25 @@ typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// Geometry of one (K, CHUNK) instantiation.
+// The tile a launch walks at a time: the chunk, or parts of a long one.  64 lanes of 16 steps are one wave; a row over two
+// waves would hand every state's sub-block products from wave to wave through LDS and a barrier (chunk 2048 on 8192 rows of
+// 4096 steps: 195 us with rows over two waves, 139 us in parts of 1024).  With more rows than the GPU holds waves the parts
+// are 512 steps: two rows share a wave's lane scan and its reads of B and C (the same layer: 135 us; 5120 rows of 16384 steps
+// 357 us in parts of 1024, 323 us in parts of 512 with the two kinds of rows below).
+constexpr int kMaxTile = 1024;
+constexpr int64_t kManyRows = 4096;   // four waves on each of the 1024 SIMDs
+__host__ __device__ inline int tile_of(int chunk, int64_t rows)
+{
+    const int most = rows > kManyRows ? 512 : kMaxTile;
+    return chunk < most ? chunk : most;
+}
+
+// Geometry of one (K, CHUNK) instantiation; CHUNK is the tile walked at a time.
 template <int K, int CHUNK> struct Geo {
-    static_assert(CHUNK >= K && CHUNK / K <= kBlock, "a tile row must fit one workgroup");
+    static_assert(CHUNK >= K && CHUNK / K <= 64, "a tile row must fit one wave");
     static constexpr int LPR = CHUNK / K;                       // lanes per row
-    static constexpr int SEG = LPR < 64 ? LPR : 64;             // lanes of a row inside one wave
-    static constexpr int WPR = LPR > 64 ? LPR / 64 : 1;         // waves per row
+    static constexpr int SEG = LPR;                             // lanes a scan runs over
     static constexpr int ROWS = kBlock / LPR;                   // rows per workgroup
-    static constexpr int kStageFloats = K < 16 ? COREY_STAGE_FLOATS_K8 : COREY_STAGE_FLOATS_K16;
     static constexpr int G = kStageFloats / CHUNK < 1 ? 1 : (kStageFloats / CHUNK > kMaxGroup ? kMaxGroup : kStageFloats / CHUNK);
     static_assert(kMaxGroup % G == 0, "the padded state count must be whole groups");
     static constexpr int STAGE = G * CHUNK;                     // floats per operand per staging buffer
@@ -99,6 +89,7 @@ template <int K, int CHUNK> struct Geo {
 // pure launches.  It runs on the host (known chunk) and on the device (chunk read from memory) with the same inputs.
 __host__ __device__ inline int64_t plan_d16(int64_t B, int64_t D, int chunk, int rows_cap)
 {
+    chunk = tile_of(chunk, B * D);
     if (chunk > 512) return D;                                   // a row of 8-step lanes would no longer fit one wave
     if (chunk < 128)                                             // 16-step rows would leave workgroup lanes idle here
         return (B * D * (chunk / 16) < 172032) ? 0 : D;
@@ -127,7 +118,7 @@ __host__ __device__ inline int plan_klo(int64_t B, int64_t D, int chunk, int64_t
 // TWO rows in the same workgroup, each with half of the states: twice the waves, each with half the per-state work and
 // all of the per-token work, and one exchange of partial y per tile through LDS.  The staging group must hold at least
 // one state of each half (tiles up to 1024 steps), and only the geometries such a launch can have are built.
-constexpr int64_t kSplitWaves = COREY_SPLIT_WAVES;
+constexpr int64_t kSplitWaves = 1536;
 template <int K, int CHUNK> constexpr bool split_exists()
 {
     return (K == 16 && CHUNK == 1024) || (K == 8 && CHUNK == 512) || (K == 4 && CHUNK >= 4 && CHUNK <= 256);
@@ -335,15 +326,99 @@ __device__ __forceinline__ float silu(float z)
     return z * __builtin_amdgcn_rcpf(1.f + fast_exp2(-z * kLog2e));
 }
 
+// ------------------------------------------------------------------------------------------- bursts
+// How a SIMD of gfx950 issues vector instructions decides the shape of this kernel.  Measured with register-only loops: a
+// plain fp32 instruction of a wave takes 2 cycles as long as ANOTHER wave of the SIMD has a plain instruction to issue beside
+// it (4.3 cycles for a wave on its own); an exponential takes 8 and a DPP instruction 4, and nothing issues beside them.  When
+// every wave mixes the kinds, some wave is nearly always at an exponential and the plain instructions of the others run at the
+// unpaired rate: a loop of the scan's own mix (83 plain, 12 DPP, 17 exponentials per state of a 16-step lane) takes 490
+// cycles per wave.  Gathered into bursts, and the bursts issued at raised wave priority so that a wave gets through
+// its burst before the others go on and the waves' plain stretches fall together, the same instructions take 355, against
+// 83 * 2 + 12 * 4.2 + 17 * 8.2 = 356 by the single rates.  Hence: transcendentals and DPP chains below are written as asm blocks
+// that raise the priority, run the burst and lower it again.
+#define COREY_BURST(body) "s_setprio 1\n\t" body "s_setprio 0"
+#define COREY_T(op, n) op " %" #n ", %" #n "\n\t"
+#define COREY_T4(op, a, b, c, d) COREY_T(op, a) COREY_T(op, b) COREY_T(op, c) COREY_T(op, d)
+#define COREY_T16(op) COREY_T4(op, 0, 1, 2, 3) COREY_T4(op, 4, 5, 6, 7) COREY_T4(op, 8, 9, 10, 11) COREY_T4(op, 12, 13, 14, 15)
+#define COREY_V4(v, i) "+v"(v[i]), "+v"(v[i + 1]), "+v"(v[i + 2]), "+v"(v[i + 3])
+#define COREY_V16(v) COREY_V4(v, 0), COREY_V4(v, 4), COREY_V4(v, 8), COREY_V4(v, 12)
+// (a result of the last transcendental may be read one wait state later: the s_setprio 0 is that wait state)
+#define COREY_BURST_FN(name, op)                                                                                             \
+    template <int K> __device__ __forceinline__ void name(float (&v)[K])                                                     \
+    {                                                                                                                        \
+        if constexpr (K == 16) asm volatile(COREY_BURST(COREY_T16(op)) : COREY_V16(v));                                      \
+        else if constexpr (K == 8)                                                                                           \
+            asm volatile(COREY_BURST(COREY_T4(op, 0, 1, 2, 3) COREY_T4(op, 4, 5, 6, 7)) : COREY_V4(v, 0), COREY_V4(v, 4));   \
+        else asm volatile(COREY_BURST(COREY_T4(op, 0, 1, 2, 3)) : COREY_V4(v, 0));                                           \
+        static_assert(K == 4 || K == 8 || K == 16, "steps per lane");                                                        \
+    }
+COREY_BURST_FN(exp2_burst, "v_exp_f32_e32")
+COREY_BURST_FN(log2_burst, "v_log_f32_e32")
+COREY_BURST_FN(rcp_burst, "v_rcp_f32_e32")
+// ... of K decays and the one over the lane's whole sub-block.  FIRST raises the priority and LAST lowers it (several states'
+// bursts one after another).
+template <int K, bool FIRST, bool LAST> __device__ __forceinline__ void decay_burst(float (&v)[K], float& p)
+{
+    static_assert(K == 4 || K == 8 || K == 16, "steps per lane");
+#define COREY_DECAYS(body, ...)                                                                              \
+    do {                                                                                                     \
+        if constexpr (FIRST && LAST) asm volatile("s_setprio 1\n\t" body "s_setprio 0" : __VA_ARGS__);       \
+        else if constexpr (FIRST) asm volatile("s_setprio 1\n\t" body "s_nop 0" : __VA_ARGS__);              \
+        else if constexpr (LAST) asm volatile(body "s_setprio 0" : __VA_ARGS__);                             \
+        else asm volatile(body "s_nop 0" : __VA_ARGS__);                                                     \
+    } while (0)
+    if constexpr (K == 16) COREY_DECAYS(COREY_T16("v_exp_f32_e32") COREY_T("v_exp_f32_e32", 16), COREY_V16(v), "+v"(p));
+    else if constexpr (K == 8)
+        COREY_DECAYS(COREY_T4("v_exp_f32_e32", 0, 1, 2, 3) COREY_T4("v_exp_f32_e32", 4, 5, 6, 7) COREY_T("v_exp_f32_e32", 8),
+                     COREY_V4(v, 0), COREY_V4(v, 4), "+v"(p));
+    else COREY_DECAYS(COREY_T4("v_exp_f32_e32", 0, 1, 2, 3) COREY_T("v_exp_f32_e32", 4), COREY_V4(v, 0), "+v"(p));
+#undef COREY_DECAYS
+}
+
+// softplus() and y *= silu(z) of a lane's K steps, stage by stage so that the transcendentals form bursts.
+template <int K> __device__ __forceinline__ void softplus_all(float (&x)[K])
+{
+    float w[K], fix[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) w[i] = -fabsf(x[i]) * kLog2e;
+    exp2_burst<K>(w);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        const float e = w[i];
+        w[i] = 1.f + e;
+        fix[i] = e - (w[i] - 1.f);
+        asm("v_max_f32_e32 %0, 0, %1" : "=v"(x[i]) : "v"(x[i]));
+    }
+    log2_burst<K>(w);
+#pragma unroll
+    for (int i = 0; i < K; ++i) x[i] += fmaf(w[i], kLn2, fix[i]);
+}
+
+template <typename T, int K> __device__ __forceinline__ void gate_all(const Raw<T, K>& z_raw, float (&y)[K])
+{
+    float z[K], s[K];
+    widen<T, K>(z_raw, z);
+#pragma unroll
+    for (int i = 0; i < K; ++i) s[i] = -z[i] * kLog2e;
+    exp2_burst<K>(s);
+#pragma unroll
+    for (int i = 0; i < K; ++i) s[i] = 1.f + s[i];
+    rcp_burst<K>(s);
+#pragma unroll
+    for (int i = 0; i < K; ++i) y[i] *= z[i] * s[i];
+}
+
 // ------------------------------------------------------------------------------------------- lane scan (DPP)
 // Inclusive scan, over the SEG consecutive lanes of a row inside one wave, of the per-lane affine maps
-// x -> P x + h (oldest lane first): a Hillis-Steele scan whose steps are single DPP instructions,
+// x -> P x + h (oldest lane first), and the fetch of the left neighbour's result: a Hillis-Steele scan whose steps are
+// single DPP instructions,
 //     h += h[lane - s] * P ;  P *= P[lane - s] ;
-// lanes without a source (DPP bound control off) keep their value, which is composing with the identity.
+// lanes without a source (DPP bound control off) keep their value, which is composing with the identity.  The last step
+// leaves P stale (only h is wanted afterwards).  `left` holds the state entering the row's first lane and leaves as the
+// state entering this lane's sub-block: the neighbour's h, unchanged in the first lane.
 // The instructions are written out because the hazard rules matter: a DPP source register needs two wait
 // states after the VALU write that produced it (inside a step pair: the other instruction plus s_nop 0), and
-// five after a VALU write of EXEC (s_nop 4 up front).  With NEED_P false the last step leaves P stale
-// (only h is wanted afterwards).
+// five after a VALU write of EXEC (s_setprio and s_nop 3 up front).
 #define COREY_DPP_H(ctrl) "v_fmac_f32_dpp %0, %0, %1 " ctrl " bank_mask:0xf\n\t"
 #define COREY_DPP_P(ctrl) "v_mul_f32_dpp %1, %1, %1 " ctrl " bank_mask:0xf\n\t"
 #define COREY_DPP_STEP(ctrl) COREY_DPP_H(ctrl) COREY_DPP_P(ctrl) "s_nop 0\n\t"
@@ -357,23 +432,37 @@ __device__ __forceinline__ float dpp_move(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
 
-template <int SEG, bool NEED_P>
-__device__ __forceinline__ void scan_inclusive(int jseg, float& P, float& h)
+// ... two of them at a time: each fills the other's wait states
+#define COREY_DPP2_H(ctrl) COREY_DPP_H(ctrl) "v_fmac_f32_dpp %3, %3, %4 " ctrl " bank_mask:0xf\n\t"
+#define COREY_DPP2_STEP(ctrl)                                                               \
+    COREY_DPP2_H(ctrl) COREY_DPP_P(ctrl) "v_mul_f32_dpp %4, %4, %4 " ctrl " bank_mask:0xf\n\t"
+#define COREY_ROW2_STEPS3                                                                   \
+    COREY_DPP2_STEP("row_shr:1 row_mask:0xf") COREY_DPP2_STEP("row_shr:2 row_mask:0xf")     \
+    COREY_DPP2_STEP("row_shr:4 row_mask:0xf")
+#define COREY_DPP2_LEFT(ctrl)                                                               \
+    "v_mov_b32_dpp %2, %0 " ctrl "\n\tv_mov_b32_dpp %5, %3 " ctrl "\n\t"
+
+template <int SEG>
+__device__ __forceinline__ void scan_segment(int jseg, float& P, float& h, float& left)
 {
     if constexpr (SEG == 64) {
-        if constexpr (NEED_P)
-            asm volatile("s_nop 4\n\t" COREY_ROW_STEPS3 COREY_DPP_STEP("row_shr:8 row_mask:0xf")
-                         COREY_DPP_STEP("row_bcast:15 row_mask:0xa") COREY_DPP_STEP("row_bcast:31 row_mask:0xc")
-                         : "+v"(h), "+v"(P));
-        else
-            asm volatile("s_nop 4\n\t" COREY_ROW_STEPS3 COREY_DPP_STEP("row_shr:8 row_mask:0xf")
-                         COREY_DPP_STEP("row_bcast:15 row_mask:0xa") COREY_DPP_H("row_bcast:31 row_mask:0xc") "s_nop 1\n\t"
-                         : "+v"(h), "+v"(P));
+        asm volatile(COREY_BURST("s_nop 3\n\t" COREY_ROW_STEPS3 COREY_DPP_STEP("row_shr:8 row_mask:0xf")
+                                 COREY_DPP_STEP("row_bcast:15 row_mask:0xa") COREY_DPP_H("row_bcast:31 row_mask:0xc") "s_nop 1\n\t"
+                                 "v_mov_b32_dpp %2, %0 wave_shr:1 row_mask:0xf bank_mask:0xf\n\t")
+                     : "+v"(h), "+v"(P), "+v"(left));
     } else if constexpr (SEG == 32) {
-        asm volatile("s_nop 4\n\t" COREY_ROW_STEPS3 COREY_DPP_STEP("row_shr:8 row_mask:0xf")
-                     COREY_DPP_H("row_bcast:15 row_mask:0xa") "s_nop 1\n\t" : "+v"(h), "+v"(P));
+        // DPP rows are 16 lanes: a shift by one inside every row leaves the rows' first lanes alone; the odd rows' first lanes
+        // (16, 48) take the last lane of the row before them first (row_bcast:15 on rows 1 and 3, limited by the bank mask to
+        // lanes 0..3 of the row, of which 1..3 are overwritten by the shift that follows)
+        asm volatile(COREY_BURST("s_nop 3\n\t" COREY_ROW_STEPS3 COREY_DPP_STEP("row_shr:8 row_mask:0xf")
+                                 COREY_DPP_H("row_bcast:15 row_mask:0xa") "s_nop 1\n\t"
+                                 "v_mov_b32_dpp %2, %0 row_bcast:15 row_mask:0xa bank_mask:0x1\n\t"
+                                 "v_mov_b32_dpp %2, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t")
+                     : "+v"(h), "+v"(P), "+v"(left));
     } else if constexpr (SEG == 16) {
-        asm volatile("s_nop 4\n\t" COREY_ROW_STEPS3 COREY_DPP_H("row_shr:8 row_mask:0xf") "s_nop 1\n\t" : "+v"(h), "+v"(P));
+        asm volatile(COREY_BURST("s_nop 3\n\t" COREY_ROW_STEPS3 COREY_DPP_H("row_shr:8 row_mask:0xf") "s_nop 1\n\t"
+                                 "v_mov_b32_dpp %2, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t")
+                     : "+v"(h), "+v"(P), "+v"(left));
     } else if constexpr (SEG > 1) {
         // segments shorter than a DPP row: the shifted-in partner must come from the same segment
         {
@@ -394,33 +483,38 @@ __device__ __forceinline__ void scan_inclusive(int jseg, float& P, float& h)
             h = take ? fmaf(P, ho, h) : h;
             P = take ? P * Po : P;
         }
+        const float ho = dpp_move<0x111>(h);
+        left = jseg == 0 ? left : ho;
     }
 }
 
-// The value of the lane to the left inside the wave (lane 0 keeps `first`).
-__device__ __forceinline__ float from_left_lane(float v, float first)
+template <int SEG, int Q>
+__device__ __forceinline__ void scan_segments(int jseg, float (&P)[Q], float (&h)[Q], float (&left)[Q])
 {
-    float r = first;
-    asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 wave_shr:1 row_mask:0xf bank_mask:0xf\n\ts_nop 0" : "+v"(r) : "v"(v));
-    return r;
-}
-
-// The value of the lane to the left inside a segment of SEG = 16 or 32 lanes (segments start at multiples of SEG); the
-// first lane of every segment keeps `first`.  DPP rows are 16 lanes: a shift by one inside every row leaves the rows'
-// first lanes alone, and for 32-lane segments the odd rows' first lanes (16, 48) take the last lane of the row before
-// them first (row_bcast:15 on rows 1 and 3, limited by the bank mask to lanes 0..3 of the row, of which 1..3 are
-// overwritten by the shift that follows).
-template <int SEG>
-__device__ __forceinline__ float from_left_in_segment(float v, float first)
-{
-    static_assert(SEG == 16 || SEG == 32, "segments of one or two DPP rows");
-    float r = first;
-    if constexpr (SEG == 32)
-        asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_bcast:15 row_mask:0xa bank_mask:0x1\n\t"
-                     "v_mov_b32_dpp %0, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\ts_nop 0" : "+v"(r) : "v"(v));
-    else
-        asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\ts_nop 0" : "+v"(r) : "v"(v));
-    return r;
+    if constexpr (Q == 1 || SEG < 16) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) scan_segment<SEG>(jseg, P[q], h[q], left[q]);
+    } else {
+        static_assert(Q % 2 == 0, "states at a time");
+#pragma unroll
+        for (int q = 0; q < Q; q += 2) {
+            if constexpr (SEG == 64)
+                asm volatile(COREY_BURST("s_nop 3\n\t" COREY_ROW2_STEPS3 COREY_DPP2_STEP("row_shr:8 row_mask:0xf")
+                                         COREY_DPP2_STEP("row_bcast:15 row_mask:0xa") COREY_DPP2_H("row_bcast:31 row_mask:0xc") "s_nop 0\n\t"
+                                         COREY_DPP2_LEFT("wave_shr:1 row_mask:0xf bank_mask:0xf"))
+                             : "+v"(h[q]), "+v"(P[q]), "+v"(left[q]), "+v"(h[q + 1]), "+v"(P[q + 1]), "+v"(left[q + 1]));
+            else if constexpr (SEG == 32)
+                asm volatile(COREY_BURST("s_nop 3\n\t" COREY_ROW2_STEPS3 COREY_DPP2_STEP("row_shr:8 row_mask:0xf")
+                                         COREY_DPP2_H("row_bcast:15 row_mask:0xa") "s_nop 0\n\t"
+                                         COREY_DPP2_LEFT("row_bcast:15 row_mask:0xa bank_mask:0x1")
+                                         COREY_DPP2_LEFT("row_shr:1 row_mask:0xf bank_mask:0xf"))
+                             : "+v"(h[q]), "+v"(P[q]), "+v"(left[q]), "+v"(h[q + 1]), "+v"(P[q + 1]), "+v"(left[q + 1]));
+            else
+                asm volatile(COREY_BURST("s_nop 3\n\t" COREY_ROW2_STEPS3 COREY_DPP2_H("row_shr:8 row_mask:0xf") "s_nop 0\n\t"
+                                         COREY_DPP2_LEFT("row_shr:1 row_mask:0xf bank_mask:0xf"))
+                             : "+v"(h[q]), "+v"(P[q]), "+v"(left[q]), "+v"(h[q + 1]), "+v"(P[q + 1]), "+v"(left[q + 1]));
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------- kernel arguments
@@ -503,6 +597,7 @@ __global__ __launch_bounds__(256) void k_relayout_bc(const T* __restrict__ Bm, c
         d16 = plan_d16(Bn, D, chunk, rows_cap);
         klo = plan_klo(Bn, D, chunk, d16);
     }
+    chunk = tile_of(chunk, Bn * D);                              // the layout is by the tiles the scan walks
     int64_t len = L;
     if (seqlens) {
         const int64_t sl = seqlens[b];
@@ -583,7 +678,7 @@ template <int K, int CHUNK>
 __host__ __device__ constexpr int lds_floats(int rows, int N, bool split = false)
 {
     // N: padded state count; a split launch adds the partial y of the rows that hold the second half of the states
-    return 4 * Geo<K, CHUNK>::STAGE + 2 * rows * N + N + 4 * kWaves + kBlock + N + (split ? kBlock / 2 * K : 0);
+    return 4 * Geo<K, CHUNK>::STAGE + 2 * rows * N + N + kMaxGroup * kBlock + N + (split ? kBlock / 2 * K : 0);
 }
 
 // ------------------------------------------------------------------------------------------- the scan
@@ -597,17 +692,21 @@ __host__ __device__ constexpr int lds_floats(int rows, int N, bool split = false
 // SPLIT: a channel has two rows of the workgroup (neighbours), the first with states [0, N/2), the second with
 // [N/2, N); `rows` counts channels.  Both do the per-token work; the second hands its partial y to the first through
 // LDS at the end of every tile, and the first adds the skip term, gates and stores.
-template <typename T, int K, int CHUNK, bool STRUCT, bool SPLIT>
+template <typename T, int K, int CHUNK, bool STRUCT, bool SPLIT, int W>
 __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, const int rows, const int d0)
 {
     using Gm = Geo<K, CHUNK>;
-    constexpr int LPR = Gm::LPR, SEG = Gm::SEG, WPR = Gm::WPR, G = Gm::G, STAGE = Gm::STAGE;
+    constexpr int LPR = Gm::LPR, SEG = Gm::SEG, G = Gm::G, STAGE = Gm::STAGE;
     constexpr int NS = SPLIT ? 2 : 1;                       // rows per channel
     constexpr int GH = G / NS;                              // states of one row per staging group
-    static_assert(!SPLIT || (G >= 2 && WPR == 1 && Gm::ROWS >= 2), "a split row needs a state of its own in every staging group");
+    static_assert(!SPLIT || (G >= 2 && Gm::ROWS >= 2), "a split row needs a state of its own in every staging group");
     constexpr int E = K < 4 ? K : 4;                        // staged B / C values a lane reads per LDS instruction
     constexpr int KQ = K / E;
+    constexpr int Q = K < 16 && GH > 1 ? 2 : 1;             // states worked on at a time: each fills the other's wait states
+    static_assert(GH % Q == 0, "whole sets of states");
+    constexpr bool kEarlyC = K < 16 || W < 4;               // C is requested ahead of the folds where there are registers for it
     typedef float BCv __attribute__((ext_vector_type(E)));
+    typedef float GHv __attribute__((ext_vector_type(GH)));
 
     const int b = blockIdx.y;
     const int tid = threadIdx.x;
@@ -633,9 +732,8 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     float* s_carry = s_stage + 4 * STAGE;                   // [rows][N] state carried tile to tile
     float* s_A2 = s_carry + rows * N;                       // [rows][N] A * log2(e)
     float* s_zero = s_A2 + rows * N;                        // [N] zeros: the "carried state" of lanes that are not first in their row
-    float* s_xchg = s_zero + N;                             // [2][kWaves][2] wave totals when a row spans several waves
-    float* s_sink = s_xchg + 4 * kWaves;                    // [kBlock + N] where lanes that are not last in their row "store" the state
-    float* s_ypart = s_sink + kBlock + N;                   // SPLIT: [K][kBlock / 2] partial y of the second rows
+    float* s_sink = s_zero + N;                             // [kMaxGroup * kBlock + N] where lanes that are not last in their row "store" the state
+    float* s_ypart = s_sink + kMaxGroup * kBlock + N;       // SPLIT: [K][kBlock / 2] partial y of the second rows
     for (int i = tid; i < rows * N; i += kBlock) {
         const int r = i / N, n = i - r * N;
         const int dd = d0 + r;
@@ -669,13 +767,12 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // uniform: addresses built from it stay in scalar registers
     const int jseg = lane & (SEG - 1);
-    const int wpos = wave & (WPR - 1);                      // this wave's position inside its row
     // per-state arrays are indexed with the state's number inside the row: the row's first state is folded into the bases
     const float* A2_row = s_A2 + rl * N + n_first;
     const float* carry_rd = ((active && j == 0) ? s_carry + rl * N : s_zero) + n_first;
-    // every lane stores its end-of-sub-block state each step (no branch in the inner loop): the row's last lane into
-    // the carried state, all others into a scratch slot of their own
-    float* carry_wr = (active && j == LPR - 1) ? s_carry + rl * N + n_first : s_sink + tid;
+    // every lane stores its end-of-sub-block states of a group (a store under a mask in this loop sends the compiler's
+    // register allocation to scratch): the row's last lane into the carried state, all others into scratch of their own
+    float* carry_wr = (active && j == LPR - 1) ? s_carry + rl * N + n_first : s_sink + tid * kMaxGroup;
     // staging: one block of GH states per row kind and operand, [half][GH][CHUNK]
     auto stage_group = [&](const int64_t tau_s, const int n_s, float* dst) __attribute__((always_inline)) {
         constexpr bool kScalarBase = CHUNK >= 1024;
@@ -692,7 +789,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     // Geometries with at most 8 steps per lane have the registers to fetch the next tile's u / delta / z while the last
     // group of states of the current tile is computed, which takes the HBM latency out of every tile's start.
     constexpr bool kTileAhead = K <= 8;
-    Raw<T, K> u_nx, d_nx, z_nx;
+    Raw<T, K> u_nx, d_nx;
     bool have_nx = false;                                   // uniform over the workgroup
     const int64_t ntiles = (len + CHUNK - 1) / CHUNK;
     for (int64_t tau = 0; tau < ntiles; ++tau) {
@@ -712,13 +809,11 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         float dl[K], du[K], yv[K];
         Raw<T, K> z_raw;                                    // the gate is fetched with the tile and used after the last state
         if (kTileAhead && have_nx) {                        // a full tile fetched one tile ago
-            z_raw = z_nx;
             widen<T, K>(d_nx, dl);
             widen<T, K>(u_nx, du);
         } else {
             const Raw<T, K> u_raw = load_raw<T, K>(at(u_grp + tile), nvalid, vec);
             const Raw<T, K> d_raw = load_raw<T, K>(at(dl_grp + tile), nvalid, vec);
-            if (z_on) z_raw = load_raw<T, K>(at(z_grp + tile), nvalid, vec);
             widen<T, K>(d_raw, dl);
             widen<T, K>(u_raw, du);
         }
@@ -726,10 +821,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         float S = 0.f;
 #pragma unroll
         for (int i = 0; i < K; ++i) dl[i] = dl[i] + bias;
-        if (sp) {
-#pragma unroll
-            for (int i = 0; i < K; ++i) dl[i] = softplus(dl[i]);
-        }
+        if (sp) softplus_all<K>(dl);
         if (!full) {
 #pragma unroll
             for (int i = 0; i < K; ++i) dl[i] = (i < nvalid) ? dl[i] : 0.f;   // padded steps: dl = 0 -> a = 1, b = 0 (identity)
@@ -746,16 +838,24 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
 #pragma unroll
             for (int i = 0; i < K; ++i) {
                 // a row that starts at state n_first starts its chain at the decay of state 0 to the power n_first
-                av_chain[i] = SPLIT ? fast_exp2(dl[i] * A20 * (float)n_first) : 1.f;
-                dl[i] = fast_exp2(dl[i] * A20);             // from here on dl holds the decay of state 0
+                dl[i] *= A20;
+                av_chain[i] = SPLIT ? dl[i] * (float)n_first : 1.f;
             }
-            P_base = fast_exp2(S * A20);
-            if constexpr (SPLIT) P_chain = fast_exp2(S * A20 * (float)n_first);
+            P_base = S * A20;
+            if constexpr (SPLIT) {
+                P_chain = P_base * (float)n_first;
+                decay_burst<K, true, true>(av_chain, P_chain);
+            }
+            decay_burst<K, true, true>(dl, P_base);                      // from here on dl holds the decay of state 0
         }
 
         for (int n0 = 0; n0 < NH; n0 += GH) {                 // n0: number inside the row of the group's first state
             const float* s_B = s_stage + buf * 2 * STAGE;
             const float* s_C = s_B + STAGE;
+            // A and the carried state of the group's states (the latter was written a tile ago by this wave's own lanes): requested
+            // here, they arrive while the wave waits below
+            GHv cin_g = *reinterpret_cast<const GHv*>(carry_rd + n0), A2_g, h_g;
+            if constexpr (!STRUCT) A2_g = *reinterpret_cast<const GHv*>(A2_row + n0);
             // this group's copy (started one group earlier) has landed; every wave is past the previous group
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
@@ -764,11 +864,11 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 int64_t ntau = tau;
                 if (nn0 >= NH) { nn0 = 0; ntau = tau + 1; }
                 if (ntau < ntiles) stage_group(ntau, nn0, s_stage + (buf ^ 1) * 2 * STAGE);
+                if (nn0 == 0 && z_on) z_raw = load_raw<T, K>(at(z_grp + tile), nvalid, vec);
                 if constexpr (kTileAhead) {                 // last group of this tile: fetch the next tile if it is a full one
                     if (nn0 == 0 && vec && tile + 2 * CHUNK <= len) {
                         u_nx = load_raw<T, K>(at(u_grp + tile + CHUNK), K, true);
                         d_nx = load_raw<T, K>(at(dl_grp + tile + CHUNK), K, true);
-                        if (z_on) z_nx = load_raw<T, K>(at(z_grp + tile + CHUNK), K, true);
                         have_nx = true;
                     }
                 }
@@ -776,85 +876,88 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
             buf ^= 1;
             const BCv* bq0 = reinterpret_cast<const BCv*>(s_B + half * GH * CHUNK) + j;
             const BCv* cq0 = reinterpret_cast<const BCv*>(s_C + half * GH * CHUNK) + j;
-            constexpr bool kEarlyC = K <= COREY_CPREFETCH_MAXK;   // C is requested before the lane scan, which covers the LDS latency
-            auto one_state = [&](const int nl, const int n) __attribute__((always_inline)) {
-                const float cin = carry_rd[n];              // carried state for the first lane of the row, 0 elsewhere
+            // Q states at a time.  Order of the work: request B (and A, the carried state) from LDS; the products dl A; the
+            // exponentials as one burst, which covers that trip; the folds; request C; the lane scans, which cover part of that
+            // one; the replays.
+            auto states = [&](const int nl) __attribute__((always_inline)) {
                 const BCv* bq = bq0 + nl * KQ * LPR;
                 const BCv* cq = cq0 + nl * KQ * LPR;
-                float A2 = 0.f;
-                if constexpr (!STRUCT) A2 = A2_row[n];
-
-                float av_local[K], bv[K];
-                float (&av)[K] = STRUCT ? av_chain : av_local;
-                float h = 0.f, P;
+                float P[Q], h[Q];
+                float av[Q][K], bv[Q][K];
+                BCv b4[Q][KQ], c4[Q][KQ];
+#pragma unroll
+                for (int s = 0; s < Q; ++s)
+#pragma unroll
+                    for (int q = 0; q < KQ; ++q) b4[s][q] = bq[(s * KQ + q) * LPR];
+                __builtin_amdgcn_sched_barrier(0);
                 if constexpr (STRUCT) {
 #pragma unroll
-                    for (int q = 0; q < KQ; ++q) {
-                        const BCv b4 = bq[q * LPR];
+                    for (int s = 0; s < Q; ++s) {
 #pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            const int i = E * q + e;
-                            av[i] *= dl[i];                 // decay of state n from that of state n - 1
-                            bv[i] = du[i] * b4[e];
-                            h = i == 0 ? bv[i] : fmaf(av[i], h, bv[i]);
+                        for (int i = 0; i < K; ++i) {
+                            av_chain[i] *= dl[i];           // decay of state n from that of state n - 1
+                            av[s][i] = av_chain[i];
                         }
+                        P_chain *= P_base;
+                        P[s] = P_chain;
                     }
-                    P_chain *= P_base;
-                    P = P_chain;
                 } else {
 #pragma unroll
-                    for (int q = 0; q < KQ; ++q) {
-                        const BCv b4 = bq[q * LPR];
+                    for (int s = 0; s < Q; ++s) {
 #pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            const int i = E * q + e;
-                            av[i] = fast_exp2(dl[i] * A2);
-                            bv[i] = du[i] * b4[e];
-                            h = i == 0 ? bv[i] : fmaf(av[i], h, bv[i]);      // the fold starts from a zero state
-                        }
+                        for (int i = 0; i < K; ++i) av[s][i] = dl[i] * A2_g[nl + s];
+                        P[s] = S * A2_g[nl + s];
                     }
-                    P = fast_exp2(S * A2);
+                    if constexpr (Q == 1) {
+                        decay_burst<K, true, true>(av[0], P[0]);
+                    } else {
+                        decay_burst<K, true, false>(av[0], P[0]);
+#pragma unroll
+                        for (int s = 1; s + 1 < Q; ++s) decay_burst<K, false, false>(av[s], P[s]);
+                        decay_burst<K, false, true>(av[Q - 1], P[Q - 1]);
+                    }
                 }
-                BCv cv[KQ];
+                __builtin_amdgcn_sched_barrier(0);          // (nothing of the folds before the burst is through)
                 if constexpr (kEarlyC) {
 #pragma unroll
-                    for (int q = 0; q < KQ; ++q) cv[q] = cq[q * LPR];
-                }
-                h = fmaf(P, cin, h);                        // the row's first lane starts from the carried state
-                scan_inclusive<SEG, (WPR > 1)>(jseg, P, h); // h: state at the end of this lane's sub-block (within the wave)
-                float first = cin;                          // state entering the first lane of this wave's part of the row
-                if constexpr (WPR > 1) {                    // a row spans several waves: add what the waves before it did
-                    float* xc = s_xchg + (n & 1) * (2 * kWaves);
-                    if (lane == 63) { xc[2 * wave] = P; xc[2 * wave + 1] = h; }
-                    __syncthreads();
-                    float hw = 0.f;                         // state at the end of the wave to the left
-                    for (int w = 0; w < wpos; ++w) hw = fmaf(xc[2 * (wave - wpos + w)], hw, xc[2 * (wave - wpos + w) + 1]);
-                    h = fmaf(P, hw, h);
-                    if (wpos > 0) first = hw;
-                }
-                carry_wr[n] = h;
-                float hh;                                   // true state entering this lane's sub-block
-                if constexpr (LPR == 1) {
-                    hh = cin;
-                } else if constexpr (SEG == 16 || SEG == 32) {
-                    hh = from_left_in_segment<SEG>(h, cin);  // a row inside one wave: its first lane enters with the carried state
-                } else {
-                    hh = from_left_lane(h, first);
-                    if constexpr (SEG < 64) hh = (jseg == 0) ? cin : hh;
+                    for (int s = 0; s < Q; ++s)
+#pragma unroll
+                        for (int q = 0; q < KQ; ++q) c4[s][q] = cq[(s * KQ + q) * LPR];
+                    __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int q = 0; q < KQ; ++q) {
-                    const BCv c4 = kEarlyC ? cv[q] : cq[q * LPR];
+                for (int i = 0; i < K; ++i)
 #pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        const int i = E * q + e;
-                        hh = fmaf(av[i], hh, bv[i]);
-                        yv[i] = fmaf(c4[e], hh, yv[i]);
+                    for (int s = 0; s < Q; ++s) {
+                        bv[s][i] = du[i] * b4[s][i / E][i % E];
+                        h[s] = i == 0 ? bv[s][i] : fmaf(av[s][i], h[s], bv[s][i]);      // the fold starts from a zero state
                     }
+                float hh[Q];                                // true state entering this lane's sub-block
+#pragma unroll
+                for (int s = 0; s < Q; ++s) {
+                    hh[s] = cin_g[nl + s];                  // the row's first lane starts from the carried state (0 elsewhere)
+                    h[s] = fmaf(P[s], hh[s], h[s]);
                 }
+                scan_segments<SEG, Q>(jseg, P, h, hh);      // h: state at the end of this lane's sub-block
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < Q; ++s) h_g[nl + s] = h[s];
+#pragma unroll
+                for (int s = 0; s < Q; ++s)
+#pragma unroll
+                    for (int q = 0; q < KQ; ++q) {
+                        if constexpr (!kEarlyC) c4[s][q] = cq[(s * KQ + q) * LPR];
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            const int i = E * q + e;
+                            hh[s] = fmaf(av[s][i], hh[s], bv[s][i]);
+                            yv[i] = fmaf(c4[s][q][e], hh[s], yv[i]);
+                        }
+                    }
             };
 #pragma unroll
-            for (int nl = 0; nl < GH; ++nl) one_state(nl, n0 + nl);      // straight-line code for the whole group
+            for (int nl = 0; nl < GH; nl += Q) states(nl);      // straight-line code for the whole group
+            *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
         }
 
         if constexpr (SPLIT) {                              // the second row of a channel hands over its part of the sum over states
@@ -874,21 +977,11 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         T* y_lane = const_cast<T*>(at(y_grp + tile));
         if (full) {
             if (!SPLIT || writer) {
-                if (z_on) {
-                    float zz[K];
-                    widen<T, K>(z_raw, zz);
-#pragma unroll
-                    for (int i = 0; i < K; ++i) yv[i] *= silu(zz[i]);
-                }
+                if (z_on) gate_all<T, K>(z_raw, yv);
                 if (active) store_items<T, K>(y_lane, K, true, yv);
             }
         } else if (nstore > 0 && (!SPLIT || writer)) {
-            if (nvalid > 0 && z_on) {
-                float zz[K];
-                widen<T, K>(z_raw, zz);
-#pragma unroll
-                for (int i = 0; i < K; ++i) yv[i] *= silu(zz[i]);
-            }
+            if (nvalid > 0 && z_on) gate_all<T, K>(z_raw, yv);
 #pragma unroll
             for (int i = 0; i < K; ++i)
                 if (i >= nvalid) yv[i] = 0.f;                // padded positions are written as zero
@@ -920,7 +1013,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
 // run-time chunk gives every workgroup exactly one group; a launch that reads the chunk from device memory sizes
 // its grid from the host's hint and is correct for any chunk (more groups than workgroups: some take several in
 // turn; fewer: the surplus leaves at once).
-template <typename T, int K, int CHUNK, bool SPLIT = false>
+template <typename T, int K, int CHUNK, bool SPLIT, int W>
 __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const int64_t d_first, const int64_t d_end,
                                           const int64_t wg, const int64_t nwg)
 {
@@ -940,28 +1033,31 @@ __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const
                 structured = __syncthreads_and(ok) != 0;
             }
         }
-        if (structured) scan_group<T, K, CHUNK, true, SPLIT>(a, s_mem, rows, (int)d0);
-        else scan_group<T, K, CHUNK, false, SPLIT>(a, s_mem, rows, (int)d0);
+        if (structured) scan_group<T, K, CHUNK, true, SPLIT, W>(a, s_mem, rows, (int)d0);
+        else scan_group<T, K, CHUNK, false, SPLIT, W>(a, s_mem, rows, (int)d0);
         __syncthreads();                                     // the LDS arrays are set up afresh for the next group
     }
 }
 
-// Register budget: K = 16 keeps 16 x (dl, du, y, a, b) per lane and is built for four waves per SIMD (128 VGPRs), and
-// so are the shorter lanes (their spare registers hold the tile fetched ahead).
-template <int K> constexpr int waves_target() { return K < 16 ? COREY_WAVES_K8 : COREY_WAVES_K16; }
+// Waves per SIMD the registers of a kernel leave room for.  512 registers serve 4 waves with 128 each, 3 with 168.  Plain
+// instructions of two waves pair only across the two halves a SIMD's waves are dealt to, so 4 waves (2 + 2) use the issue slots
+// better than 3, but with 128 registers a 16-step lane cannot hold C ahead of its use.  Measured: 4096 + 1024 rows of 16384 steps
+// at chunk 512 (a mixed launch: 3 waves per SIMD whatever the budget) 329 us with 168 registers, 347 with 128; 8192 rows of 4096
+// (4 waves per SIMD) 143 and 135.
+template <int K, int CHUNK> constexpr int waves_target() { return K == 16 && CHUNK > 512 ? 3 : 4; }
 
 // One geometry, chosen on the host from the run-time chunk.
 template <typename T, int K, int CHUNK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_target<K>()))) void k_scan(const ScanArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_target<K, CHUNK>()))) void k_scan(const ScanArgs a)
 {
-    extern __shared__ float s_mem[];
+    extern __shared__ __align__(16) float s_mem[];
     if constexpr (split_exists<K, CHUNK>()) {
         if (a.split) {
-            scan_rows<T, K, CHUNK, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            scan_rows<T, K, CHUNK, true, waves_target<K, CHUNK>()>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
             return;
         }
     }
-    scan_rows<T, K, CHUNK>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+    scan_rows<T, K, CHUNK, false, waves_target<K, CHUNK>()>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
 }
 
 // Workgroup `wg` of `nwg` takes its share of one sequence's channels: those below d16 with 16 steps per lane (the first
@@ -984,11 +1080,11 @@ __device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, co
 {
     if (split) {                                                 // one kind of row, two rows per channel
         if (d16 >= a.D) {
-            if constexpr (split_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK, true, 3>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         } else if (klo == 8) {
-            if constexpr (split_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK, true, 3>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         } else {
-            if constexpr (split_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK, true, 3>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         }
         return;
     }
@@ -1006,31 +1102,31 @@ __device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, co
         }
         const int64_t wg = (int64_t)blockIdx.x - g16;
         if ((int64_t)blockIdx.x < g16) {
-            if constexpr (geometry_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK>(a, s_mem, 0, d16, blockIdx.x, g16);
+            if constexpr (geometry_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK, false, 3>(a, s_mem, 0, d16, blockIdx.x, g16);
         } else if (klo == 8) {
-            if constexpr (geometry_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK>(a, s_mem, d16, a.D, wg, nwg - g16);
+            if constexpr (geometry_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK, false, 3>(a, s_mem, d16, a.D, wg, nwg - g16);
         } else {
-            if constexpr (geometry_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK>(a, s_mem, d16, a.D, wg, nwg - g16);
+            if constexpr (geometry_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK, false, 3>(a, s_mem, d16, a.D, wg, nwg - g16);
         }
     } else {
-        scan_rows<T, 16, CHUNK>(a, s_mem, 0, a.D, blockIdx.x, nwg);
+        scan_rows<T, 16, CHUNK, false, 3>(a, s_mem, 0, a.D, blockIdx.x, nwg);
     }
 }
 
 // Both kinds of workgroups in one launch (host chunk, 0 < d16 < D).
 template <typename T, int CHUNK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COREY_WAVES_K16))) void k_scan_mix(const ScanArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_scan_mix(const ScanArgs a)
 {
-    extern __shared__ float s_mem[];
+    extern __shared__ __align__(16) float s_mem[];
     scan_by_kind<T, CHUNK>(a, s_mem, a.d16, a.klo, 0);
 }
 
 // Per-sequence chunk read from device memory: every geometry in one kernel, selected per workgroup (register budget
 // of the 16-step geometries).
 template <typename T>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COREY_WAVES_K16))) void k_scan_any(const ScanArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_scan_any(const ScanArgs a)
 {
-    extern __shared__ float s_mem[];
+    extern __shared__ __align__(16) float s_mem[];
     const int chunk = resolve_chunk(a, blockIdx.y);
     if (a.route.parts && a.route.rezero && blockIdx.x == 0 && blockIdx.y == 0) {
         // the statistic's partial histograms live in the buffer its producer handed over and have been reduced by the kernel
@@ -1045,9 +1141,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COREY_WA
     case C:                                                                                 \
         scan_by_kind<T, C>(a, s_mem, d16, klo, split);                                      \
         break;
-    switch (chunk) {
+    switch (tile_of(chunk, a.rows_total)) {
         COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
-        COREY_CASE(2048)
     default: break;
     }
 #undef COREY_CASE
@@ -1111,16 +1206,24 @@ inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
     if (p.routed) {
         // grid from the host's chunk (the caller's hint: workgroups take row groups grid-stride, so any grid is correct),
         // LDS for the largest need of any geometry the device-side plan can pick
-#define COREY_GEO(C)                                                                        \
-        {                                                                                   \
-            const int64_t d16_c = plan_d16(p.B, p.D, C, a.rows_cap);                        \
-            const int klo_c = plan_klo(p.B, p.D, C, d16_c);                                 \
-            launch_geometry<C>(p, a.rows_cap, d16_c, klo_c, plan_split(p.B, p.D, (int)p.N, C, d16_c, klo_c, a.allow_split), g, l);    \
-        }                                                                                   \
-        lds = l > lds ? l : lds;                                                            \
-        if (C == p.chunk) gx = g;
-        COREY_GEO(16) COREY_GEO(32) COREY_GEO(64) COREY_GEO(128) COREY_GEO(256) COREY_GEO(512) COREY_GEO(1024) COREY_GEO(2048)
-#undef COREY_GEO
+        for (int c = COREY_MIN_CHUNK; c <= COREY_MAX_CHUNK; c *= 2) {
+            const int64_t d16_c = plan_d16(p.B, p.D, c, a.rows_cap);
+            const int klo_c = plan_klo(p.B, p.D, c, d16_c);
+            const int split_c = plan_split(p.B, p.D, (int)p.N, c, d16_c, klo_c, a.allow_split);
+            g = 0;
+            l = 0;
+#define COREY_CASE(C)                                                                       \
+    case C:                                                                                 \
+        launch_geometry<C>(p, a.rows_cap, d16_c, klo_c, split_c, g, l);                     \
+        break;
+            switch (tile_of(c, p.B * p.D)) {
+                COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
+            default: break;
+            }
+#undef COREY_CASE
+            lds = l > lds ? l : lds;
+            if (c == p.chunk) gx = g;
+        }
         if (gx < 2) gx = 2;     // two kinds of rows decided on the device need a workgroup for each kind (a surplus one leaves at once)
         k_scan_any<T><<<dim3((unsigned)gx, (unsigned)p.B), dim3(kBlock), lds, p.stream>>>(a);
         return;
@@ -1138,9 +1241,8 @@ inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
             else { COREY_LAUNCH(4, C); }                                                    \
         }                                                                                   \
         break;
-    switch (p.chunk) {
+    switch (tile_of(p.chunk, p.B * p.D)) {
         COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
-        COREY_CASE(2048)
     default: break;
     }
 #undef COREY_CASE
