@@ -302,7 +302,8 @@ int causal_conv1d_silu_fwd(const void* x, const float* weight, const float* bias
  *
  * The sequence is processed in tiles of `chunk` time steps per workgroup iteration with the fp32 state
  * carried on chip from tile to tile; the result does not depend on `chunk` beyond floating-point
- * reassociation (the paper's patched kernel is "recurrence-preserving").
+ * reassociation (the paper's patched kernel is "recurrence-preserving").  A tile longer than one wave's lanes take (1024
+ * steps; 512 in launches of more than 4096 rows) is walked in parts of that length, the state carried the same way.
  *
  *   u, delta, z, y   DEVICE [B, D, L] in `dt`; z may be NULL (no gate).
  *   A                DEVICE float[D, N].     Bm, Cm: DEVICE [B, N, L] in `dt`.
@@ -317,8 +318,8 @@ int causal_conv1d_silu_fwd(const void* x, const float* weight, const float* bias
  *                    non-power-of-two entries fall back to `chunk`.
  *   last_state       DEVICE float[B, D, N], required.
  *   workspace        DEVICE, at least selective_scan_fwd_workspace(B, N, L) bytes, 16-byte aligned; scratch only
- *                    (the call first rewrites B and C there as fp32 in the order, or the two orders, the scan reads
- *                    them in).
+ *                    (launches of many rows first rewrite B and C there as fp32 in the order, or the two orders, the
+ *                    scan reads them in).
  *   1 <= N <= COREY_MAX_STATE;  B*D*L and B*N*L must fit in int64 and B*D in int32.
  *   flags            bitwise OR of COREY_SCAN_* options, 0 for the defaults.
  *                    COREY_SCAN_GENERAL_A: never take the fast path for structured A.  By default, when

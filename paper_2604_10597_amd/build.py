@@ -12,9 +12,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcorey.so")
 NATIVE = os.path.join(HERE, "_native.so")          # Python extension: marshals torch tensors into libcorey
-# one translation unit per storage type of the scan: they compile side by side
-SOURCES = ["corey_host.cpp", "corey_entropy.hip", "corey_table.hip", "corey_conv.hip", "corey_decode.hip", "corey_scan.hip", "corey_scan_bf16.hip", "corey_scan_f16.hip",
-           "corey_scan_f32.hip"]
+# the scan's kernels in several translation units: they compile side by side (the longest first)
+SOURCES = [f"corey_scan_any_{t}_w{w}.hip" for t in ("bf16", "f16", "f32") for w in (3, 4)] + [
+    "corey_scan_bf16.hip", "corey_scan_f16.hip", "corey_scan_f32.hip", "corey_conv.hip", "corey_entropy.hip", "corey_table.hip",
+    "corey_decode.hip", "corey_scan.hip", "corey_host.cpp"]
 
 # Packed-FP32 instruction selection is switched off for all device code (plain fp32 VALU ops only).
 HIPCC_FLAGS = [
@@ -47,7 +48,7 @@ def build_native(verbose: bool = False) -> str:
     return NATIVE
 
 
-def build_lib(verbose: bool = False, extra: list[str] | None = None, jobs: int = 6) -> str:
+def build_lib(verbose: bool = False, extra: list[str] | None = None, jobs: int = 8) -> str:
     """Always recompiles the library and the torch extension; returns the path of the library."""
     cc = hipcc()
     inc = [f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]

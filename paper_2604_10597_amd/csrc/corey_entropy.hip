@@ -743,6 +743,14 @@ int check_device_policy(const char* who, const corey_policy* p, int64_t L)
     return COREY_OK;
 }
 
+int launch_finalise(const corey_finalise::Args& a, hipStream_t stream)
+{
+    k_entropy_finalise<<<dim3((unsigned)a.nh), dim3(kThreads), 0, stream>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "entropy reduction launch");
+    return COREY_OK;
+}
+
 int launch_entropy_finalise(const uint32_t* parts, uint32_t* counts, int32_t K, double eps, const void* slot, double* H_out,
                             double* r_out, float* range_out, const corey_policy* pol, int32_t* chunks_out, int64_t L,
                             hipStream_t stream)
@@ -753,10 +761,7 @@ int launch_entropy_finalise(const uint32_t* parts, uint32_t* counts, int32_t K, 
     if (pol) fa.pol = *pol;
     fa.K = K; fa.nh = 1;
     fa.rezero = 1;                                              // the next statistic from the same table adds into them again
-    k_entropy_finalise<<<dim3(1), dim3(kThreads), 0, stream>>>(fa);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "entropy reduction launch");
-    return COREY_OK;
+    return launch_finalise(fa, stream);
 }
 
 }  // namespace corey

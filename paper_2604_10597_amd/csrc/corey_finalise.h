@@ -36,6 +36,13 @@ struct Args {
                                        // count sweep adds into without a clearing launch of its own)
 };
 
+}  // namespace corey_finalise
+namespace corey {
+// The reduction as a launch of its own, one workgroup per histogram (corey_entropy.hip).
+int launch_finalise(const corey_finalise::Args& a, hipStream_t stream);
+}  // namespace corey
+namespace corey_finalise {
+
 // Eq. 2 and the scheduler family around it for one histogram (see corey_select_chunk for the rule); 0 when r is NaN
 // in an entropy mode.
 __device__ __forceinline__ int32_t chunk_rule(double rv, int64_t L, const corey_policy& p)

@@ -73,10 +73,6 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return fail(COREY_EWORKSPACE, "%s: workspace must be 16-byte aligned", who);
 
     const size_t esz = dt == COREY_F32 ? 4 : 2;
-    bool vector_ok = (L * (int64_t)esz) % 16 == 0;
-    for (const void* p : {u, delta, Bm, Cm, z, (const void*)y})
-        if (p && reinterpret_cast<uintptr_t>(p) % 16 != 0) vector_ok = false;
-
     corey_scan::ScanArgs a;
     a.u = u; a.delta = delta; a.A = A; a.Bm = Bm; a.Cm = Cm; a.Dv = Dv; a.z = z; a.dbias = delta_bias; a.h0 = h0;
     a.seqlens = seqlens; a.chunks_dev = chunks_dev; a.y = y; a.last_state = last_state;
@@ -87,10 +83,12 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     a.ws_B8 = a.ws_C + (size_t)B * a.Np * a.Lpad;
     a.ws_C8 = a.ws_B8 + (size_t)B * a.Np * a.Lpad;
     a.L = L; a.rows_total = B * D; a.D = (int32_t)D; a.N = (int32_t)N; a.chunk = chunk; a.softplus = delta_softplus ? 1 : 0;
-    a.vector_ok = vector_ok ? 1 : 0;
     a.allow_structured = (flags & COREY_SCAN_GENERAL_A) ? 0 : 1;
     a.one_chunk = (flags & COREY_SCAN_ONE_CHUNK) ? 1 : 0;
+    a.direct = corey_scan::direct_launch(B, D, N, L) ? 1 : 0;
     a.allow_split = (flags & COREY_SCAN_WHOLE_ROWS) ? 0 : 1;
+    // the second row of a channel finds its half of the states at a 32-bit byte offset
+    if (a.direct && (double)N * (double)L * (double)esz >= 2147483648.0) a.allow_split = 0;
     a.route = corey_finalise::Args{};
     if (route) {
         if (!route->parts || !route->chunks_out || route->K < 2 || route->K > COREY_MAX_BINS || (route->nh != 1 && route->nh != B))
@@ -98,6 +96,11 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
         a.route = *route;
         a.chunks_dev = route->chunks_out;                       // written by this call's first kernel, read by its second
         a.one_chunk = route->nh == 1 ? 1 : 0;
+        if (a.direct) {                                         // no kernel before the scan to carry the reduction: a launch of its own
+            a.route = corey_finalise::Args{};
+            const int st = corey::launch_finalise(*route, static_cast<hipStream_t>(hip_stream));
+            if (st != COREY_OK) return st;
+        }
     }
     // LDS budget for the per-row arrays (carried state and A): at most 32 rows and 8 KiB each, so that the staging
     // buffers and the rows of a workgroup stay below what a compute unit gives four workgroups (chunks below 64,

@@ -1,0 +1,7 @@
+// k_scan_any for bf16 storage with registers for 3 waves per SIMD.
+#define COREY_SCAN_ANY_HERE
+#include "corey_scan_impl.h"
+
+namespace corey_scan {
+COREY_SCAN_ANY(, uint16_t, 3)
+}  // namespace corey_scan

@@ -1,6 +1,7 @@
 // Kernels of selective_scan_fwd (Mamba-1 selective-scan forward with a run-time chunk) for gfx950, as templates
-// over the storage type.  Each storage type is instantiated in a translation unit of its own (corey_scan_f32.hip,
-// corey_scan_bf16.hip, corey_scan_f16.hip) so that they compile in parallel; corey_scan.hip holds the host entry.
+// over the storage type.  Each storage type is instantiated in translation units of its own (corey_scan_f32.hip,
+// corey_scan_bf16.hip, corey_scan_f16.hip, and corey_scan_any_*.hip for the kernels that read the chunk from device memory) so
+// that they compile in parallel; corey_scan.hip holds the host entry.
 //
 // Two kernels per call.
 //
@@ -31,6 +32,8 @@
 #define COREY_SCAN_IMPL_H
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "corey_finalise.h"
 #include "corey_internal.h"
@@ -119,10 +122,6 @@ __host__ __device__ inline int plan_klo(int64_t B, int64_t D, int chunk, int64_t
 // all of the per-token work, and one exchange of partial y per tile through LDS.  The staging group must hold at least
 // one state of each half (tiles up to 1024 steps), and only the geometries such a launch can have are built.
 constexpr int64_t kSplitWaves = 1536;
-template <int K, int CHUNK> constexpr bool split_exists()
-{
-    return (K == 16 && CHUNK == 1024) || (K == 8 && CHUNK == 512) || (K == 4 && CHUNK >= 4 && CHUNK <= 256);
-}
 __host__ __device__ inline int plan_split(int64_t B, int64_t D, int N, int chunk, int64_t d16, int klo, int allow)
 {
     if (!allow || N < 4 || (d16 > 0 && d16 < D)) return 0;    // (fewer than four states: the second row would hold padding only)
@@ -220,39 +219,85 @@ template <typename T, int K> struct Raw {
     uint4v w[kWords];                                          // a short run uses the first kBytes of w[0]
 };
 
-// K consecutive stored values starting at p (the first nvalid exist); missing ones read as zero bits.
-template <typename T, int K>
-__device__ __forceinline__ Raw<T, K> load_raw(const T* p, int nvalid, bool vector_ok)
+// Rows of [.., L] tensors start at any multiple of the element size (L may be odd): vector accesses are written as copies of
+// unaligned memory, which gfx950 does with the same 16-byte instructions.
+template <typename T, int K> __device__ __forceinline__ Raw<T, K> load_full(const T* p)
 {
-    constexpr int V = Io<T>::kVec;
     Raw<T, K> r;
-    if constexpr (Raw<T, K>::kBytes < 16) {                    // 2 or 4 values of a 16-bit type, 2 of binary32
-        r.w[0] = uint4v{0u, 0u, 0u, 0u};
-        if (vector_ok && nvalid == K) {
-            if constexpr (Raw<T, K>::kBytes == 8) {
-                const uint2v q = *reinterpret_cast<const uint2v*>(p);
-                r.w[0].x = q.x;
-                r.w[0].y = q.y;
-            } else {
-                r.w[0].x = *reinterpret_cast<const uint32_t*>(p);
-            }
-        } else {
-            T tmp[V];
+    r.w[0] = uint4v{0u, 0u, 0u, 0u};                           // (a short run fills the first kBytes only)
+    __builtin_memcpy(&r, p, Raw<T, K>::kBytes);
+    return r;
+}
+
+// Drop the first `s` values (uniform, 0 < s < K) and fill with zero bits from behind.
+template <typename T, int K> __device__ __forceinline__ void drop_first(Raw<T, K>& r, int s)
+{
+    constexpr int NW = (Raw<T, K>::kBytes + 3) / 4;
+    uint32_t w[NW + 1];
 #pragma unroll
-            for (int i = 0; i < V; ++i) tmp[i] = (i < K && i < nvalid) ? p[i < K ? i : 0] : T(0);
-            __builtin_memcpy(&r.w[0], tmp, 16);
+    for (int k = 0; k < NW; ++k) w[k] = r.w[k / 4][k % 4];
+    w[NW] = 0u;
+    int words = s;
+    if constexpr (sizeof(T) == 2) {
+        words = s >> 1;
+        if (s & 1) {
+#pragma unroll
+            for (int k = 0; k < NW; ++k) w[k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], 16);
         }
-    } else if (vector_ok && nvalid == K) {
-        const uint4v* pv = reinterpret_cast<const uint4v*>(p);
-#pragma unroll
-        for (int v = 0; v < Raw<T, K>::kWords; ++v) r.w[v] = pv[v];
-    } else {
-        T tmp[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) tmp[i] = (i < nvalid) ? p[i] : T(0);
-#pragma unroll
-        for (int v = 0; v < Raw<T, K>::kWords; ++v) __builtin_memcpy(&r.w[v], &tmp[v * V], 16);
     }
+#pragma unroll
+    for (int step = 1; step < NW; step *= 2) {
+        if (words & step) {
+#pragma unroll
+            for (int k = 0; k < NW; ++k) w[k] = k + step < NW ? w[k + step] : 0u;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NW; ++k) r.w[k / 4][k % 4] = w[k];
+}
+
+// The end of the rows.  In a sequence's last, partial tile a lane's vector may reach beyond its row into the next one: those
+// values become zero bits where they are used (keep).  In the last row of a tensor it would reach beyond the tensor: there the
+// lane takes the K values that end the row instead, and they are shifted down to their places (shift).  Reading the straddling
+// lane's values one by one would be K loads.
+template <typename T, int K> struct Tail {
+    static constexpr int NW = (Raw<T, K>::kBytes + 3) / 4;
+    int shift;                 // uniform: K - L % K, what the lane at the end of the last row has to shift by (0: L is a multiple of K)
+    bool at_end;               // this lane's steps reach beyond L
+    uint32_t keep[NW];         // bits of the values before nvalid
+    __device__ __forceinline__ void init(int64_t L, int64_t t0, int nvalid)
+    {
+        shift = (int)(L % K) == 0 ? 0 : K - (int)(L % K);
+        at_end = t0 + K > L;
+        constexpr int PER = sizeof(T) == 2 ? 2 : 1;
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            keep[w] = nvalid >= PER * (w + 1) ? 0xffffffffu : (nvalid <= PER * w ? 0u : 0xffffu);
+    }
+    // (a lane wholly beyond the row holds nothing of use before or after)
+    __device__ __forceinline__ void place(Raw<T, K>& r) const
+    {
+        if (shift != 0 && at_end) drop_first<T, K>(r, shift);
+    }
+    __device__ __forceinline__ void mask(Raw<T, K>& r) const
+    {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) r.w[w / 4][w % 4] &= keep[w];
+    }
+};
+
+// The same for rows shorter than one lane's run, value by value.
+template <typename T, int K> __device__ __forceinline__ Raw<T, K> load_few(const T* p, int nvalid)
+{
+    T tmp[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) tmp[i] = T(0);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+        if (i < nvalid) tmp[i] = p[i];
+    Raw<T, K> r;
+    r.w[0] = uint4v{0u, 0u, 0u, 0u};
+    __builtin_memcpy(&r, tmp, Raw<T, K>::kBytes);
     return r;
 }
 
@@ -271,32 +316,21 @@ __device__ __forceinline__ void widen(const Raw<T, K>& r, float (&out)[K])
 }
 
 template <typename T, int K>
-__device__ __forceinline__ void store_items(T* p, int nstore, bool vector_ok, const float (&v)[K])
+__device__ __forceinline__ void store_items(T* p, int nstore, const float (&v)[K])
 {
     constexpr int V = Io<T>::kVec;
-    if constexpr (Raw<T, K>::kBytes < 16) {
-        if (vector_ok && nstore == K) {
+    if (nstore == K) {
+        Raw<T, K> r;
+        if constexpr (Raw<T, K>::kBytes < 16) {
             float all[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) all[i] = i < K ? v[i < K ? i : 0] : 0.f;
-            const uint4v q = Io<T>::pack(all);
-            if constexpr (Raw<T, K>::kBytes == 8) {
-                uint2v o;
-                o.x = q.x;
-                o.y = q.y;
-                *reinterpret_cast<uint2v*>(p) = o;
-            } else {
-                *reinterpret_cast<uint32_t*>(p) = q.x;
-            }
+            r.w[0] = Io<T>::pack(all);
         } else {
 #pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (i < nstore) Io<T>::st(p + i, v[i]);
+            for (int k = 0; k < K / V; ++k) r.w[k] = Io<T>::pack(&v[k * V]);
         }
-    } else if (vector_ok && nstore == K) {
-        uint4v* pv = reinterpret_cast<uint4v*>(p);
-#pragma unroll
-        for (int k = 0; k < K / V; ++k) pv[k] = Io<T>::pack(&v[k * V]);
+        __builtin_memcpy(p, &r, Raw<T, K>::kBytes);
     } else {
 #pragma unroll
         for (int i = 0; i < K; ++i)
@@ -539,6 +573,7 @@ struct ScanArgs {
     int64_t d16;            // channels below d16 take 16 steps per lane, the others klo (host chunk; see plan_d16)
     int32_t klo;            // 8 or 4 (host chunk; see plan_klo)
     int32_t split;          // the states of a channel are shared by two rows (host chunk; see plan_split)
+    int32_t direct;         // B and C are read as stored (see kDirectRows); the workspace is not used
     int32_t allow_split;    // 0: every channel keeps one row whatever the size of the launch
     int64_t L, Lpad;
     int64_t rows_total;     // B * D (input of the items-per-lane rule)
@@ -548,7 +583,6 @@ struct ScanArgs {
     int32_t rows_cap;       // most rows a workgroup may hold (LDS budget for the carried state)
     int32_t softplus;
     int32_t allow_structured;   // take the power-chain path when A[d, n] = (n + 1) A[d, 0] (16-bit storage only)
-    int32_t vector_ok;      // rows of the [.., L] tensors are 16-byte aligned
     int32_t one_chunk;      // chunks_dev holds a single entry that applies to every sequence
     corey_finalise::Args route;   // route.parts != NULL: the statistic's reduction and the chunk rule run at the start of this call
 };
@@ -608,9 +642,7 @@ __global__ __launch_bounds__(256) void k_relayout_bc(const T* __restrict__ Bm, c
     const int64_t total = (ntiles * N) << slots_log2;
     const T* Bs = Bm + (int64_t)b * Nreal * L;
     const T* Cs = Cm + (int64_t)b * Nreal * L;
-    struct alignas(4 * sizeof(T)) Quad { T v[4]; };
-    // t is always a multiple of 4: rows of whole, aligned quads can be fetched four values at a time
-    const bool quads_ok = L % 4 == 0 && reinterpret_cast<uintptr_t>(Bm) % sizeof(Quad) == 0 && reinterpret_cast<uintptr_t>(Cm) % sizeof(Quad) == 0;
+    struct Quad { T v[4]; };
     for (int pass = 0; pass < 2; ++pass) {                       // the order of the 16-step rows, then that of the others
         const int K = pass == 0 ? 16 : (klo == 8 ? 8 : 4);       // 4 or fewer steps per lane read B / C in time order
         if (pass == 0 ? d16 <= 0 : d16 >= D) continue;           // no channel of this sequence uses it
@@ -630,10 +662,10 @@ __global__ __launch_bounds__(256) void k_relayout_bc(const T* __restrict__ Bm, c
             const T* pb = Bs + (int64_t)n * L + t;
             const T* pc = Cs + (int64_t)n * L + t;
             float4v vb, vc;
-            if (quads_ok && t + 4 <= len) {                      // four values of each operand in one load
+            if (t + 4 <= len) {                      // four values of each operand in one load
                 Quad qb, qc;
-                __builtin_memcpy(&qb, __builtin_assume_aligned(pb, sizeof(Quad)), sizeof(Quad));
-                __builtin_memcpy(&qc, __builtin_assume_aligned(pc, sizeof(Quad)), sizeof(Quad));
+                __builtin_memcpy(&qb, pb, sizeof(Quad));
+                __builtin_memcpy(&qc, pc, sizeof(Quad));
                 vb.x = Io<T>::ld(&qb.v[0]); vb.y = Io<T>::ld(&qb.v[1]); vb.z = Io<T>::ld(&qb.v[2]); vb.w = Io<T>::ld(&qb.v[3]);
                 vc.x = Io<T>::ld(&qc.v[0]); vc.y = Io<T>::ld(&qc.v[1]); vc.z = Io<T>::ld(&qc.v[2]); vc.w = Io<T>::ld(&qc.v[3]);
             } else {
@@ -675,10 +707,10 @@ __device__ __forceinline__ void stage_async(const float* __restrict__ srcB, cons
 
 // Floats of dynamic LDS one workgroup of the (K, CHUNK) geometry needs for `rows` rows of N states.
 template <int K, int CHUNK>
-__host__ __device__ constexpr int lds_floats(int rows, int N, bool split = false)
+__host__ __device__ constexpr int lds_floats(int rows, int N, bool split, bool direct)
 {
     // N: padded state count; a split launch adds the partial y of the rows that hold the second half of the states
-    return 4 * Geo<K, CHUNK>::STAGE + 2 * rows * N + N + kMaxGroup * kBlock + N + (split ? kBlock / 2 * K : 0);
+    return (direct ? 0 : 4 * Geo<K, CHUNK>::STAGE) + 2 * rows * N + N + kMaxGroup * kBlock + N + (split ? (direct ? 2 : 1) * (kBlock / 2) * K : 0);
 }
 
 // ------------------------------------------------------------------------------------------- the scan
@@ -692,12 +724,15 @@ __host__ __device__ constexpr int lds_floats(int rows, int N, bool split = false
 // SPLIT: a channel has two rows of the workgroup (neighbours), the first with states [0, N/2), the second with
 // [N/2, N); `rows` counts channels.  Both do the per-token work; the second hands its partial y to the first through
 // LDS at the end of every tile, and the first adds the skip term, gates and stores.
-template <typename T, int K, int CHUNK, bool STRUCT, bool SPLIT, int W>
+// DIRECT: B and C are read where they are, as stored: every lane loads the K values of its steps (one or two 16-byte words per
+// operand and state, a set of states ahead) and widens them, two instructions per value more than from the fp32 copy.  In
+// return there is no staging, no barrier in the loop, and no launch before this one.  Which launches: see kDirectRows.
+template <typename T, int K, int CHUNK, bool STRUCT, bool SPLIT, int W, bool DIRECT>
 __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, const int rows, const int d0)
 {
     using Gm = Geo<K, CHUNK>;
-    constexpr int LPR = Gm::LPR, SEG = Gm::SEG, G = Gm::G, STAGE = Gm::STAGE;
     constexpr int NS = SPLIT ? 2 : 1;                       // rows per channel
+    constexpr int LPR = Gm::LPR, SEG = Gm::SEG, G = DIRECT ? (K == 16 ? NS : kMaxGroup) : Gm::G, STAGE = DIRECT ? 0 : Gm::STAGE;
     constexpr int GH = G / NS;                              // states of one row per staging group
     static_assert(!SPLIT || (G >= 2 && Gm::ROWS >= 2), "a split row needs a state of its own in every staging group");
     constexpr int E = K < 4 ? K : 4;                        // staged B / C values a lane reads per LDS instruction
@@ -709,7 +744,10 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     typedef float GHv __attribute__((ext_vector_type(GH)));
 
     const int b = blockIdx.y;
-    const int tid = threadIdx.x;
+    // opaque: a kernel holds several of these bodies, and lane numbers computed for all of them in advance would fill the
+    // registers of each
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     const int row_local = tid / LPR;
     const int j = tid % LPR;                                // sub-block of this lane inside the tile
     const int ch_local = SPLIT ? row_local >> 1 : row_local; // channel of this lane inside the group
@@ -762,7 +800,6 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     const float* wsC = (K < 16 ? a.ws_C8 : a.ws_C) + (int64_t)b * N * a.Lpad;
     const float bias = (a.dbias && active) ? a.dbias[d] : 0.f;
     const float Dd = (a.Dv && active && half == 0) ? a.Dv[d] : 0.f;      // the skip term enters once per channel
-    const bool vec = a.vector_ok != 0;
     const bool sp = a.softplus != 0;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // uniform: addresses built from it stay in scalar registers
@@ -773,6 +810,24 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     // every lane stores its end-of-sub-block states of a group (a store under a mask in this loop sends the compiler's
     // register allocation to scratch): the row's last lane into the carried state, all others into scratch of their own
     float* carry_wr = (active && j == LPR - 1) ? s_carry + rl * N + n_first : s_sink + tid * kMaxGroup;
+    // DIRECT: the set of states after the one being worked on, as stored.  A lane's place inside a row of B / C is a 32-bit
+    // offset from a uniform base: its steps of a full tile, or of the row's last part (see Tail)
+    const T* Bseq = static_cast<const T*>(a.Bm) + (int64_t)b * N * L;
+    const T* Cseq = static_cast<const T*>(a.Cm) + (int64_t)b * N * L;
+    const uint32_t half_off = (uint32_t)((int64_t)n_first * L * (int64_t)sizeof(T));
+    uint32_t bc_off = 0, bc_off_last = 0;                   // (the latter: in the tensor's last row, see Tail)
+    const int n_last = b == (int)gridDim.y - 1 ? NH - 1 : -1;   // the state (of the second half, if there are two) whose row that is
+    Raw<T, K> b_nx[Q], c_nx[Q];
+    auto fetch = [&](auto full_c, const int n, const int64_t from) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < Q; ++s) {
+            const int64_t row = (int64_t)(n + s) * L + from;
+            uint32_t off = bc_off;
+            if constexpr (!decltype(full_c)::value) off = n + s == n_last ? bc_off_last : bc_off;
+            b_nx[s] = load_full<T, K>(reinterpret_cast<const T*>(reinterpret_cast<const char*>(Bseq + row) + off));
+            c_nx[s] = load_full<T, K>(reinterpret_cast<const T*>(reinterpret_cast<const char*>(Cseq + row) + off));
+        }
+    };
     // staging: one block of GH states per row kind and operand, [half][GH][CHUNK]
     auto stage_group = [&](const int64_t tau_s, const int n_s, float* dst) __attribute__((always_inline)) {
         constexpr bool kScalarBase = CHUNK >= 1024;
@@ -784,36 +839,65 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     };
 
     int buf = 0;                                            // staging buffer holding the group about to be used
-    if (len > 0) stage_group(0, 0, s_stage);
+    const int64_t ntiles = (len + CHUNK - 1) / CHUNK;
+    const int64_t nfull = len / CHUNK;                      // tiles that lie inside the sequence: no masks anywhere
+    if constexpr (!DIRECT) {
+        if (len > 0) stage_group(0, 0, s_stage);
+    }
 
-    // Geometries with at most 8 steps per lane have the registers to fetch the next tile's u / delta / z while the last
+    // Geometries with at most 8 steps per lane have the registers to fetch the next tile's u and delta while the last
     // group of states of the current tile is computed, which takes the HBM latency out of every tile's start.
     constexpr bool kTileAhead = K <= 8;
     Raw<T, K> u_nx, d_nx;
     bool have_nx = false;                                   // uniform over the workgroup
-    const int64_t ntiles = (len + CHUNK - 1) / CHUNK;
-    for (int64_t tau = 0; tau < ntiles; ++tau) {
+    GHv cin_nx, A2_nx;
+    if constexpr (DIRECT) {
+        cin_nx = *reinterpret_cast<const GHv*>(carry_rd);
+        if constexpr (!STRUCT) A2_nx = *reinterpret_cast<const GHv*>(A2_row);
+    }
+    auto walk_tile = [&](auto full_c, const int64_t tau) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(full_c)::value;
         const int64_t tile = tau * CHUNK;
         const int64_t t0 = tile + (int64_t)j * K;
-        // A full tile lies inside the sequence with aligned rows: no masks anywhere (idle lanes read row d0).
-        const bool full = vec && tile + CHUNK <= len;       // uniform over the workgroup
-        // otherwise: valid steps of this lane (within the sequence) and steps that get a y written (within L)
+        // the sequence's last, partial tile: valid steps of this lane (within the sequence) and steps that get a y written (within L)
         int nvalid = K, nstore = K;
-        if (!full) {
+        Tail<T, K> tail;
+        if constexpr (!FULL) {
             nvalid = nstore = 0;
             if (active) {
                 nvalid = (t0 >= len) ? 0 : (len - t0 < K ? (int)(len - t0) : K);
                 nstore = (t0 >= L) ? 0 : (L - t0 < K ? (int)(L - t0) : K);
             }
+            tail.init(L, t0, nvalid);
+        }
+        // Where this lane's vectors start: its steps; in the partial tile no lane reads beyond the tensor (L < K: value by value)
+        const int64_t t0_last = FULL || t0 + K <= L ? t0 : L - K;                   // in the tensor's last row
+        const bool in_last = !FULL && b == (int)gridDim.y - 1 && d0 + rl == a.D - 1;    // ... which is this lane's row of u, delta and z
+        const int64_t t0_row = FULL || in_last || t0 >= L ? t0_last : t0;
+        auto load_row = [&](const T* base) __attribute__((always_inline)) {
+            if constexpr (FULL) return load_full<T, K>(at(base + tile));
+            if (DIRECT || L >= K) {
+                Raw<T, K> r = load_full<T, K>(at(base + tile) + (t0_row - t0));
+                if (in_last) tail.place(r);
+                return r;
+            }
+            return load_few<T, K>(at(base + tile), nvalid);
+        };
+        if constexpr (DIRECT) {
+            bc_off = half_off + (uint32_t)((FULL ? (int64_t)j * K : (t0 >= L ? t0_last : t0)) * (int64_t)sizeof(T));
+            bc_off_last = half_off + (uint32_t)(t0_last * (int64_t)sizeof(T));
+            if (!FULL || tau == 0) fetch(full_c, 0, FULL ? tile : 0);
         }
         float dl[K], du[K], yv[K];
         Raw<T, K> z_raw;                                    // the gate is fetched with the tile and used after the last state
-        if (kTileAhead && have_nx) {                        // a full tile fetched one tile ago
+        if (FULL && kTileAhead && have_nx) {                // fetched one tile ago
             widen<T, K>(d_nx, dl);
             widen<T, K>(u_nx, du);
         } else {
-            const Raw<T, K> u_raw = load_raw<T, K>(at(u_grp + tile), nvalid, vec);
-            const Raw<T, K> d_raw = load_raw<T, K>(at(dl_grp + tile), nvalid, vec);
+            Raw<T, K> u_raw = load_row(u_grp), d_raw = load_row(dl_grp);
+            if constexpr (!FULL) {
+                tail.mask(u_raw);
+            }
             widen<T, K>(d_raw, dl);
             widen<T, K>(u_raw, du);
         }
@@ -822,7 +906,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
 #pragma unroll
         for (int i = 0; i < K; ++i) dl[i] = dl[i] + bias;
         if (sp) softplus_all<K>(dl);
-        if (!full) {
+        if constexpr (!FULL) {
 #pragma unroll
             for (int i = 0; i < K; ++i) dl[i] = (i < nvalid) ? dl[i] : 0.f;   // padded steps: dl = 0 -> a = 1, b = 0 (identity)
         }
@@ -852,23 +936,32 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         for (int n0 = 0; n0 < NH; n0 += GH) {                 // n0: number inside the row of the group's first state
             const float* s_B = s_stage + buf * 2 * STAGE;
             const float* s_C = s_B + STAGE;
-            // A and the carried state of the group's states (the latter was written a tile ago by this wave's own lanes): requested
-            // here, they arrive while the wave waits below
-            GHv cin_g = *reinterpret_cast<const GHv*>(carry_rd + n0), A2_g, h_g;
-            if constexpr (!STRUCT) A2_g = *reinterpret_cast<const GHv*>(A2_row + n0);
-            // this group's copy (started one group earlier) has landed; every wave is past the previous group
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            {   // start the copy of the next group: same tile, or the first group of the next tile
-                int nn0 = n0 + GH;
-                int64_t ntau = tau;
-                if (nn0 >= NH) { nn0 = 0; ntau = tau + 1; }
-                if (ntau < ntiles) stage_group(ntau, nn0, s_stage + (buf ^ 1) * 2 * STAGE);
-                if (nn0 == 0 && z_on) z_raw = load_raw<T, K>(at(z_grp + tile), nvalid, vec);
-                if constexpr (kTileAhead) {                 // last group of this tile: fetch the next tile if it is a full one
-                    if (nn0 == 0 && vec && tile + 2 * CHUNK <= len) {
-                        u_nx = load_raw<T, K>(at(u_grp + tile + CHUNK), K, true);
-                        d_nx = load_raw<T, K>(at(dl_grp + tile + CHUNK), K, true);
+            // A and the carried state of the group's states (the latter was written a tile ago by this wave's own lanes).  Staged:
+            // requested here, they arrive while the wave waits below.  DIRECT: requested during the last replays of the group before.
+            GHv cin_g, A2_g, h_g;
+            if constexpr (DIRECT) {
+                cin_g = cin_nx;
+                A2_g = A2_nx;
+            } else {
+                cin_g = *reinterpret_cast<const GHv*>(carry_rd + n0);
+                if constexpr (!STRUCT) A2_g = *reinterpret_cast<const GHv*>(A2_row + n0);
+            }
+            if constexpr (!DIRECT) {
+                // this group's copy (started one group earlier) has landed; every wave is past the previous group
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+            }
+            const bool last_group = n0 + GH >= NH;
+            if constexpr (!DIRECT) {                        // start the copy of the next group: same tile, or the first group of the next
+                if (!last_group) stage_group(tau, n0 + GH, s_stage + (buf ^ 1) * 2 * STAGE);
+                else if (tau + 1 < ntiles) stage_group(tau + 1, 0, s_stage + (buf ^ 1) * 2 * STAGE);
+            }
+            if (last_group) {                               // the gate, and the next tile if it is a full one, arrive while it is computed
+                if (z_on) z_raw = load_row(z_grp);
+                if constexpr (kTileAhead) {
+                    if (FULL && tau + 1 < nfull) {
+                        u_nx = load_full<T, K>(at(u_grp + tile + CHUNK));
+                        d_nx = load_full<T, K>(at(dl_grp + tile + CHUNK));
                         have_nx = true;
                     }
                 }
@@ -885,10 +978,22 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 float P[Q], h[Q];
                 float av[Q][K], bv[Q][K];
                 BCv b4[Q][KQ], c4[Q][KQ];
+                Raw<T, K> b_raw[Q], c_raw[Q];
+                if constexpr (DIRECT) {
 #pragma unroll
-                for (int s = 0; s < Q; ++s)
+                    for (int s = 0; s < Q; ++s) {
+                        b_raw[s] = b_nx[s];
+                        c_raw[s] = c_nx[s];
+                    }
+                    // (after the row's last full tile this reads a set nobody uses: cheaper than a branch among the states)
+                    const bool more = n0 + nl + Q < NH;
+                    fetch(full_c, more ? n0 + nl + Q : 0, FULL ? (more || tau + 1 >= nfull ? tile : tile + CHUNK) : 0);
+                } else {
 #pragma unroll
-                    for (int q = 0; q < KQ; ++q) b4[s][q] = bq[(s * KQ + q) * LPR];
+                    for (int s = 0; s < Q; ++s)
+#pragma unroll
+                        for (int q = 0; q < KQ; ++q) b4[s][q] = bq[(s * KQ + q) * LPR];
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (STRUCT) {
 #pragma unroll
@@ -918,7 +1023,18 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);          // (nothing of the folds before the burst is through)
-                if constexpr (kEarlyC) {
+                float bw[Q][K], cw[Q][K];                   // DIRECT
+                if constexpr (DIRECT) {
+#pragma unroll
+                    for (int s = 0; s < Q; ++s) {
+                        if constexpr (!FULL) {
+                            if (n0 + nl + s == n_last) tail.place(b_raw[s]);
+                            tail.mask(b_raw[s]);
+                        }
+                        widen<T, K>(b_raw[s], bw[s]);
+                    }
+                }
+                if constexpr (kEarlyC && !DIRECT) {
 #pragma unroll
                     for (int s = 0; s < Q; ++s)
 #pragma unroll
@@ -929,7 +1045,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 for (int i = 0; i < K; ++i)
 #pragma unroll
                     for (int s = 0; s < Q; ++s) {
-                        bv[s][i] = du[i] * b4[s][i / E][i % E];
+                        bv[s][i] = du[i] * (DIRECT ? bw[s][i] : b4[s][i / E][i % E]);
                         h[s] = i == 0 ? bv[s][i] : fmaf(av[s][i], h[s], bv[s][i]);      // the fold starts from a zero state
                     }
                 float hh[Q];                                // true state entering this lane's sub-block
@@ -942,31 +1058,46 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int s = 0; s < Q; ++s) h_g[nl + s] = h[s];
+                if (DIRECT && nl + Q == GH) {
+                    *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
+                    const int nn = last_group ? 0 : n0 + GH;
+                    cin_nx = *reinterpret_cast<const GHv*>(carry_rd + nn);
+                    if constexpr (!STRUCT) A2_nx = *reinterpret_cast<const GHv*>(A2_row + nn);
+                }
 #pragma unroll
                 for (int s = 0; s < Q; ++s)
 #pragma unroll
                     for (int q = 0; q < KQ; ++q) {
-                        if constexpr (!kEarlyC) c4[s][q] = cq[(s * KQ + q) * LPR];
+                        if constexpr (DIRECT) {
+                            if (q == 0) {
+                                if constexpr (!FULL)
+                                    if (n0 + nl + s == n_last) tail.place(c_raw[s]);
+                                widen<T, K>(c_raw[s], cw[s]);
+                            }
+                        } else if constexpr (!kEarlyC) {
+                            c4[s][q] = cq[(s * KQ + q) * LPR];
+                        }
 #pragma unroll
                         for (int e = 0; e < E; ++e) {
                             const int i = E * q + e;
                             hh[s] = fmaf(av[s][i], hh[s], bv[s][i]);
-                            yv[i] = fmaf(c4[s][q][e], hh[s], yv[i]);
+                            yv[i] = fmaf(DIRECT ? cw[s][i] : c4[s][q][e], hh[s], yv[i]);
                         }
                     }
             };
 #pragma unroll
             for (int nl = 0; nl < GH; nl += Q) states(nl);      // straight-line code for the whole group
-            *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
+            if constexpr (!DIRECT) *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
         }
 
         if constexpr (SPLIT) {                              // the second row of a channel hands over its part of the sum over states
-            float* yp = s_ypart + ch_local * LPR + j;
+            // (DIRECT: two buffers in turn, because nothing else separates these reads from the next tile's writes)
+            float* yp = s_ypart + (DIRECT ? (int)(tau & 1) * (K * (kBlock / 2)) : 0) + ch_local * LPR + j;
             if (half == 1 && active) {
 #pragma unroll
                 for (int i = 0; i < K; ++i) yp[i * (kBlock / 2)] = yv[i];
             }
-            __syncthreads();                                // (the next tile's barriers separate these reads from its writes)
+            __syncthreads();                                // (staged: the next tile's barriers separate these reads from its writes)
             if (half == 0 && active) {
 #pragma unroll
                 for (int i = 0; i < K; ++i) yv[i] += yp[i * (kBlock / 2)];
@@ -975,19 +1106,21 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         const bool writer = active && half == 0;            // the row that gates and stores y
 
         T* y_lane = const_cast<T*>(at(y_grp + tile));
-        if (full) {
+        if constexpr (FULL) {
             if (!SPLIT || writer) {
                 if (z_on) gate_all<T, K>(z_raw, yv);
-                if (active) store_items<T, K>(y_lane, K, true, yv);
+                if (active) store_items<T, K>(y_lane, K, yv);
             }
         } else if (nstore > 0 && (!SPLIT || writer)) {
             if (nvalid > 0 && z_on) gate_all<T, K>(z_raw, yv);
 #pragma unroll
             for (int i = 0; i < K; ++i)
                 if (i >= nvalid) yv[i] = 0.f;                // padded positions are written as zero
-            store_items<T, K>(y_lane, nstore, vec, yv);
+            store_items<T, K>(y_lane, nstore, yv);
         }
-    }
+    };
+    for (int64_t tau = 0; tau < nfull; ++tau) walk_tile(std::true_type{}, tau);
+    if (nfull < ntiles) walk_tile(std::false_type{}, nfull);
 
     // tiles wholly beyond the sequence: y is written as zero
     if (active && half == 0) {
@@ -997,7 +1130,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         for (int64_t tile = ntiles * CHUNK; tile < L; tile += CHUNK) {
             const int64_t t0 = tile + (int64_t)j * K;
             const int nstore = (t0 >= L) ? 0 : (L - t0 < K ? (int)(L - t0) : K);
-            if (nstore > 0) store_items<T, K>(const_cast<T*>(at(y_grp + tile)), nstore, vec, zero);
+            if (nstore > 0) store_items<T, K>(const_cast<T*>(at(y_grp + tile)), nstore, zero);
         }
     }
     __syncthreads();                                         // last writes of the carried state are visible
@@ -1013,7 +1146,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
 // run-time chunk gives every workgroup exactly one group; a launch that reads the chunk from device memory sizes
 // its grid from the host's hint and is correct for any chunk (more groups than workgroups: some take several in
 // turn; fewer: the surplus leaves at once).
-template <typename T, int K, int CHUNK, bool SPLIT, int W>
+template <typename T, int K, int CHUNK, bool SPLIT, int W, bool DIRECT>
 __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const int64_t d_first, const int64_t d_end,
                                           const int64_t wg, const int64_t nwg)
 {
@@ -1033,39 +1166,55 @@ __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const
                 structured = __syncthreads_and(ok) != 0;
             }
         }
-        if (structured) scan_group<T, K, CHUNK, true, SPLIT, W>(a, s_mem, rows, (int)d0);
-        else scan_group<T, K, CHUNK, false, SPLIT, W>(a, s_mem, rows, (int)d0);
+        if (structured) scan_group<T, K, CHUNK, true, SPLIT, W, DIRECT>(a, s_mem, rows, (int)d0);
+        else scan_group<T, K, CHUNK, false, SPLIT, W, DIRECT>(a, s_mem, rows, (int)d0);
         __syncthreads();                                     // the LDS arrays are set up afresh for the next group
     }
 }
 
-// Waves per SIMD the registers of a kernel leave room for.  512 registers serve 4 waves with 128 each, 3 with 168.  Plain
-// instructions of two waves pair only across the two halves a SIMD's waves are dealt to, so 4 waves (2 + 2) use the issue slots
-// better than 3, but with 128 registers a 16-step lane cannot hold C ahead of its use.  Measured: 4096 + 1024 rows of 16384 steps
-// at chunk 512 (a mixed launch: 3 waves per SIMD whatever the budget) 329 us with 168 registers, 347 with 128; 8192 rows of 4096
-// (4 waves per SIMD) 143 and 135.
-template <int K, int CHUNK> constexpr int waves_target() { return K == 16 && CHUNK > 512 ? 3 : 4; }
+// Launches of at most this many rows read B and C directly (three waves of one row per SIMD): with few waves to fill in, what
+// staging costs (a launch before the scan, a barrier per group of states, the copies' share of every wave's issue slots) is
+// more than the widening.  Measured, staged scan plus relayout against direct: 1024 rows of 4096 steps 38 and 32 us, 1536 of
+// 2048 28 and 22, 2048 of 4096 50 and 47; 8192 rows of 4096 141 and 147.
+constexpr int64_t kDirectRows = 3072;
+inline bool direct_launch(int64_t B, int64_t D, int64_t N, int64_t L) { return B * D <= kDirectRows && N % kMaxGroup == 0 && L >= 16; }
+
+// Which geometries the plan can give a launch of either kind.
+template <int K, int CHUNK, bool DIRECT> constexpr bool geometry_exists()
+{
+    if (DIRECT) return (K == 16 && CHUNK == 1024) || (K == 8 && CHUNK == 512) || (K == 4 && CHUNK >= 4 && CHUNK <= 256);
+    return CHUNK >= K && (K == 16 || (K == 8 && CHUNK <= 512) || (K == 4 && CHUNK <= 256));
+}
+template <int K, int CHUNK, bool DIRECT> constexpr bool split_exists()
+{
+    return (K == 16 && CHUNK == 1024) || (K == 8 && CHUNK == 512) || (K == 4 && CHUNK >= 4 && CHUNK <= 256);
+}
+
+// Waves per SIMD the registers of a kernel leave room for.  512 registers serve 4 waves with 128 each, 3 with 168, 2 with 256.
+// Plain instructions of two waves pair only across the two halves a SIMD's waves are dealt to, so 4 waves (2 + 2) use the issue
+// slots better than 3, but with 128 registers a 16-step lane cannot hold C ahead of its use.  Measured: 4096 + 1024 rows of
+// 16384 steps at chunk 512 (a mixed launch: 3 waves per SIMD whatever the budget) 329 us with 168 registers, 347 with 128; 8192
+// rows of 4096 (4 waves per SIMD) 143 and 135.  Direct launches have at most 3 waves per SIMD (binary32 runs of 16 steps need 256
+// registers).
+template <typename T, int K, int CHUNK, bool DIRECT> constexpr int waves_target()
+{
+    if (DIRECT) return sizeof(T) == 4 ? 2 : 3;
+    return K == 16 && CHUNK > 512 ? 3 : 4;
+}
 
 // One geometry, chosen on the host from the run-time chunk.
-template <typename T, int K, int CHUNK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_target<K, CHUNK>()))) void k_scan(const ScanArgs a)
+template <typename T, int K, int CHUNK, bool DIRECT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_target<T, K, CHUNK, DIRECT>()))) void k_scan(const ScanArgs a)
 {
     extern __shared__ __align__(16) float s_mem[];
-    if constexpr (split_exists<K, CHUNK>()) {
+    constexpr int W = waves_target<T, K, CHUNK, DIRECT>();
+    if constexpr (split_exists<K, CHUNK, DIRECT>()) {
         if (a.split) {
-            scan_rows<T, K, CHUNK, true, waves_target<K, CHUNK>()>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            scan_rows<T, K, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
             return;
         }
     }
-    scan_rows<T, K, CHUNK, false, waves_target<K, CHUNK>()>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
-}
-
-// Workgroup `wg` of `nwg` takes its share of one sequence's channels: those below d16 with 16 steps per lane (the first
-// g16 workgroups), the others with 8.  With a grid sized for exactly these two kinds every workgroup has one row group;
-// any other grid is still correct (row groups are taken grid-stride within each kind).
-template <int K, int CHUNK> constexpr bool geometry_exists()
-{
-    return CHUNK >= K && (K == 16 || (K == 8 && CHUNK <= 512) || (K == 4 && CHUNK <= 256));
+    scan_rows<T, K, CHUNK, false, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
 }
 
 template <int CHUNK> __host__ __device__ inline int rows_of(int K, int rows_cap, int split = 0)
@@ -1075,41 +1224,40 @@ template <int CHUNK> __host__ __device__ inline int rows_of(int K, int rows_cap,
     return rows < rows_cap ? rows : rows_cap;
 }
 
-template <typename T, int CHUNK>
+// Workgroup `wg` of `nwg` takes its share of one sequence's channels: those below d16 with 16 steps per lane (the first
+// g16 workgroups), the others with 8.  With a grid sized for exactly these two kinds every workgroup has one row group;
+// any other grid is still correct (row groups are taken grid-stride within each kind).
+template <typename T, int CHUNK, int W, bool DIRECT>
 __device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, const int64_t d16, const int klo, const int split)
 {
     if (split) {                                                 // one kind of row, two rows per channel
         if (d16 >= a.D) {
-            if constexpr (split_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK, true, 3>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<16, CHUNK, DIRECT>()) scan_rows<T, 16, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         } else if (klo == 8) {
-            if constexpr (split_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK, true, 3>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<8, CHUNK, DIRECT>()) scan_rows<T, 8, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         } else {
-            if constexpr (split_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK, true, 3>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<4, CHUNK, DIRECT>()) scan_rows<T, 4, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         }
         return;
     }
     const int rows16 = rows_of<CHUNK>(16, a.rows_cap);
     const int64_t n16 = (d16 + rows16 - 1) / rows16;
     const int64_t nwg = gridDim.x;
-    if constexpr (CHUNK <= 512) {
-        const int rows8 = rows_of<CHUNK>(klo, a.rows_cap);
-        const int64_t n8 = (a.D - d16 + rows8 - 1) / rows8;
-        int64_t g16 = n16;                                       // workgroups of the 16-step kind
-        if (n16 + n8 != nwg) {                                   // a grid sized for another chunk: share it in proportion
-            g16 = n8 == 0 ? nwg : (n16 == 0 ? 0 : (nwg * n16 + (n16 + n8) / 2) / (n16 + n8));
-            if (n16 > 0 && g16 < 1) g16 = 1;
-            if (n8 > 0 && g16 > nwg - 1) g16 = nwg - 1;
-        }
-        const int64_t wg = (int64_t)blockIdx.x - g16;
-        if ((int64_t)blockIdx.x < g16) {
-            if constexpr (geometry_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK, false, 3>(a, s_mem, 0, d16, blockIdx.x, g16);
-        } else if (klo == 8) {
-            if constexpr (geometry_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK, false, 3>(a, s_mem, d16, a.D, wg, nwg - g16);
-        } else {
-            if constexpr (geometry_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK, false, 3>(a, s_mem, d16, a.D, wg, nwg - g16);
-        }
+    const int rows8 = rows_of<CHUNK>(klo, a.rows_cap);
+    const int64_t n8 = (a.D - d16 + rows8 - 1) / rows8;
+    int64_t g16 = n16;                                           // workgroups of the 16-step kind
+    if (n16 + n8 != nwg) {                                       // a grid sized for another chunk: share it in proportion
+        g16 = n8 == 0 ? nwg : (n16 == 0 ? 0 : (nwg * n16 + (n16 + n8) / 2) / (n16 + n8));
+        if (n16 > 0 && g16 < 1) g16 = 1;
+        if (n8 > 0 && g16 > nwg - 1) g16 = nwg - 1;
+    }
+    const int64_t wg = (int64_t)blockIdx.x - g16;
+    if ((int64_t)blockIdx.x < g16) {
+        if constexpr (geometry_exists<16, CHUNK, DIRECT>()) scan_rows<T, 16, CHUNK, false, W, DIRECT>(a, s_mem, 0, d16, blockIdx.x, g16);
+    } else if (klo == 8) {
+        if constexpr (geometry_exists<8, CHUNK, DIRECT>()) scan_rows<T, 8, CHUNK, false, W, DIRECT>(a, s_mem, d16, a.D, wg, nwg - g16);
     } else {
-        scan_rows<T, 16, CHUNK, false, 3>(a, s_mem, 0, a.D, blockIdx.x, nwg);
+        if constexpr (geometry_exists<4, CHUNK, DIRECT>()) scan_rows<T, 4, CHUNK, false, W, DIRECT>(a, s_mem, d16, a.D, wg, nwg - g16);
     }
 }
 
@@ -1118,13 +1266,12 @@ template <typename T, int CHUNK>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_scan_mix(const ScanArgs a)
 {
     extern __shared__ __align__(16) float s_mem[];
-    scan_by_kind<T, CHUNK>(a, s_mem, a.d16, a.klo, 0);
+    scan_by_kind<T, CHUNK, 3, false>(a, s_mem, a.d16, a.klo, 0);
 }
 
-// Per-sequence chunk read from device memory: every geometry in one kernel, selected per workgroup (register budget
-// of the 16-step geometries).
-template <typename T>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_scan_any(const ScanArgs a)
+// Per-sequence chunk read from device memory: every geometry of the launch's kind in one kernel, selected per workgroup.
+template <typename T, int W, bool DIRECT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W))) void k_scan_any(const ScanArgs a)
 {
     extern __shared__ __align__(16) float s_mem[];
     const int chunk = resolve_chunk(a, blockIdx.y);
@@ -1139,7 +1286,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     const int split = plan_split(gridDim.y, a.D, a.N, chunk, d16, klo, a.allow_split);
 #define COREY_CASE(C)                                                                       \
     case C:                                                                                 \
-        scan_by_kind<T, C>(a, s_mem, d16, klo, split);                                      \
+        scan_by_kind<T, C, W, DIRECT>(a, s_mem, d16, klo, split);                           \
         break;
     switch (tile_of(chunk, a.rows_total)) {
         COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
@@ -1147,6 +1294,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     }
 #undef COREY_CASE
 }
+
+// The two large kernels of a storage type have a translation unit of their own (they take as long to compile as the rest).
+#define COREY_SCAN_ANY(how, T, W) how template __global__ void k_scan_any<T, W, false>(const ScanArgs);
+#ifndef COREY_SCAN_ANY_HERE
+COREY_SCAN_ANY(extern, float, 3) COREY_SCAN_ANY(extern, float, 4)
+COREY_SCAN_ANY(extern, uint16_t, 3) COREY_SCAN_ANY(extern, uint16_t, 4)
+COREY_SCAN_ANY(extern, _Float16, 3) COREY_SCAN_ANY(extern, _Float16, 4)
+#endif
 
 // ------------------------------------------------------------------------------------------- launch
 struct LaunchPlan {
@@ -1158,21 +1313,21 @@ struct LaunchPlan {
 
 inline int a_np(int64_t N) { return (int)((N + kMaxGroup - 1) / kMaxGroup * kMaxGroup); }
 
-template <int K, int CHUNK>
+template <int K, int CHUNK, bool DIRECT>
 inline void geometry(int64_t nrows, int64_t N, int rows_cap, int split, int64_t& gx, size_t& lds)
 {
     gx = 0;
     lds = 0;
-    if constexpr (geometry_exists<K, CHUNK>()) {
+    if constexpr (geometry_exists<K, CHUNK, DIRECT>()) {
         const int full = Geo<K, CHUNK>::ROWS / (split ? 2 : 1);
         int rows = full < rows_cap ? full : rows_cap;
         gx = (nrows + rows - 1) / rows;
-        lds = (size_t)lds_floats<K, CHUNK>(rows, a_np(N), split != 0) * sizeof(float);
+        lds = (size_t)lds_floats<K, CHUNK>(rows, a_np(N), split != 0, DIRECT) * sizeof(float);
     }
 }
 
 // Grid and LDS of a launch whose channels below d16 take 16 steps per lane and the others klo.
-template <int CHUNK>
+template <int CHUNK, bool DIRECT>
 inline void launch_geometry(const LaunchPlan& p, int rows_cap, int64_t d16, int klo, int split, int64_t& gx, size_t& lds)
 {
     gx = 0;
@@ -1180,27 +1335,21 @@ inline void launch_geometry(const LaunchPlan& p, int rows_cap, int64_t d16, int 
     int64_t g = 0;
     size_t l = 0;
     if (d16 > 0) {
-        geometry<16, CHUNK>(d16, p.N, rows_cap, split, g, l);
+        geometry<16, CHUNK, DIRECT>(d16, p.N, rows_cap, split, g, l);
         gx += g;
         lds = l > lds ? l : lds;
     }
     if (d16 < p.D) {
-        if (klo == 8) geometry<8, CHUNK>(p.D - d16, p.N, rows_cap, split, g, l);
-        else geometry<4, CHUNK>(p.D - d16, p.N, rows_cap, split, g, l);
+        if (klo == 8) geometry<8, CHUNK, DIRECT>(p.D - d16, p.N, rows_cap, split, g, l);
+        else geometry<4, CHUNK, DIRECT>(p.D - d16, p.N, rows_cap, split, g, l);
         gx += g;
         lds = l > lds ? l : lds;
     }
 }
 
-template <typename T>
-inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
+template <typename T, bool DIRECT>
+inline void launch_kernels(const ScanArgs& a, const LaunchPlan& p)
 {
-    // relayout of B and C: one 16-byte word per lane, enough workgroups to cover the operand a few times over
-    int64_t rb = (a.Np * a.Lpad / 4 + 255) / 256;
-    rb = rb < 1 ? 1 : (rb > 2048 ? 2048 : rb);
-    k_relayout_bc<T><<<dim3((unsigned)rb, (unsigned)p.B), dim3(256), 0, p.stream>>>(
-        static_cast<const T*>(a.Bm), static_cast<const T*>(a.Cm), a.ws_B, a.ws_C, a.ws_B8, a.ws_C8, a.seqlens, a.chunks_dev,
-        a.one_chunk, p.chunk, a.d16, a.klo, p.B, p.D, a.rows_cap, (int)p.N, a.Np, a.L, a.Lpad, a.route);
     int64_t gx = 0, g;
     size_t lds = 0, l;
     if (p.routed) {
@@ -1214,7 +1363,7 @@ inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
             l = 0;
 #define COREY_CASE(C)                                                                       \
     case C:                                                                                 \
-        launch_geometry<C>(p, a.rows_cap, d16_c, klo_c, split_c, g, l);                     \
+        launch_geometry<C, DIRECT>(p, a.rows_cap, d16_c, klo_c, split_c, g, l);             \
         break;
             switch (tile_of(c, p.B * p.D)) {
                 COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
@@ -1225,21 +1374,30 @@ inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
             if (c == p.chunk) gx = g;
         }
         if (gx < 2) gx = 2;     // two kinds of rows decided on the device need a workgroup for each kind (a surplus one leaves at once)
-        k_scan_any<T><<<dim3((unsigned)gx, (unsigned)p.B), dim3(kBlock), lds, p.stream>>>(a);
+        const dim3 grid((unsigned)gx, (unsigned)p.B), block(kBlock);
+        if constexpr (DIRECT) {
+            k_scan_any<T, waves_target<T, 16, 1024, true>(), true><<<grid, block, lds, p.stream>>>(a);
+        } else {
+            // registers for the long tiles: three waves per SIMD if those give two kinds of rows, or if the sequences' lengths
+            // differ (the longest one's waves, a part of the launch, decide: 233 us against 254 for the padded pair); else four
+            const int64_t d16_512 = plan_d16(p.B, p.D, 512, a.rows_cap);
+            if ((d16_512 > 0 && d16_512 < p.D) || a.seqlens) k_scan_any<T, 3, false><<<grid, block, lds, p.stream>>>(a);
+            else k_scan_any<T, 4, false><<<grid, block, lds, p.stream>>>(a);
+        }
         return;
     }
+    const dim3 block(kBlock);
 #define COREY_LAUNCH(K, C)                                                                  \
-    if constexpr (geometry_exists<K, C>())                                                  \
-        k_scan<T, K, C><<<dim3((unsigned)gx, (unsigned)p.B), dim3(kBlock), lds, p.stream>>>(a)
+    if constexpr (geometry_exists<K, C, DIRECT>()) k_scan<T, K, C, DIRECT><<<dim3((unsigned)gx, (unsigned)p.B), block, lds, p.stream>>>(a)
 #define COREY_CASE(C)                                                                       \
     case C:                                                                                 \
-        launch_geometry<C>(p, a.rows_cap, a.d16, a.klo, a.split, gx, lds);                   \
+        launch_geometry<C, DIRECT>(p, a.rows_cap, a.d16, a.klo, a.split, gx, lds);           \
         if (a.d16 >= p.D) { COREY_LAUNCH(16, C); }                                          \
-        else if constexpr (C <= 512) {                                                      \
-            if (a.d16 > 0) k_scan_mix<T, C><<<dim3((unsigned)gx, (unsigned)p.B), dim3(kBlock), lds, p.stream>>>(a);                 \
-            else if (a.klo == 8) { COREY_LAUNCH(8, C); }                                    \
-            else { COREY_LAUNCH(4, C); }                                                    \
+        else if (a.d16 > 0) {                                                               \
+            if constexpr (!DIRECT && C <= 512) k_scan_mix<T, C><<<dim3((unsigned)gx, (unsigned)p.B), block, lds, p.stream>>>(a);   \
         }                                                                                   \
+        else if (a.klo == 8) { COREY_LAUNCH(8, C); }                                        \
+        else { COREY_LAUNCH(4, C); }                                                        \
         break;
     switch (tile_of(p.chunk, p.B * p.D)) {
         COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
@@ -1247,6 +1405,22 @@ inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
     }
 #undef COREY_CASE
 #undef COREY_LAUNCH
+}
+
+template <typename T>
+inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
+{
+    if (a.direct) {
+        launch_kernels<T, true>(a, p);
+        return;
+    }
+    // relayout of B and C: one 16-byte word per lane, enough workgroups to cover the operand a few times over
+    int64_t rb = (a.Np * a.Lpad / 4 + 255) / 256;
+    rb = rb < 1 ? 1 : (rb > 2048 ? 2048 : rb);
+    k_relayout_bc<T><<<dim3((unsigned)rb, (unsigned)p.B), dim3(256), 0, p.stream>>>(
+        static_cast<const T*>(a.Bm), static_cast<const T*>(a.Cm), a.ws_B, a.ws_C, a.ws_B8, a.ws_C8, a.seqlens, a.chunks_dev,
+        a.one_chunk, p.chunk, a.d16, a.klo, p.B, p.D, a.rows_cap, (int)p.N, a.Np, a.L, a.Lpad, a.route);
+    launch_kernels<T, false>(a, p);
 }
 
 }  // namespace corey_scan

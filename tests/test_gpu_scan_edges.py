@@ -1,0 +1,66 @@
+"""The scan at the edges of its dispatch: rows of any length (vectors that straddle a row's end, rows shorter than a lane's
+run), launches on either side of the row counts where B and C are read directly and where long chunks are walked in parts of
+512, padding that holds NaN."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_10597_amd as corey
+from gpu_util import assert_close, check_y, fp32_rtol, oracle_scan, upload, y_to_f64
+from paper_2604_10597_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _scan(d, chunk, **kw):
+    return corey.selective_scan_fwd(d["u"], d["delta"], d["A"], d["B"], d["C"], Dv=d["D"], z=d["z"], delta_bias=d["delta_bias"],
+                                    h0=d.get("h0"), seqlens=d["seqlens"], chunk=chunk, **kw)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
+@pytest.mark.parametrize("B,D,N,L", [(1, 5, 16, 1), (2, 3, 16, 15), (2, 3, 16, 16), (1, 7, 16, 17), (2, 5, 8, 1031), (1, 3, 4, 1023),
+                                     (2, 2, 16, 2049), (1, 6, 20, 527), (2, 3, 6, 77), (1, 4, 1, 1025)])
+def test_rows_of_any_length(B, D, N, L, dtype):
+    cfg = wl.Config("edges", B, D, N, L, dtype, 16, (), seed=4000 + L + N)
+    w = wl.make(cfg, a_kind="random", with_h0=True)
+    d = upload(w)
+    y_ref, s_ref = oracle_scan(w)
+    for chunk in (16, 64, 256, 512, 1024, 2048):
+        for whole in (False, True):
+            y, s = _scan(d, chunk, whole_rows=whole)
+            check_y(y_to_f64(y), y_ref, cfg, f"y chunk {chunk}")
+            assert_close(s.cpu().numpy(), s_ref, fp32_rtol(L), f"state chunk {chunk}")
+
+
+@pytest.mark.parametrize("dtype,D", [(wl.BF16, 3), (wl.F32, 3), (wl.BF16, 1100)])
+def test_padding_is_never_read_into_a_result(dtype, D):
+    """Sequences shorter than L whose padded positions hold NaN in every input."""
+    lens = (1, 29, 543, 1030)
+    cfg = wl.Config("edges_nan", 4, D, 16, 1031, dtype, 16, (), seqlens=lens, seed=4100)
+    w = wl.make(cfg, a_kind="random")
+    d = upload(w)
+    for b, n in enumerate(lens):
+        for name in ("u", "delta", "z", "B", "C"):
+            d[name][b, :, n:] = float("nan")
+    rows = np.arange(3) if D > 3 else None
+    y_ref, s_ref = oracle_scan(w, rows=rows)
+    for chunk in (64, 512, 1024):
+        y, s = _scan(d, chunk)
+        assert torch.isfinite(y.float()).all() and torch.isfinite(s).all()
+        check_y(y_to_f64(y)[:, :3], y_ref, cfg, f"y chunk {chunk}")
+        assert_close(s.cpu().numpy()[:, :3], s_ref, fp32_rtol(cfg.L), f"state chunk {chunk}")
+
+
+@pytest.mark.parametrize("B,D", [(1, 3072), (1, 3073), (1, 4096), (1, 4097), (3, 1366)])
+def test_either_side_of_the_row_counts_the_launch_changes_at(B, D):
+    """3072 rows read B and C directly, more are staged; beyond 4096 rows tiles are at most 512 steps, of two kinds of rows."""
+    cfg = wl.Config("edges_rows", B, D, 16, 1100, wl.BF16, 16, (), seed=4200)
+    w = wl.make(cfg, a_kind="random")
+    d = upload(w)
+    rows = np.unique(np.concatenate([[0, 1, D - 2, D - 1], np.random.default_rng(3).integers(0, D, 6)]))
+    y_ref, s_ref = oracle_scan(w, rows=rows)
+    routed = torch.full((B,), 1024, dtype=torch.int32, device="cuda")
+    for chunk, dev in ((512, None), (1024, None), (2048, None), (512, routed)):
+        y, s = _scan(d, chunk, chunks_dev=dev)
+        check_y(y_to_f64(y)[:, rows], y_ref, cfg, f"y chunk {chunk}")
+        assert_close(s.cpu().numpy()[:, rows], s_ref, fp32_rtol(cfg.L), f"state chunk {chunk}")
