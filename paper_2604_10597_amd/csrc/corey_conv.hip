@@ -1,17 +1,20 @@
 // causal_conv1d_silu_fwd: the causal depthwise convolution and SiLU that produce the scan input u, with the range of
 // u (what the histogram's first sweep would compute) taken in the same pass.
 //
-// One kernel.  A workgroup of 256 lanes takes (row, segment) units grid-stride, two at a time so that their loads are
-// in flight together; per unit a lane owns one 16-byte vector of consecutive time steps, loads it and the vector
-// before it (the W - 1 <= 3 earlier inputs the taps reach back to;
-// at the start of a row they come from state_in or are zero), accumulates the taps oldest first with fused
-// multiply-adds in binary32, applies v * sigmoid(v), rounds to the storage type and stores 16 bytes.  The minimum
-// and maximum are taken over the values as stored (the histogram will see those bits), kept per lane and reduced
-// once per workgroup into a partial range; corey_entropy_hist reduces the COREY_RANGE_PARTS partials.
+// Three kernels, one launch each:
+//   k_conv1d_silu        rows of at least two vectors.  A lane takes 16-byte vectors of consecutive time steps, whichever rows
+//                        they fall in, two at a time so that their loads are in flight together.
+//   k_conv1d_silu_step   one step (generation): a lane takes the 4 bytes of x that one (fp32) or two rows make up, and the
+//                        window of earlier inputs beside them.
+//   k_conv1d_silu_short  what is left, a lane per row.
+// The taps are accumulated oldest first with fused multiply-adds in binary32, v * sigmoid(v) is rounded once to the storage
+// type.  The minimum and maximum are taken over the values as stored (the histogram will see those bits), kept per lane and
+// reduced once per workgroup into a partial range; corey_entropy_hist reduces the COREY_RANGE_PARTS partials.
 // Bandwidth work (x in, u out): no matrix instructions.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "corey_internal.h"
 #include "corey_range.h"
@@ -26,12 +29,9 @@ using corey_range::Handoff;
 using corey_range::RangePart;
 using corey_range::reduce_range_keys;
 
-#ifndef COREY_CONV_UNITS
-#define COREY_CONV_UNITS 2
-#endif
-
 constexpr float kLog2e = 1.4426950408889634f;
 typedef uint32_t word4 __attribute__((ext_vector_type(4)));
+typedef uint32_t word4e __attribute__((ext_vector_type(4), aligned(2)));     // at any element
 typedef float float2v __attribute__((ext_vector_type(2)));
 
 // Storage type: widen one element, round a vector of values (to nearest even), elements per 16-byte vector.
@@ -66,7 +66,11 @@ template <> struct St<_Float16> {
     static __device__ __forceinline__ void narrow(const float (&v)[8], _Float16 (&out)[8])
     {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = (_Float16)v[e];
+        for (int e = 0; e < 8; ++e) {
+            float f = v[e];
+            asm("" : "+v"(f));      // the binary32 value, which the range follows too, is what is rounded: seen together with the
+            out[e] = (_Float16)f;   // product it comes from, the compiler may round that to binary16 in one step (v_fma_mixlo)
+        }
     }
 };
 
@@ -87,38 +91,22 @@ __device__ __forceinline__ float vmax(float a, float b)
 
 constexpr int H = COREY_MAX_CONV - 1;                     // most earlier inputs a tap reaches back to
 
-// The inputs one lane needs for one vector of outputs: xs[H + e] = x[t0 + e] and the H inputs before them
-// (xs[H - k] = x[t0 - k]), from the previous vector of the row, from state_in before the row starts, or zero.
+// The inputs one lane needs for one vector of outputs, one by one: xs[H + e] = x[t0 + e] and the H inputs before them
+// (xs[H - k] = x[t0 - k]), from state_in before the row starts, or zero.
 template <typename T>
 __device__ __forceinline__ void load_inputs(const T* __restrict__ xr, const T* __restrict__ state_row, int64_t t0, int nvalid,
-                                            int W, bool vector_ok, float (&xs)[H + St<T>::kVec])
+                                            int W, float (&xs)[H + St<T>::kVec])
 {
     constexpr int V = St<T>::kVec;
-    if (vector_ok && nvalid == V) {
-        T cur[V];
-        const word4 q = *reinterpret_cast<const word4*>(xr + t0);
-        __builtin_memcpy(cur, &q, 16);
 #pragma unroll
-        for (int e = 0; e < V; ++e) xs[H + e] = St<T>::widen(cur[e]);
-    } else {
+    for (int e = 0; e < V; ++e) xs[H + e] = (e < nvalid) ? St<T>::widen(xr[t0 + e]) : 0.f;
 #pragma unroll
-        for (int e = 0; e < V; ++e) xs[H + e] = (e < nvalid) ? St<T>::widen(xr[t0 + e]) : 0.f;
-    }
-    if (t0 >= V && vector_ok) {
-        T prev[V];
-        const word4 q = *reinterpret_cast<const word4*>(xr + t0 - V);
-        __builtin_memcpy(prev, &q, 16);
-#pragma unroll
-        for (int k = 1; k <= H; ++k) xs[H - k] = St<T>::widen(prev[V - k]);
-    } else {
-#pragma unroll
-        for (int k = 1; k <= H; ++k) {
-            const int64_t t = t0 - k;
-            float v = 0.f;
-            if (t >= 0) v = St<T>::widen(xr[t]);
-            else if (state_row && t + (W - 1) >= 0) v = St<T>::widen(state_row[t + (W - 1)]);
-            xs[H - k] = v;
-        }
+    for (int k = 1; k <= H; ++k) {
+        const int64_t t = t0 - k;
+        float v = 0.f;
+        if (t >= 0) v = St<T>::widen(xr[t]);
+        else if (state_row && t + (W - 1) >= 0) v = St<T>::widen(state_row[t + (W - 1)]);
+        xs[H - k] = v;
     }
 }
 
@@ -146,39 +134,43 @@ __device__ __forceinline__ void conv_vector(const float (&xs)[H + St<T>::kVec], 
     St<T>::narrow(val, out);
 }
 
-// Position of a workgroup's next unit: row, segment within the row, channel of the row.  Units are numbered
-// row * nseg + seg and a workgroup visits every gridDim.x-th one; stepping the three coordinates by the quotient and
-// remainder of that stride keeps the 64-bit divisions out of the loop.
+// A lane's position: vector v of row `row`, whose channel is d.  A lane visits every step-th vector (step: the lanes of the
+// launch), numbered row * nvec + v; the host divides that stride once (q rows, rem vectors, qd channels), the lane only adds.
 struct Cursor {
-    int64_t row, seg, d;
+    int64_t row, v, d;
 };
-struct Stride {
-    int64_t q, rem, qd, nseg, D;
+struct Walk {
+    int64_t rows, D, L;
+    int64_t nvec;            // vectors of a row: ceil(L / V)
+    int64_t turns;           // vectors of a lane
+    int64_t q, rem, qd;
 };
-__device__ __forceinline__ Cursor advance(Cursor c, const Stride& s)
+__device__ __forceinline__ Cursor advance(Cursor c, const Walk& s)
 {
-    c.seg += s.rem;
-    const int64_t carry = (c.seg >= s.nseg) ? 1 : 0;
-    c.seg -= carry ? s.nseg : 0;
+    c.v += s.rem;
+    const int64_t carry = (c.v >= s.nvec) ? 1 : 0;
+    c.v -= carry ? s.nvec : 0;
     c.row += s.q + carry;
     c.d += s.qd + carry;
     c.d -= (c.d >= s.D) ? s.D : 0;
     return c;
 }
+// n / d of a lane or workgroup number: 32 bits whatever the tensor (a divisor beyond them gives 0 either way)
+__device__ __forceinline__ uint32_t quotient(uint32_t n, int64_t d) { return n / (uint32_t)min(d, (int64_t)0x7fffffff); }
 
-// Count the stored values of one vector in the workgroup's bit-pattern table (16-bit storage).
+// Count the values of one vector, without its first `skip`, in the workgroup's bit-pattern table (16-bit storage).
 template <typename T>
-__device__ __forceinline__ void table_add_vector(uint32_t* s_tab, corey_table::Shared& sh, const T (&out)[St<T>::kVec], int nvalid)
+__device__ __forceinline__ void table_add_vector(uint32_t* s_tab, corey_table::Shared& sh, const T (&out)[St<T>::kVec], int skip, int nvalid)
 {
     if constexpr (sizeof(T) == 2) {
-        if (nvalid == St<T>::kVec) {
+        if (skip == 0 && nvalid == St<T>::kVec) {
             uint32_t w[4];
             __builtin_memcpy(w, out, 16);
             corey_table::add_word4(s_tab, sh, w);
         } else {
 #pragma unroll
             for (int e = 0; e < St<T>::kVec; ++e) {
-                if (e < nvalid) {
+                if (e >= skip && e < nvalid) {
                     uint16_t bits;
                     __builtin_memcpy(&bits, &out[e], 2);
                     corey_table::add(s_tab, sh, bits);
@@ -188,20 +180,53 @@ __device__ __forceinline__ void table_add_vector(uint32_t* s_tab, corey_table::S
     }
 }
 
-// NT lanes per workgroup.  TABLE: the workgroup also counts the bit patterns of the values it stores (corey_table.h:
-// NT = corey_table::kLanes, at most corey_table::kMaxSlabs workgroups, 16-bit storage); a turn of the unit loop adds at
-// most U * NT * 8 = 16384 values and ends at a barrier, inside the table's bound of 32768 per round.
-template <typename T, int W, int NT, bool TABLE>
+// What a workgroup leaves for the statistic: the extremes rounded once to the storage type, the workgroup's partial range
+// (entries no workgroup owns say "nothing seen").
+template <typename T> __device__ __forceinline__ void round_extremes(float& lo, float& hi)
+{
+    if (lo <= hi) {
+        float pad[St<T>::kVec];
+        T st[St<T>::kVec];
+#pragma unroll
+        for (int e = 0; e < St<T>::kVec; ++e) pad[e] = (e == 0) ? lo : hi;
+        St<T>::narrow(pad, st);
+        lo = St<T>::widen(st[0]);
+        hi = St<T>::widen(st[1]);
+    }
+}
+template <int NT> __device__ __forceinline__ void write_parts(RangePart* rparts, uint32_t klo, uint32_t khi, uint32_t knan)
+{
+    if (threadIdx.x == 0) {
+        RangePart rp;
+        rp.lo_key = klo; rp.hi_key = khi; rp.saw_nan = knan; rp.pad = 0u;
+        rparts[blockIdx.x] = rp;
+    }
+    if (blockIdx.x == 0)
+        for (int i = gridDim.x + threadIdx.x; i < COREY_RANGE_PARTS; i += NT) {
+            RangePart rp;
+            rp.lo_key = 0xffffffffu; rp.hi_key = 0u; rp.saw_nan = 0u; rp.pad = 0u;
+            rparts[i] = rp;
+        }
+}
+
+// NT lanes per workgroup.  A row's last vector is moved back to end with the row, so that every vector is whole: the values it
+// shares with the one before are computed and stored twice, with the same bits (and their range is the same).  That needs
+// L >= 2 V (the H inputs before a vector that does not start its row are then in the row, too).  Lanes beyond the last vector
+// redo it.  No row needs to be aligned: gfx950 takes 16-byte accesses at any element's address.
+// TABLE: the workgroup also counts the bit patterns of the values it stores (corey_table.h: NT = corey_table::kLanes, at most
+// corey_table::kMaxSlabs workgroups, 16-bit storage; each value once: the shared ones by the vector before); a turn of the
+// loop adds at most U * NT * 8 = 16384 values and ends at a barrier, inside the table's bound of 32768 per round.  Rows of
+// fewer than two vectors come here with TABLE only, and are read value by value.
+template <typename T, int W, int NT, bool TABLE, bool WAVES>
 __global__ __launch_bounds__(NT) void k_conv1d_silu(const T* __restrict__ x, const float* __restrict__ weight,
                                                     const float* __restrict__ bias, const T* __restrict__ state_in,
                                                     T* __restrict__ u, T* __restrict__ state_out, Handoff* __restrict__ handoff,
-                                                    void* table_ws, int64_t rows, int64_t D, int64_t L, int vector_ok)
+                                                    void* table_ws, const Walk wk)
 {
-    RangePart* rparts = handoff ? handoff->parts : nullptr;
     if (handoff) corey_range::clear_handoff_counts(handoff);   // the statistic's count sweep adds into them
-    constexpr int kThreads = NT;                              // (shadows the 256 of the other kernels in this file)
     constexpr int V = St<T>::kVec;
-    constexpr int U = COREY_CONV_UNITS;                       // units in flight per lane: their loads go out together
+    constexpr int U = 2;                                      // vectors in flight per lane
+    constexpr int P = H + 1;                                  // values fetched before a vector: 8 or 16 bytes
     static_assert(!TABLE || (NT == corey_table::kLanes && U * NT * 8 <= corey_table::kRoundAdds && sizeof(T) == 2),
                   "a turn must stay inside the table's round");
     __shared__ uint32_t s_tab[TABLE ? corey_table::kWords : 1];
@@ -211,121 +236,101 @@ __global__ __launch_bounds__(NT) void k_conv1d_silu(const T* __restrict__ x, con
         tws = corey_table::carve(table_ws);
         corey_table::begin(s_tab, sh, tws);
     }
-    constexpr int64_t kSeg = (int64_t)kThreads * V;
-    const int64_t nseg = (L + kSeg - 1) / kSeg;
-    const int64_t nfull = vector_ok ? L / kSeg : 0;           // segments of a row that are whole and aligned
-    Stride st;
-    st.nseg = nseg;
-    st.D = D;
-    st.q = (int64_t)gridDim.x / nseg;
-    st.rem = (int64_t)gridDim.x - st.q * nseg;
-    st.qd = st.q % D;
+    const int64_t L = wk.L;
+    // WAVES: the position of the wave's first lane, uniform
+    const uint32_t tid = WAVES ? __builtin_amdgcn_readfirstlane(threadIdx.x) : threadIdx.x;
+    const int64_t sub = WAVES ? threadIdx.x & 63 : 0;
+    const uint32_t lane = blockIdx.x * NT + tid;
     Cursor cur;
-    cur.row = (int64_t)blockIdx.x / nseg;
-    cur.seg = (int64_t)blockIdx.x - cur.row * nseg;
-    cur.d = cur.row % D;
+    cur.row = quotient(lane, wk.nvec);
+    cur.v = lane - cur.row * wk.nvec;
+    cur.d = cur.row - quotient((uint32_t)cur.row, wk.D) * wk.D;
     float lo = INFINITY, hi = -INFINITY;
     bool nan = false;
 
-    while (cur.row < rows) {
-        Cursor c[U];
-        c[0] = cur;
-        bool all_full = cur.seg < nfull;
+    auto vectors = [&](auto nu) {
+        constexpr int NU = decltype(nu)::value;
+        Cursor c[NU];
+        int64_t t0[NU], off[NU];
+        bool past[NU];
+        T curv[NU][V], prev[NU][P];
+        float w[NU][W], bs[NU];
 #pragma unroll
-        for (int j = 1; j < U; ++j) {
-            c[j] = advance(c[j - 1], st);
-            all_full = all_full && c[j].row < rows && c[j].seg < nfull;
-        }
-        cur = advance(c[U - 1], st);
-        if (all_full) {                                       // uniform over the workgroup
-            float xs[U][H + V], w[U][W], bs[U];
-            word4 qc[U], qp[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {                     // every load of these units before any use
-                const T* xr = x + c[j].row * L;
-                const int64_t t0 = c[j].seg * kSeg + (int64_t)threadIdx.x * V;
-                qc[j] = *reinterpret_cast<const word4*>(xr + t0);
-                qp[j] = *reinterpret_cast<const word4*>(xr + (t0 >= V ? t0 - V : 0));
-#pragma unroll
-                for (int k = 0; k < W; ++k) w[j][k] = weight[c[j].d * W + k];
-                bs[j] = bias ? bias[c[j].d] : 0.f;
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                T curv[V], prev[V];
-                __builtin_memcpy(curv, &qc[j], 16);
-                __builtin_memcpy(prev, &qp[j], 16);
-#pragma unroll
-                for (int e = 0; e < V; ++e) xs[j][H + e] = St<T>::widen(curv[e]);
-#pragma unroll
-                for (int k = 1; k <= H; ++k) xs[j][H - k] = St<T>::widen(prev[V - k]);
-                if (c[j].seg == 0) {                          // the row starts in this unit: its first lane looks before t = 0
-#pragma unroll
-                    for (int k = 1; k <= H; ++k) {
-                        float head = 0.f;
-                        if (state_in && k <= W - 1) head = St<T>::widen(state_in[c[j].row * (W - 1) + (W - 1 - k)]);
-                        xs[j][H - k] = (threadIdx.x == 0) ? head : xs[j][H - k];
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                T out[V];
-                conv_vector<T, W, true>(xs[j], w[j], bs[j], V, out, lo, hi, nan);
-                word4 q;
-                __builtin_memcpy(&q, out, 16);
-                // streaming store: u is written once and far exceeds the caches; leaving them to the loads measured 9 %
-                // faster (5.4 against 4.9 TB/s, what a device copy reaches) with the next kernel's reads no slower
-                __builtin_nontemporal_store(q, reinterpret_cast<word4*>(u + c[j].row * L + c[j].seg * kSeg + (int64_t)threadIdx.x * V));
-                if constexpr (TABLE) table_add_vector<T>(s_tab, sh, out, V);
-            }
-            if constexpr (TABLE) __syncthreads();             // end of the table's round
-            continue;
+        for (int j = 0; j < NU; ++j) {                        // every load of these vectors before any use
+            past[j] = cur.row >= wk.rows;
+            c[j] = cur;
+            if (past[j]) c[j] = Cursor{wk.rows - 1, wk.nvec - (WAVES ? 64 : 1), wk.D - 1};
+            cur = advance(cur, wk);
+            t0[j] = WAVES ? (c[j].v + sub) * V : min(c[j].v * V, L - V);
+            off[j] = c[j].row * L + t0[j];
+            __builtin_memcpy(curv[j], x + off[j], 16);
+            __builtin_memcpy(prev[j], x + (t0[j] > 0 ? off[j] - P : off[j]), sizeof(T) * P);
+            __builtin_memcpy(w[j], weight + c[j].d * W, sizeof(float) * W);
+            bs[j] = bias ? bias[c[j].d] : 0.f;
         }
 #pragma unroll
-        for (int j = 0; j < U; ++j) {                         // ragged or unaligned units, one at a time
-            if (c[j].row >= rows) break;
-            const int64_t t0 = c[j].seg * kSeg + (int64_t)threadIdx.x * V;
-            if (t0 >= L) continue;
-            const int nvalid = (L - t0 < V) ? (int)(L - t0) : V;
-            float xs[H + V], w[W];
-            load_inputs<T>(x + c[j].row * L, state_in ? state_in + c[j].row * (W - 1) : nullptr, t0, nvalid, W, vector_ok != 0, xs);
+        for (int j = 0; j < NU; ++j) {
+            float xs[H + V];
 #pragma unroll
-            for (int k = 0; k < W; ++k) w[k] = weight[c[j].d * W + k];
+            for (int e = 0; e < V; ++e) xs[H + e] = St<T>::widen(curv[j][e]);
+#pragma unroll
+            for (int k = 1; k <= H; ++k) xs[H - k] = St<T>::widen(prev[j][P - k]);
+            if ((!WAVES || c[j].v == 0) && t0[j] == 0) {                                 // the row starts here: its past is in state_in, or zero
+#pragma unroll
+                for (int k = 1; k <= H; ++k)
+                    xs[H - k] = (state_in && k <= W - 1) ? St<T>::widen(state_in[c[j].row * (W - 1) + (W - 1 - k)]) : 0.f;
+            }
             T out[V];
-            conv_vector<T, W, false>(xs, w, bias ? bias[c[j].d] : 0.f, nvalid, out, lo, hi, nan);
-            T* ur = u + c[j].row * L + t0;
-            if (vector_ok && nvalid == V) {
-                word4 q;
-                __builtin_memcpy(&q, out, 16);
-                *reinterpret_cast<word4*>(ur) = q;
-            } else {
-#pragma unroll
-                for (int e = 0; e < V; ++e)
-                    if (e < nvalid) ur[e] = out[e];
-            }
-            if constexpr (TABLE) table_add_vector<T>(s_tab, sh, out, nvalid);
+            conv_vector<T, W, true>(xs, w[j], bs[j], V, out, lo, hi, nan);
+            word4 q;
+            __builtin_memcpy(&q, out, 16);
+            __builtin_nontemporal_store(q, reinterpret_cast<word4e*>(u + off[j]));
+            if constexpr (TABLE)
+                if (!past[j]) table_add_vector<T>(s_tab, sh, out, (int)(c[j].v * V - t0[j]), V);
         }
-        if constexpr (TABLE) __syncthreads();                 // end of the table's round (the loop condition is uniform)
-    }
-    if (lo <= hi) {                                           // the stored extremes: one rounding each
-        float pad[V], two[V];
-        T st[V];
+    };
+    auto values = [&]() {                                     // one vector of a row of fewer than two
+        const Cursor c = cur;
+        cur = advance(cur, wk);
+        if (c.row >= wk.rows) return;
+        const T* xr = x + c.row * L;
+        const T* sr = state_in ? state_in + c.row * (W - 1) : nullptr;
+        const int64_t t0 = c.v * V;
+        const int nvalid = (L - t0 < V) ? (int)(L - t0) : V;
+        float xs[H + V], w[W];
+        load_inputs<T>(xr, sr, t0, nvalid, W, xs);
 #pragma unroll
-        for (int e = 0; e < V; ++e) pad[e] = (e == 0) ? lo : hi;
-        St<T>::narrow(pad, st);
-        two[0] = St<T>::widen(st[0]);
-        two[1] = St<T>::widen(st[1]);
-        lo = two[0];
-        hi = two[1];
+        for (int k = 0; k < W; ++k) w[k] = weight[c.d * W + k];
+        T out[V];
+        conv_vector<T, W, false>(xs, w, bias ? bias[c.d] : 0.f, nvalid, out, lo, hi, nan);
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (e < nvalid) u[c.row * L + t0 + e] = out[e];
+        table_add_vector<T>(s_tab, sh, out, 0, nvalid);
+    };
+
+    int64_t left = wk.turns;                                  // uniform
+    if (TABLE && L < 2 * V) {
+        for (; left > 0; --left) {
+            values();
+            __syncthreads();                                  // end of the table's round
+        }
+    } else {
+        for (; left >= U; left -= U) {
+            vectors(std::integral_constant<int, U>{});
+            if constexpr (TABLE) __syncthreads();
+        }
+        if (left > 0) {
+            vectors(std::integral_constant<int, 1>{});
+            if constexpr (TABLE) __syncthreads();
+        }
     }
 
-    if (state_out && W > 1) {                                 // the last W - 1 inputs of every row, oldest first
-        const int64_t n = rows * (W - 1);
-        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
-            const int64_t r = i / (W - 1);
-            const int k = (int)(i - r * (W - 1));
-            const int64_t t = L - (W - 1) + k;
+    if (W > 1 && state_out) {                                 // the last W - 1 inputs of every row, oldest first: side by side
+        const int64_t n = wk.rows * (W - 1);                  // over the lanes (written with the rows' last vectors, a few bytes
+        for (int64_t i = blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {     // of a line from each XCD, they cost 5 % of the kernel)
+            const int64_t r = i / (W - 1 > 0 ? W - 1 : 1);
+            const int64_t t = L - (W - 1) + (i - r * (W - 1));
             T v = T(0);
             if (t >= 0) v = x[r * L + t];
             else if (state_in) v = state_in[r * (W - 1) + (t + (W - 1))];
@@ -333,43 +338,120 @@ __global__ __launch_bounds__(NT) void k_conv1d_silu(const T* __restrict__ x, con
         }
     }
 
-    if (rparts || TABLE) {
+    if (handoff || TABLE) {
+        round_extremes<T>(lo, hi);
         uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
         uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
         uint32_t knan = nan ? 1u : 0u;
         if constexpr (TABLE) corey_table::end(s_tab, sh, tws, klo, khi, knan);     // also reduces the keys into thread 0
         else reduce_range_keys<NT>(klo, khi, knan);
-        if (rparts && threadIdx.x == 0) {
-            RangePart rp;
-            rp.lo_key = klo; rp.hi_key = khi; rp.saw_nan = knan; rp.pad = 0u;
-            rparts[blockIdx.x] = rp;
-        }
-        // entries no workgroup owns say "nothing seen"
-        if (rparts && blockIdx.x == 0)
-            for (int i = gridDim.x + threadIdx.x; i < COREY_RANGE_PARTS; i += kThreads) {
-                RangePart rp;
-                rp.lo_key = 0xffffffffu; rp.hi_key = 0u; rp.saw_nan = 0u; rp.pad = 0u;
-                rparts[i] = rp;
-            }
+        if (handoff) write_parts<NT>(handoff->parts, klo, khi, knan);
     }
 }
 
-// Sequences of a few steps (generation: L = 1 with the carried state): one lane per row instead of one workgroup
-// per row segment.  A lane keeps the row's window of W - 1 earlier inputs in registers and walks its L steps.
-constexpr int kShortL = 16;
+// One step with the carried state (generation): bound by the window it moves (W - 1 values in, W - 1 out beside one of x and u).
+// A lane takes R rows, as many as 4 bytes of x hold: the windows of R rows are then whole words (12 bytes at four taps), side by
+// side over the wave.  Up to kStepUnits groups of rows of a lane are in flight together.
+// R = 2 needs an even D and rows that start at words (the caller checks); other 16-bit tensors take the kernel below.
+constexpr int kStepUnits = 4;
 
+template <typename T, int W>
+__global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restrict__ x, const float* __restrict__ weight,
+                                                               const float* __restrict__ bias, const T* __restrict__ state_in,
+                                                               T* __restrict__ u, T* __restrict__ state_out,
+                                                               Handoff* __restrict__ handoff, const Walk wk, int units)
+{
+    if (handoff) corey_range::clear_handoff_counts(handoff);
+    constexpr int R = 4 / (int)sizeof(T);
+    constexpr int NS = R * (W - 1);                           // values of R windows
+    float lo = INFINITY, hi = -INFINITY;
+    bool nan = false;
+    const uint32_t lane = blockIdx.x * kThreads + threadIdx.x;
+    Cursor cur;                                               // row: sequence; v: group of R channels within it
+    cur.row = quotient(lane, wk.nvec);
+    cur.v = lane - cur.row * wk.nvec;
+    cur.d = 0;
+    for (int64_t left = wk.turns; left > 0; left -= units) {  // uniform, like the tests of `units` below
+        const int nu = left < units ? (int)left : units;
+        int64_t r[kStepUnits];                                // first row of the group
+        T xv[kStepUnits][R], win[kStepUnits][NS > 0 ? NS : 1];
+        float w[kStepUnits][R * W], bs[kStepUnits][R];
+#pragma unroll
+        for (int j = 0; j < kStepUnits; ++j) {
+            if (j < nu) {
+                Cursor c = cur;
+                if (c.row >= wk.rows) c = Cursor{wk.rows - 1, wk.nvec - 1, 0};     // lanes beyond the last group redo it
+                cur.v += wk.rem;
+                const int64_t carry = (cur.v >= wk.nvec) ? 1 : 0;
+                cur.v -= carry ? wk.nvec : 0;
+                cur.row += wk.q + carry;
+                r[j] = (c.row * wk.nvec + c.v) * R;
+                const int64_t d = c.v * R;
+                __builtin_memcpy(xv[j], __builtin_assume_aligned(x + r[j], 4), 4);
+                if (W > 1) {
+                    if (state_in) {
+                        __builtin_memcpy(win[j], __builtin_assume_aligned(state_in + r[j] * (W - 1), 4), sizeof(T) * NS);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < NS; ++k) win[j][k] = T(0);
+                    }
+                }
+                __builtin_memcpy(w[j], weight + d * W, sizeof(float) * R * W);
+#pragma unroll
+                for (int i = 0; i < R; ++i) bs[j][i] = bias ? bias[d + i] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kStepUnits; ++j) {
+            if (j < nu) {
+                T out[R], moved[NS > 0 ? NS : 1];
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    float acc = bs[j][i];
+#pragma unroll
+                    for (int k = 0; k < W - 1; ++k) acc = fmaf(w[j][i * W + k], St<T>::widen(win[j][i * (W - 1) + k]), acc);
+                    acc = fmaf(w[j][i * W + W - 1], St<T>::widen(xv[j][i]), acc);
+                    const float val = acc * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-acc * kLog2e));
+                    nan |= (val != val);
+                    lo = vmin(lo, val);
+                    hi = vmax(hi, val);
+                    float one[St<T>::kVec];
+                    T st[St<T>::kVec];
+#pragma unroll
+                    for (int e = 0; e < St<T>::kVec; ++e) one[e] = val;
+                    St<T>::narrow(one, st);
+                    out[i] = st[0];
+#pragma unroll
+                    for (int k = 0; k < W - 1; ++k) moved[i * (W - 1) + k] = (k + 1 < W - 1) ? win[j][i * (W - 1) + k + 1] : xv[j][i];
+                }
+                __builtin_memcpy(__builtin_assume_aligned(u + r[j], 4), out, 4);
+                if (W > 1 && state_out) __builtin_memcpy(__builtin_assume_aligned(state_out + r[j] * (W - 1), 4), moved, sizeof(T) * NS);
+            }
+        }
+    }
+    if (handoff) {
+        round_extremes<T>(lo, hi);
+        uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
+        uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
+        uint32_t knan = nan ? 1u : 0u;
+        reduce_range_keys(klo, khi, knan);
+        write_parts<kThreads>(handoff->parts, klo, khi, knan);
+    }
+}
+
+// Rows of fewer than two vectors (a few steps with the carried state): one lane per row.  A lane keeps the row's window of
+// W - 1 earlier inputs in registers and walks its L steps.
 template <typename T, int W>
 __global__ __launch_bounds__(kThreads) void k_conv1d_silu_short(const T* __restrict__ x, const float* __restrict__ weight,
                                                                 const float* __restrict__ bias, const T* __restrict__ state_in,
                                                                 T* __restrict__ u, T* __restrict__ state_out,
                                                                 Handoff* __restrict__ handoff, int64_t rows, int64_t D, int L)
 {
-    RangePart* rparts = handoff ? handoff->parts : nullptr;
     if (handoff) corey_range::clear_handoff_counts(handoff);
     float lo = INFINITY, hi = -INFINITY;
     bool nan = false;
     for (int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x; r < rows; r += (int64_t)gridDim.x * kThreads) {
-        const int64_t d = r % D;
+        const int64_t d = ((uint64_t)r >> 32 || (uint64_t)D >> 32) ? r % D : (int64_t)((uint32_t)r % (uint32_t)D);
         float w[W], win[W];                                   // win[k]: the input the tap w[k] multiplies at the current step
 #pragma unroll
         for (int k = 0; k < W; ++k) w[k] = weight[d * W + k];
@@ -405,70 +487,87 @@ __global__ __launch_bounds__(kThreads) void k_conv1d_silu_short(const T* __restr
 #pragma unroll
             for (int k = 0; k < W - 1; ++k) state_out[r * (W - 1) + k] = raw[k];
     }
-    if (lo <= hi) {                                           // the stored extremes: one rounding each
-        float pad[St<T>::kVec];
-        T st[St<T>::kVec];
-#pragma unroll
-        for (int e = 0; e < St<T>::kVec; ++e) pad[e] = (e == 0) ? lo : hi;
-        St<T>::narrow(pad, st);
-        lo = St<T>::widen(st[0]);
-        hi = St<T>::widen(st[1]);
-    }
-    if (rparts) {
+    if (handoff) {
+        round_extremes<T>(lo, hi);
         uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
         uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
         uint32_t knan = nan ? 1u : 0u;
         reduce_range_keys(klo, khi, knan);
-        if (threadIdx.x == 0) {
-            RangePart rp;
-            rp.lo_key = klo; rp.hi_key = khi; rp.saw_nan = knan; rp.pad = 0u;
-            rparts[blockIdx.x] = rp;
-        }
-        if (blockIdx.x == 0)                                  // entries no workgroup owns say "nothing seen"
-            for (int i = gridDim.x + threadIdx.x; i < COREY_RANGE_PARTS; i += kThreads) {
-                RangePart rp;
-                rp.lo_key = 0xffffffffu; rp.hi_key = 0u; rp.saw_nan = 0u; rp.pad = 0u;
-                rparts[i] = rp;
-            }
+        write_parts<kThreads>(handoff->parts, klo, khi, knan);
     }
 }
 
+// Fewest workgroups of a launch that also clears the hand-over's 256 KiB of counters: one 16-byte store per lane.  (Left to the
+// one workgroup that 64 rows of 16 steps fill, the clearing was 1.5 of 5.3 us.)
+constexpr int64_t kClearBlocks = corey_range::kParts * COREY_MAX_BINS / 4 / kThreads;
+
+// How `rows` rows of `nvec` vectors are walked by `least` to `most` workgroups of `threads` lanes, each lane the same number of
+// vectors.
+Walk plan_walk(int64_t rows, int64_t D, int64_t L, int64_t nvec, int threads, int64_t least, int64_t most, int64_t* blocks)
+{
+    Walk w = {};
+    w.rows = rows; w.D = D; w.L = L; w.nvec = nvec;
+    const int64_t total = rows * nvec;
+    w.turns = (total + threads * most - 1) / (threads * most);
+    *blocks = (total + threads * w.turns - 1) / (threads * w.turns);
+    if (*blocks < least) *blocks = least;
+    const int64_t step = *blocks * threads;
+    w.q = step / nvec;
+    w.rem = step - w.q * nvec;
+    w.qd = w.q % D;
+    return w;
+}
+
 template <typename T>
-void launch(const void* x, const float* weight, const float* bias, const void* state_in, void* u, void* state_out, void* rparts,
+void launch(const void* x_, const float* weight, const float* bias, const void* state_in_, void* u_, void* state_out_, void* rparts,
             void* table_ws, int64_t B, int64_t D, int64_t L, int W, hipStream_t stream)
 {
     constexpr int V = St<T>::kVec;
-    bool vector_ok = (L % V) == 0;
-    for (const void* p : {x, (const void*)u})
-        if (reinterpret_cast<uintptr_t>(p) % 16 != 0) vector_ok = false;
+    const T *x = static_cast<const T*>(x_), *state_in = static_cast<const T*>(state_in_);
+    T *u = static_cast<T*>(u_), *state_out = static_cast<T*>(state_out_);
+    Handoff* handoff = static_cast<Handoff*>(rparts);
     const int64_t rows = B * D;
+    int64_t blocks = 0;
     if constexpr (sizeof(T) == 2) {
         if (table_ws) {                                       // one workgroup of 1024 lanes per compute unit, each with a table
             constexpr int NT = corey_table::kLanes;
-            const int64_t seg = (int64_t)NT * V;
-            int64_t blocks = rows * ((L + seg - 1) / seg);
-            blocks = blocks < 1 ? 1 : (blocks > corey_table::kMaxSlabs ? corey_table::kMaxSlabs : blocks);
+            const Walk wk = plan_walk(rows, D, L, (L + V - 1) / V, NT, 1, corey_table::kMaxSlabs, &blocks);
             auto go_table = [&](auto kernel) {
-                kernel<<<dim3((unsigned)blocks), dim3(NT), 0, stream>>>(
-                    static_cast<const T*>(x), weight, bias, static_cast<const T*>(state_in), static_cast<T*>(u), static_cast<T*>(state_out),
-                    static_cast<Handoff*>(rparts), table_ws, rows, D, L, vector_ok ? 1 : 0);
+                kernel<<<dim3((unsigned)blocks), dim3(NT), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, table_ws, wk);
             };
             switch (W) {
-            case 1: go_table(k_conv1d_silu<T, 1, NT, true>); break;
-            case 2: go_table(k_conv1d_silu<T, 2, NT, true>); break;
-            case 3: go_table(k_conv1d_silu<T, 3, NT, true>); break;
-            default: go_table(k_conv1d_silu<T, 4, NT, true>); break;
+            case 1: go_table(k_conv1d_silu<T, 1, NT, true, false>); break;
+            case 2: go_table(k_conv1d_silu<T, 2, NT, true, false>); break;
+            case 3: go_table(k_conv1d_silu<T, 3, NT, true, false>); break;
+            default: go_table(k_conv1d_silu<T, 4, NT, true, false>); break;
             }
             return;
         }
     }
-    if (L <= kShortL) {
-        int64_t nb = (rows + kThreads - 1) / kThreads;
-        nb = nb > COREY_RANGE_PARTS ? COREY_RANGE_PARTS : nb;
+    constexpr int R = 4 / (int)sizeof(T);
+    bool words = D % R == 0;
+    for (const void* p : {x_, (const void*)u_, state_in_, (const void*)state_out_})
+        if (reinterpret_cast<uintptr_t>(p) % 4 != 0) words = false;
+    if (L == 1 && words) {
+        const Walk wk = plan_walk(B, D, 1, D / R, kThreads, handoff ? kClearBlocks : 1, COREY_RANGE_PARTS, &blocks);
+        const int64_t passes = (wk.turns + kStepUnits - 1) / kStepUnits;
+        const int units = (int)((wk.turns + passes - 1) / passes);
+        auto go_step = [&](auto kernel) {
+            kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, wk, units);
+        };
+        switch (W) {
+        case 1: go_step(k_conv1d_silu_step<T, 1>); break;
+        case 2: go_step(k_conv1d_silu_step<T, 2>); break;
+        case 3: go_step(k_conv1d_silu_step<T, 3>); break;
+        default: go_step(k_conv1d_silu_step<T, 4>); break;
+        }
+        return;
+    }
+    if (L < 2 * V) {
+        blocks = (rows + kThreads - 1) / kThreads;
+        blocks = blocks > COREY_RANGE_PARTS ? COREY_RANGE_PARTS : (handoff && blocks < kClearBlocks ? kClearBlocks : blocks);
         auto go_short = [&](auto kernel) {
-            kernel<<<dim3((unsigned)nb), dim3(kThreads), 0, stream>>>(
-                static_cast<const T*>(x), weight, bias, static_cast<const T*>(state_in), static_cast<T*>(u), static_cast<T*>(state_out),
-                static_cast<Handoff*>(rparts), rows, D, (int)L);
+            kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, rows, D, (int)L);
         };
         switch (W) {
         case 1: go_short(k_conv1d_silu_short<T, 1>); break;
@@ -478,20 +577,21 @@ void launch(const void* x, const float* weight, const float* bias, const void* s
         }
         return;
     }
-    const int64_t seg = (int64_t)kThreads * V;
-    int64_t blocks = rows * ((L + seg - 1) / seg);
-    blocks = blocks < 1 ? 1 : (blocks > COREY_RANGE_PARTS ? COREY_RANGE_PARTS : blocks);
+    const Walk wk = plan_walk(rows, D, L, (L + V - 1) / V, kThreads, handoff ? kClearBlocks : 1, COREY_RANGE_PARTS, &blocks);
     auto go = [&](auto kernel) {
-        kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(
-            static_cast<const T*>(x), weight, bias, static_cast<const T*>(state_in), static_cast<T*>(u), static_cast<T*>(state_out),
-            static_cast<Handoff*>(rparts), nullptr, rows, D, L, vector_ok ? 1 : 0);
+        kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, nullptr, wk);
     };
-    switch (W) {                                              // the tap count is a compile-time constant of the kernel
-    case 1: go(k_conv1d_silu<T, 1, kThreads, false>); break;
-    case 2: go(k_conv1d_silu<T, 2, kThreads, false>); break;
-    case 3: go(k_conv1d_silu<T, 3, kThreads, false>); break;
-    default: go(k_conv1d_silu<T, 4, kThreads, false>); break;
-    }
+    auto taps = [&](auto waves) {                             // the tap count is a compile-time constant of the kernel
+        constexpr bool WV = decltype(waves)::value;
+        switch (W) {
+        case 1: go(k_conv1d_silu<T, 1, kThreads, false, WV>); break;
+        case 2: go(k_conv1d_silu<T, 2, kThreads, false, WV>); break;
+        case 3: go(k_conv1d_silu<T, 3, kThreads, false, WV>); break;
+        default: go(k_conv1d_silu<T, 4, kThreads, false, WV>); break;
+        }
+    };
+    if (L % (64 * V) == 0) taps(std::true_type{});            // 64 vectors in a row: whole waves stay in one row
+    else taps(std::false_type{});
 }
 
 }  // namespace

@@ -47,7 +47,9 @@ static_assert(sizeof(Handoff) == COREY_HANDOFF_BYTES, "the header's size of the 
 // Clear the hand-over buffer's partial histograms, spread over the workgroups of the kernel that calls it.
 __device__ __forceinline__ void clear_handoff_counts(Handoff* h)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kParts * COREY_MAX_BINS; i += gridDim.x * blockDim.x) h->counts[i] = 0u;
+    typedef uint32_t w4 __attribute__((ext_vector_type(4)));      // (the buffer is 16-byte aligned)
+    w4* c = reinterpret_cast<w4*>(h->counts);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kParts * COREY_MAX_BINS / 4; i += gridDim.x * blockDim.x) c[i] = w4{0u, 0u, 0u, 0u};
 }
 
 // Workgroup reduction of (lo, hi, nan flag) as order-preserving keys over NT lanes; the result is valid in thread 0.
