@@ -23,13 +23,82 @@ using corey_scan::softplus;
 constexpr int kThreads = 256;
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-template <typename T>
+// Sets of 256 lanes a workgroup takes.  Below kManySets, what the GPU holds at eight workgroups per compute unit, every set is a
+// workgroup of its own: all are resident at once (16 sequences of 5120 channels, 1280 sets: 5.1 us, in pairs 5.8).  Above, pairs
+// (512 sequences, 40960 sets: 72.8 us one by one, 70.9 in pairs, 74.4 in fours, 89.6 in eights; 64 sequences, 5120 sets: 12.67,
+// 12.71, 13.4, 15.5).
+constexpr int kSets = 2;
+constexpr uint64_t kManySets = 2048;
+
+// States in whole, aligned groups of four: U sets of rows per workgroup, every load of theirs issued before any use, B and C by
+// words of four values (value by value they are eight loads of two bytes in a lane, and the trips to memory queue behind them).
+// Bound by memory: 512 sequences of 5120 channels with 16 states, fresh from HBM, 88.6 -> 70.9 us, 4.1 -> 5.1 TB/s (a copy reaches
+// 5.4); 64 sequences 15.0 -> 12.7 us.  Same operations in the same order as below.
+template <typename T, int U>
 __global__ __launch_bounds__(kThreads) void k_state_update(float* __restrict__ state, const T* __restrict__ x,
                                                            const T* __restrict__ delta, const float* __restrict__ A,
                                                            const T* __restrict__ Bt, const T* __restrict__ Ct,
                                                            const float* __restrict__ Dv, const T* __restrict__ z,
                                                            const float* __restrict__ dbias, T* __restrict__ y, uint32_t rows,
-                                                           uint32_t D, int N, int lpr_log2, int use_softplus, int vector_ok)
+                                                           uint32_t D, int N, int lpr_log2, int use_softplus)
+{
+    const int LPR = 1 << lpr_log2;                          // 4 LPR >= N: a lane has one group at most
+    const int j = (int)threadIdx.x & (LPR - 1);
+    const bool on = 4 * j < N;
+    const int n = on ? 4 * j : 0;                           // lanes without a group load the row's first and store nothing
+    uint32_t row[U];
+    bool active[U];
+    float4v h[U], a[U];
+    T bv[U][4], cv[U][4], xr[U], dr[U], zr[U];
+    float bias[U], skip[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        const uint32_t r = (uint32_t)((((uint64_t)blockIdx.x * U + k) * kThreads + threadIdx.x) >> lpr_log2);
+        active[k] = r < rows;                               // whole rows are active or not: LPR divides the wave
+        row[k] = active[k] ? r : rows - 1;
+        const uint32_t b = row[k] / D, d = row[k] - b * D;
+        h[k] = *reinterpret_cast<const float4v*>(state + (size_t)row[k] * N + n);
+        a[k] = *reinterpret_cast<const float4v*>(A + (size_t)d * N + n);
+        __builtin_memcpy(bv[k], Bt + (size_t)b * N + n, sizeof(bv[k]));
+        __builtin_memcpy(cv[k], Ct + (size_t)b * N + n, sizeof(cv[k]));
+        xr[k] = x[row[k]];
+        dr[k] = delta[row[k]];
+        zr[k] = z ? z[row[k]] : T(0);
+        bias[k] = dbias ? dbias[d] : 0.f;
+        skip[k] = Dv ? Dv[d] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        const float xv = Io<T>::ld(&xr[k]);
+        float dl = Io<T>::ld(&dr[k]) + bias[k];
+        if (use_softplus) dl = softplus(dl);
+        const float dx = dl * xv;
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float hn = fmaf(fast_exp2(dl * (a[k][i] * kLog2e)), h[k][i], dx * Io<T>::ld(&bv[k][i]));
+            h[k][i] = hn;
+            acc = fmaf(Io<T>::ld(&cv[k][i]), hn, acc);
+        }
+        if (!on) acc = 0.f;
+        if (active[k] && on) *reinterpret_cast<float4v*>(state + (size_t)row[k] * N + n) = h[k];
+        for (int m = LPR >> 1; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+        if (active[k] && j == 0) {
+            float yv = acc + (Dv ? skip[k] * xv : 0.f);
+            if (z) yv *= silu(Io<T>::ld(&zr[k]));
+            Io<T>::st(y + row[k], yv);
+        }
+    }
+}
+
+// Any N and any alignment of the states and of A: value by value.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_state_update_any(float* __restrict__ state, const T* __restrict__ x,
+                                                               const T* __restrict__ delta, const float* __restrict__ A,
+                                                               const T* __restrict__ Bt, const T* __restrict__ Ct,
+                                                               const float* __restrict__ Dv, const T* __restrict__ z,
+                                                               const float* __restrict__ dbias, T* __restrict__ y, uint32_t rows,
+                                                               uint32_t D, int N, int lpr_log2, int use_softplus)
 {
     const uint64_t gid = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
     const uint32_t row = (uint32_t)(gid >> lpr_log2);
@@ -49,24 +118,10 @@ __global__ __launch_bounds__(kThreads) void k_state_update(float* __restrict__ s
         const float* arow = A + (size_t)d * N;
         const T* brow = Bt + (size_t)b * N;
         const T* crow = Ct + (size_t)b * N;
-        for (int n = 4 * j; n < N; n += 4 * LPR) {
-            if (vector_ok && n + 4 <= N) {
-                float4v h = *reinterpret_cast<const float4v*>(hrow + n);
-                const float4v a = *reinterpret_cast<const float4v*>(arow + n);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float hn = fmaf(fast_exp2(dl * (a[i] * kLog2e)), h[i], dx * Io<T>::ld(brow + n + i));
-                    h[i] = hn;
-                    acc = fmaf(Io<T>::ld(crow + n + i), hn, acc);
-                }
-                *reinterpret_cast<float4v*>(hrow + n) = h;
-            } else {
-                for (int i = n; i < N && i < n + 4; ++i) {
-                    const float hn = fmaf(fast_exp2(dl * (arow[i] * kLog2e)), hrow[i], dx * Io<T>::ld(brow + i));
-                    hrow[i] = hn;
-                    acc = fmaf(Io<T>::ld(crow + i), hn, acc);
-                }
-            }
+        for (int i = 4 * j; i < N && i < 4 * j + 4; ++i) {
+            const float hn = fmaf(fast_exp2(dl * (arow[i] * kLog2e)), hrow[i], dx * Io<T>::ld(brow + i));
+            hrow[i] = hn;
+            acc = fmaf(Io<T>::ld(crow + i), hn, acc);
         }
     }
     for (int m = LPR >> 1; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
@@ -81,15 +136,21 @@ template <typename T>
 void launch(void* state, const void* x, const void* delta, const float* A, const void* Bt, const void* Ct, const float* Dv,
             const void* z, const float* dbias, void* y, int64_t B, int64_t D, int64_t N, int softplus_on, hipStream_t stream)
 {
+    static_assert(COREY_MAX_STATE <= 4 * 64, "a lane has one group of four states at most");
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < (N + 3) / 4 && lpr_log2 < 6) ++lpr_log2;
     const bool vector_ok = (N % 4) == 0 && reinterpret_cast<uintptr_t>(state) % 16 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
     const uint64_t lanes = (uint64_t)(B * D) << lpr_log2;
-    const uint64_t blocks = (lanes + kThreads - 1) / kThreads;
-    k_state_update<T><<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(
-        static_cast<float*>(state), static_cast<const T*>(x), static_cast<const T*>(delta), A, static_cast<const T*>(Bt),
-        static_cast<const T*>(Ct), Dv, static_cast<const T*>(z), dbias, static_cast<T*>(y), (uint32_t)(B * D), (uint32_t)D, (int)N,
-        lpr_log2, softplus_on, vector_ok ? 1 : 0);
+    const uint64_t sets = (lanes + kThreads - 1) / kThreads;
+    auto go = [&](auto kernel, uint64_t blocks) {
+        kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(
+            static_cast<float*>(state), static_cast<const T*>(x), static_cast<const T*>(delta), A, static_cast<const T*>(Bt),
+            static_cast<const T*>(Ct), Dv, static_cast<const T*>(z), dbias, static_cast<T*>(y), (uint32_t)(B * D), (uint32_t)D, (int)N,
+            lpr_log2, softplus_on);
+    };
+    if (!vector_ok) go(k_state_update_any<T>, sets);
+    else if (sets >= kManySets) go(k_state_update<T, kSets>, (sets + kSets - 1) / kSets);
+    else go(k_state_update<T, 1>, sets);
 }
 
 }  // namespace

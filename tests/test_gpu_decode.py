@@ -58,6 +58,14 @@ def test_batched_decode_at_the_benchmark_size():
     _step(cfg)
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16, wl.F16])
+@pytest.mark.parametrize("B,D,N", [(1, 131008, 16), (1, 131009, 16), (33, 3989, 16), (7, 18740, 12), (3, 2731, 256), (5, 13124, 20)])
+def test_either_side_of_the_size_where_a_workgroup_takes_several_sets(B, D, N, dtype):
+    """2047 and 2048 sets of 256 lanes; last workgroups of one set and of two, the last of them partial."""
+    _say(f"decode sets B{B} D{D} N{N} {dtype}")
+    _step(wl.Config(name="dec", B=B, D=D, N=N, L=1, dtype=dtype, K=16, chunks=(64,), seed=17 + N))
+
+
 def test_generation_continues_a_prompt():
     """Prompt through selective_scan_fwd, then 6 tokens one at a time from its last_state: the outputs and the final state
     are those of the oracle's scan over the whole sequence."""
