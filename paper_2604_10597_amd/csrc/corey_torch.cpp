@@ -97,6 +97,11 @@ void want(const at::Tensor* t, const char* name, at::ScalarType type, at::IntArr
     raise(PyExc_TypeError, "%s must be %s)", name, s.c_str());
 }
 
+void want(const at::Tensor& t, const char* name, at::ScalarType type, at::IntArrayRef shape)
+{
+    if (t.defined()) want(&t, name, type, shape);
+}
+
 corey_dtype dtype_code(at::ScalarType t)
 {
     if (t == at::kFloat) return COREY_F32;
@@ -105,20 +110,27 @@ corey_dtype dtype_code(at::ScalarType t)
     raise(PyExc_TypeError, "unsupported storage type %s", c10::toString(t));
 }
 
+// A whole number: an int or what offers itself as one (__index__); floats and strings are refused, not truncated or parsed.
 int64_t integer(PyObject* o)
 {
-    int64_t v;
-    if (PyLong_Check(o)) {
-        v = PyLong_AsLongLong(o);
-    } else {
-        PyObject* n = PyNumber_Long(o);
-        if (!n) throw PyError{};
-        v = PyLong_AsLongLong(n);
-        Py_DECREF(n);
-    }
+    PyObject* n = PyNumber_Index(o);
+    if (!n) throw PyError{};
+    const int64_t v = PyLong_AsLongLong(n);
+    Py_DECREF(n);
     if (v == -1 && PyErr_Occurred()) throw PyError{};
     return v;
 }
+
+// What int(o) and float(o) make of it, for the arguments that are converted so: `chunk`, L of the chunk rule, `ema_lambda`.
+struct Converted {
+    PyObject* o;
+    explicit Converted(PyObject* p) : o(p)
+    {
+        if (!o) throw PyError{};
+    }
+    ~Converted() { Py_DECREF(o); }
+    Converted(const Converted&) = delete;
+};
 
 int32_t integer32(PyObject* o)
 {
@@ -156,7 +168,7 @@ template <typename S> S* structure(PyObject* o, const char* name)
 const corey_policy* policy_or_default(PyObject* o) { return o == Py_None ? &default_policy : structure<corey_policy>(o, "policy"); }
 
 void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
-void* ptr(const at::Tensor& t) { return t.data_ptr(); }
+void* ptr(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 template <typename P> P* ptr_as(const at::Tensor* t) { return static_cast<P*>(ptr(t)); }
 template <typename P> P* ptr_as(const at::Tensor& t) { return static_cast<P*>(ptr(t)); }
 
@@ -194,16 +206,16 @@ Shape3 shape3(const at::Tensor& x)
 }
 
 // ------------------------------------------------------------------------------------------- the result dict
-// out[key], which must be there (KeyError otherwise) unless `optional`.
-const at::Tensor* out_tensor(PyObject* out, const char* key, bool optional = false)
+// out[key], which must be there (KeyError otherwise) unless `optional`; undefined for None.  The tensor is held, not borrowed:
+// other Python code (another thread, once the library is called without the interpreter lock; an argument's __float__) may take
+// it out of the dict before the work on it is enqueued, and its memory must not go to another tensor by then.
+at::Tensor out_tensor(PyObject* out, const char* key, bool optional = false)
 {
     PyObject* o = PyDict_GetItemString(out, key);
-    if (!o || o == Py_None) {
-        if (optional) return nullptr;
-        raise(PyExc_KeyError, "%s", key);
-    }
+    if (!o && !optional) raise(PyExc_KeyError, "%s", key);
+    if (!o || o == Py_None) return at::Tensor();
     if (!THPVariable_Check(o)) raise(PyExc_TypeError, "out[%s] must be a tensor", key);
-    return &THPVariable_Unpack(o);
+    return THPVariable_Unpack(o);
 }
 
 void put(PyObject* out, const char* key, const at::Tensor& t)
@@ -237,6 +249,15 @@ PyObject* result_dict(PyObject* out, int64_t nh, int64_t K, bool with_chunks, co
     return d;
 }
 
+// The tensors of the result dict.
+struct Results {
+    at::Tensor counts, H, r, range;
+    explicit Results(PyObject* out)
+        : counts(out_tensor(out, "counts")), H(out_tensor(out, "H")), r(out_tensor(out, "r")), range(out_tensor(out, "range", true))
+    {
+    }
+};
+
 struct Owned {                          // a reference that goes with its scope
     PyObject* o;
     explicit Owned(PyObject* p) : o(p) {}
@@ -250,23 +271,19 @@ struct Owned {                          // a reference that goes with its scope
     Owned(const Owned&) = delete;
 };
 
-// The workspace tensor of a statistic: the argument, the dict's, or a new one; also kept in the dict.
-const at::Tensor* statistic_workspace(PyObject* arg, PyObject* out, bool from_dict, int64_t B, int32_t K, const at::Tensor& x,
-                                      at::Tensor& made)
+// The workspace tensor of a statistic: the argument, the dict's, or a new one.
+at::Tensor statistic_workspace(PyObject* arg, PyObject* out, bool from_dict, int64_t B, int32_t K, const at::Tensor& x)
 {
-    const at::Tensor* ws = nullptr;
     if (arg != Py_None) {
         if (!THPVariable_Check(arg)) raise(PyExc_TypeError, "workspace must be a tensor");
-        ws = &THPVariable_Unpack(arg);
-        if (PyDict_SetItemString(out, "workspace", arg)) throw PyError{};
-        return ws;
+        return THPVariable_Unpack(arg);
     }
-    if (from_dict) ws = out_tensor(out, "workspace", true);
-    if (ws) return ws;
+    if (from_dict) {
+        const at::Tensor kept = out_tensor(out, "workspace", true);
+        if (kept.defined()) return kept;
+    }
     const int64_t need = (int64_t)lib.corey_entropy_hist_workspace(B, K);
-    made = empty({need < 256 ? 256 : need}, at::kByte, x);
-    put(out, "workspace", made);
-    return &made;
+    return empty({need < 256 ? 256 : need}, at::kByte, x);
 }
 
 // ------------------------------------------------------------------------------------------- entry points
@@ -386,17 +403,15 @@ PyObject* hist(PyObject* const* a)      // x, K, eps, stride, seqlens, out, work
     const at::Tensor* parts = optional_tensor(a[8], "range_parts");
     const corey_dtype dt = dtype_code(x.scalar_type());
     Owned out(result_dict(a[5], nh, K, false, x));
-    at::Tensor made;
-    const at::Tensor* ws = statistic_workspace(a[6], out.o, false, g.B, K, x, made);
-    uint32_t* counts = ptr_as<uint32_t>(out_tensor(out.o, "counts"));
-    double* H = ptr_as<double>(out_tensor(out.o, "H"));
-    double* r = ptr_as<double>(out_tensor(out.o, "r"));
-    float* range = ptr_as<float>(out_tensor(out.o, "range", true));
+    const at::Tensor ws = statistic_workspace(a[6], out.o, false, g.B, K, x);
+    const Results o(out.o);
     void* s = stream();
     call([&] {
-        return lib.corey_entropy_hist(ptr(x), dt, g.B, g.D, g.L, ptr_as<int32_t>(seqlens), K, eps, stride, block, counts, H, r, range,
-                                      ptr(parts), ptr(ws), (size_t)ws->numel(), s);
+        return lib.corey_entropy_hist(ptr(x), dt, g.B, g.D, g.L, ptr_as<int32_t>(seqlens), K, eps, stride, block, ptr_as<uint32_t>(o.counts),
+                                      ptr_as<double>(o.H), ptr_as<double>(o.r), ptr_as<float>(o.range), ptr(parts), ptr(ws),
+                                      (size_t)ws.numel(), s);
     });
+    put(out.o, "workspace", ws);
     return out.release();
 }
 
@@ -409,12 +424,11 @@ PyObject* hist_static(PyObject* const* a)      // x, K, out, eps, stride, seqlen
     want(seqlens, "seqlens", at::kInt, {g.B});
     const int32_t K = integer32(a[1]);
     if (!PyDict_Check(a[2])) raise(PyExc_TypeError, "out must be a dict");
-    const at::Tensor *counts = out_tensor(a[2], "counts"), *H = out_tensor(a[2], "H"), *r = out_tensor(a[2], "r");
-    const at::Tensor* range = out_tensor(a[2], "range", true);
-    want(counts, "counts", at::kInt, {nh, K});
-    want(H, "H", at::kDouble, {nh});
-    want(r, "r", at::kDouble, {nh});
-    want(range, "range", at::kFloat, {nh, 2});
+    const Results o(a[2]);
+    want(o.counts, "counts", at::kInt, {nh, K});
+    want(o.H, "H", at::kDouble, {nh});
+    want(o.r, "r", at::kDouble, {nh});
+    want(o.range, "range", at::kFloat, {nh, 2});
     const double eps = number(a[3]);
     const int64_t stride = integer(a[4]), block = integer(a[6]);
     const at::Tensor* parts = optional_tensor(a[7], "range_parts");
@@ -422,7 +436,8 @@ PyObject* hist_static(PyObject* const* a)      // x, K, out, eps, stride, seqlen
     void* s = stream();
     call([&] {
         return lib.corey_entropy_hist_static(ptr(x), dt, g.B, g.D, g.L, ptr_as<int32_t>(seqlens), K, eps, stride, block,
-                                             ptr_as<uint32_t>(counts), ptr_as<double>(H), ptr_as<double>(r), ptr_as<float>(range), ptr(parts), s);
+                                             ptr_as<uint32_t>(o.counts), ptr_as<double>(o.H), ptr_as<double>(o.r), ptr_as<float>(o.range),
+                                             ptr(parts), s);
     });
     Py_INCREF(a[2]);
     return a[2];
@@ -430,26 +445,19 @@ PyObject* hist_static(PyObject* const* a)      // x, K, out, eps, stride, seqlen
 
 // Both forms of the one-sweep statistic: the arguments after the tensor or table.
 struct TableCall {
-    const corey_policy* policy;
-    int32_t* chunks;
-    uint32_t* counts;
-    double *H, *r;
-    float* range;
-};
-TableCall table_call(PyObject* policy, PyObject* out, const at::Tensor& like)
-{
-    TableCall t = {};
-    if (policy != Py_None) {
-        t.policy = structure<corey_policy>(policy, "policy");
-        if (!out_tensor(out, "chunks", true)) put(out, "chunks", empty({1}, at::kInt, like));
-        t.chunks = ptr_as<int32_t>(out_tensor(out, "chunks"));
+    const corey_policy* policy = nullptr;
+    at::Tensor chunks;
+    Results o;
+    TableCall(PyObject* p, PyObject* out, const at::Tensor& like) : o(out)
+    {
+        if (p == Py_None) return;
+        policy = structure<corey_policy>(p, "policy");
+        chunks = out_tensor(out, "chunks", true);
+        if (chunks.defined()) return;
+        chunks = empty({1}, at::kInt, like);
+        put(out, "chunks", chunks);
     }
-    t.counts = ptr_as<uint32_t>(out_tensor(out, "counts"));
-    t.H = ptr_as<double>(out_tensor(out, "H"));
-    t.r = ptr_as<double>(out_tensor(out, "r"));
-    t.range = ptr_as<float>(out_tensor(out, "range", true));
-    return t;
-}
+};
 
 PyObject* onesweep(PyObject* const* a)      // x, K, eps, policy, out, table_ws
 {
@@ -460,7 +468,7 @@ PyObject* onesweep(PyObject* const* a)      // x, K, eps, policy, out, table_ws
     const double eps = number(a[2]);
     const corey_dtype dt = dtype_code(x.scalar_type());
     Owned out(result_dict(a[4], 1, K, false, x));
-    const TableCall t = table_call(a[3], out.o, x);
+    const TableCall t(a[3], out.o, x);
     at::Tensor made;
     if (!ws) {
         made = empty({(int64_t)lib.corey_pattern_table_workspace()}, at::kByte, x);
@@ -468,11 +476,11 @@ PyObject* onesweep(PyObject* const* a)      // x, K, eps, policy, out, table_ws
     }
     void* s = stream();
     call([&] {
-        return lib.corey_entropy_hist_onesweep(ptr(x), dt, g.B, g.D, g.L, K, eps, t.policy, t.chunks, t.counts, t.H, t.r, t.range, ptr(ws),
-                                               (size_t)ws->numel(), s);
+        return lib.corey_entropy_hist_onesweep(ptr(x), dt, g.B, g.D, g.L, K, eps, t.policy, ptr_as<int32_t>(t.chunks),
+                                               ptr_as<uint32_t>(t.o.counts), ptr_as<double>(t.o.H), ptr_as<double>(t.o.r),
+                                               ptr_as<float>(t.o.range), ptr(ws), (size_t)ws->numel(), s);
     });
-    if (ws == &made) put(out.o, "table_ws", made);
-    else if (PyDict_SetItemString(out.o, "table_ws", a[5])) throw PyError{};
+    put(out.o, "table_ws", *ws);
     return out.release();
 }
 
@@ -484,10 +492,11 @@ PyObject* from_table(PyObject* const* a)      // table_ws, dtype code, L, K, eps
     const int32_t K = integer32(a[3]);
     const double eps = number(a[4]);
     Owned out(result_dict(a[6], 1, K, false, ws));
-    const TableCall t = table_call(a[5], out.o, ws);
+    const TableCall t(a[5], out.o, ws);
     void* s = stream();
     call([&] {
-        return lib.corey_entropy_hist_from_table(dt, L, K, eps, t.policy, t.chunks, t.counts, t.H, t.r, t.range, ptr(ws),
+        return lib.corey_entropy_hist_from_table(dt, L, K, eps, t.policy, ptr_as<int32_t>(t.chunks), ptr_as<uint32_t>(t.o.counts),
+                                                 ptr_as<double>(t.o.H), ptr_as<double>(t.o.r), ptr_as<float>(t.o.range), ptr(ws),
                                                  (size_t)ws.numel(), s);
     });
     return out.release();
@@ -511,13 +520,9 @@ template <bool DEFERRED> PyObject* route(PyObject* const* a)
     const at::Tensor* parts = optional_tensor(a[10], "range_parts");
     const corey_dtype dt = dtype_code(x.scalar_type());
     Owned out(result_dict(a[7], nh, K, true, x));
-    at::Tensor made;
-    const at::Tensor* ws = statistic_workspace(a[8], out.o, true, g.B, K, x, made);
-    uint32_t* counts = ptr_as<uint32_t>(out_tensor(out.o, "counts"));
-    double* H = ptr_as<double>(out_tensor(out.o, "H"));
-    double* r = ptr_as<double>(out_tensor(out.o, "r"));
-    float* range = ptr_as<float>(out_tensor(out.o, "range", true));
-    int32_t* chunks = ptr_as<int32_t>(out_tensor(out.o, "chunks"));
+    const at::Tensor ws = statistic_workspace(a[8], out.o, true, g.B, K, x);
+    const Results o(out.o);
+    const at::Tensor chunks = out_tensor(out.o, "chunks");
     const int32_t* lens = ptr_as<int32_t>(seqlens);
     uint32_t* cc = ptr_as<uint32_t>(calls);
     void* s = stream();
@@ -527,18 +532,22 @@ template <bool DEFERRED> PyObject* route(PyObject* const* a)
         if (!ticket.o) throw PyError{};
         corey_deferred_route* t = structure<corey_deferred_route>(ticket.o, "route");
         call([&] {
-            return lib.corey_route_device_deferred(ptr(x), dt, g.B, g.D, g.L, lens, K, eps, stride, block, p, cc, counts, H, r, range,
-                                                   ptr(parts), chunks, ptr(ws), (size_t)ws->numel(), t, s);
+            return lib.corey_route_device_deferred(ptr(x), dt, g.B, g.D, g.L, lens, K, eps, stride, block, p, cc, ptr_as<uint32_t>(o.counts),
+                                                   ptr_as<double>(o.H), ptr_as<double>(o.r), ptr_as<float>(o.range), ptr(parts),
+                                                   ptr_as<int32_t>(chunks), ptr(ws), (size_t)ws.numel(), t, s);
         });
+        put(out.o, "workspace", ws);
         if (PyDict_SetItemString(out.o, "route", ticket.o)) throw PyError{};
     } else {
-        const double lambda = number(a[11]);
+        const double lambda = number(Converted(PyNumber_Float(a[11])).o);
         const at::Tensor* ema = optional_tensor(a[12], "ema_state");
         want(ema, "ema_state", at::kDouble, {nh});
         call([&] {
-            return lib.corey_route_device(ptr(x), dt, g.B, g.D, g.L, lens, K, eps, stride, block, p, lambda, ptr_as<double>(ema), cc, counts,
-                                          H, r, range, ptr(parts), chunks, ptr(ws), (size_t)ws->numel(), s);
+            return lib.corey_route_device(ptr(x), dt, g.B, g.D, g.L, lens, K, eps, stride, block, p, lambda, ptr_as<double>(ema), cc,
+                                          ptr_as<uint32_t>(o.counts), ptr_as<double>(o.H), ptr_as<double>(o.r), ptr_as<float>(o.range),
+                                          ptr(parts), ptr_as<int32_t>(chunks), ptr(ws), (size_t)ws.numel(), s);
         });
+        put(out.o, "workspace", ws);
     }
     return out.release();
 }
@@ -551,7 +560,7 @@ PyObject* select_chunk_device(PyObject* const* a)      // r_dev, L, policy, seql
     const int64_t nh = r.numel();
     want(seqlens, "seqlens", at::kInt, {nh});
     const corey_policy* p = policy_or_default(a[2]);
-    const int64_t L = integer(a[1]);
+    const int64_t L = integer(Converted(PyNumber_Long(a[1])).o);
     at::Tensor made;
     const at::Tensor* out = optional_tensor(a[4], "out");
     if (!out) {
@@ -580,7 +589,7 @@ PyObject* scan(PyObject* const* a)
     const int softplus = truth(a[8]) ? 1 : 0;
     const at::Tensor* h0 = optional_tensor(a[9], "h0");
     const at::Tensor* seqlens = optional_tensor(a[10], "seqlens");
-    const int32_t chunk = integer32(a[11]);
+    const int32_t chunk = integer32(Converted(PyNumber_Long(a[11])).o);
     const at::Tensor* chunks = optional_tensor(a[12], "chunks_dev");
     const at::Tensor* y = optional_tensor(a[13], "y");
     const at::Tensor* last = optional_tensor(a[14], "last_state");
