@@ -206,31 +206,56 @@ Shape3 shape3(const at::Tensor& x)
 }
 
 // ------------------------------------------------------------------------------------------- the result dict
+struct Owned {                          // a reference that goes with its scope
+    PyObject* o;
+    explicit Owned(PyObject* p) : o(p) {}
+    ~Owned() { Py_XDECREF(o); }
+    PyObject* release()
+    {
+        PyObject* p = o;
+        o = nullptr;
+        return p;
+    }
+    Owned(const Owned&) = delete;
+};
+
+// A new reference to out[key]; for an `optional` one out.get(key) or NULL.  `out` is any mapping, in practice a dict.
+PyObject* out_entry(PyObject* out, const char* key, bool optional)
+{
+    PyObject* o;
+    if (PyDict_CheckExact(out)) {
+        o = PyDict_GetItemString(out, key);
+        if (!o && !optional) raise(PyExc_KeyError, "%s", key);
+        Py_XINCREF(o);
+        return o;
+    }
+    o = optional ? PyObject_CallMethod(out, "get", "s", key) : PyMapping_GetItemString(out, key);
+    if (!o) throw PyError{};
+    return o;
+}
+
 // out[key], which must be there (KeyError otherwise) unless `optional`; undefined for None.  The tensor is held, not borrowed:
 // other Python code (another thread, once the library is called without the interpreter lock; an argument's __float__) may take
 // it out of the dict before the work on it is enqueued, and its memory must not go to another tensor by then.
 at::Tensor out_tensor(PyObject* out, const char* key, bool optional = false)
 {
-    PyObject* o = PyDict_GetItemString(out, key);
-    if (!o && !optional) raise(PyExc_KeyError, "%s", key);
-    if (!o || o == Py_None) return at::Tensor();
-    if (!THPVariable_Check(o)) raise(PyExc_TypeError, "out[%s] must be a tensor", key);
-    return THPVariable_Unpack(o);
+    const Owned e(out_entry(out, key, optional));
+    if (!e.o || e.o == Py_None) return at::Tensor();
+    if (!THPVariable_Check(e.o)) raise(PyExc_TypeError, "out[%s] must be a tensor", key);
+    return THPVariable_Unpack(e.o);
 }
 
-void put(PyObject* out, const char* key, const at::Tensor& t)
+void put(PyObject* out, const char* key, PyObject* o)
 {
-    PyObject* o = wrap(t);
-    const int rc = PyDict_SetItemString(out, key, o);
-    Py_DECREF(o);
-    if (rc) throw PyError{};
+    if (PyDict_CheckExact(out) ? PyDict_SetItemString(out, key, o) : PyMapping_SetItemString(out, key, o)) throw PyError{};
 }
+
+void put(PyObject* out, const char* key, const at::Tensor& t) { put(out, key, Owned(wrap(t)).o); }
 
 // A new reference to the dict to fill: the caller's, or a new one with new tensors.
 PyObject* result_dict(PyObject* out, int64_t nh, int64_t K, bool with_chunks, const at::Tensor& like)
 {
     if (out != Py_None) {
-        if (!PyDict_Check(out)) raise(PyExc_TypeError, "out must be a dict");
         Py_INCREF(out);
         return out;
     }
@@ -256,19 +281,6 @@ struct Results {
         : counts(out_tensor(out, "counts")), H(out_tensor(out, "H")), r(out_tensor(out, "r")), range(out_tensor(out, "range", true))
     {
     }
-};
-
-struct Owned {                          // a reference that goes with its scope
-    PyObject* o;
-    explicit Owned(PyObject* p) : o(p) {}
-    ~Owned() { Py_XDECREF(o); }
-    PyObject* release()
-    {
-        PyObject* p = o;
-        o = nullptr;
-        return p;
-    }
-    Owned(const Owned&) = delete;
 };
 
 // The workspace tensor of a statistic: the argument, the dict's, or a new one.
@@ -423,7 +435,6 @@ PyObject* hist_static(PyObject* const* a)      // x, K, out, eps, stride, seqlen
     const int64_t nh = seqlens ? g.B : 1;
     want(seqlens, "seqlens", at::kInt, {g.B});
     const int32_t K = integer32(a[1]);
-    if (!PyDict_Check(a[2])) raise(PyExc_TypeError, "out must be a dict");
     const Results o(a[2]);
     want(o.counts, "counts", at::kInt, {nh, K});
     want(o.H, "H", at::kDouble, {nh});
@@ -527,8 +538,8 @@ template <bool DEFERRED> PyObject* route(PyObject* const* a)
     uint32_t* cc = ptr_as<uint32_t>(calls);
     void* s = stream();
     if constexpr (DEFERRED) {
-        PyObject* given = PyDict_GetItemString(out.o, "route");
-        Owned ticket(given && given != Py_None ? (Py_INCREF(given), given) : PyObject_CallNoArgs(route_class));
+        const Owned given(out_entry(out.o, "route", true));
+        const Owned ticket(given.o && given.o != Py_None ? (Py_INCREF(given.o), given.o) : PyObject_CallNoArgs(route_class));
         if (!ticket.o) throw PyError{};
         corey_deferred_route* t = structure<corey_deferred_route>(ticket.o, "route");
         call([&] {
@@ -537,7 +548,7 @@ template <bool DEFERRED> PyObject* route(PyObject* const* a)
                                                    ptr_as<int32_t>(chunks), ptr(ws), (size_t)ws.numel(), t, s);
         });
         put(out.o, "workspace", ws);
-        if (PyDict_SetItemString(out.o, "route", ticket.o)) throw PyError{};
+        put(out.o, "route", ticket.o);
     } else {
         const double lambda = number(Converted(PyNumber_Float(a[11])).o);
         const at::Tensor* ema = optional_tensor(a[12], "ema_state");

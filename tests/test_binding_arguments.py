@@ -1,6 +1,7 @@
 """What the binding makes of its arguments before the library sees them.  The tensors are fake ones: they report the GPU, a
 type and a shape and own no memory, so a call whose arguments pass ends with a RuntimeError at the stream of a GPU that is not
 there, or at their data pointers, and nothing is ever launched."""
+from collections import OrderedDict, UserDict
 from fractions import Fraction
 
 import numpy as np
@@ -27,12 +28,12 @@ X = lambda: gpu(2, 3, 64, dtype=torch.bfloat16)
 WS = lambda: gpu(1 << 20, dtype=torch.uint8)
 
 STATISTICS = {
-    "hist": lambda **kw: corey.corey_entropy_hist(X(), workspace=WS(), out=results(), **{"K": 16, **kw}),
-    "static": lambda **kw: corey.corey_entropy_hist_static(X(), out=results(), **{"K": 16, **kw}),
-    "route": lambda **kw: corey.corey_route_device(X(), workspace=WS(), out=results(), **{"K": 16, **kw}),
-    "deferred": lambda **kw: corey.corey_route_device_deferred(X(), workspace=WS(), out=results(), **{"K": 16, **kw}),
-    "onesweep": lambda **kw: corey.corey_entropy_hist_onesweep(X(), table_ws=WS(), out=results(), **{"K": 16, **kw}),
-    "from_table": lambda **kw: corey.corey_entropy_hist_from_table(WS(), torch.bfloat16, out=results(), **{"K": 16, "L": 64, **kw}),
+    "hist": lambda **kw: corey.corey_entropy_hist(X(), workspace=WS(), **{"out": results(), "K": 16, **kw}),
+    "static": lambda **kw: corey.corey_entropy_hist_static(X(), **{"out": results(), "K": 16, **kw}),
+    "route": lambda **kw: corey.corey_route_device(X(), workspace=WS(), **{"out": results(), "K": 16, **kw}),
+    "deferred": lambda **kw: corey.corey_route_device_deferred(X(), workspace=WS(), **{"out": results(), "K": 16, **kw}),
+    "onesweep": lambda **kw: corey.corey_entropy_hist_onesweep(X(), table_ws=WS(), **{"out": results(), "K": 16, **kw}),
+    "from_table": lambda **kw: corey.corey_entropy_hist_from_table(WS(), torch.bfloat16, **{"out": results(), "K": 16, "L": 64, **kw}),
 }
 
 
@@ -68,3 +69,14 @@ def test_arguments_that_are_converted():
     for lam in (0.5, 0, "0.5"):
         with pytest.raises(RuntimeError):
             STATISTICS["route"](ema_lambda=lam, ema_state=gpu(1, dtype=torch.float64))
+
+
+@pytest.mark.parametrize("call", STATISTICS)
+@pytest.mark.parametrize("kind", [dict, OrderedDict, UserDict])
+def test_results_go_into_any_mapping(call, kind):
+    with pytest.raises(RuntimeError):
+        STATISTICS[call](out=kind(results()))
+    part = results()
+    del part["counts"]
+    with pytest.raises(KeyError):
+        STATISTICS[call](out=kind(part))
