@@ -102,6 +102,32 @@ void want(const at::Tensor& t, const char* name, at::ScalarType type, at::IntArr
     if (t.defined()) want(&t, name, type, shape);
 }
 
+// Memory kernels reach: on the GPU, or host memory pinned for it (results may go straight there).
+void want_reachable(const at::Tensor& t, const char* name)
+{
+    if (!(t.is_cuda() || t.is_pinned()) || !t.is_contiguous()) raise(PyExc_ValueError, "%s must be a contiguous GPU tensor", name);
+}
+
+// A buffer the kernels read or write through its pointer: reachable, contiguous, of this type and with room for n values.  Its
+// shape is the caller's business (counts of one histogram may be [K], an output longer than needed is filled at its start).
+void want_room(const at::Tensor* t, const char* name, at::ScalarType type, int64_t n)
+{
+    if (!t || !t->defined()) return;
+    want_reachable(*t, name);
+    const bool bits = type == at::kInt && t->scalar_type() == at::kUInt32;      // counts and chunks: 32-bit patterns either way
+    if ((t->scalar_type() == type || bits) && t->numel() >= n) return;
+    const std::string s = std::string(c10::toString(type)) + " with room for " + std::to_string(n) + " values";
+    raise(PyExc_TypeError, "%s must be %s", name, s.c_str());
+}
+// ... of at least n bytes, whatever its type (workspaces)
+void want_bytes(const at::Tensor* t, const char* name, int64_t n)
+{
+    if (!t || !t->defined()) return;
+    want_reachable(*t, name);
+    if ((int64_t)t->nbytes() >= n) return;
+    raise(PyExc_TypeError, "%s must have at least %s bytes", name, std::to_string(n).c_str());
+}
+
 corey_dtype dtype_code(at::ScalarType t)
 {
     if (t == at::kFloat) return COREY_F32;
@@ -277,23 +303,28 @@ PyObject* result_dict(PyObject* out, int64_t nh, int64_t K, bool with_chunks, co
 // The tensors of the result dict.
 struct Results {
     at::Tensor counts, H, r, range;
-    explicit Results(PyObject* out)
+    Results(PyObject* out, int64_t nh, int64_t K)
         : counts(out_tensor(out, "counts")), H(out_tensor(out, "H")), r(out_tensor(out, "r")), range(out_tensor(out, "range", true))
     {
+        want_room(&counts, "counts", at::kInt, K > 0 ? nh * K : 0);      // (the library refuses any other K)
+        want_room(&H, "H", at::kDouble, nh);
+        want_room(&r, "r", at::kDouble, nh);
+        want_room(&range, "range", at::kFloat, 2 * nh);
     }
 };
 
 // The workspace tensor of a statistic: the argument, the dict's, or a new one.
 at::Tensor statistic_workspace(PyObject* arg, PyObject* out, bool from_dict, int64_t B, int32_t K, const at::Tensor& x)
 {
+    at::Tensor given;
     if (arg != Py_None) {
         if (!THPVariable_Check(arg)) raise(PyExc_TypeError, "workspace must be a tensor");
-        return THPVariable_Unpack(arg);
+        given = THPVariable_Unpack(arg);
+    } else if (from_dict) {
+        given = out_tensor(out, "workspace", true);
     }
-    if (from_dict) {
-        const at::Tensor kept = out_tensor(out, "workspace", true);
-        if (kept.defined()) return kept;
-    }
+    want_bytes(&given, "workspace", 0);                         // (the library checks how many)
+    if (given.defined()) return given;
     const int64_t need = (int64_t)lib.corey_entropy_hist_workspace(B, K);
     return empty({need < 256 ? 256 : need}, at::kByte, x);
 }
@@ -345,6 +376,7 @@ PyObject* state_update(PyObject* const* a)
     want(&Ct, "Ct", type, {B, N});
     want(Dv, "Dv", at::kFloat, {D});
     want(bias, "delta_bias", at::kFloat, {D});
+    want_room(y, "y", type, B * D);
     const corey_dtype dt = dtype_code(type);
     at::Tensor made;
     if (!y) {
@@ -378,6 +410,9 @@ PyObject* conv(PyObject* const* a)
         raise(PyExc_TypeError, "weight [D, W] and bias [D] must be float32");
     const int64_t W = weight.size(1);
     const corey_dtype dt = dtype_code(x.scalar_type());
+    want_room(bias, "bias", at::kFloat, g.D);
+    want_room(state_in, "state_in", x.scalar_type(), g.B * g.D * (W - 1));
+    want_room(u, "u", x.scalar_type(), g.B * g.D * g.L);
     at::Tensor made_u, made_state, made_parts;
     if (!u) {
         made_u = empty({g.B, g.D, g.L}, x.scalar_type(), x);
@@ -413,10 +448,11 @@ PyObject* hist(PyObject* const* a)      // x, K, eps, stride, seqlens, out, work
     const double eps = number(a[2]);
     const int64_t stride = integer(a[3]), block = integer(a[7]);
     const at::Tensor* parts = optional_tensor(a[8], "range_parts");
+    want_bytes(parts, "range_parts", COREY_HANDOFF_BYTES);
     const corey_dtype dt = dtype_code(x.scalar_type());
     Owned out(result_dict(a[5], nh, K, false, x));
     const at::Tensor ws = statistic_workspace(a[6], out.o, false, g.B, K, x);
-    const Results o(out.o);
+    const Results o(out.o, nh, K);
     void* s = stream();
     call([&] {
         return lib.corey_entropy_hist(ptr(x), dt, g.B, g.D, g.L, ptr_as<int32_t>(seqlens), K, eps, stride, block, ptr_as<uint32_t>(o.counts),
@@ -435,7 +471,7 @@ PyObject* hist_static(PyObject* const* a)      // x, K, out, eps, stride, seqlen
     const int64_t nh = seqlens ? g.B : 1;
     want(seqlens, "seqlens", at::kInt, {g.B});
     const int32_t K = integer32(a[1]);
-    const Results o(a[2]);
+    const Results o(a[2], nh, K);
     want(o.counts, "counts", at::kInt, {nh, K});
     want(o.H, "H", at::kDouble, {nh});
     want(o.r, "r", at::kDouble, {nh});
@@ -443,6 +479,7 @@ PyObject* hist_static(PyObject* const* a)      // x, K, out, eps, stride, seqlen
     const double eps = number(a[3]);
     const int64_t stride = integer(a[4]), block = integer(a[6]);
     const at::Tensor* parts = optional_tensor(a[7], "range_parts");
+    want_bytes(parts, "range_parts", COREY_HANDOFF_BYTES);
     const corey_dtype dt = dtype_code(x.scalar_type());
     void* s = stream();
     call([&] {
@@ -459,11 +496,12 @@ struct TableCall {
     const corey_policy* policy = nullptr;
     at::Tensor chunks;
     Results o;
-    TableCall(PyObject* p, PyObject* out, const at::Tensor& like) : o(out)
+    TableCall(PyObject* p, PyObject* out, int64_t K, const at::Tensor& like) : o(out, 1, K)
     {
         if (p == Py_None) return;
         policy = structure<corey_policy>(p, "policy");
         chunks = out_tensor(out, "chunks", true);
+        want_room(&chunks, "chunks", at::kInt, 1);
         if (chunks.defined()) return;
         chunks = empty({1}, at::kInt, like);
         put(out, "chunks", chunks);
@@ -479,7 +517,7 @@ PyObject* onesweep(PyObject* const* a)      // x, K, eps, policy, out, table_ws
     const double eps = number(a[2]);
     const corey_dtype dt = dtype_code(x.scalar_type());
     Owned out(result_dict(a[4], 1, K, false, x));
-    const TableCall t(a[3], out.o, x);
+    const TableCall t(a[3], out.o, K, x);
     at::Tensor made;
     if (!ws) {
         made = empty({(int64_t)lib.corey_pattern_table_workspace()}, at::kByte, x);
@@ -503,7 +541,7 @@ PyObject* from_table(PyObject* const* a)      // table_ws, dtype code, L, K, eps
     const int32_t K = integer32(a[3]);
     const double eps = number(a[4]);
     Owned out(result_dict(a[6], 1, K, false, ws));
-    const TableCall t(a[5], out.o, ws);
+    const TableCall t(a[5], out.o, K, ws);
     void* s = stream();
     call([&] {
         return lib.corey_entropy_hist_from_table(dt, L, K, eps, t.policy, ptr_as<int32_t>(t.chunks), ptr_as<uint32_t>(t.o.counts),
@@ -529,11 +567,13 @@ template <bool DEFERRED> PyObject* route(PyObject* const* a)
     const double eps = number(a[3]);
     const int64_t stride = integer(a[4]), block = integer(a[5]);
     const at::Tensor* parts = optional_tensor(a[10], "range_parts");
+    want_bytes(parts, "range_parts", COREY_HANDOFF_BYTES);
     const corey_dtype dt = dtype_code(x.scalar_type());
     Owned out(result_dict(a[7], nh, K, true, x));
     const at::Tensor ws = statistic_workspace(a[8], out.o, true, g.B, K, x);
-    const Results o(out.o);
+    const Results o(out.o, nh, K);
     const at::Tensor chunks = out_tensor(out.o, "chunks");
+    want_room(&chunks, "chunks", at::kInt, nh);
     const int32_t* lens = ptr_as<int32_t>(seqlens);
     uint32_t* cc = ptr_as<uint32_t>(calls);
     void* s = stream();
@@ -574,6 +614,7 @@ PyObject* select_chunk_device(PyObject* const* a)      // r_dev, L, policy, seql
     const int64_t L = integer(Converted(PyNumber_Long(a[1])).o);
     at::Tensor made;
     const at::Tensor* out = optional_tensor(a[4], "out");
+    want_room(out, "out", at::kInt, nh);
     if (!out) {
         made = empty({nh}, at::kInt, r);
         out = &made;

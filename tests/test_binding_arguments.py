@@ -25,7 +25,7 @@ def results(nh=1, K=16):
 
 
 X = lambda: gpu(2, 3, 64, dtype=torch.bfloat16)
-WS = lambda: gpu(1 << 20, dtype=torch.uint8)
+WS = lambda: gpu(1 << 20, dtype=torch.uint8)          # more than any buffer asked for below
 
 STATISTICS = {
     "hist": lambda **kw: corey.corey_entropy_hist(X(), workspace=WS(), **{"out": results(), "K": 16, **kw}),
@@ -80,3 +80,63 @@ def test_results_go_into_any_mapping(call, kind):
     del part["counts"]
     with pytest.raises(KeyError):
         STATISTICS[call](out=kind(part))
+
+
+BAD_RESULTS = {
+    "counts": [gpu(1, 15, dtype=torch.int32), gpu(1, 16), gpu(1, 16, dtype=torch.int64), gpu(2, 16, dtype=torch.int32)[:, ::2]],
+    "H": [gpu(1), gpu(0, dtype=torch.float64)],
+    "r": [gpu(1), gpu(0, dtype=torch.float64)],
+    "range": [gpu(1), gpu(2, dtype=torch.float64)],
+    "chunks": [gpu(1, dtype=torch.int64), gpu(0, dtype=torch.int32)],
+}
+
+
+@pytest.mark.parametrize("call", STATISTICS)
+def test_results_must_have_room_on_the_gpu(call):
+    """A result tensor of another type, with too few values, with gaps or in host memory never reaches a kernel."""
+    kw = dict(policy=corey.policy_default()) if call in ("onesweep", "from_table") else {}
+    for name, bad in BAD_RESULTS.items():
+        if name == "chunks" and call in ("hist", "static"):
+            continue
+        for t in bad + [torch.zeros(64, dtype=results()[name].dtype)]:
+            with pytest.raises((TypeError, ValueError)):
+                STATISTICS[call](out=dict(results(), **{name: t}), **kw)
+
+
+def test_results_of_any_shape_with_room_are_taken():
+    for name, t in dict(counts=gpu(16, dtype=torch.uint32), H=gpu(8, dtype=torch.float64), range=gpu(2), chunks=gpu(1, 1, dtype=torch.int32)).items():
+        with pytest.raises(RuntimeError):
+            STATISTICS["route"](out=dict(results(), **{name: t}))
+
+
+def test_other_buffers_must_have_room_on_the_gpu():
+    bf16 = dict(dtype=torch.bfloat16)
+    small = gpu(1000, dtype=torch.uint8)
+    host = torch.zeros(1 << 20, dtype=torch.uint8)
+    for call in ("hist", "static", "route", "deferred"):
+        for parts in (small, host):
+            with pytest.raises((TypeError, ValueError)):
+                STATISTICS[call](range_parts=parts)
+    for call in (corey.corey_entropy_hist, corey.corey_route_device, corey.corey_route_device_deferred):
+        with pytest.raises(ValueError):
+            call(X(), 16, workspace=host, out=results())
+    for call in (corey.corey_route_device, corey.corey_route_device_deferred):
+        with pytest.raises(ValueError):
+            call(X(), 16, out=dict(results(), workspace=host))
+    conv = lambda **kw: corey.causal_conv1d_silu_fwd(X(), gpu(3, 4), **{"u": X(), "range_parts": WS(), **kw})
+    for kw in (dict(u=gpu(2, 3, 64)), dict(u=gpu(2, 3, 63, **bf16)), dict(state_in=gpu(2, 3, 3)), dict(state_in=gpu(2, 3, 2, **bf16)),
+               dict(bias=gpu(2)), dict(bias=gpu(3, **bf16))):
+        with pytest.raises(TypeError):
+            conv(**kw)
+    with pytest.raises(RuntimeError):
+        conv(u=gpu(6, 64, **bf16), state_in=gpu(6, 3, **bf16), bias=gpu(3, 1))
+    step = lambda y: corey.selective_state_update(gpu(2, 3, 16), gpu(2, 3, **bf16), gpu(2, 3, **bf16), gpu(3, 16), gpu(2, 16, **bf16),
+                                                  gpu(2, 16, **bf16), y=y)
+    for y in (gpu(2, 3), gpu(2, 2, **bf16)):
+        with pytest.raises(TypeError):
+            step(y)
+    with pytest.raises(RuntimeError):
+        step(gpu(6, **bf16))
+    for out in (gpu(1, dtype=torch.int32), gpu(2, dtype=torch.int64)):
+        with pytest.raises(TypeError):
+            corey.corey_select_chunk_device(gpu(2, dtype=torch.float64), 64, out=out)
