@@ -73,6 +73,13 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return fail(COREY_EWORKSPACE, "%s: workspace must be 16-byte aligned", who);
 
     const size_t esz = dt == COREY_F32 ? 4 : 2;
+    // a lane addresses its row inside a group by a 32-bit byte offset from the group's first row
+    const int64_t row_bytes = L * (int64_t)esz;
+    if (row_bytes >= ((int64_t)1 << 31)) return fail(COREY_ESHAPE, "%s: a row of %lld bytes exceeds the kernels' 2 GiB", who, (long long)row_bytes);
+    if (route && (!route->parts || !route->chunks_out || route->K < 2 || route->K > COREY_MAX_BINS || (route->nh != 1 && route->nh != B)))
+        return fail(COREY_EINVAL, "%s: route was not filled by corey_route_device_deferred for this batch", who);
+    // nothing is refused from here on: a refused call has launched nothing, and its route can be used again
+
     corey_scan::ScanArgs a;
     a.u = u; a.delta = delta; a.A = A; a.Bm = Bm; a.Cm = Cm; a.Dv = Dv; a.z = z; a.dbias = delta_bias; a.h0 = h0;
     a.seqlens = seqlens; a.chunks_dev = chunks_dev; a.y = y; a.last_state = last_state;
@@ -91,8 +98,6 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     if (a.direct && (double)N * (double)L * (double)esz >= 2147483648.0) a.allow_split = 0;
     a.route = corey_finalise::Args{};
     if (route) {
-        if (!route->parts || !route->chunks_out || route->K < 2 || route->K > COREY_MAX_BINS || (route->nh != 1 && route->nh != B))
-            return fail(COREY_EINVAL, "%s: route was not filled by corey_route_device_deferred for this batch", who);
         a.route = *route;
         a.chunks_dev = route->chunks_out;                       // written by this call's first kernel, read by its second
         a.one_chunk = route->nh == 1 ? 1 : 0;
@@ -107,9 +112,6 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     // which would put more than 32 rows into a workgroup, run with idle lanes).
     int rows_cap = (int)(2048 / a.Np);
     a.rows_cap = rows_cap < 1 ? 1 : (rows_cap > 32 ? 32 : rows_cap);
-    // a lane addresses its row inside a group by a 32-bit byte offset from the group's first row
-    const int64_t row_bytes = L * (int64_t)esz;
-    if (row_bytes >= ((int64_t)1 << 31)) return fail(COREY_ESHAPE, "%s: a row of %lld bytes exceeds the kernels' 2 GiB", who, (long long)row_bytes);
     const int64_t fit = (((int64_t)1 << 32) - 1) / row_bytes;
     if (a.rows_cap > fit) a.rows_cap = (int)fit;
 

@@ -141,6 +141,21 @@ def test_gpu_entry_points_reject_bad_arguments_before_any_launch():
     assert lib.selective_scan_fwd_workspace(0, 16, 64) == 0 and lib.selective_scan_fwd_workspace(1, 300, 64) == 0
 
 
+def test_a_refused_routed_scan_has_launched_nothing():
+    """The one refusal that depends on the row's bytes comes before the reduction of the route is enqueued (without a GPU that
+    launch would fail with COREY_EHIP instead; with one it would use up the ticket)."""
+    lib = binding.lib()
+    fake, none = ctypes.c_void_p(0x1000), ctypes.c_void_p(0)
+    ticket = binding.DeferredRoute()
+    for i in range(7):                                   # the partial histograms, ranges and results of a whole-tensor statistic
+        ticket.opaque[i] = 0x1000
+    ctypes.memmove(ctypes.addressof(ticket) + 152, ctypes.byref((ctypes.c_int32 * 2)(16, 1)), 8)       # K and the histogram count
+    call = lambda t, L: lib.selective_scan_fwd_routed(fake, fake, fake, fake, fake, none, none, none, 1, none, none, 256, ctypes.byref(t),
+                                                      fake, fake, 1, 1, 1, 4, L, 0, fake, 1 << 40, none)
+    assert call(ticket, 1 << 30) == 3 and b"2 GiB" in lib.corey_last_error()
+    assert call(binding.DeferredRoute(), 64) == 1        # not a route
+
+
 def test_device_rule_rejects_a_policy_that_can_pick_a_chunk_the_scan_cannot_run():
     """corey_select_chunk_device / corey_route_device feed selective_scan_fwd's chunks_dev and the chunk-distribution
     counters (one slot per power of two up to COREY_MAX_CHUNK): a policy that can select more is refused on the host."""
