@@ -66,6 +66,14 @@ def test_either_side_of_the_size_where_a_workgroup_takes_several_sets(B, D, N, d
     _step(wl.Config(name="dec", B=B, D=D, N=N, L=1, dtype=dtype, K=16, chunks=(64,), seed=17 + N))
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16, wl.F16])
+@pytest.mark.parametrize("B,D,N", [(1, 409600, 16), (1, 409601, 16), (7, 58515, 12), (3, 8535, 256)])
+def test_either_side_of_the_line_between_single_sets_and_pairs(B, D, N, dtype):
+    """6400 sets of 256 lanes (one each) and 6401 (pairs, the last of one set, partial)."""
+    _say(f"decode sets B{B} D{D} N{N} {dtype}")
+    _step(wl.Config(name="dec", B=B, D=D, N=N, L=1, dtype=dtype, K=16, chunks=(64,), seed=18 + N))
+
+
 def test_generation_continues_a_prompt():
     """Prompt through selective_scan_fwd, then 6 tokens one at a time from its last_state: the outputs and the final state
     are those of the oracle's scan over the whole sequence."""
