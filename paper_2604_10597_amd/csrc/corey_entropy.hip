@@ -396,18 +396,21 @@ __global__ __launch_bounds__(kThreads) void k_entropy_range_flat(const word4* __
 
 constexpr int kMaxLdsBins = 8192;   // uint32 counters in LDS (32 KiB)
 
-// Private copies of the K counters a workgroup keeps in LDS: a power of two, as many as fit, 32 at most.  The copies of one bin
+// Private copies of the K counters a workgroup keeps in LDS: a power of two below what fits, 32 at most.  The copies of one bin
 // are neighbours (word bin * copies + copy, a lane's copy being its number modulo the copies): with 32 of them a lane's
 // counters all sit in a bank of the lane's own, so the adds of a wave never queue on a bank whatever the bins; with fewer,
 // lanes of different copies still never meet.  (Copies K + 1 words apart met by chance: 33.5 million values at K = 1024 34.3 us
-// against 33.1; at K = 256, where the sweep is bound by memory, 31.3 against 31.1.)
+// against 33.1; at K = 256, where the sweep is bound by memory, 31.3 against 31.1.)  Where only two fit, one: clearing and adding up
+// the second costs what its fewer meetings give back (K = 4096, two and one: 64 x 256 values 27.2 and 25.8 us for the statistic,
+// 33.5 million 44.8 and 44.6; K = 2500, where three fit, 33.5 million: two 40.0, one 40.6).
 struct LdsBins {
     uint32_t* s;
     int log2;                                                   // copies = 1 << log2
     uint32_t lane_byte, shift;
     __device__ __forceinline__ LdsBins(uint32_t* s_bins, int K) : s(s_bins)
     {
-        log2 = min(5, 31 - __clz(kMaxLdsBins / K));
+        const int fit = kMaxLdsBins / K;
+        log2 = fit < 3 ? 0 : min(5, 31 - __clz(fit));
         lane_byte = (threadIdx.x & ((1u << log2) - 1u)) * 4u;
         shift = (uint32_t)log2 + 2u;
     }

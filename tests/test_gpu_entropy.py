@@ -113,6 +113,15 @@ def test_bin_limits_and_eps():
     _check(store, val, wl.BF16, 64, eps=1e-12)
 
 
+@pytest.mark.parametrize("K", [255, 256, 257, 2048, 2049, 2730, 2731, 4095])
+def test_bin_counts_where_the_number_of_counter_copies_changes(K):
+    """32, 16 ... 2 copies of the counters per workgroup, one beyond 2730 bins; whole-tensor and per-sequence sweeps."""
+    _say(f"entropy counter copies K {K}")
+    store, val = wl.store(np.random.default_rng(K).laplace(0, 3, (2, 16, 512)).astype(np.float32), wl.BF16)
+    _check(store, val, wl.BF16, K)
+    _check(store, val, wl.BF16, K, seqlens=np.array([512, 77], np.int32))
+
+
 def test_degenerate_inputs():
     _say("entropy degenerate")
     const = np.full((1, 4, 96), 2.5, dtype=np.float32)
