@@ -737,7 +737,11 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     static_assert(!SPLIT || (G >= 2 && Gm::ROWS >= 2), "a split row needs a state of its own in every staging group");
     constexpr int E = K < 4 ? K : 4;                        // staged B / C values a lane reads per LDS instruction
     constexpr int KQ = K / E;
-    constexpr int Q = K < 16 && GH > 1 ? 2 : 1;             // states worked on at a time: each fills the other's wait states
+    // States worked on at a time: with two, each fills the other's wait states.  The binary32 rows of 8 steps have one where the
+    // registers are 128: the stored values take twice the room there, and two states spilled in the loop (4096 rows of 4096 steps
+    // at chunk 512: 107.8 us, with one 97.2; at chunk 256 115.4 and 106.7).
+    constexpr bool kTight = sizeof(T) == 4 && K == 8 && W == 4 && !DIRECT;
+    constexpr int Q = K < 16 && GH > 1 && !kTight ? 2 : 1;
     static_assert(GH % Q == 0, "whole sets of states");
     constexpr bool kEarlyC = K < 16 || W < 4;               // C is requested ahead of the folds where there are registers for it
     typedef float BCv __attribute__((ext_vector_type(E)));
