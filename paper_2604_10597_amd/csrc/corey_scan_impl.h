@@ -1178,10 +1178,27 @@ __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const
 
 // Launches of at most this many rows read B and C directly (three waves of one row per SIMD): with few waves to fill in, what
 // staging costs (a launch before the scan, a barrier per group of states, the copies' share of every wave's issue slots) is
-// more than the widening.  Measured, staged scan plus relayout against direct: 1024 rows of 4096 steps 38 and 32 us, 1536 of
+// more than the widening.  Measured in bf16, staged scan plus relayout against direct: 1024 rows of 4096 steps 38 and 32 us, 1536 of
 // 2048 28 and 22, 2048 of 4096 50 and 47; 8192 rows of 4096 141 and 147.
-constexpr int64_t kDirectRows = 3072;
-inline bool direct_launch(int64_t B, int64_t D, int64_t N, int64_t L) { return B * D <= kDirectRows && N % kMaxGroup == 0 && L >= 16; }
+// In binary32 a lane of 8 or 16 steps has twice the bytes in flight: two waves per SIMD fit, and the words of a 16-step lane are 64
+// bytes apart.  Beyond 1024 rows those launches read directly only where they know that all of their waves fit (4096 steps,
+// staged and direct, us: chunk 512, 1536 rows in pairs of rows 50.4 and 58.4, 2048 rows one each 62.3 and 55.0, 2560 rows 67.3 and
+// 81.4; chunk 1024, 1536 rows 46.1 and 64.8, 2048 53.6 and 74.9, 3072 66.1 and 110; chunk 256, lanes of 4 steps, four waves per SIMD,
+// 1536 rows 56 and 52.5, 3072 75.8 and 76.7, 1000 steps 26.9 and 24.8); with the chunk in device memory they are staged (chunk
+// 256 76.5 and 100 at 3072 rows, 1024 60 and 77 at 2048; 512 62.6 and 56 there).
+constexpr int64_t kDirectRows = 3072, kDirectRowsF32 = 1024, kDirectWavesF32 = 2048;
+inline bool direct_launch(int64_t B, int64_t D, int64_t N, int64_t L, bool f32, bool routed, int64_t d16, int klo, int split)
+{
+    const int64_t rows = B * D;
+    if (rows > kDirectRows || N % kMaxGroup != 0 || L < 16) return false;
+    if (!f32 || rows <= kDirectRowsF32) return true;
+    if (routed || d16 > 0) return false;
+    return klo == 4 || rows * (split ? 2 : 1) <= kDirectWavesF32;      // (a row of 8-step lanes is a wave: only tiles of 512 have them here)
+}
+// The geometries of direct launches (below) are those that the plan gives so few rows.
+static_assert(kDirectRows * (256 / 8) / 64 <= kFewWaves, "tiles up to 256 take 4 steps per lane");
+static_assert(kDirectRows * (512 / 8) / 64 <= 4096 && kDirectRows * (64 / 16) < 172032, "no 16-step lanes below tiles of 1024");
+static_assert(kDirectRows <= kManyRows, "tiles of 1024 are not divided");
 
 // Which geometries the plan can give a launch of either kind.
 template <int K, int CHUNK, bool DIRECT> constexpr bool geometry_exists()

@@ -64,3 +64,34 @@ def test_either_side_of_the_row_counts_the_launch_changes_at(B, D):
         y, s = _scan(d, chunk, chunks_dev=dev)
         check_y(y_to_f64(y)[:, rows], y_ref, cfg, f"y chunk {chunk}")
         assert_close(s.cpu().numpy()[:, rows], s_ref, fp32_rtol(cfg.L), f"state chunk {chunk}")
+
+
+@pytest.mark.parametrize("a_kind", ["mamba", "random"])
+@pytest.mark.parametrize("dtype,B,D", [(wl.F32, 1, 1024), (wl.F32, 1, 1025), (wl.F32, 2, 1024), (wl.F32, 1, 2049), (wl.F32, 1, 3072),
+                                       (wl.F32, 1, 3073), (wl.F32, 1, 4096), (wl.F32, 3, 1400), (wl.F16, 1, 3072), (wl.F16, 1, 3073),
+                                       (wl.F16, 1, 4200), (wl.F16, 3, 1400)])
+def test_direct_and_staged_launches_of_the_other_storage_types(dtype, B, D, a_kind):
+    """Which launches read B and C directly (they leave the workspace alone) and what either kind gives: static chunks, the chunk
+    in device memory, sequences of unequal lengths; one kind of rows and two (beyond 4096 rows)."""
+    L = 1100
+    cfg = wl.Config("edges_kinds", B, D, 16, L, dtype, 16, (), seqlens=None if B == 1 else (L, 530, 1024)[:B], seed=4300 + D)
+    w = wl.make(cfg, a_kind=a_kind)
+    d = upload(w)
+    rows = np.unique(np.concatenate([[0, 1, D - 2, D - 1], np.random.default_rng(5).integers(0, D, 4)]))
+    y_ref, s_ref = oracle_scan(w, rows=rows)
+    n = B * D
+    ws = torch.empty(corey.selective_scan_fwd_workspace(B, 16, L), dtype=torch.uint8, device="cuda")
+    for chunk in (256, 512, 1024):
+        for routed in (False, True):
+            if dtype != wl.F32 or n <= 1024 or n > 3072:
+                direct = n <= 3072
+            else:                                         # binary32: as long as the waves of the launch are resident together
+                pairs = corey.selective_scan_fwd_plan_split(B, D, 16, chunk)
+                direct = not routed and (chunk == 256 or (chunk == 512 and n * (1 + pairs) <= 2048))
+            ws.fill_(0x5A)
+            dev = torch.full((B,), chunk, dtype=torch.int32, device="cuda") if routed else None
+            y, s = _scan(d, 512 if routed else chunk, chunks_dev=dev, workspace=ws)
+            what = f"chunk {chunk} routed {routed}"
+            assert bool((ws == 0x5A).all()) == direct, what
+            check_y(y_to_f64(y)[:, rows], y_ref, cfg, "y " + what)
+            assert_close(s.cpu().numpy()[:, rows], s_ref, fp32_rtol(L), "state " + what)
