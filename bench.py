@@ -531,9 +531,9 @@ def main() -> int:
                        "r": round(p_ent["r"].item(), 4), "routed_chunk": p_chunk,
                        "scan_ms": {str(c): round(p_time(c), 4) for c in (64, 256, 512, 1024, 2048)},
                        "scan_ms_one_row_per_channel": {str(c): round(p_time(c, True), 4) for c in (64, 256, 512, 1024)},
-                       "two_rows_per_channel": {str(c): bool(corey.selective_scan_fwd_plan_split(pc.B, pc.D, pc.N, c)) for c in (64, 256, 512, 1024, 2048)},
-                       "note": "a launch this small gives every channel two rows of lanes with half of the states each (up to chunk "
-                               "1024); scan_ms_one_row_per_channel is the same launch under COREY_SCAN_WHOLE_ROWS",
+                       "two_rows_per_channel": {str(c): bool(corey.selective_scan_fwd_plan_split(pc.B, pc.D, pc.N, min(c, 1024))) for c in (64, 256, 512, 1024, 2048)},
+                       "note": "a launch this small gives every channel two rows of lanes with half of the states each (2048 is walked in tiles "
+                               "of 1024); scan_ms_one_row_per_channel is the same launch under COREY_SCAN_WHOLE_ROWS",
                        "scan_bytes": wl.scan_bytes(pc)}
         del pd, pw, p_ws, p_y
 

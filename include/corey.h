@@ -368,10 +368,11 @@ size_t selective_scan_fwd_workspace(int64_t B, int64_t N, int64_t L);
  * launch would otherwise leave most of the GPU without a wave (short tiles, few channels).  d16 = 0 or D means one lane
  * geometry for all channels.  The shape never changes results beyond floating-point reassociation (each channel is an
  * independent recurrence; the steps of a tile are combined by an associative scan).  -1 if the arguments are invalid.
- * selective_scan_fwd_plan_split: 1 when the launch gives every channel two rows of lanes, each with half of the N states
- * (launches of one lane geometry that would leave most SIMDs with at most one wave: small layers, short tiles; tiles of
- * at most 1024 steps, N >= 4): the two partial sums over states of the read-out y_t = C_t h_t (Method, Preliminaries) are added
- * once per tile.  0 otherwise, and always 0 under COREY_SCAN_WHOLE_ROWS. */
+ * selective_scan_fwd_plan_split: for a tile of `chunk` steps, 1 when the launch gives every channel two rows of lanes, each
+ * with half of the N states (launches of one lane geometry that would leave most SIMDs with at most one wave: small layers,
+ * short tiles; N >= 4): the two partial sums over states of the read-out y_t = C_t h_t (Method, Preliminaries) are added
+ * once per tile.  0 otherwise, and for 2048, which is no tile: it is walked in tiles of 1024 (512 in launches of more than 4096
+ * rows) and launched as that chunk is.  COREY_SCAN_WHOLE_ROWS keeps one row per channel in any launch. */
 int64_t selective_scan_fwd_plan(int64_t B, int64_t D, int64_t N, int32_t chunk);
 int32_t selective_scan_fwd_plan_steps(int64_t B, int64_t D, int64_t N, int32_t chunk);
 int32_t selective_scan_fwd_plan_split(int64_t B, int64_t D, int64_t N, int32_t chunk);

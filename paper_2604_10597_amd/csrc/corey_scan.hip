@@ -42,6 +42,7 @@ extern "C" int32_t selective_scan_fwd_plan_split(int64_t B, int64_t D, int64_t N
 {
     const int64_t d16 = selective_scan_fwd_plan(B, D, N, chunk);
     if (d16 < 0) return -1;
+    if (chunk > corey_scan::kMaxTile) return 0;               // not a tile (the header): such a chunk takes the launch of the tile it is walked in
     return corey_scan::plan_split(B, D, (int)N, chunk, d16, corey_scan::plan_klo(B, D, chunk, d16), 1);
 }
 

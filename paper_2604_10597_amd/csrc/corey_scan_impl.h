@@ -120,11 +120,14 @@ __host__ __device__ inline int plan_klo(int64_t B, int64_t D, int chunk, int64_t
 // A launch of one kind of row that still leaves the SIMDs short of waves (small layers, short tiles) gives every channel
 // TWO rows in the same workgroup, each with half of the states: twice the waves, each with half the per-state work and
 // all of the per-token work, and one exchange of partial y per tile through LDS.  The staging group must hold at least
-// one state of each half (tiles up to 1024 steps), and only the geometries such a launch can have are built.
+// one state of each half (every tile does), and only the geometries such a launch can have are built.  What counts is the tile
+// walked: chunk 2048 takes the launch of 1024 (bf16, 64 rows of 4096 steps: one row per channel 37.1 us, two 23.5; 256 of 32768 264
+// and 159; binary32 284 and 175).
 constexpr int64_t kSplitWaves = 1536;
 __host__ __device__ inline int plan_split(int64_t B, int64_t D, int N, int chunk, int64_t d16, int klo, int allow)
 {
     if (!allow || N < 4 || (d16 > 0 && d16 < D)) return 0;    // (fewer than four states: the second row would hold padding only)
+    chunk = tile_of(chunk, B * D);
     const int K = d16 >= D ? 16 : klo;
     if (!((K == 16 && chunk == 1024) || (K == 8 && chunk == 512) || (K == 4 && chunk <= 256))) return 0;
     const int lpr = chunk / K < 1 ? 1 : chunk / K;

@@ -95,3 +95,15 @@ def test_direct_and_staged_launches_of_the_other_storage_types(dtype, B, D, a_ki
             assert bool((ws == 0x5A).all()) == direct, what
             check_y(y_to_f64(y)[:, rows], y_ref, cfg, "y " + what)
             assert_close(s.cpu().numpy()[:, rows], s_ref, fp32_rtol(L), "state " + what)
+
+
+@pytest.mark.parametrize("dtype,B,D,N", [(wl.BF16, 1, 64, 16), (wl.F32, 2, 33, 4), (wl.F16, 1, 1536, 8), (wl.BF16, 1, 1537, 16)])
+def test_the_longest_chunk_is_launched_as_the_tiles_it_is_walked_in(dtype, B, D, N):
+    """Chunk 2048 on few rows takes the launch of chunk 1024, two rows per channel where that has them: the same bits, static and
+    with the chunk in device memory."""
+    cfg = wl.Config("edges_2048", B, D, N, 2500, dtype, 16, (), seed=4400 + D)
+    d = upload(wl.make(cfg, a_kind="random", with_h0=True))
+    want = _scan(d, 1024)
+    for dev in (None, torch.full((B,), 2048, dtype=torch.int32, device="cuda")):
+        got = _scan(d, 512 if dev is not None else 2048, chunks_dev=dev)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
