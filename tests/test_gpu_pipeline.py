@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2604_10597_amd as corey
-from gpu_util import assert_close, counts_u32, fp32_rtol, to_dev, upload
+from gpu_util import assert_close, check_y, counts_u32, fp32_rtol, oracle_scan, to_dev, upload, y_to_f64
 from paper_2604_10597_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -134,3 +134,50 @@ def test_deferred_route_argument_errors():
                                        ptr(t), 1, 3, 4, 16, 64, 2, ptr(ws), ws.numel(), None)
     assert st == 1                                                # COREY_SCAN_ONE_CHUNK is not the caller's to set here
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("case", ["whole_tensor_batch", "per_sequence", "producer_exact", "producer_sampled", "binary32"])
+def test_deferred_route_inside_a_staged_scan(case):
+    """Launches that rewrite B and C first (beyond 3072 rows; 1024 in binary32) carry the deferred reduction in that kernel and clear
+    the partial histograms in the scan: against corey_route_device + selective_scan_fwd, bit for bit, the hand-over buffer of the
+    producer used over three calls in a row; y and the state against the oracle."""
+    print(f"[case] deferred route, staged: {case}", flush=True)
+    pol = corey.policy_default()
+    lens = (700, 33, 512) if case == "per_sequence" else None
+    B, dtype = {"whole_tensor_batch": (3, wl.BF16), "per_sequence": (3, wl.F16), "binary32": (1, wl.F32)}.get(case, (1, wl.BF16))
+    cfg = wl.Config("staged_route", B, 1100 if B == 3 else (1100 if dtype == wl.F32 else 4300), 16, 700, dtype, 64, (), seqlens=lens, seed=4500)
+    if lens:
+        pol.mode = 1
+    w = wl.make(cfg, a_kind="random")
+    d = upload(w)
+    u, parts, kw = d["u"], None, {}
+    if case.startswith("producer"):
+        conv = wl.make_conv(cfg, 4)
+        x = to_dev(conv["dev"]["x"], cfg.dtype)
+        cw, cb = torch.from_numpy(conv["dev"]["weight"]).cuda(), torch.from_numpy(conv["dev"]["bias"]).cuda()
+        u, _, parts = corey.causal_conv1d_silu_fwd(x, cw, cb)
+        kw = dict(stride=8, block=512) if case == "producer_sampled" else {}
+    calls_a, calls_b = (torch.zeros(12, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.empty(corey.selective_scan_fwd_workspace(B, 16, cfg.L), dtype=torch.uint8, device="cuda")
+    for rep in range(3):
+        a = corey.corey_route_device(u, cfg.K, pol, seqlens=d["seqlens"], range_parts=parts, chunk_calls=calls_a, **kw)
+        ya, sa = corey.selective_scan_fwd(u, d["delta"], d["A"], d["B"], d["C"], chunk=256, chunks_dev=a["chunks"], **_scan_args(d))
+        b = corey.corey_route_device_deferred(u, cfg.K, pol, seqlens=d["seqlens"], range_parts=parts, chunk_calls=calls_b, **kw)
+        ws.fill_(0x5A)
+        yb, sb = corey.selective_scan_fwd(u, d["delta"], d["A"], d["B"], d["C"], chunk=256, route=b["route"], workspace=ws, **_scan_args(d))
+        torch.cuda.synchronize()
+        assert not bool((ws == 0x5A).all())                        # staged: the kernel in front of the scan has run
+        for k in ("counts", "chunks", "range"):
+            assert torch.equal(a[k], b[k]), (case, rep, k)
+        for k in ("H", "r"):
+            assert torch.equal(a[k].view(torch.int64), b[k].view(torch.int64)), (case, rep, k)
+        bits = torch.int32 if dtype == wl.F32 else torch.int16
+        assert torch.equal(ya.view(bits), yb.view(bits)) and torch.equal(sa, sb), (case, rep)
+        assert int(b["counts"].sum()) > 0 and torch.equal(calls_a, calls_b)
+    ref = oracle.entropy_hist(u.float().cpu().numpy(), cfg.K, seqlens=w.seqlens if lens else None, range_all=(case == "producer_sampled"), **kw)
+    assert np.array_equal(counts_u32(b["counts"]).reshape(ref["counts"].shape), ref["counts"])
+    if parts is None:
+        rows = np.array([0, 1, 537, cfg.D - 1])
+        y_ref, s_ref = oracle_scan(w, rows=rows, use_h0=False)
+        check_y(y_to_f64(yb)[:, rows], y_ref, cfg, "y")
+        assert_close(sb.cpu().numpy()[:, rows], s_ref, fp32_rtol(cfg.L), "state")
