@@ -554,6 +554,11 @@ __device__ __forceinline__ void scan_segments(int jseg, float (&P)[Q], float (&h
     }
 }
 
+// The state goes from a row's last lane to its first through LDS, between two tiles or, in a row of a single group of states, two
+// statements.  A row lies inside one wave, whose LDS accesses are done in order: no wait and no barrier, only the compiler has
+// to leave them in that order.
+__device__ __forceinline__ void carry_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 // ------------------------------------------------------------------------------------------- kernel arguments
 struct ScanArgs {
     const void* u;
@@ -1075,6 +1080,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 for (int s = 0; s < Q; ++s) h_g[nl + s] = h[s];
                 if (DIRECT && nl + Q == GH) {
                     *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
+                    carry_fence();
                     const int nn = last_group ? 0 : n0 + GH;
                     cin_nx = *reinterpret_cast<const GHv*>(carry_rd + nn);
                     if constexpr (!STRUCT) A2_nx = *reinterpret_cast<const GHv*>(A2_row + nn);
@@ -1102,7 +1108,10 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
             };
 #pragma unroll
             for (int nl = 0; nl < GH; nl += Q) states(nl);      // straight-line code for the whole group
-            if constexpr (!DIRECT) *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
+            if constexpr (!DIRECT) {
+                *reinterpret_cast<GHv*>(carry_wr + n0) = h_g;
+                carry_fence();
+            }
         }
 
         if constexpr (SPLIT) {                              // the second row of a channel hands over its part of the sum over states
