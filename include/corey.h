@@ -211,15 +211,17 @@ int corey_route_device(const void* x, corey_dtype dt, int64_t B, int64_t D, int6
                        int32_t* chunks_out, void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* -------------------------------------------------------------------------------------------------------
- * corey_route_device_deferred / selective_scan_fwd_routed -- the routed path with one launch fewer.  The paper names
- * "histogram construction, synchronization boundaries around runtime feature collection, and scheduler dispatch
+ * corey_route_device_deferred / selective_scan_fwd_routed -- the routed path with the reduction left to the scan's call, which
+ * launches of many rows need no launch of its own for.  The paper names "histogram construction, synchronization boundaries around runtime feature collection, and scheduler dispatch
  * overhead" as the costs that make routing lose end to end: each dependent launch between the producer of u and the
  * scan is such a cost.  corey_route_device_deferred runs the sweeps of corey_route_device but not its O(K) reduction;
  * it fills *route (HOST, caller-owned, opaque) instead.  selective_scan_fwd_routed is selective_scan_fwd with the
- * reduction and the chunk rule evaluated at the start of its own first kernel: every result corey_route_device
- * would have written (counts, H, r, range, chunk, chunk counters) is written then, bit for bit the same, and the scan
+ * reduction and the chunk rule evaluated first: at the start of the kernel that rewrites B and C, or, in launches that read B
+ * and C directly (at most 3072 rows B * D, 1024 in COREY_F32; see workspace of selective_scan_fwd), by the reduction's own kernel, as many
+ * launches as corey_route_device takes then.  Every result corey_route_device would have written (counts, H, r, range, chunk, chunk counters) is written then, bit for bit the same, and the scan
  * runs with the chunk so selected (per sequence when the statistic was per sequence, else one chunk for all).
- * With range_parts from the producer the whole routed path is: producer, one count sweep, scan.
+ * With range_parts from the producer the whole routed path is: producer, one count sweep, scan.  A refused call has launched
+ * nothing and leaves *route as it was.
  *   Arguments as for corey_route_device and selective_scan_fwd (which has no chunks_dev here).  ema_state must be NULL
  *   (COREY_EUNSUPPORTED: the smoothed rule needs the reduction in a launch of its own).  *route is valid for ONE
  *   selective_scan_fwd_routed call on the same stream, with the buffers it names still alive; `chunk` of that call is
@@ -318,8 +320,9 @@ int causal_conv1d_silu_fwd(const void* x, const float* weight, const float* bias
  *                    non-power-of-two entries fall back to `chunk`.
  *   last_state       DEVICE float[B, D, N], required.
  *   workspace        DEVICE, at least selective_scan_fwd_workspace(B, N, L) bytes, 16-byte aligned; scratch only
- *                    (launches of many rows first rewrite B and C there as fp32 in the order, or the two orders, the
- *                    scan reads them in).
+ *                    (launches of more than 3072 rows B * D, most COREY_F32 ones of more than 1024, and those with L < 16
+ *                    or an N that is no multiple of 4 first rewrite B and C there as fp32 in the order, or the two orders,
+ *                    the scan reads them in; the others read B and C directly).
  *   1 <= N <= COREY_MAX_STATE;  B*D*L and B*N*L must fit in int64 and B*D in int32.
  *   flags            bitwise OR of COREY_SCAN_* options, 0 for the defaults.
  *                    COREY_SCAN_GENERAL_A: never take the fast path for structured A.  By default, when

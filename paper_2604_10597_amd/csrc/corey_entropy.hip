@@ -19,7 +19,7 @@
 // starts by reducing those partials, and only the sampled 16-byte words are fetched at all.  When the producer of the
 // tensor hands over its partial ranges (and, beside them, partial histograms it cleared) the statistic is ONE launch,
 // the count sweep, plus the reduction; the reduction leaves those partial histograms cleared for the next call.  The
-// reduction itself (corey_finalise.h) can also be left to the first kernel of a routed scan (corey_route_device_deferred).
+// reduction itself (corey_finalise.h) can also be left to a routed scan (corey_route_device_deferred).
 // All of it is bandwidth work: no matrix instructions.
 #include <hip/hip_runtime.h>
 
@@ -739,7 +739,7 @@ int launch(const void* x, int64_t B, int64_t D, int64_t L, const int32_t* seqlen
     fa.chunk_calls = tail.chunk_calls; fa.L_all = L; fa.eps = eps; fa.ema_lambda = tail.ema_lambda;
     if (tail.pol) fa.pol = *tail.pol;
     fa.K = K; fa.nh = nh; fa.rezero = rezero ? 1 : 0;
-    if (tail.defer) *tail.defer = fa;                           // the scan's first kernel will do it
+    if (tail.defer) *tail.defer = fa;                           // the scan's call will do it
     else k_entropy_finalise<<<dim3((unsigned)nh), dim3(kThreads), 0, stream>>>(fa);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return corey::hip_fail(e, "corey_entropy_hist launch");

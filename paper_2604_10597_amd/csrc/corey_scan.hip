@@ -110,7 +110,7 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     a.route = corey_finalise::Args{};
     if (route) {
         a.route = *route;
-        a.chunks_dev = route->chunks_out;                       // written by this call's first kernel, read by its second
+        a.chunks_dev = route->chunks_out;                       // written by this call's first kernel, read by its last
         a.one_chunk = route->nh == 1 ? 1 : 0;
         if (a.direct) {                                         // no kernel before the scan to carry the reduction: a launch of its own
             a.route = corey_finalise::Args{};

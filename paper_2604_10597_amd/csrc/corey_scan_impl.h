@@ -3,9 +3,9 @@
 // corey_scan_bf16.hip, corey_scan_f16.hip, and corey_scan_any_*.hip for the kernels that read the chunk from device memory) so
 // that they compile in parallel; corey_scan.hip holds the host entry.
 //
-// Two kernels per call.
+// One kernel per call for launches of few rows (see kDirectRows), two for the others.
 //
-// k_relayout_bc   converts B and C ([B, N, L]) once to fp32 in the caller's workspace, tile by tile, in exactly
+// k_relayout_bc   (launches of many rows) converts B and C ([B, N, L]) once to fp32 in the caller's workspace, tile by tile, in exactly
 //                 the order the scan's lanes read them.  B and C are shared by every channel of a sequence, so
 //                 doing this once per call removes all conversion work from the scan (a few MB of traffic against
 //                 the scan's hundreds).
@@ -16,14 +16,15 @@
 //                 Inside a tile a row is spread over LPR = CHUNK / K consecutive lanes, each lane owning K (16, 8 or
 //                 4) consecutive time steps: loads of u / delta / z and the store of y are one vector per lane (16 bytes
 //                 or more; 8 for four 16-bit values), contiguous along L.  The fp32 B / C values of a few states at a time are copied from the
-//                 workspace straight into LDS (global_load_lds, no registers), double buffered.  For every state
-//                 index n a lane
+//                 workspace straight into LDS (global_load_lds, no registers), double buffered; in a launch of few rows a
+//                 lane loads those of its own steps as stored.  A chunk longer than a wave's lanes take is walked in parts
+//                 (tile_of).  For every state index n a lane
 //   1. discretises its K steps (a_i = exp2(dl_i A log2e), b_i = dl_i B_i u_i) and folds them, from a zero state,
 //      into the pair (P, h) of the affine map  x -> P x + h  of its sub-block (P is one exp2 of the summed dl);
 //      the first lane of the row also applies its map to the state carried from the previous tile;
 //   2. takes part in an inclusive scan of the pairs across the lanes of the row (the pair operator is associative),
-//      written as single DPP instructions; h then is the true state at the end of the lane's sub-block.  Rows
-//      wider than a wave pass the wave totals through LDS;
+//      written as single DPP instructions; h then is the true state at the end of the lane's sub-block.  No row is
+//      wider than a wave;
 //   3. receives the state entering its sub-block from the lane to its left, replays its K steps from it and
 //      accumulates y_i += C_i h_i.
 // The fp32 state carried from tile to tile lives in LDS; the last lane of a row refreshes it.
@@ -704,8 +705,8 @@ __device__ __forceinline__ void stage_async(const float* __restrict__ srcB, cons
             uint32_t voff = (uint32_t)(s + lane) * 16u;
             // SCALAR_BASE: the empty asm keeps the offset from being widened to 64 bits outside the tile loop, so that the
             // copy uses its scalar-base addressing mode; otherwise the compiler adds base and offset with one vector
-            // instruction per copy.  Long tiles stage few states per group and gain from it (chunk 1024: -7 %, 2048:
-            // -5 % on 5120 channels); at chunk 512 and below the other schedule measured 1 % faster.
+            // instruction per copy.  Tiles of 1024 stage few states per group and gain from it (-7 %, measured
+            // on 5120 channels while those walked such tiles); at 512 and below the other schedule measured 1 % faster.
             if constexpr (SCALAR_BASE) asm volatile("" : "+v"(voff));
             __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(srcB) + voff, dstB + (size_t)s * 4, 16, 0, 0);
             __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(srcC) + voff, dstC + (size_t)s * 4, 16, 0, 0);
