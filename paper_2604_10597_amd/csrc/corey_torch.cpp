@@ -108,16 +108,22 @@ void want_reachable(const at::Tensor& t, const char* name)
     if (!(t.is_cuda() || t.is_pinned()) || !t.is_contiguous()) raise(PyExc_ValueError, "%s must be a contiguous GPU tensor", name);
 }
 
-// A buffer the kernels read or write through its pointer: reachable, contiguous, of this type and with room for n values.  Its
-// shape is the caller's business (counts of one histogram may be [K], an output longer than needed is filled at its start).
+// A tensor argument the kernels read or write through its pointer: of this type and with room for n values.  Its shape is the
+// caller's business (counts of one histogram may be [K], an output longer than needed is filled at its start).
 void want_room(const at::Tensor* t, const char* name, at::ScalarType type, int64_t n)
 {
-    if (!t || !t->defined()) return;
-    want_reachable(*t, name);
-    const bool bits = type == at::kInt && t->scalar_type() == at::kUInt32;      // counts and chunks: 32-bit patterns either way
-    if ((t->scalar_type() == type || bits) && t->numel() >= n) return;
+    if (!t) return;
+    const at::ScalarType have = t->scalar_type();
+    if ((have == type || (type == at::kInt && have == at::kUInt32)) && t->numel() >= n) return;      // (counts and chunks: 32-bit patterns either way)
     const std::string s = std::string(c10::toString(type)) + " with room for " + std::to_string(n) + " values";
     raise(PyExc_TypeError, "%s must be %s", name, s.c_str());
+}
+// ... an entry of a result dict, which nobody has looked at yet
+void want_room(const at::Tensor& t, const char* name, at::ScalarType type, int64_t n)
+{
+    if (!t.defined()) return;
+    want_reachable(t, name);
+    want_room(&t, name, type, n);
 }
 // ... of at least n bytes, whatever its type (workspaces)
 void want_bytes(const at::Tensor* t, const char* name, int64_t n)
@@ -306,10 +312,10 @@ struct Results {
     Results(PyObject* out, int64_t nh, int64_t K)
         : counts(out_tensor(out, "counts")), H(out_tensor(out, "H")), r(out_tensor(out, "r")), range(out_tensor(out, "range", true))
     {
-        want_room(&counts, "counts", at::kInt, K > 0 ? nh * K : 0);      // (the library refuses any other K)
-        want_room(&H, "H", at::kDouble, nh);
-        want_room(&r, "r", at::kDouble, nh);
-        want_room(&range, "range", at::kFloat, 2 * nh);
+        want_room(counts, "counts", at::kInt, K > 0 ? nh * K : 0);      // (the library refuses any other K)
+        want_room(H, "H", at::kDouble, nh);
+        want_room(r, "r", at::kDouble, nh);
+        want_room(range, "range", at::kFloat, 2 * nh);
     }
 };
 
@@ -501,7 +507,7 @@ struct TableCall {
         if (p == Py_None) return;
         policy = structure<corey_policy>(p, "policy");
         chunks = out_tensor(out, "chunks", true);
-        want_room(&chunks, "chunks", at::kInt, 1);
+        want_room(chunks, "chunks", at::kInt, 1);
         if (chunks.defined()) return;
         chunks = empty({1}, at::kInt, like);
         put(out, "chunks", chunks);
@@ -573,7 +579,7 @@ template <bool DEFERRED> PyObject* route(PyObject* const* a)
     const at::Tensor ws = statistic_workspace(a[8], out.o, true, g.B, K, x);
     const Results o(out.o, nh, K);
     const at::Tensor chunks = out_tensor(out.o, "chunks");
-    want_room(&chunks, "chunks", at::kInt, nh);
+    want_room(chunks, "chunks", at::kInt, nh);
     const int32_t* lens = ptr_as<int32_t>(seqlens);
     uint32_t* cc = ptr_as<uint32_t>(calls);
     void* s = stream();

@@ -494,7 +494,7 @@ def test_full_size_sampled_rows(name):
         worst[:] = max(worst[0], a), max(worst[1], b), max(worst[2], c)
 
     for general_a in (True, False):
-        for c in sorted({chunk, 64, 512, 1024, 2048}):      # (small layers: two rows per channel up to 1024, one beyond)
+        for c in sorted({chunk, 64, 512, 1024, 2048}):      # (small layers: two rows per channel)
             _say(f"scan full size {name} chunk={c} (routed={chunk}) general_a={general_a}")
             y, last = corey.selective_scan_fwd(d["u"], d["delta"], d["A"], d["B"], d["C"], Dv=d["D"], z=d["z"],
                                                delta_bias=d["delta_bias"], seqlens=d["seqlens"], chunk=c, general_a=general_a)
