@@ -10,7 +10,7 @@ memory (no host round trip inside a step).  Prints ONE JSON line.
              events on the launch stream inside the timed region, against the 8 TB/s HBM peak; the `alu` block
              beside it prices the same launches against the fp32 vector peak, which is the bound that binds
   ceilings   a plain device copy of the same bytes on this machine, and the time the scan's own instruction count needs
-             at one plain wave64 instruction per 4 cycles and one transcendental per 8 on each SIMD
+             at one plain wave64 instruction per 2 cycles and one transcendental per 8 on each SIMD
   per_chunk  scan-only latency, GB/s and tokens/s for every chunk of the sweep
   producer   the causal convolution + SiLU that writes u and its range, and the statistic with and without that range
              (two sweeps, one sweep, one sweep over every 8th block), each also as a percentage of the scan
@@ -53,11 +53,11 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published (256 CUs x 2.4 GHz x 256 flop/clk)
 # HBM bytes per scan launch measured with `rocprofv3 --pmc FETCH_SIZE` / `WRITE_SIZE`, scaled by what the same counters
 # read for a 256 MiB device copy (profiles/hot_path_c4_mamba2p8b_counters.txt); not re-measured by this script
-MEASURED_TRAFFIC_BYTES = {"c4_mamba2p8b": 749_400_000}
+MEASURED_TRAFFIC_BYTES = {"c4_mamba2p8b": 710_000_000}
 TRAFFIC_FROM = "profiles/hot_path_c4_mamba2p8b_counters.txt"
 # vector instructions per wave-level state update of the scan at the routed chunk, from SQ_INSTS_VALU and
 # SQ_INSTS_VALU_TRANS_F32 of the same counter summary
-COUNTED_INSTRUCTIONS = {"c4_mamba2p8b": {"plain": 7.42, "trans": 1.325, "from": "profiles/hot_path_c4_mamba2p8b_counters.txt"}}
+COUNTED_INSTRUCTIONS = {"c4_mamba2p8b": {"plain": 7.35, "trans": 1.326, "from": "profiles/hot_path_c4_mamba2p8b_counters.txt"}}
 
 
 def cpu_model() -> str:
@@ -276,8 +276,9 @@ def main() -> int:
 
     # ---- ceilings beside the HBM peak: what a plain device copy reaches on this machine, and the time the scan's own
     # instruction stream needs when every SIMD issues without a gap (counts per wave-level state update from the
-    # committed counter summary; a SIMD issues one plain wave64 fp32 instruction per 4 cycles and one transcendental per
-    # 8 -- packed fp32 instructions are not used -- as the same counters and register-only probes show)
+    # committed counter summary; a SIMD issues one plain wave64 fp32 instruction per 2 cycles while another of its waves
+    # has one to issue beside it, and one transcendental per 8, as register-only loops show: a lower bound, the lane scan's DPP
+    # instructions take 4)
     src = torch.empty(scan_bytes // 2, dtype=torch.uint8, device="cuda")
     dst = torch.empty_like(src)
     for _ in range(3):
@@ -294,13 +295,14 @@ def main() -> int:
     wave_updates = state_updates / 64.0
     counted = COUNTED_INSTRUCTIONS.get(cfg.name)
     ceilings = {"device_copy_GBps": round(scan_bytes / copy_ms * 1e-6, 1), "device_copy_ms_for_scan_bytes": round(copy_ms, 4),
-                "floor_cycles_per_wave_update": 28.0,
-                "floor_note": "the two-pass recurrence needs 5 plain vector instructions (4 cycles each on a SIMD) and one "
-                              "exponential (8 cycles) per wave-level state update: 28 SIMD cycles"}
+                "floor_cycles_per_wave_update": 18.0,
+                "floor_note": "the two-pass recurrence needs 5 plain vector instructions (2 cycles each on a SIMD while "
+                              "another wave has one to issue beside it) and one exponential (8 cycles) per wave-level state "
+                              "update: 18 SIMD cycles"}
     if counted:
-        issue_cycles = wave_updates / 1024.0 * (counted["plain"] * 4.0 + counted["trans"] * 8.0)          # per SIMD (256 CUs x 4)
+        issue_cycles = wave_updates / 1024.0 * (counted["plain"] * 2.0 + counted["trans"] * 8.0)          # per SIMD (256 CUs x 4)
         ceilings.update({"counted_plain_per_wave_update": counted["plain"], "counted_transcendental_per_wave_update": counted["trans"],
-                         "counted_cycles_per_wave_update": round(counted["plain"] * 4.0 + counted["trans"] * 8.0, 2),
+                         "counted_cycles_per_wave_update": round(counted["plain"] * 2.0 + counted["trans"] * 8.0, 2),
                          "counted_from": counted["from"],
                          "issue_model_ms_at_2p4GHz": round(issue_cycles / 2.4e9 * 1e3, 4)})
 
@@ -624,11 +626,9 @@ def main() -> int:
                      "avg_launch_ms": round(scan_ms, 4)},
         "alu": {"achieved": round(scan_flop / scan_ms * 1e-9, 2), "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(scan_flop / scan_ms * 1e-9 / FP32_VECTOR_PEAK_TFLOPS, 4),
-                "peak_plain_instructions": FP32_VECTOR_PEAK_TFLOPS / 2,      # 16 lanes per SIMD and cycle: packed fp32 is not used
-                "frac_plain_instructions": round(scan_flop / scan_ms * 1e-9 / (FP32_VECTOR_PEAK_TFLOPS / 2), 4),
                 "simd_cycles_per_wave_update_if_2p4GHz": round(scan_ms * 1e-3 * 2.4e9 * 1024.0 / wave_updates, 2),
                 "cycles_note": "launch time x 2.4 GHz x 1024 SIMDs / wave-level state updates: an upper bound on the cycles a SIMD spends "
-                               "per update (the chip holds 2.1 to 2.3 GHz under this load); floor of the formulation: 28",
+                               "per update (the chip holds 2.1 to 2.3 GHz under this load); floor of the formulation: 18",
                 "flop_per_state_update": 7, "state_updates": state_updates},
         "graph_replay": {"ms_per_step": round(ms_step_graph, 4), "GBps": round(scan_bytes / ms_step_graph * 1e-6, 1),
                          "routed_chunk": chunk_graph,
