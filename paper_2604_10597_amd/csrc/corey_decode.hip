@@ -23,12 +23,13 @@ using corey_scan::softplus;
 constexpr int kThreads = 256;
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Sets of 256 lanes a workgroup takes.  Up to kManySets every set is a workgroup of its own (states that are
-// still in cache, one by one and in pairs: 5120 channels of 16 states, 16 sequences or 1280 sets 5.1 and 5.8 us, 26 or 2080 sets 5.9 and 6.4, 64 or 5120 sets 9.2 and 9.4, 80 or 6400 sets 10.5 and 11.1, 96 or 7680
-// sets 12.85 and 12.87; 128 sequences of 1024 channels of 64 states, 8192 sets, 14.5 and 13.8).  Above, pairs (512 sequences, 40960
-// sets, from HBM: 72.8 us one by one, 70.9 in pairs, 74.4 in fours, 89.6 in eights).
+// Sets of 256 lanes a workgroup takes.  Up to a line every set is a workgroup of its own, above it pairs.  One by one and in pairs,
+// states from HBM, us: binary32, 5120 channels of 16 states, 26 sequences (2080 sets) 6.4 and 7.2, 40 8.6 and 9.4, 64 (5120 sets) 11.9
+// and 12.7, 80 14.3 and 15.3, 96 (7680 sets) 17.7 and 17.8; bf16 26 7.1 and 7.3, 40 9.4 and 9.6, 52 (4160 sets) 11.1 and 11.4, 64
+// 12.9 and 12.9 (14.4 and 14.2 with the convolution's step in front), 64 of 1024 channels of 64 states (4096 sets) 11.1 and 10.8.
+// More sets than two: 512 sequences (40960 sets, bf16) 72.8 us one by one, 70.9 in pairs, 74.4 in fours, 89.6 in eights.
 constexpr int kSets = 2;
-constexpr uint64_t kManySets = 6400;
+template <typename T> constexpr uint64_t many_sets() { return sizeof(T) == 4 ? 6400 : 4000; }
 
 // States in whole, aligned groups of four: U sets of rows per workgroup, every load of theirs issued before any use, B and C by
 // words of four values (value by value they are eight loads of two bytes in a lane, and the trips to memory queue behind them).
@@ -149,7 +150,7 @@ void launch(void* state, const void* x, const void* delta, const float* A, const
             lpr_log2, softplus_on);
     };
     if (!vector_ok) go(k_state_update_any<T>, sets);
-    else if (sets > kManySets) go(k_state_update<T, kSets>, (sets + kSets - 1) / kSets);
+    else if (sets > many_sets<T>()) go(k_state_update<T, kSets>, (sets + kSets - 1) / kSets);
     else go(k_state_update<T, 1>, sets);
 }
 

@@ -67,9 +67,9 @@ def test_either_side_of_the_size_where_a_workgroup_takes_several_sets(B, D, N, d
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16, wl.F16])
-@pytest.mark.parametrize("B,D,N", [(1, 409600, 16), (1, 409601, 16), (7, 58515, 12), (3, 8535, 256)])
+@pytest.mark.parametrize("B,D,N", [(1, 409600, 16), (1, 409601, 16), (7, 58515, 12), (3, 8535, 256), (1, 256000, 16), (1, 256001, 16)])
 def test_either_side_of_the_line_between_single_sets_and_pairs(B, D, N, dtype):
-    """6400 sets of 256 lanes (one each) and 6401 (pairs, the last of one set, partial)."""
+    """6400 sets of 256 lanes (one each in binary32) and 6401 (pairs, the last of one set, partial); 4000 and 4001, the line in 16 bits."""
     _say(f"decode sets B{B} D{D} N{N} {dtype}")
     _step(wl.Config(name="dec", B=B, D=D, N=N, L=1, dtype=dtype, K=16, chunks=(64,), seed=18 + N))
 
