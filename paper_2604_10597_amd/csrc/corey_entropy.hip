@@ -13,8 +13,8 @@
 //                       of many workgroups do not all queue on the same few cache lines)
 //   k_entropy_finalise  sums the partial histograms into counts, then p_k, H = -sum p log(p + eps) and r in
 //                       double, one workgroup per histogram
-// The common call (one histogram over the whole tensor, aligned, every value or every stride-th block of a
-// power-of-two number of 16-byte words) takes the *_flat kernels: the range sweep leaves one partial range per
+// The common calls (one histogram over the whole tensor, aligned, every value or every stride-th block of a
+// power-of-two number of 16-byte words; a histogram per sequence, rows starting at words) take the *_flat kernels: the range sweep leaves one partial range per
 // workgroup (no atomics, so nothing has to be cleared first; it also clears the partial counts), the count sweep
 // starts by reducing those partials, and only the sampled 16-byte words are fetched at all.  When the producer of the
 // tensor hands over its partial ranges (and, beside them, partial histograms it cleared) the statistic is ONE launch,
@@ -48,6 +48,7 @@ using corey_range::reduce_range_keys;
 constexpr int kVecBytes = 16;
 using corey_range::kParts;     // partial histograms per histogram in the workspace
 constexpr int kMaxBlocks = COREY_RANGE_PARTS;  // most workgroups per sweep (four per compute unit) and partial ranges kept
+constexpr int kMostRowHistograms = 64;          // per-sequence flat sweeps: at least 16 workgroups for a histogram
 constexpr int kFlatBlocks = 512;               // workgroups of a flat sweep: two per compute unit measured 4 % (exact) to
                                                // 11 % (sampled) faster than four (fewer LDS clears, merges and range folds)
 
@@ -319,11 +320,6 @@ __device__ __forceinline__ void publish_range(float lo, float hi, bool nan, Rang
     }
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// Fast path for the common call: one histogram over the whole tensor, every value used, 16-byte aligned.
-// The tensor is then a flat array of 16-byte words; a workgroup walks it grid-stride with kUnroll loads in
-// flight per lane and nothing but straight-line code in between.
-
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_entropy_range(const T* __restrict__ x, int64_t B, int64_t D, int64_t L,
                                                             const int32_t* __restrict__ seqlens, int64_t stride, int64_t block,
@@ -348,41 +344,110 @@ __global__ __launch_bounds__(kThreads) void k_entropy_range(const T* __restrict_
     publish_range(lo, hi, nan, &subs[h * kSubSlots + blockIdx.x % kSubSlots]);
 }
 
-// The 16-byte words of a flat sweep.  Unsampled: word i is word i.  Sampled: the tensor is cut into blocks of
-// 2^bw_log2 words and every stride-th block is used; the sampled words are numbered consecutively.
-template <bool SAMPLED> struct WordMap {
+// ---------------------------------------------------------------------------------------------------------
+// The common calls: the values are a flat array of 16-byte words; a workgroup walks it grid-stride with kUnroll loads in
+// flight per lane and little but straight-line code in between.
+
+// The 16-byte words of a flat sweep, numbered consecutively.  kAll: the tensor's words.  kSampled: the tensor is cut into blocks of
+// 2^bw_log2 words and every stride-th block is used.  kRows: histogram h is the valid part of sequence h, D rows of seqlens[h]
+// values; rows start at words, and the last word of a row may hold values beyond the valid ones (`rem` of it are valid, 0: all).
+enum Mode { kAll, kSampled, kRows };
+struct Words {
+    int64_t nwords, stride;     // kAll, kSampled
+    const int32_t* seqlens;     // kRows
+    int64_t D, L;
     int bw_log2;
-    int64_t stride;
+};
+template <typename T, int MODE> struct WordMap {
+    static constexpr int V = Elem<T>::kVec;
+    int64_t nwords, stride, base;
+    int bw_log2, rem;
+    uint32_t wpr, row_words, magic;
+    __device__ __forceinline__ WordMap(const Words& w, int h) : nwords(w.nwords), stride(w.stride), base(0), bw_log2(w.bw_log2), rem(0)
+    {
+        if constexpr (MODE == kRows) {
+            int64_t len = w.seqlens[h];
+            len = len < 0 ? 0 : (len > w.L ? w.L : len);
+            rem = (int)(len % V);
+            wpr = (uint32_t)((len + V - 1) / V);
+            row_words = (uint32_t)(w.L / V);
+            nwords = w.D * (int64_t)wpr;
+            base = (int64_t)h * w.D * row_words;
+            magic = wpr > 1 ? (uint32_t)(0xffffffffu / wpr) + 1u : 0u;       // ceil(2^32 / wpr) or one more
+        }
+    }
+    // (kRows: the host keeps the words of a histogram below 2^31; the quotient by the rounded-up reciprocal is then right or one
+    // too large)
     __device__ __forceinline__ int64_t operator()(int64_t i) const
     {
-        if constexpr (!SAMPLED) return i;
-        const int64_t sb = i >> bw_log2;
-        return ((sb * stride) << bw_log2) + (i - (sb << bw_log2));
+        if constexpr (MODE == kSampled) {
+            const int64_t sb = i >> bw_log2;
+            return ((sb * stride) << bw_log2) + (i - (sb << bw_log2));
+        } else if constexpr (MODE == kRows) {
+            const uint32_t n = (uint32_t)i;
+            uint32_t r = wpr > 1 ? __umulhi(n, magic) : n;
+            r -= r * wpr > n ? 1u : 0u;
+            return base + (int64_t)r * row_words + (n - r * wpr);
+        } else {
+            return i;
+        }
+    }
+    // valid values of word i
+    __device__ __forceinline__ int valid(int64_t i) const
+    {
+        if constexpr (MODE != kRows) return V;
+        if (rem == 0) return V;                                // uniform
+        const uint32_t n = (uint32_t)i + 1u;
+        uint32_t r = wpr > 1 ? __umulhi(n, magic) : n;
+        r -= r * wpr > n ? 1u : 0u;
+        return r * wpr == n ? rem : V;                          // the next word starts a row
     }
 };
 
-template <typename T, bool SAMPLED>
-__global__ __launch_bounds__(kThreads) void k_entropy_range_flat(const word4* __restrict__ x, int64_t nwords, WordMap<SAMPLED> map,
+// The first `valid` values of a word, the others replaced by the first one (for a range).
+template <typename T> __device__ __forceinline__ word4 only_valid(word4 q, int valid)
+{
+    const uint32_t first = sizeof(T) == 2 ? (q.x & 0xffffu) * 0x10001u : q.x;
+    constexpr int PER = sizeof(T) == 2 ? 2 : 1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t keep = valid >= PER * (k + 1) ? 0xffffffffu : (valid <= PER * k ? 0u : 0xffffu);
+        q[k] = (q[k] & keep) | (first & ~keep);
+    }
+    return q;
+}
+
+// Bound by memory.  Histogram blockIdx.y, one partial range per workgroup, no atomics.  A padded batch of two (8192 and 2048 of 8192
+// steps, 4096 channels, bf16, 84 MB valid) by the general kernels (a row cursor, ranges published by atomics, a launch that clears
+// their slots): 31.7 us and 4.8 for the clearing, the counts 23.0; as rows of words 21.1 and 18.5 (4.0 and 4.5 TB/s), the step with
+// its scan 226.5 -> 208.6.
+template <typename T, int MODE>
+__global__ __launch_bounds__(kThreads) void k_entropy_range_flat(const word4* __restrict__ x, const Words words,
                                                                  RangePart* __restrict__ rparts, uint32_t* __restrict__ parts,
-                                                                 int nparts)
+                                                                 int64_t nparts)
 {
     // the partial counts the next sweep adds into
-    for (int i = blockIdx.x * kThreads + threadIdx.x; i < nparts; i += gridDim.x * kThreads) parts[i] = 0u;
+    for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kThreads + threadIdx.x; i < nparts;
+         i += (int64_t)gridDim.y * gridDim.x * kThreads)
+        parts[i] = 0u;
+    const WordMap<T, MODE> map(words, blockIdx.y);
+    const int64_t nwords = map.nwords;
     float lo = INFINITY, hi = -INFINITY;
     uint32_t mag = 0u;
     const int64_t step = (int64_t)gridDim.x * kThreads * kUnroll;
     int64_t base = (int64_t)blockIdx.x * kThreads * kUnroll;
+    auto fold = [&](const word4& q, int64_t i) {
+        if (MODE == kRows && map.rem != 0) RangeFold<T>::fold(only_valid<T>(q, map.valid(i)), lo, hi, mag);
+        else RangeFold<T>::fold(q, lo, hi, mag);
+    };
     for (; base + kThreads * kUnroll <= nwords; base += step) {
         word4 q[kUnroll];
 #pragma unroll
         for (int k = 0; k < kUnroll; ++k) q[k] = x[map(base + k * kThreads + threadIdx.x)];
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) RangeFold<T>::fold(q[k], lo, hi, mag);
+        for (int k = 0; k < kUnroll; ++k) fold(q[k], base + k * kThreads + threadIdx.x);
     }
-    for (int64_t i = base + threadIdx.x; i < nwords; i += kThreads) {     // ragged end: at most one workgroup gets here
-        const word4 q = x[map(i)];
-        RangeFold<T>::fold(q, lo, hi, mag);
-    }
+    for (int64_t i = base + threadIdx.x; i < nwords; i += kThreads) fold(x[map(i)], i);     // ragged end: at most one workgroup
     uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
     uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
     uint32_t knan = RangeFold<T>::saw_nan(mag) ? 1u : 0u;
@@ -390,7 +455,7 @@ __global__ __launch_bounds__(kThreads) void k_entropy_range_flat(const word4* __
     if (threadIdx.x == 0) {
         RangePart rp;
         rp.lo_key = klo; rp.hi_key = khi; rp.saw_nan = knan; rp.pad = 0u;
-        rparts[blockIdx.x] = rp;
+        rparts[blockIdx.y * gridDim.x + blockIdx.x] = rp;
     }
 }
 
@@ -403,7 +468,7 @@ constexpr int kMaxLdsBins = 8192;   // uint32 counters in LDS (32 KiB)
 // against 33.1; at K = 256, where the sweep is bound by memory, 31.3 against 31.1.)  Where only two fit, one: clearing and adding up
 // the second costs what its fewer meetings give back (K = 4096, two and one: 64 x 256 values 27.2 and 25.8 us for the statistic,
 // 33.5 million 44.8 and 44.6; K = 2500, where three fit, 33.5 million: two 40.0, one 40.6).
-struct LdsBins {
+template <int NT = kThreads> struct LdsBins {
     uint32_t* s;
     int log2;                                                   // copies = 1 << log2
     uint32_t lane_byte, shift;
@@ -416,7 +481,7 @@ struct LdsBins {
     }
     __device__ __forceinline__ void clear(int K) const
     {
-        for (int i = threadIdx.x; i < ((K << log2) + 3) / 4; i += kThreads) reinterpret_cast<word4*>(s)[i] = word4{0u, 0u, 0u, 0u};
+        for (int i = threadIdx.x; i < ((K << log2) + 3) / 4; i += NT) reinterpret_cast<word4*>(s)[i] = word4{0u, 0u, 0u, 0u};
     }
     __device__ __forceinline__ void add(uint32_t k, uint32_t n = 1u) const
     {
@@ -469,7 +534,7 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count(const T* __restrict_
     }
     float lo, hi;
     if (!usable_range(s_slot, &lo, &hi)) return;              // counts stay zero, H and r become NaN
-    const LdsBins bins(s_bins, K);
+    const LdsBins<> bins(s_bins, K);
     bins.clear(K);
     __syncthreads();
 
@@ -497,17 +562,54 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count(const T* __restrict_
     }
 }
 
-template <typename T, bool SAMPLED>
-__global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __restrict__ x, int64_t nwords, WordMap<SAMPLED> map, int K,
+// Adds values to a workgroup's counters: the bin index as the interface defines it.
+template <typename T, int NT> struct Binner {
+    LdsBins<NT> bins;
+    float lo, scale;
+    uint32_t top;
+    __device__ __forceinline__ Binner(uint32_t* s_bins, int K, float lo_, float hi) : bins(s_bins, K), lo(lo_), top((uint32_t)K - 1u)
+    {
+        scale = hi == lo ? 0.f : (float)((double)K / ((double)hi - (double)lo));     // degenerate range: everything in bin 0
+    }
+    __device__ __forceinline__ void bin(float v) const
+    {
+        const float q = __fmul_rn(__fsub_rn(v, lo), scale);    // two separate binary32 roundings
+        // truncation; q >= 0 (a degenerate range has scale 0: bin 0).  The conversion to unsigned saturates, so a value
+        // outside a stale range still lands inside the counters.
+        bins.add(min(__float2uint_rz(q), top));
+    }
+    template <bool SOME> __device__ __forceinline__ void fold(const word4& q, int valid) const      // SOME: the first `valid` values
+    {
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (sizeof(T) == 2) {
+                float a, b;
+                Elem<T>::widen2(w[k], a, b);
+                if (!SOME || 2 * k < valid) bin(a);
+                if (!SOME || 2 * k + 1 < valid) bin(b);
+            } else {
+                if (!SOME || k < valid) bin(__uint_as_float(w[k]));
+            }
+        }
+    }
+};
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __restrict__ x, const Words words, int K,
                                                                  const RangePart* __restrict__ rparts, int nrparts,
                                                                  RangeSlot* __restrict__ slots, uint32_t* parts)
 {
     __shared__ __align__(16) uint32_t s_bins[kMaxLdsBins];
     __shared__ RangeSlot s_slot;
+    const int h = blockIdx.y;
+    const WordMap<T, MODE> map(words, h);
+    const int64_t nwords = map.nwords;
     // the first words are requested before anything else, so that their trip from HBM overlaps the range fold and the
     // clearing of the counters below (a sampled sweep is only two or three such turns long: their latency is its time)
     const int64_t step = (int64_t)gridDim.x * kThreads * kUnroll;
     int64_t base = (int64_t)blockIdx.x * kThreads * kUnroll;
+    if (MODE == kRows && base >= nwords && blockIdx.x > 0) return;      // uniform: a sequence too short for this workgroup
     word4 q[kUnroll], qn[kUnroll];
     bool have = base + kThreads * kUnroll <= nwords;
     if (have) {
@@ -518,7 +620,7 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __
         // from L2)
         uint32_t klo = 0xffffffffu, khi = 0u, knan = 0u;
         for (int i = threadIdx.x; i < nrparts; i += kThreads) {
-            const RangePart rp = rparts[i];
+            const RangePart rp = rparts[h * nrparts + i];
             klo = min(klo, rp.lo_key);
             khi = max(khi, rp.hi_key);
             knan |= rp.saw_nan;
@@ -526,39 +628,21 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __
         reduce_range_keys(klo, khi, knan);
         if (threadIdx.x == 0) {
             s_slot.lo_key = klo; s_slot.hi_key = khi; s_slot.saw_nan = knan; s_slot.pad = 0u;
-            if (blockIdx.x == 0) slots[0] = s_slot;           // for the reduction
+            if (blockIdx.x == 0) slots[h] = s_slot;           // for the reduction
         }
         __syncthreads();
     }
     float lo, hi;
     if (!usable_range(s_slot, &lo, &hi)) return;              // counts stay zero, H and r become NaN
-    const LdsBins bins(s_bins, K);
-    bins.clear(K);
+    const Binner<T, kThreads> b(s_bins, K, lo, hi);
+    b.bins.clear(K);
     __syncthreads();
-    const float scale = hi == lo ? 0.f : (float)((double)K / ((double)hi - (double)lo));     // degenerate range: everything in bin 0
-    const uint32_t top = (uint32_t)K - 1u;
-    auto bin = [&](float v) {
-        const float q = __fmul_rn(__fsub_rn(v, lo), scale);    // two separate binary32 roundings
-        // truncation; q >= 0 (a degenerate range has scale 0: bin 0).  The conversion to unsigned saturates, so a value
-        // outside a stale range still lands inside the counters.
-        const uint32_t k = min(__float2uint_rz(q), top);
-        bins.add(k);
-    };
-    auto fold = [&](const word4& q) {
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if constexpr (sizeof(T) == 2) {
-                float a, b;
-                Elem<T>::widen2(w[k], a, b);
-                bin(a);
-                bin(b);
-            } else {
-                bin(__uint_as_float(w[k]));
-            }
-        }
+    auto fold = [&](const word4& w, int64_t i) {
+        if (MODE == kRows && map.rem != 0) b.template fold<true>(w, map.valid(i));
+        else b.template fold<false>(w, 0);
     };
     while (have) {                                            // the next turn's words are requested before this turn's are counted;
+        int64_t at = base + threadIdx.x;
         base += step;                                         // two turns per iteration, so the two sets of registers swap roles
         have = base + kThreads * kUnroll <= nwords;           // without being copied
         if (have) {
@@ -566,8 +650,9 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __
             for (int k = 0; k < kUnroll; ++k) qn[k] = x[map(base + k * kThreads + threadIdx.x)];
         }
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) fold(q[k]);
+        for (int k = 0; k < kUnroll; ++k) fold(q[k], at + k * kThreads);
         if (!have) break;
+        at = base + threadIdx.x;
         base += step;
         have = base + kThreads * kUnroll <= nwords;
         if (have) {
@@ -575,13 +660,13 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __
             for (int k = 0; k < kUnroll; ++k) q[k] = x[map(base + k * kThreads + threadIdx.x)];
         }
 #pragma unroll
-        for (int k = 0; k < kUnroll; ++k) fold(qn[k]);
+        for (int k = 0; k < kUnroll; ++k) fold(qn[k], at + k * kThreads);
     }
-    for (int64_t i = base + threadIdx.x; i < nwords; i += kThreads) fold(x[map(i)]);     // ragged end: at most one workgroup
+    for (int64_t i = base + threadIdx.x; i < nwords; i += kThreads) fold(x[map(i)], i);     // ragged end: at most one workgroup
     __syncthreads();
     for (int k = threadIdx.x; k < K; k += kThreads) {
-        const uint32_t c = bins.total(k);
-        if (c) atomicAdd(&parts[(size_t)(blockIdx.x % kParts) * K + k], c);
+        const uint32_t c = b.bins.total(k);
+        if (c) atomicAdd(&parts[((size_t)h * kParts + blockIdx.x % kParts) * K + k], c);
     }
 }
 
@@ -629,15 +714,39 @@ __global__ __launch_bounds__(kThreads) void k_entropy_fold_parts(const RangePart
     }
 }
 
-template <typename T, bool SAMPLED>
-void launch_flat(const word4* x, int64_t nwords, WordMap<SAMPLED> map, int32_t K, RangeSlot* slots, uint32_t* parts,
+// Workgroups of a flat sweep over `nwords` words.
+int64_t flat_blocks(int64_t nwords, int64_t most)
+{
+    const int64_t blocks = (nwords + (int64_t)kThreads * kUnroll - 1) / ((int64_t)kThreads * kUnroll);
+    return blocks < 1 ? 1 : (blocks > most ? most : blocks);
+}
+
+// Both sweeps of nh histograms; the largest has `most_words` words.
+template <typename T, int MODE>
+void launch_flat(const void* x, const Words& words, int64_t most_words, int nh, int32_t K, RangeSlot* slots, uint32_t* parts,
                  RangePart* rparts, hipStream_t stream)
 {
-    int64_t blocks = (nwords + (int64_t)kThreads * kUnroll - 1) / ((int64_t)kThreads * kUnroll);
-    blocks = blocks < 1 ? 1 : (blocks > kFlatBlocks ? kFlatBlocks : blocks);
-    k_entropy_range_flat<T, SAMPLED><<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, nwords, map, rparts, parts, kParts * K);
-    k_entropy_count_flat<T, SAMPLED><<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, nwords, map, K, rparts, (int)blocks,
-                                                                                          slots, parts);
+    int64_t most = kMaxBlocks / nh;                            // partial ranges there is room for
+    most = most > kFlatBlocks ? kFlatBlocks : most;
+    const int64_t blocks = flat_blocks(most_words, most);
+    const dim3 grid((unsigned)blocks, (unsigned)nh);
+    const word4* xw = static_cast<const word4*>(x);
+    k_entropy_range_flat<T, MODE><<<grid, dim3(kThreads), 0, stream>>>(xw, words, rparts, parts, (int64_t)nh * kParts * K);
+    k_entropy_count_flat<T, MODE><<<grid, dim3(kThreads), 0, stream>>>(xw, words, K, rparts, (int)blocks, slots, parts);
+}
+
+// The sampled words of a tensor of `nwords` words: every stride-th block of bw of them.
+Words sampled_words(int64_t nwords, int64_t bw, int64_t stride)
+{
+    Words w = {};
+    const int64_t nb = (nwords + bw - 1) / bw;                  // blocks in the tensor (the last may be short)
+    const int64_t ns = (nb + stride - 1) / stride;              // sampled blocks
+    const int64_t last_first = (ns - 1) * stride * bw;          // first word of the last sampled block
+    const int64_t last_words = nwords - last_first < bw ? nwords - last_first : bw;
+    while (((int64_t)1 << w.bw_log2) < bw) ++w.bw_log2;
+    w.nwords = (ns - 1) * bw + last_words;
+    w.stride = stride;
+    return w;
 }
 
 // What the caller wants done with the partial histograms once the sweeps are enqueued.
@@ -667,29 +776,23 @@ int launch(const void* x, int64_t B, int64_t D, int64_t L, const int32_t* seqlen
     const int64_t E = B * D * L;
     const bool flat_ok = !seqlens && reinterpret_cast<uintptr_t>(x) % kVecBytes == 0 && E % V == 0;
     const int64_t bw = block / V;                              // 16-byte words per sampling block
-    const bool flat_blocks = flat_ok && block % V == 0 && corey::is_pow2(bw);    // sampled runs are whole 16-byte words
-    if (handoff && flat_ok && (stride == 1 || flat_blocks)) {
+    const bool blocks_ok = flat_ok && block % V == 0 && corey::is_pow2(bw);      // sampled runs are whole 16-byte words
+    // per sequence: rows of whole words, and a partial range for every workgroup
+    const bool rows_ok = seqlens && stride == 1 && reinterpret_cast<uintptr_t>(x) % kVecBytes == 0 && L % V == 0 &&
+                         D * (L / V) < ((int64_t)1 << 31) && nh <= kMostRowHistograms;
+    Words all = {};
+    all.nwords = E / V;
+    if (handoff && flat_ok && (stride == 1 || blocks_ok)) {
         // the producer of x left its partial ranges and cleared partial histograms beside them: one launch, the count sweep
         // (over every word, or over the words of every stride-th block), whose workgroups fold the partial ranges themselves
-        int64_t nwords = E / V;
-        int bw_log2 = 0;
-        if (stride > 1) {
-            const int64_t nb = (nwords + bw - 1) / bw;
-            const int64_t ns = (nb + stride - 1) / stride;
-            const int64_t last_first = (ns - 1) * stride * bw;
-            const int64_t last_words = nwords - last_first < bw ? nwords - last_first : bw;
-            while (((int64_t)1 << bw_log2) < bw) ++bw_log2;
-            nwords = (ns - 1) * bw + last_words;
-        }
-        int64_t blocks = (nwords + (int64_t)kThreads * kUnroll - 1) / ((int64_t)kThreads * kUnroll);
-        blocks = blocks < 1 ? 1 : (blocks > kFlatBlocks ? kFlatBlocks : blocks);
+        const Words w = stride > 1 ? sampled_words(E / V, bw, stride) : all;
+        const dim3 grid((unsigned)flat_blocks(w.nwords, kFlatBlocks));
         if (stride == 1)
-            k_entropy_count_flat<T, false><<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(
-                static_cast<const word4*>(x), nwords, WordMap<false>{0, 1}, K, handoff->parts, COREY_RANGE_PARTS, slots, handoff->counts);
+            k_entropy_count_flat<T, kAll><<<grid, dim3(kThreads), 0, stream>>>(static_cast<const word4*>(x), w, K, handoff->parts,
+                                                                             COREY_RANGE_PARTS, slots, handoff->counts);
         else
-            k_entropy_count_flat<T, true><<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(
-                static_cast<const word4*>(x), nwords, WordMap<true>{bw_log2, stride}, K, handoff->parts, COREY_RANGE_PARTS, slots,
-                handoff->counts);
+            k_entropy_count_flat<T, kSampled><<<grid, dim3(kThreads), 0, stream>>>(static_cast<const word4*>(x), w, K, handoff->parts,
+                                                                                 COREY_RANGE_PARTS, slots, handoff->counts);
         final_parts = handoff->counts;
         rezero = true;                                          // left cleared for the next statistic on this buffer
     } else if (handoff) {
@@ -703,19 +806,14 @@ int launch(const void* x, int64_t B, int64_t D, int64_t L, const int32_t* seqlen
         k_entropy_count<T><<<dim3((unsigned)blocks, 1), dim3(kThreads), 0, stream>>>(static_cast<const T*>(x), B, D, L, nullptr, stride,
                                                                                    block, vector_ok ? 1 : 0, K, subs, slots, parts);
     } else if (flat_ok && stride == 1) {
-        // whole tensor, every value, aligned: flat sweeps
-        launch_flat<T, false>(static_cast<const word4*>(x), E / V, WordMap<false>{0, 1}, K, slots, parts, rparts, stream);
-    } else if (flat_blocks) {
-        // whole tensor, every stride-th block of a power-of-two number of words: flat sweeps over the sampled words only
-        const int64_t nwords_all = E / V;
-        const int64_t nb = (nwords_all + bw - 1) / bw;          // blocks in the tensor (the last may be short)
-        const int64_t ns = (nb + stride - 1) / stride;          // sampled blocks
-        const int64_t last_first = (ns - 1) * stride * bw;      // first word of the last sampled block
-        const int64_t last_words = nwords_all - last_first < bw ? nwords_all - last_first : bw;
-        int bw_log2 = 0;
-        while (((int64_t)1 << bw_log2) < bw) ++bw_log2;
-        launch_flat<T, true>(static_cast<const word4*>(x), (ns - 1) * bw + last_words, WordMap<true>{bw_log2, stride}, K, slots,
-                             parts, rparts, stream);
+        launch_flat<T, kAll>(x, all, all.nwords, 1, K, slots, parts, rparts, stream);
+    } else if (blocks_ok) {
+        const Words w = sampled_words(E / V, bw, stride);
+        launch_flat<T, kSampled>(x, w, w.nwords, 1, K, slots, parts, rparts, stream);
+    } else if (rows_ok) {
+        Words w = {};
+        w.seqlens = seqlens; w.D = D; w.L = L;
+        launch_flat<T, kRows>(x, w, D * (L / V), nh, K, slots, parts, rparts, stream);
     } else {
         k_entropy_init<<<dim3((unsigned)((nparts + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(parts, nparts, slots, nh, subs);
         const bool vector_ok = (reinterpret_cast<uintptr_t>(x) % kVecBytes == 0) && (L % V == 0);
