@@ -13,6 +13,7 @@
 //                       of many workgroups do not all queue on the same few cache lines)
 //   k_entropy_finalise  sums the partial histograms into counts, then p_k, H = -sum p log(p + eps) and r in
 //                       double, one workgroup per histogram
+// Few values take one launch, k_entropy_small: range, counts and reduction of a histogram in one workgroup.
 // The common calls (one histogram over the whole tensor, aligned, every value or every stride-th block of a
 // power-of-two number of 16-byte words; a histogram per sequence, rows starting at words) take the *_flat kernels: the range sweep leaves one partial range per
 // workgroup (no atomics, so nothing has to be cleared first; it also clears the partial counts), the count sweep
@@ -670,6 +671,77 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __
     }
 }
 
+// A histogram of few words, start to end in one workgroup: its words stay in registers between the range and the counts, and
+// the counts in LDS until they are reduced.  Bound by latency: one trip to memory instead of a chain of launches and their trips.
+// Range, counts, reduction and rule of 64 x 256 binary32 values at K = 16: 8.8 us in three launches, 7.2 in one (with the scan 16.4 and
+// 14.3 a step).  The one compute unit's counts are what grows: the line lies at 40960 values (us, three launches and one: K = 16,
+// binary32, 32768 values 9.4 and 8.4, 49152 9.2 and 9.7; bf16, 32768 9.5 and 8.2, 49152 9.6 and 9.4, 65536 9.6 and 10.5; K = 256 the
+// same within 0.4; K = 4096 24 and 14 at 32768, 23 and 17 at 65536).
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallValues = 40960;
+template <typename T, int MODE>
+__global__ __launch_bounds__(kSmallThreads) void k_entropy_small(const word4* __restrict__ x, const Words words, const corey_finalise::Args a)
+{
+    __shared__ __align__(16) uint32_t s_bins[kMaxLdsBins];
+    __shared__ RangeSlot s_slot;
+    const int h = blockIdx.x;
+    const WordMap<T, MODE> map(words, h);
+    const int nwords = (int)map.nwords;
+    constexpr int kSmallWords = (int)(kSmallValues / Elem<T>::kVec / kSmallThreads);      // words a lane keeps at most
+    static_assert((int64_t)kSmallWords * Elem<T>::kVec * kSmallThreads == kSmallValues, "whole turns of the workgroup");
+    word4 q[kSmallWords];
+#pragma unroll
+    for (int k = 0; k < kSmallWords; ++k) {
+        if (k * kSmallThreads >= nwords) break;                // uniform
+        const int i = (int)threadIdx.x + k * kSmallThreads;
+        if (i < nwords) q[k] = x[map(i)];
+    }
+    corey_finalise::Context cx(a, h, RangeSlot{});
+    cx.take_log(a.K);
+    const LdsBins<kSmallThreads> bins(s_bins, a.K);
+    bins.clear(a.K);
+    float lo = INFINITY, hi = -INFINITY;
+    uint32_t mag = 0u;
+#pragma unroll
+    for (int k = 0; k < kSmallWords; ++k) {
+        if (k * kSmallThreads >= nwords) break;
+        const int i = (int)threadIdx.x + k * kSmallThreads;
+        if (i >= nwords) continue;
+        if (MODE == kRows && map.rem != 0) RangeFold<T>::fold(only_valid<T>(q[k], map.valid(i)), lo, hi, mag);
+        else RangeFold<T>::fold(q[k], lo, hi, mag);
+    }
+    uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
+    uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
+    uint32_t knan = RangeFold<T>::saw_nan(mag) ? 1u : 0u;
+    reduce_range_keys<kSmallThreads>(klo, khi, knan);
+    if (threadIdx.x == 0) {
+        s_slot.lo_key = klo; s_slot.hi_key = khi; s_slot.saw_nan = knan; s_slot.pad = 0u;
+    }
+    __syncthreads();                                            // the range; the counters are cleared
+    cx.slot = s_slot;
+    const bool ok = usable_range(s_slot, &lo, &hi);             // uniform; else the counts stay zero, H and r become NaN
+    if (ok) {
+        const Binner<T, kSmallThreads> b(s_bins, a.K, lo, hi);
+#pragma unroll
+        for (int k = 0; k < kSmallWords; ++k) {
+            if (k * kSmallThreads >= nwords) break;
+            const int i = (int)threadIdx.x + k * kSmallThreads;
+            if (i >= nwords) continue;
+            if (MODE == kRows && map.rem != 0) b.template fold<true>(q[k], map.valid(i));
+            else b.template fold<false>(q[k], 0);
+        }
+    }
+    __syncthreads();
+    uint32_t c[corey_finalise::kPer] = {};
+#pragma unroll
+    for (int i = 0; i < corey_finalise::kPer; ++i) {
+        if (i * kThreads >= a.K) break;
+        const int k = (int)threadIdx.x + i * kThreads;
+        if (threadIdx.x < kThreads && k < a.K) c[i] = bins.total(k);
+    }
+    corey_finalise::reduce_counts<kSmallThreads>(a, h, true, cx, c);
+}
+
 // The O(K) reduction and the chunk rule (corey_finalise.h), one workgroup per histogram.
 __global__ __launch_bounds__(kThreads) void k_entropy_finalise(const corey_finalise::Args a)
 {
@@ -778,10 +850,24 @@ int launch(const void* x, int64_t B, int64_t D, int64_t L, const int32_t* seqlen
     const int64_t bw = block / V;                              // 16-byte words per sampling block
     const bool blocks_ok = flat_ok && block % V == 0 && corey::is_pow2(bw);      // sampled runs are whole 16-byte words
     // per sequence: rows of whole words, and a partial range for every workgroup
-    const bool rows_ok = seqlens && stride == 1 && reinterpret_cast<uintptr_t>(x) % kVecBytes == 0 && L % V == 0 &&
-                         D * (L / V) < ((int64_t)1 << 31) && nh <= kMostRowHistograms;
+    const bool row_words = seqlens && stride == 1 && reinterpret_cast<uintptr_t>(x) % kVecBytes == 0 && L % V == 0;
+    const bool rows_ok = row_words && D * (L / V) < ((int64_t)1 << 31) && nh <= kMostRowHistograms;
     Words all = {};
     all.nwords = E / V;
+    corey_finalise::Args fa = {};
+    fa.slots = slots; fa.counts = counts; fa.H_out = H_out; fa.r_out = r_out; fa.range_out = range_out;
+    fa.chunks_out = tail.pol ? tail.chunks_out : nullptr; fa.seqlens = seqlens; fa.ema_state = tail.ema_state;
+    fa.chunk_calls = tail.chunk_calls; fa.L_all = L; fa.eps = eps; fa.ema_lambda = tail.ema_lambda;
+    if (tail.pol) fa.pol = *tail.pol;
+    fa.K = K; fa.nh = nh;
+    if (!handoff && !tail.defer && stride == 1 && (seqlens ? row_words && D * L <= kSmallValues : flat_ok && E <= kSmallValues)) {
+        all.seqlens = seqlens; all.D = D; all.L = L;
+        auto go = [&](auto kernel) { kernel<<<dim3((unsigned)nh), dim3(kSmallThreads), 0, stream>>>(static_cast<const word4*>(x), all, fa); };
+        if (seqlens) go(k_entropy_small<T, kRows>);
+        else go(k_entropy_small<T, kAll>);
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess ? corey::hip_fail(e, "corey_entropy_hist launch") : COREY_OK;
+    }
     if (handoff && flat_ok && (stride == 1 || blocks_ok)) {
         // the producer of x left its partial ranges and cleared partial histograms beside them: one launch, the count sweep
         // (over every word, or over the words of every stride-th block), whose workgroups fold the partial ranges themselves
@@ -831,12 +917,7 @@ int launch(const void* x, int64_t B, int64_t D, int64_t L, const int32_t* seqlen
         k_entropy_count<T><<<grid, dim3(kThreads), 0, stream>>>(static_cast<const T*>(x), B, D, L, seqlens, stride, block,
                                                                vector_ok ? 1 : 0, K, subs, slots, parts);
     }
-    corey_finalise::Args fa = {};
-    fa.parts = final_parts; fa.slots = slots; fa.counts = counts; fa.H_out = H_out; fa.r_out = r_out; fa.range_out = range_out;
-    fa.chunks_out = tail.pol ? tail.chunks_out : nullptr; fa.seqlens = seqlens; fa.ema_state = tail.ema_state;
-    fa.chunk_calls = tail.chunk_calls; fa.L_all = L; fa.eps = eps; fa.ema_lambda = tail.ema_lambda;
-    if (tail.pol) fa.pol = *tail.pol;
-    fa.K = K; fa.nh = nh; fa.rezero = rezero ? 1 : 0;
+    fa.parts = final_parts; fa.rezero = rezero ? 1 : 0;
     if (tail.defer) *tail.defer = fa;                           // the scan's call will do it
     else k_entropy_finalise<<<dim3((unsigned)nh), dim3(kThreads), 0, stream>>>(fa);
     const hipError_t e = hipGetLastError();

@@ -77,69 +77,46 @@ __device__ __forceinline__ int32_t chunk_rule(double rv, int64_t L, const corey_
     return (int32_t)c;
 }
 
-// Histogram h of the call, by all kThreads lanes of a workgroup.  Returns the chunk the rule selects (0: no rule, or r is
-// NaN in an entropy mode) in every lane; with `publish` the workgroup also writes counts, H, r, range and chunk, updates
-// the moving average and the chunk counters.  Two workgroups that evaluate the same histogram add the same numbers in
-// the same order and get the same bits.
-// One workgroup: bound by latency, i.e. by trips to memory one after another and by code fetched for the first time, so
-// everything thread 0 will need is requested with the counts, log K is taken while they arrive, and the unrolled loops are left
-// at the last bin (the bodies of absent bins, a logarithm each, were jumped over one by one: every jump a fetch).  In front of
-// the scan, statistic and rule of 64 x 256 values at K = 16: step 16.99 -> 16.17 us; of 4 x 2048 x 4096 at K = 256: 178.1 -> 174.6.
-__device__ __forceinline__ int32_t finalise(const Args& a, int h, bool publish)
+constexpr int kPer = COREY_MAX_BINS / kThreads;                 // bins a lane owns at most
+
+// What the reduction's thread 0 needs beside the counts; requested with them, each would be a trip to memory of its own later.
+struct Context {
+    corey_range::RangeSlot slot;
+    int64_t L;
+    double ema_prev, log_K;
+    __device__ __forceinline__ Context(const Args& a, int h, const corey_range::RangeSlot& s)
+        : slot(s), L(a.seqlens ? (int64_t)a.seqlens[h] : a.L_all), ema_prev(a.ema_state ? a.ema_state[h] : NAN), log_K(0.0)
+    {
+    }
+    __device__ __forceinline__ void take_log(int K)             // while the counts are on their way, and not where it is used
+    {
+        log_K = log((double)K);
+        asm volatile("" : "+v"(log_K));
+    }
+};
+
+// Histogram h of the call from the counts its first kThreads lanes hold (lane t: bins t, t + kThreads, ...), by all NT lanes of a
+// workgroup.  Returns the chunk the rule selects (0: no rule, or r is NaN in an entropy mode) in every lane; with `publish` the
+// workgroup also writes counts, H, r, range and chunk, updates the moving average and the chunk counters.  Two workgroups that
+// evaluate the same histogram add the same numbers in the same order and get the same bits.
+template <int NT = kThreads>
+__device__ __forceinline__ int32_t reduce_counts(const Args& a, int h, bool publish, const Context& cx, const uint32_t (&c)[kPer])
 {
-    using corey_range::kParts;
-    constexpr int kPer = COREY_MAX_BINS / kThreads;             // bins a lane owns at most
     const int K = a.K;
-    uint32_t* ph = a.parts + (int64_t)h * kParts * K;
-    // requested with the counts, not when thread 0 comes to need them: each would be a trip to memory of its own
-    const corey_range::RangeSlot slot = a.slots[h];
-    const int64_t L = a.seqlens ? (int64_t)a.seqlens[h] : a.L_all;
-    const double ema_prev = a.ema_state ? a.ema_state[h] : NAN;
-    double log_K = 0.0;                                         // used by thread 0 alone
-    uint32_t c[kPer] = {};
     unsigned long long n_part = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         if (i * kThreads >= K) break;
+        n_part += c[i];
         const int k = (int)threadIdx.x + i * kThreads;
-        uint32_t sum = 0;
-        if (k < K) {
-            uint32_t v[kParts];
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) v[q] = ph[(size_t)q * K + k];
-            if (i == 0) {                                       // while the counts are on their way
-                log_K = log((double)K);
-                asm volatile("" : "+v"(log_K));                 // (here, and not where it is used)
-            }
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) sum += v[q];
-        }
-        c[i] = sum;
-        n_part += sum;
-    }
-    if (publish) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            if (i * kThreads >= K) break;
-            const int k = (int)threadIdx.x + i * kThreads;
-            if (k < K) a.counts[(int64_t)h * K + k] = c[i];
-        }
-        if (a.rezero) {
-#pragma unroll
-            for (int i = 0; i < kPer; ++i) {
-                if (i * kThreads >= K) break;
-                const int k = (int)threadIdx.x + i * kThreads;
-                if (k < K)
-                    for (int q = 0; q < kParts; ++q) ph[(size_t)q * K + k] = 0u;
-            }
-        }
+        if (publish && threadIdx.x < kThreads && k < K) a.counts[(int64_t)h * K + k] = c[i];
     }
     float lo = 0.f, hi = 0.f;
-    const bool ok = corey_range::usable_range(slot, &lo, &hi);
+    const bool ok = corey_range::usable_range(cx.slot, &lo, &hi);
     // two workgroup sums (the sample count, then the entropy terms): butterfly inside each wave, the waves' totals
     // through LDS; every lane ends up with the same total, added in the same order
-    __shared__ double s_red[kThreads / 64];
-    __shared__ unsigned long long s_n[kThreads / 64];
+    __shared__ double s_red[NT / 64];
+    __shared__ unsigned long long s_n[NT / 64];
     __shared__ int32_t s_chunk;
     const int wave = threadIdx.x >> 6;
 
@@ -169,21 +146,21 @@ __device__ __forceinline__ int32_t finalise(const Args& a, int h, bool publish)
             double acc = 0.0;
             for (int w = 0; w < kThreads / 64; ++w) acc += s_red[w];
             H = -acc;
-            r = H / log_K;
+            r = H / cx.log_K;
             r = r < 0.0 ? 0.0 : (r > 1.0 ? 1.0 : r);
         }
         int32_t chunk = 0;
         if (a.chunks_out) {
             double r_rule = r;
             if (a.ema_state) {                                 // the rule sees the entropy smoothed across calls
-                const double prev = ema_prev;
+                const double prev = cx.ema_prev;
                 double Hs = prev;
                 if (H == H) Hs = (prev != prev) ? H : a.ema_lambda * prev + (1.0 - a.ema_lambda) * H;
                 if (publish) a.ema_state[h] = Hs;
-                r_rule = Hs / log_K;
+                r_rule = Hs / cx.log_K;
                 r_rule = r_rule < 0.0 ? 0.0 : (r_rule > 1.0 ? 1.0 : r_rule);
             }
-            chunk = chunk_rule(r_rule, L, a.pol);
+            chunk = chunk_rule(r_rule, cx.L, a.pol);
         }
         s_chunk = chunk;
         if (publish) {
@@ -194,13 +171,52 @@ __device__ __forceinline__ int32_t finalise(const Args& a, int h, bool publish)
                 if (a.chunk_calls && chunk > 0 && 31 - __clz(chunk) < COREY_CHUNK_SLOTS) atomicAdd(&a.chunk_calls[31 - __clz(chunk)], 1u);
             }
             if (a.range_out) {
-                a.range_out[2 * h] = (slot.lo_key == 0xffffffffu) ? INFINITY : corey_range::key_value(slot.lo_key);
-                a.range_out[2 * h + 1] = (slot.hi_key == 0u) ? -INFINITY : corey_range::key_value(slot.hi_key);
+                a.range_out[2 * h] = (cx.slot.lo_key == 0xffffffffu) ? INFINITY : corey_range::key_value(cx.slot.lo_key);
+                a.range_out[2 * h + 1] = (cx.slot.hi_key == 0u) ? -INFINITY : corey_range::key_value(cx.slot.hi_key);
             }
         }
     }
     __syncthreads();
     return s_chunk;
+}
+
+// The same from the call's partial histograms, by a workgroup of kThreads lanes.
+// One workgroup: bound by latency, i.e. by trips to memory one after another and by code fetched for the first time, so
+// everything thread 0 will need is requested with the counts, log K is taken while they arrive, and the unrolled loops are left
+// at the last bin (the bodies of absent bins, a logarithm each, were jumped over one by one: every jump a fetch).  In front of
+// the scan, statistic and rule of 4 x 2048 x 4096 values at K = 256: step 178.1 -> 174.6 us.
+__device__ __forceinline__ int32_t finalise(const Args& a, int h, bool publish)
+{
+    using corey_range::kParts;
+    const int K = a.K;
+    uint32_t* ph = a.parts + (int64_t)h * kParts * K;
+    Context cx(a, h, a.slots[h]);
+    uint32_t c[kPer] = {};
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        if (i * kThreads >= K) break;
+        const int k = (int)threadIdx.x + i * kThreads;
+        uint32_t sum = 0;
+        if (k < K) {
+            uint32_t v[kParts];
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) v[q] = ph[(size_t)q * K + k];
+            if (i == 0) cx.take_log(K);
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) sum += v[q];
+        }
+        c[i] = sum;
+    }
+    if (publish && a.rezero) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (i * kThreads >= K) break;
+            const int k = (int)threadIdx.x + i * kThreads;
+            if (k < K)
+                for (int q = 0; q < kParts; ++q) ph[(size_t)q * K + k] = 0u;
+        }
+    }
+    return reduce_counts(a, h, publish, cx, c);
 }
 
 }  // namespace corey_finalise

@@ -1,9 +1,13 @@
-"""The per-sequence statistic at the edges of its flat sweeps: rows of whole 16-byte words of which the last may be partly valid,
+"""The statistic of few values in one launch and of more in three, on either side of the line between them; the per-sequence
+statistic at the edges of its flat sweeps: rows of whole 16-byte words of which the last may be partly valid,
 one word a row, empty and full sequences, sequences of very different lengths, more histograms than the flat sweeps take, and NaN
 or infinities in the padding (which must not be seen) or among the valid values (which must)."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2604_10597_amd as corey
+from gpu_util import to_dev
 from paper_2604_10597_amd import workloads as wl
 from test_gpu_entropy import _check
 
@@ -33,3 +37,28 @@ def test_constant_rows(dtype):
     x = np.full((2, 9, 24), 1.5, dtype=np.float32)
     store, val = wl.store(x, dtype)
     _check(store, val, dtype, 32, seqlens=np.array([21, 24], dtype=np.int32))
+
+
+@pytest.mark.parametrize("dtype,V", [(wl.BF16, 8), (wl.F16, 8), (wl.F32, 4)])
+@pytest.mark.parametrize("values", [8, 8184, 8192, 8200, 40952, 40960, 40968])
+@pytest.mark.parametrize("K", [2, 300, 4096])
+def test_few_values(values, K, dtype, V):
+    """One launch up to 40960 values: a lane's last word there or not, bins beyond the reducing lanes."""
+    print(f"[case] few values {values} K{K} {dtype}", flush=True)
+    rng = np.random.default_rng(values + K)
+    store, val = wl.store(rng.standard_normal((1, values // V, V)).astype(np.float32), dtype)
+    out, _ = _check(store, val, dtype, K)
+    pol = corey.policy_default()
+    xd = to_dev(store, dtype)
+    routed = corey.corey_route_device(xd, K, pol)
+    assert torch.equal(routed["counts"], out["counts"]) and routed["r"].item() == out["r"].item()
+    assert routed["chunks"].item() == corey.corey_select_chunk(out["r"].item(), V, pol)
+    route = corey.corey_route_device_deferred(xd, K, pol)          # the reduction of partial histograms adds the same numbers in the same order
+    N = 4
+    z = torch.zeros_like(xd)
+    B, C = torch.zeros((1, N, V), dtype=xd.dtype, device="cuda"), torch.zeros((1, N, V), dtype=xd.dtype, device="cuda")
+    A = -torch.ones((values // V, N), device="cuda")
+    corey.selective_scan_fwd(xd, z, A, B, C, chunk=16, route=route["route"])
+    assert route["r"].item() == out["r"].item() and route["H"].item() == out["H"].item()
+    store, val = wl.store(np.full((1, values // V, V), -2.0, dtype=np.float32), dtype)
+    _check(store, val, dtype, K)
