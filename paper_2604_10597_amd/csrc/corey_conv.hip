@@ -343,7 +343,7 @@ __global__ __launch_bounds__(NT) void k_conv1d_silu(const T* __restrict__ x, con
         uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
         uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
         uint32_t knan = nan ? 1u : 0u;
-        if constexpr (TABLE) corey_table::end(s_tab, sh, tws, klo, khi, knan);     // also reduces the keys into thread 0
+        if constexpr (TABLE) corey_table::end<T, false>(s_tab, sh, tws, klo, khi, knan);     // also reduces the keys into thread 0
         else reduce_range_keys<NT>(klo, khi, knan);
         if (handoff) write_parts<NT>(handoff->parts, klo, khi, knan);
     }

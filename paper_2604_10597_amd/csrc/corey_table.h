@@ -19,8 +19,8 @@
 // 16-byte word (8 elements) before it looks at what they returned, and it looks first at the OR of the returned words:
 // a guard crossing needs bit 14 of a counter set beforehand, so when neither half of any returned word has it (the usual
 // case: a workgroup sees a few dozen occurrences of a pattern) no element needs the exact test.
-// At the end the workgroup writes its table as it is (128 KiB, two bytes per pattern) plus a small tail (zeros, overflow
-// list) to its own slab of the caller's workspace: no global atomics, nothing to clear beforehand.
+// At the end the workgroup writes the parts of its table that hold counts (two bytes per pattern) plus a small tail (zeros,
+// overflow list) to its own slab of the caller's workspace: no global atomics, nothing to clear beforehand.
 #ifndef COREY_TABLE_H
 #define COREY_TABLE_H
 
@@ -38,9 +38,13 @@ constexpr int kMaxSlabs = 256;          // most workgroups that fill tables in o
 constexpr int kMaxOver = 1024;          // overflow entries a workgroup can record: 32768 elements each, 2^25 elements per workgroup
 constexpr int kParts = corey_range::kParts;
 
+constexpr int kUnitWords = 256;         // words of a slab that are written and read, or left out, together: a wave's 16-byte words
+constexpr int kUnits = kWords / kUnitWords;
+
 struct Head {                           // per workgroup: what its slab does not hold
     uint32_t n_over;                    // entries of the workgroup's overflow list in use
     uint32_t zeros;                     // occurrences of pattern 0x0000
+    uint32_t units[kUnits / 32];        // the units of its slab that were written; the others hold no counts
 };
 struct Tail {                           // per workgroup: the overflow list
     uint16_t over[kMaxOver];            // patterns that crossed the guard bit (each entry stands for 32768 occurrences)
@@ -50,6 +54,23 @@ struct Shared {                         // LDS bookkeeping beside the table
     uint32_t n_over;
     uint16_t over[kMaxOver];
     uint32_t zeros[kLanes];             // per lane: occurrences of pattern 0x0000
+    uint32_t units[kUnits / 32];
+};
+
+template <typename T> struct Pattern;   // values of the storage bit patterns
+template <> struct Pattern<uint16_t> {  // bfloat16
+    static constexpr uint32_t kInf = 0x7f80u;
+    static __device__ __forceinline__ float value(uint32_t p) { return __uint_as_float(p << 16); }
+};
+template <> struct Pattern<_Float16> {
+    static constexpr uint32_t kInf = 0x7c00u;
+    static __device__ __forceinline__ float value(uint32_t p)
+    {
+        const uint16_t b = (uint16_t)p;
+        _Float16 h;
+        __builtin_memcpy(&h, &b, 2);
+        return (float)h;
+    }
 };
 
 // Layout of the caller's workspace (corey_pattern_table_workspace() bytes, 256-byte aligned).
@@ -67,7 +88,7 @@ constexpr size_t kSlotsBytes = 256;
 constexpr size_t kPartsBytes = (size_t)kParts * COREY_MAX_BINS * sizeof(uint32_t);
 constexpr size_t kRpartsBytes = (size_t)kMaxSlabs * sizeof(corey_range::RangePart);
 constexpr size_t kCountBytes = 256;
-constexpr size_t kHeadsBytes = (size_t)kMaxSlabs * sizeof(Head);
+constexpr size_t kHeadsBytes = (size_t)kMaxSlabs * sizeof(Head);      // (whole 256 bytes)
 constexpr size_t kTailsBytes = ((size_t)kMaxSlabs * sizeof(Tail) + 255) / 256 * 256;
 constexpr size_t kSlabsBytes = (size_t)kMaxSlabs * kWords * sizeof(uint32_t);
 constexpr size_t kWorkspaceBytes = kSlotsBytes + kPartsBytes + kRpartsBytes + kCountBytes + kHeadsBytes + kTailsBytes + kSlabsBytes;
@@ -100,6 +121,7 @@ __device__ __forceinline__ void begin(uint32_t* s_tab, Shared& sh, const Workspa
     const word4 zero = {0u, 0u, 0u, 0u};
     for (int i = threadIdx.x; i < kWords / 4; i += kLanes) reinterpret_cast<word4*>(s_tab)[i] = zero;
     if (threadIdx.x == 0) sh.n_over = 0u;
+    if (threadIdx.x < kUnits / 32) sh.units[threadIdx.x] = 0u;
     sh.zeros[threadIdx.x] = 0u;
     for (int i = blockIdx.x * kLanes + threadIdx.x; i < kParts * COREY_MAX_BINS; i += gridDim.x * kLanes) ws.parts[i] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) *ws.nslabs = gridDim.x;
@@ -134,14 +156,29 @@ __device__ __forceinline__ void add(uint32_t* s_tab, Shared& sh, uint32_t p)
     settle(s_tab, sh, p, add_issue(s_tab, sh, p));
 }
 
-// The eight elements of one 16-byte word: all adds first, then one look at the OR of what they returned.
+// The eight elements of one 16-byte word: all adds first, then one look at the OR of what they returned.  A word without a zero
+// pattern needs no look at each of its elements for one: an element is then its place (two instructions), its half (two) and
+// its add.
 __device__ __forceinline__ void add_word4(uint32_t* s_tab, Shared& sh, const uint32_t (&w)[4])
 {
+    typedef uint16_t half2 __attribute__((ext_vector_type(2)));
+    half2 h[4];
+    __builtin_memcpy(h, w, 16);
+    const half2 least = __builtin_elementwise_min(__builtin_elementwise_min(h[0], h[1]), __builtin_elementwise_min(h[2], h[3]));
     uint32_t old[8], any = 0u;
+    if (least.x != 0 && least.y != 0) {
+        char* tab = reinterpret_cast<char*>(s_tab);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        old[2 * k] = add_issue(s_tab, sh, w[k] & 0xffffu);
-        old[2 * k + 1] = add_issue(s_tab, sh, w[k] >> 16);
+        for (int k = 0; k < 4; ++k) {
+            old[2 * k] = atomicAdd(reinterpret_cast<uint32_t*>(tab + ((w[k] << 2) & 0x1fffcu)), __umul24((w[k] >> 15) & 1u, 0xffffu) + 1u);
+            old[2 * k + 1] = atomicAdd(reinterpret_cast<uint32_t*>(tab + ((w[k] >> 14) & 0x1fffcu)), __umul24(w[k] >> 31, 0xffffu) + 1u);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            old[2 * k] = add_issue(s_tab, sh, w[k] & 0xffffu);
+            old[2 * k + 1] = add_issue(s_tab, sh, w[k] >> 16);
+        }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) any |= old[e];
@@ -154,21 +191,54 @@ __device__ __forceinline__ void add_word4(uint32_t* s_tab, Shared& sh, const uin
     }
 }
 
-// Write the workgroup's table, tail and partial range to its slab.  The range keys are reduced over the workgroup on the
-// way (valid in thread 0 afterwards); the barriers of that reduction also see every add land before the table is read.
+// Fold a pattern that occurs into a range.
+template <typename T> __device__ __forceinline__ void fold_pattern(uint32_t p, uint32_t& klo, uint32_t& khi, uint32_t& knan)
+{
+    if ((p & 0x7fffu) > Pattern<T>::kInf) {
+        knan = 1u;
+        return;
+    }
+    const uint32_t key = corey_range::order_key(Pattern<T>::value(p));
+    klo = min(klo, key);
+    khi = max(khi, key);
+}
+
+// Write the workgroup's table, tail and partial range to its slab.  FROM_TABLE: the range is read off the table (three instructions
+// a value less in the loop that fills it); otherwise the lanes hand in what they saw.  Reduced over the workgroup either way (valid
+// in thread 0 afterwards).  Only the units of the table that hold counts are written: a tensor's values lie in a dozen
+// of bfloat16's 128 pairs of exponents, and 128 KiB per workgroup, mostly zeros, went to memory and back.
+template <typename T, bool FROM_TABLE>
 __device__ __forceinline__ void end(uint32_t* s_tab, Shared& sh, const Workspace& ws, uint32_t& klo, uint32_t& khi, uint32_t& knan)
 {
     typedef uint32_t word4 __attribute__((ext_vector_type(4)));
-    corey_range::reduce_range_keys<kLanes>(klo, khi, knan);   // holds a barrier: every add has landed
+    __syncthreads();                                          // every add has landed
     uint32_t zeros = sh.zeros[threadIdx.x];
-    for (int off = 32; off > 0; off >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, off);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh.zeros[threadIdx.x >> 6] = zeros;      // the waves' totals (all lanes have read their own)
-    __syncthreads();
-    word4* slab = reinterpret_cast<word4*>(ws.slabs + (size_t)blockIdx.x * kWords);
-    for (int i = threadIdx.x; i < kWords / 4; i += kLanes) slab[i] = reinterpret_cast<const word4*>(s_tab)[i];
-    Tail* tail = ws.tails + blockIdx.x;
     const uint32_t n_over = sh.n_over < (uint32_t)kMaxOver ? sh.n_over : (uint32_t)kMaxOver;
+    if constexpr (FROM_TABLE) {
+        klo = 0xffffffffu; khi = 0u; knan = 0u;
+        if (zeros) fold_pattern<T>(0u, klo, khi, knan);
+        for (uint32_t i = threadIdx.x; i < n_over; i += kLanes) fold_pattern<T>(sh.over[i], klo, khi, knan);
+    }
+    for (int off = 32; off > 0; off >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, off);
+    word4* slab = reinterpret_cast<word4*>(ws.slabs + (size_t)blockIdx.x * kWords);
+    for (int i = threadIdx.x; i < kWords / 4; i += kLanes) {
+        const word4 v = reinterpret_cast<const word4*>(s_tab)[i];
+        if (__ballot((v.x | v.y | v.z | v.w) != 0u) == 0ull) continue;       // uniform over the wave
+        slab[i] = v;
+        const int unit = i / (kUnitWords / 4);
+        if ((threadIdx.x & 63) == 0) atomicOr(&sh.units[unit >> 5], 1u << (unit & 31));
+        if constexpr (FROM_TABLE) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (v[e] & 0xffffu) fold_pattern<T>(4 * i + e, klo, khi, knan);
+                if (v[e] >> 16) fold_pattern<T>((4 * i + e) | 0x8000u, klo, khi, knan);
+            }
+        }
+    }
+    corey_range::reduce_range_keys<kLanes>(klo, khi, knan);   // holds a barrier: the units are known, all zero counts have been read
+    if ((threadIdx.x & 63) == 0) sh.zeros[threadIdx.x >> 6] = zeros;         // the waves' totals
+    __syncthreads();
+    Tail* tail = ws.tails + blockIdx.x;
     for (uint32_t i = threadIdx.x; i < n_over; i += kLanes) tail->over[i] = sh.over[i];
     if (threadIdx.x == 0) {
         uint32_t z = 0u;
@@ -176,6 +246,8 @@ __device__ __forceinline__ void end(uint32_t* s_tab, Shared& sh, const Workspace
         Head h;
         h.n_over = n_over;
         h.zeros = z;
+#pragma unroll
+        for (int k = 0; k < kUnits / 32; ++k) h.units[k] = sh.units[k];
         ws.heads[blockIdx.x] = h;
         corey_range::RangePart rp;
         rp.lo_key = klo; rp.hi_key = khi; rp.saw_nan = knan; rp.pad = 0u;

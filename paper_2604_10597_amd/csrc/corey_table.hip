@@ -7,7 +7,10 @@
 //                   occurs is binned once, with its multiplicity, by the very binary32 expression the two-pass kernels
 //                   apply to every element, so the K counts are bit-identical to theirs
 //   k_entropy_finalise (corey_entropy.hip)  H, r and the chunk rule from the counts
-// Bandwidth and LDS-atomic work: no matrix instructions.
+// Bandwidth and LDS-atomic work: no matrix instructions.  33.5 million bf16 values at K = 256: counting 23.2 -> 18.9 us (bound by the
+// adds, 7 to 8 a clock and compute unit, and six instructions a value), binning 11.4 -> 9.0 (a chain of four trips to memory), the
+// statistic 39.2 -> 32.1: only the parts of a slab that hold counts move, the range is read off the table, a word without a zero
+// needs no look at each value, the slabs of a group are one trip.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -18,9 +21,6 @@
 
 namespace {
 
-using corey_range::key_value;
-using corey_range::order_key;
-using corey_range::RangeFold;
 using corey_range::RangePart;
 using corey_range::RangeSlot;
 using corey_range::usable_range;
@@ -29,15 +29,6 @@ using corey_table::kLanes;
 using corey_table::kWords;
 
 constexpr int kRoundWords = corey_table::kRoundAdds / 8 / kLanes;      // 16-byte words per lane and round: 4
-
-__device__ __forceinline__ float pattern_value(uint32_t p, uint16_t) { return __uint_as_float(p << 16); }     // bfloat16
-__device__ __forceinline__ float pattern_value(uint32_t p, _Float16)
-{
-    const uint16_t b = (uint16_t)p;
-    _Float16 h;
-    __builtin_memcpy(&h, &b, 2);
-    return (float)h;
-}
 
 // x: the tensor as `nwords` aligned 16-byte words starting at `body`, plus up to 7 single elements before and after
 // them (an unaligned or ragged tensor), which workgroup 0 counts in a round of their own.
@@ -48,63 +39,69 @@ __global__ __launch_bounds__(kLanes) void k_table_count(const T* __restrict__ x,
     __shared__ uint32_t s_tab[kWords];
     __shared__ corey_table::Shared sh;
     const corey_table::Workspace ws = corey_table::carve(workspace);
+    // rounds of kRoundWords words per lane; the next round's words are requested before this round's are counted (the first ones before
+    // the table is cleared), two rounds per iteration, so that the two sets of registers swap roles without being copied
+    constexpr int64_t kRound = (int64_t)kLanes * kRoundWords;
+    const int64_t step = (int64_t)gridDim.x * kRound;
+    int64_t base = (int64_t)blockIdx.x * kRound;
+    word4 q[kRoundWords], qn[kRoundWords];
+    auto fetch = [&](int64_t b, word4 (&dst)[kRoundWords]) {
+        if (b + kRound <= nwords) {                              // uniform
+#pragma unroll
+            for (int k = 0; k < kRoundWords; ++k) dst[k] = body[b + (int64_t)k * kLanes + threadIdx.x];
+        } else {
+#pragma unroll
+            for (int k = 0; k < kRoundWords; ++k) {
+                const int64_t i = b + (int64_t)k * kLanes + threadIdx.x;
+                dst[k] = i < nwords ? body[i] : word4{0u, 0u, 0u, 0u};
+            }
+        }
+    };
+    auto add = [&](const word4& v) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        corey_table::add_word4(s_tab, sh, w);
+    };
+    auto count = [&](int64_t b, const word4 (&src)[kRoundWords]) {
+        if (b + kRound <= nwords) {
+#pragma unroll
+            for (int k = 0; k < kRoundWords; ++k) add(src[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kRoundWords; ++k)
+                if (b + (int64_t)k * kLanes + threadIdx.x < nwords) add(src[k]);
+        }
+        __syncthreads();                                         // round boundary: every guard crossing has been undone
+    };
+    if (base < nwords) fetch(base, q);
     corey_table::begin(s_tab, sh, ws);
-    float lo = INFINITY, hi = -INFINITY;
-    uint32_t mag = 0u;
-
-    bool nan_single = false;
     if (blockIdx.x == 0 && head + tail > 0) {                   // uniform over the workgroup: a round of its own
         if ((int64_t)threadIdx.x < head + tail) {
             const int64_t i = (int64_t)threadIdx.x < head ? (int64_t)threadIdx.x : head + nwords * 8 + ((int64_t)threadIdx.x - head);
             uint16_t bits;
             __builtin_memcpy(&bits, &x[i], 2);
-            const float v = pattern_value(bits, T());
-            nan_single = v != v;
-            lo = fminf(lo, v);                                  // fminf / fmaxf drop a NaN operand; NaN is flagged separately
-            hi = fmaxf(hi, v);
             corey_table::add(s_tab, sh, bits);
         }
         __syncthreads();
     }
-
-    // rounds of kRoundWords words per lane; the next round's words are requested before this round's are counted
-    const int64_t step = (int64_t)gridDim.x * kLanes * kRoundWords;
-    int64_t base = (int64_t)blockIdx.x * kLanes * kRoundWords;
-    word4 q[kRoundWords], qn[kRoundWords];
-    auto fetch = [&](int64_t b, word4 (&dst)[kRoundWords]) {
-#pragma unroll
-        for (int k = 0; k < kRoundWords; ++k) {
-            const int64_t i = b + (int64_t)k * kLanes + threadIdx.x;
-            dst[k] = i < nwords ? body[i] : word4{0u, 0u, 0u, 0u};
-        }
-    };
-    if (base < nwords) fetch(base, q);
-    for (; base < nwords; base += step) {                        // uniform over the workgroup
+    while (base < nwords) {                                      // uniform over the workgroup
         if (base + step < nwords) fetch(base + step, qn);
-#pragma unroll
-        for (int k = 0; k < kRoundWords; ++k) {
-            if (base + (int64_t)k * kLanes + threadIdx.x < nwords) {
-                RangeFold<T>::fold(q[k], lo, hi, mag);
-                const uint32_t w[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
-                corey_table::add_word4(s_tab, sh, w);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kRoundWords; ++k) q[k] = qn[k];
-        __syncthreads();                                         // round boundary: every guard crossing has been undone
+        count(base, q);
+        base += step;
+        if (base >= nwords) break;
+        if (base + step < nwords) fetch(base + step, q);
+        count(base, qn);
+        base += step;
     }
-    uint32_t klo = (lo <= hi) ? order_key(lo) : 0xffffffffu;
-    uint32_t khi = (lo <= hi) ? order_key(hi) : 0u;
-    uint32_t knan = (RangeFold<T>::saw_nan(mag) || nan_single) ? 1u : 0u;
-    corey_table::end(s_tab, sh, ws, klo, khi, knan);
+    uint32_t klo, khi, knan;
+    corey_table::end<T, true>(s_tab, sh, ws, klo, khi, knan);
 }
 
 // Grid: (kWords / 1024 blocks of 1024 table words) x kSlabGroups; a workgroup adds up, for its 1024 words (2048
 // patterns), the slabs s = group, group + kSlabGroups, ...: a lane owns 4 consecutive words (8 patterns).
 constexpr int kBinLanes = 256;
 constexpr int kWordBlock = kBinLanes * 4;
-constexpr int kSlabGroups = 8;
-constexpr int kBinBatch = 8;        // slab loads a lane keeps in flight
+constexpr int kSlabGroups = 16;
+constexpr int kBinBatch = 16;       // slab loads a lane keeps in flight: a group's slabs are one trip to memory
 
 template <typename T>
 __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
@@ -112,19 +109,32 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
     __shared__ uint32_t s_extra[2 * kWordBlock];                // overflow entries and zeros that belong to this block's patterns
     __shared__ uint32_t s_bins[COREY_MAX_BINS];
     __shared__ RangeSlot s_slot;
+    constexpr int kGroupSlabs = (corey_table::kMaxSlabs + kSlabGroups - 1) / kSlabGroups;
+    __shared__ uint32_t s_nover[kGroupSlabs], s_units[kGroupSlabs];
+    static_assert(kGroupSlabs <= 32 && kWordBlock == 4 * corey_table::kUnitWords, "a wave reads one unit, of 32 slabs at most");
     const corey_table::Workspace ws = corey_table::carve(workspace);
-    const int nslabs = (int)min(*ws.nslabs, (uint32_t)corey_table::kMaxSlabs);
+    // what describes the slabs is requested in one go, before it is known how many there are
     const int wb = blockIdx.x, group = blockIdx.y;
     const int wg = blockIdx.y * gridDim.x + blockIdx.x;
     for (int i = threadIdx.x; i < 2 * kWordBlock; i += kBinLanes) s_extra[i] = 0u;
     for (int i = threadIdx.x; i < K; i += kBinLanes) s_bins[i] = 0u;
+    corey_table::Head head = {};
+    const int mine = group + (int)threadIdx.x * kSlabGroups;     // one slab of the group per lane
+    if (threadIdx.x < kGroupSlabs) head = ws.heads[mine];
+    static_assert(corey_table::kMaxSlabs == kBinLanes && kGroupSlabs * kSlabGroups == corey_table::kMaxSlabs, "a partial range per lane");
+    const RangePart rp = ws.rparts[threadIdx.x];
+    const int nslabs = (int)min(*ws.nslabs, (uint32_t)corey_table::kMaxSlabs);
+    if (threadIdx.x < kGroupSlabs) {
+        if (mine >= nslabs) head = corey_table::Head{};
+        s_nover[threadIdx.x] = min(head.n_over, (uint32_t)corey_table::kMaxOver);
+        s_units[threadIdx.x] = head.units[wb >> 3] >> ((wb & 7) * 4);         // this block's four units
+    }
     {   // the range: fold of the partial ranges of the workgroups that filled the tables
         uint32_t klo = 0xffffffffu, khi = 0u, knan = 0u;
-        for (int i = threadIdx.x; i < nslabs; i += kBinLanes) {
-            const RangePart rp = ws.rparts[i];
-            klo = min(klo, rp.lo_key);
-            khi = max(khi, rp.hi_key);
-            knan |= rp.saw_nan;
+        if ((int)threadIdx.x < nslabs) {
+            klo = rp.lo_key;
+            khi = rp.hi_key;
+            knan = rp.saw_nan;
         }
         corey_range::reduce_range_keys<kBinLanes>(klo, khi, knan);
         if (threadIdx.x == 0) {
@@ -138,12 +148,16 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
 
     uint32_t tot_lo[4] = {0u, 0u, 0u, 0u}, tot_hi[4] = {0u, 0u, 0u, 0u};
     const size_t my = (size_t)wb * kWordBlock + (size_t)threadIdx.x * 4;
-    for (int s0 = group; s0 < nslabs; s0 += kSlabGroups * kBinBatch) {
+    // the slabs of the group that hold counts in this wave's unit, kBinBatch of them in flight
+    const uint32_t unit = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    uint32_t left = (uint32_t)__ballot(lane < kGroupSlabs && (s_units[lane % kGroupSlabs] >> unit & 1u));
+    while (left) {                                              // uniform over the wave
         word4 q[kBinBatch];
 #pragma unroll
         for (int k = 0; k < kBinBatch; ++k) {
-            const int s = s0 + k * kSlabGroups;
-            q[k] = s < nslabs ? *reinterpret_cast<const word4*>(ws.slabs + (size_t)s * kWords + my) : word4{0u, 0u, 0u, 0u};
+            const int s = group + (left ? __builtin_ctz(left) : 0) * kSlabGroups;
+            q[k] = left ? *reinterpret_cast<const word4*>(ws.slabs + (size_t)s * kWords + my) : word4{0u, 0u, 0u, 0u};
+            left &= left - 1u;
         }
 #pragma unroll
         for (int k = 0; k < kBinBatch; ++k) {
@@ -155,28 +169,15 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
             }
         }
     }
-    {   // what the same slabs keep outside their tables: the zero pattern's count and the overflow lists (usually empty)
-        constexpr int kGroupSlabs = (corey_table::kMaxSlabs + kSlabGroups - 1) / kSlabGroups;
-        __shared__ uint32_t s_nover[kGroupSlabs];
-        if (threadIdx.x < kGroupSlabs) {                         // one slab of the group per lane: the heads in one go
-            const int s = group + (int)threadIdx.x * kSlabGroups;
-            uint32_t n_over = 0u;
-            if (s < nslabs) {
-                const corey_table::Head h = ws.heads[s];
-                n_over = min(h.n_over, (uint32_t)corey_table::kMaxOver);
-                if (wb == 0 && h.zeros) atomicAdd(&s_extra[0], h.zeros);      // pattern 0x0000 is the low half of word 0
-            }
-            s_nover[threadIdx.x] = n_over;
-        }
-        __syncthreads();
-        for (int t = 0; t < kGroupSlabs; ++t) {                  // uniform
-            const uint32_t n = s_nover[t];
-            const corey_table::Tail* tail = ws.tails + (group + t * kSlabGroups);
-            for (uint32_t i = threadIdx.x; i < n; i += kBinLanes) {
-                const uint32_t p = tail->over[i];
-                const uint32_t m = p & 0x7fffu;
-                if ((int)(m / kWordBlock) == wb) atomicAdd(&s_extra[(m % kWordBlock) * 2 + (p >> 15)], 32768u);
-            }
+    // what the same slabs keep outside their tables: the zero pattern's count and the overflow lists (usually empty)
+    if (wb == 0 && head.zeros) atomicAdd(&s_extra[0], head.zeros);      // pattern 0x0000 is the low half of word 0
+    for (int t = 0; t < kGroupSlabs; ++t) {                      // uniform
+        const uint32_t n = s_nover[t];
+        const corey_table::Tail* tail = ws.tails + (group + t * kSlabGroups);
+        for (uint32_t i = threadIdx.x; i < n; i += kBinLanes) {
+            const uint32_t p = tail->over[i];
+            const uint32_t m = p & 0x7fffu;
+            if ((int)(m / kWordBlock) == wb) atomicAdd(&s_extra[(m % kWordBlock) * 2 + (p >> 15)], 32768u);
         }
     }
     __syncthreads();
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
         for (int sign = 0; sign < 2; ++sign) {
             const uint32_t total = (sign ? tot_hi[e] : tot_lo[e]) + s_extra[local * 2 + sign];
             if (total == 0u) continue;
-            const float v = pattern_value(m | (sign ? 0x8000u : 0u), T());
+            const float v = corey_table::Pattern<T>::value(m | (sign ? 0x8000u : 0u));
             const float qv = __fmul_rn(__fsub_rn(v, lo), scale);          // two separate binary32 roundings
             int k = (int)qv;                                             // truncation; qv >= 0
             k = flat ? 0 : (k > top ? top : (k < 0 ? 0 : k));

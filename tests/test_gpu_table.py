@@ -179,3 +179,27 @@ def test_producer_table_at_full_size():
     torch.cuda.synchronize()
     ref = oracle.entropy_hist(u.float().cpu().numpy(), cfg.K)
     _compare(out, ref, cfg.K)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+def test_occupied_units(dtype):
+    """Every 256-word unit of a slab is written or left out as a whole: values at the ends of units (neighbouring patterns on either
+    side of a unit's edge), one value per unit, all magnitudes and both signs, and a range whose ends only one value or only the
+    overflow list holds (32768 times the largest value leaves its counter empty)."""
+    inf = 0x7F80 if dtype == wl.BF16 else 0x7C00
+    edges = np.array([m for u in range(0, inf, 256) for m in (u, u + 255) if m < inf], dtype=np.uint16)
+
+    def tensor(bits):
+        bits = np.asarray(bits, dtype=np.uint16)
+        bits = np.concatenate([bits, np.full(-bits.size % 8, bits[-1], dtype=np.uint16)]).reshape(1, -1, 8)
+        if dtype == wl.BF16:
+            return bits, (bits.astype(np.uint32) << 16).view(np.float32)
+        return bits.view(np.float16), bits.view(np.float16).astype(np.float32)
+
+    for bits in (edges, edges | 0x8000, np.concatenate([edges[1::2], edges[::2] | 0x8000]), np.arange(1, inf, dtype=np.uint16),
+                 [0x3C00, 0xBC01], [0x3C00] * 8, np.concatenate([[0x4000] * 32768, [0xBC00] * 32768, edges[:40]])):
+        store, val = tensor(bits)
+        small = np.abs(val) < 1e30 if dtype == wl.BF16 else np.isfinite(val)
+        if not small.all():                                # keep the range finite in binary32
+            store, val = tensor(np.asarray(bits, dtype=np.uint16)[small.ravel()[:len(bits)]])
+        _check(store, val, dtype, 64)
