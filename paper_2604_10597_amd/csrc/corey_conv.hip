@@ -155,6 +155,13 @@ __device__ __forceinline__ Cursor advance(Cursor c, const Walk& s)
     c.d -= (c.d >= s.D) ? s.D : 0;
     return c;
 }
+// How a launch of single steps is walked: `groups` groups of channels in each of B sequences; lane l takes group l mod groups of the
+// sequences l / groups, l / groups + across, ..., `units` of them at a time.
+struct StepWalk {
+    int64_t B, groups, lanes;
+    uint32_t across;
+    int units;
+};
 // n / d of a lane or workgroup number: 32 bits whatever the tensor (a divisor beyond them gives 0 either way)
 __device__ __forceinline__ uint32_t quotient(uint32_t n, int64_t d) { return n / (uint32_t)min(d, (int64_t)0x7fffffff); }
 
@@ -350,16 +357,19 @@ __global__ __launch_bounds__(NT) void k_conv1d_silu(const T* __restrict__ x, con
 }
 
 // One step with the carried state (generation): bound by the window it moves (W - 1 values in, W - 1 out beside one of x and u).
-// A lane takes R rows, as many as 4 bytes of x hold: the windows of R rows are then whole words (12 bytes at four taps), side by
-// side over the wave.  Up to kStepUnits groups of rows of a lane are in flight together.
+// A lane takes R channels, as many as 4 bytes of x hold: the windows of R rows are then whole words (12 bytes at four taps), side by
+// side over the wave.  It keeps its channels and walks the sequences, so that taps and bias, more bytes than the step itself, are
+// loaded once per lane, and has up to kStepUnits sequences in flight.  512 sequences of 5120 channels, bf16: 16.9 us (2.5 TB/s) with lanes
+// that walked rows of any channel and loaded the taps with each, 13.6 (3.1 TB/s) now; with non-temporal stores of the window 13.2, but
+// 64 sequences, whose window the next step finds in a cache, lose 0.3; three in flight 14.3.
 // R = 2 needs an even D and rows that start at words (the caller checks); other 16-bit tensors take the kernel below.
-constexpr int kStepUnits = 4;
+constexpr int kStepUnits = 6;
 
 template <typename T, int W>
 __global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restrict__ x, const float* __restrict__ weight,
                                                                const float* __restrict__ bias, const T* __restrict__ state_in,
                                                                T* __restrict__ u, T* __restrict__ state_out,
-                                                               Handoff* __restrict__ handoff, const Walk wk, int units)
+                                                               Handoff* __restrict__ handoff, const StepWalk wk)
 {
     if (handoff) corey_range::clear_handoff_counts(handoff);
     constexpr int R = 4 / (int)sizeof(T);
@@ -367,65 +377,59 @@ __global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restri
     float lo = INFINITY, hi = -INFINITY;
     bool nan = false;
     const uint32_t lane = blockIdx.x * kThreads + threadIdx.x;
-    Cursor cur;                                               // row: sequence; v: group of R channels within it
-    cur.row = quotient(lane, wk.nvec);
-    cur.v = lane - cur.row * wk.nvec;
-    cur.d = 0;
-    for (int64_t left = wk.turns; left > 0; left -= units) {  // uniform, like the tests of `units` below
-        const int nu = left < units ? (int)left : units;
-        int64_t r[kStepUnits];                                // first row of the group
-        T xv[kStepUnits][R], win[kStepUnits][NS > 0 ? NS : 1];
-        float w[kStepUnits][R * W], bs[kStepUnits][R];
+    const uint32_t s0 = quotient(lane, wk.groups);            // the first sequence of this lane (0 where the lanes are fewer than the groups)
+    if (s0 < wk.across) {
+        for (int64_t v = (int64_t)lane - (int64_t)s0 * wk.groups; v < wk.groups; v += wk.lanes) {      // (one turn but for very many channels)
+            float w[R * W], bs[R];
+            __builtin_memcpy(w, weight + v * R * W, sizeof(w));
 #pragma unroll
-        for (int j = 0; j < kStepUnits; ++j) {
-            if (j < nu) {
-                Cursor c = cur;
-                if (c.row >= wk.rows) c = Cursor{wk.rows - 1, wk.nvec - 1, 0};     // lanes beyond the last group redo it
-                cur.v += wk.rem;
-                const int64_t carry = (cur.v >= wk.nvec) ? 1 : 0;
-                cur.v -= carry ? wk.nvec : 0;
-                cur.row += wk.q + carry;
-                r[j] = (c.row * wk.nvec + c.v) * R;
-                const int64_t d = c.v * R;
-                __builtin_memcpy(xv[j], __builtin_assume_aligned(x + r[j], 4), 4);
-                if (W > 1) {
-                    if (state_in) {
-                        __builtin_memcpy(win[j], __builtin_assume_aligned(state_in + r[j] * (W - 1), 4), sizeof(T) * NS);
-                    } else {
+            for (int i = 0; i < R; ++i) bs[i] = bias ? bias[v * R + i] : 0.f;
+            for (int64_t s = s0; s < wk.B; s += (int64_t)wk.units * wk.across) {
+                int64_t r[kStepUnits];                        // first row of the group
+                T xv[kStepUnits][R], win[kStepUnits][NS > 0 ? NS : 1];
 #pragma unroll
-                        for (int k = 0; k < NS; ++k) win[j][k] = T(0);
+                for (int j = 0; j < kStepUnits; ++j) {
+                    if (j < wk.units) {                       // uniform
+                        const int64_t sj = s + (int64_t)j * wk.across;
+                        r[j] = ((sj < wk.B ? sj : s) * wk.groups + v) * R;      // beyond the last sequence the lane's first is done again
+                        __builtin_memcpy(xv[j], __builtin_assume_aligned(x + r[j], 4), 4);
+                        if (W > 1) {
+                            if (state_in) {
+                                __builtin_memcpy(win[j], __builtin_assume_aligned(state_in + r[j] * (W - 1), 4), sizeof(T) * NS);
+                            } else {
+#pragma unroll
+                                for (int k = 0; k < NS; ++k) win[j][k] = T(0);
+                            }
+                        }
                     }
                 }
-                __builtin_memcpy(w[j], weight + d * W, sizeof(float) * R * W);
 #pragma unroll
-                for (int i = 0; i < R; ++i) bs[j][i] = bias ? bias[d + i] : 0.f;
-            }
-        }
+                for (int j = 0; j < kStepUnits; ++j) {
+                    if (j < wk.units) {
+                        T out[R], moved[NS > 0 ? NS : 1];
 #pragma unroll
-        for (int j = 0; j < kStepUnits; ++j) {
-            if (j < nu) {
-                T out[R], moved[NS > 0 ? NS : 1];
+                        for (int i = 0; i < R; ++i) {
+                            float acc = bs[i];
 #pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    float acc = bs[j][i];
+                            for (int k = 0; k < W - 1; ++k) acc = fmaf(w[i * W + k], St<T>::widen(win[j][i * (W - 1) + k]), acc);
+                            acc = fmaf(w[i * W + W - 1], St<T>::widen(xv[j][i]), acc);
+                            const float val = acc * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-acc * kLog2e));
+                            nan |= (val != val);
+                            lo = vmin(lo, val);
+                            hi = vmax(hi, val);
+                            float one[St<T>::kVec];
+                            T st[St<T>::kVec];
 #pragma unroll
-                    for (int k = 0; k < W - 1; ++k) acc = fmaf(w[j][i * W + k], St<T>::widen(win[j][i * (W - 1) + k]), acc);
-                    acc = fmaf(w[j][i * W + W - 1], St<T>::widen(xv[j][i]), acc);
-                    const float val = acc * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-acc * kLog2e));
-                    nan |= (val != val);
-                    lo = vmin(lo, val);
-                    hi = vmax(hi, val);
-                    float one[St<T>::kVec];
-                    T st[St<T>::kVec];
+                            for (int e = 0; e < St<T>::kVec; ++e) one[e] = val;
+                            St<T>::narrow(one, st);
+                            out[i] = st[0];
 #pragma unroll
-                    for (int e = 0; e < St<T>::kVec; ++e) one[e] = val;
-                    St<T>::narrow(one, st);
-                    out[i] = st[0];
-#pragma unroll
-                    for (int k = 0; k < W - 1; ++k) moved[i * (W - 1) + k] = (k + 1 < W - 1) ? win[j][i * (W - 1) + k + 1] : xv[j][i];
+                            for (int k = 0; k < W - 1; ++k) moved[i * (W - 1) + k] = (k + 1 < W - 1) ? win[j][i * (W - 1) + k + 1] : xv[j][i];
+                        }
+                        __builtin_memcpy(__builtin_assume_aligned(u + r[j], 4), out, 4);
+                        if (W > 1 && state_out) __builtin_memcpy(__builtin_assume_aligned(state_out + r[j] * (W - 1), 4), moved, sizeof(T) * NS);
+                    }
                 }
-                __builtin_memcpy(__builtin_assume_aligned(u + r[j], 4), out, 4);
-                if (W > 1 && state_out) __builtin_memcpy(__builtin_assume_aligned(state_out + r[j] * (W - 1), 4), moved, sizeof(T) * NS);
             }
         }
     }
@@ -549,11 +553,20 @@ void launch(const void* x_, const float* weight, const float* bias, const void* 
     for (const void* p : {x_, (const void*)u_, state_in_, (const void*)state_out_})
         if (reinterpret_cast<uintptr_t>(p) % 4 != 0) words = false;
     if (L == 1 && words) {
-        const Walk wk = plan_walk(B, D, 1, D / R, kThreads, handoff ? kClearBlocks : 1, COREY_RANGE_PARTS, &blocks);
-        const int64_t passes = (wk.turns + kStepUnits - 1) / kStepUnits;
-        const int units = (int)((wk.turns + passes - 1) / passes);
+        StepWalk wk = {};
+        wk.B = B;
+        wk.groups = D / R;
+        const int64_t most = (int64_t)COREY_RANGE_PARTS * kThreads / wk.groups;     // sequences side by side, at most
+        const int64_t turns = most < 1 ? B : (B + most - 1) / most;
+        wk.across = (uint32_t)(most < 1 ? 1 : (B + turns - 1) / turns);
+        const int64_t passes = (turns + kStepUnits - 1) / kStepUnits;
+        wk.units = (int)((turns + passes - 1) / passes);
+        blocks = most < 1 ? COREY_RANGE_PARTS : (wk.across * wk.groups + kThreads - 1) / kThreads;
+        const int64_t least = handoff ? kClearBlocks : 1;
+        blocks = blocks < least ? least : blocks;
+        wk.lanes = blocks * kThreads;
         auto go_step = [&](auto kernel) {
-            kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, wk, units);
+            kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, wk);
         };
         switch (W) {
         case 1: go_step(k_conv1d_silu_step<T, 1>); break;
