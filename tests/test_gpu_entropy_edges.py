@@ -62,3 +62,22 @@ def test_few_values(values, K, dtype, V):
     assert route["r"].item() == out["r"].item() and route["H"].item() == out["H"].item()
     store, val = wl.store(np.full((1, values // V, V), -2.0, dtype=np.float32), dtype)
     _check(store, val, dtype, K)
+
+
+@pytest.mark.parametrize("L", [8, 8184, 8192, 8200, 8192 * 3 + 16])
+@pytest.mark.parametrize("stride", [1, 4])
+def test_producers_range(L, stride):
+    """The count sweep on the producer's range: less than one turn of a workgroup, exactly one, one and a word, several and two words."""
+    print(f"[case] producer's range L{L} stride {stride}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randn((1, 5, L), generator=g, device="cuda").to(torch.bfloat16)
+    u, _, parts = corey.causal_conv1d_silu_fwd(x, torch.randn((5, 4), generator=g, device="cuda"), torch.zeros(5, device="cuda"))
+    block = 8 if stride > 1 else 1
+    out = corey.corey_entropy_hist(u, 64, stride=stride, block=block, range_parts=parts)
+    lo, hi = (float(v) for v in out["range"].flatten().tolist())
+    v = u.float().flatten().cpu().numpy()
+    if stride > 1:
+        v = v.reshape(-1, block)[::stride].ravel()
+    scale = np.float32(64 / (hi - lo))
+    k = np.clip((v - np.float32(lo)) * scale, 0.0, 63.0).astype(np.int64)      # the range is that of u before it was stored
+    assert np.array_equal(out["counts"].cpu().numpy().ravel(), np.bincount(k, minlength=64))
