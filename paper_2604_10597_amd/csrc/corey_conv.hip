@@ -362,10 +362,13 @@ __global__ __launch_bounds__(NT) void k_conv1d_silu(const T* __restrict__ x, con
 // loaded once per lane, and has up to kStepUnits sequences in flight.  512 sequences of 5120 channels, bf16: 16.9 us (2.5 TB/s) with lanes
 // that walked rows of any channel and loaded the taps with each, 13.6 (3.1 TB/s) now; with non-temporal stores of the window 13.2, but
 // 64 sequences, whose window the next step finds in a cache, lose 0.3; three in flight 14.3.
+// UNITS: 1 where every lane has one sequence, else kStepUnits.  A small batch is one trip to memory and the code's own way into the
+// compute units: five absent bodies, jumped over twice, were 0.4 of its 3.4 us (bf16, 5120 channels, state and inputs in a cache: 1 sequence
+// 3.44 -> 3.04 us, 64 4.20 -> 3.83; 128 and more, which take kStepUnits, unchanged).
 // R = 2 needs an even D and rows that start at words (the caller checks); other 16-bit tensors take the kernel below.
 constexpr int kStepUnits = 6;
 
-template <typename T, int W>
+template <typename T, int W, int UNITS>
 __global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restrict__ x, const float* __restrict__ weight,
                                                                const float* __restrict__ bias, const T* __restrict__ state_in,
                                                                T* __restrict__ u, T* __restrict__ state_out,
@@ -378,18 +381,19 @@ __global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restri
     bool nan = false;
     const uint32_t lane = blockIdx.x * kThreads + threadIdx.x;
     const uint32_t s0 = quotient(lane, wk.groups);            // the first sequence of this lane (0 where the lanes are fewer than the groups)
+    const int units = UNITS == 1 ? 1 : wk.units;
     if (s0 < wk.across) {
         for (int64_t v = (int64_t)lane - (int64_t)s0 * wk.groups; v < wk.groups; v += wk.lanes) {      // (one turn but for very many channels)
             float w[R * W], bs[R];
             __builtin_memcpy(w, weight + v * R * W, sizeof(w));
 #pragma unroll
             for (int i = 0; i < R; ++i) bs[i] = bias ? bias[v * R + i] : 0.f;
-            for (int64_t s = s0; s < wk.B; s += (int64_t)wk.units * wk.across) {
-                int64_t r[kStepUnits];                        // first row of the group
-                T xv[kStepUnits][R], win[kStepUnits][NS > 0 ? NS : 1];
+            for (int64_t s = s0; s < wk.B; s += (int64_t)units * wk.across) {
+                int64_t r[UNITS];                             // first row of the group
+                T xv[UNITS][R], win[UNITS][NS > 0 ? NS : 1];
 #pragma unroll
-                for (int j = 0; j < kStepUnits; ++j) {
-                    if (j < wk.units) {                       // uniform
+                for (int j = 0; j < UNITS; ++j) {
+                    if (j < units) {                          // uniform
                         const int64_t sj = s + (int64_t)j * wk.across;
                         r[j] = ((sj < wk.B ? sj : s) * wk.groups + v) * R;      // beyond the last sequence the lane's first is done again
                         __builtin_memcpy(xv[j], __builtin_assume_aligned(x + r[j], 4), 4);
@@ -404,8 +408,8 @@ __global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restri
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < kStepUnits; ++j) {
-                    if (j < wk.units) {
+                for (int j = 0; j < UNITS; ++j) {
+                    if (j < units) {
                         T out[R], moved[NS > 0 ? NS : 1];
 #pragma unroll
                         for (int i = 0; i < R; ++i) {
@@ -430,6 +434,7 @@ __global__ __launch_bounds__(kThreads) void k_conv1d_silu_step(const T* __restri
                         if (W > 1 && state_out) __builtin_memcpy(__builtin_assume_aligned(state_out + r[j] * (W - 1), 4), moved, sizeof(T) * NS);
                     }
                 }
+                if (UNITS == 1) break;
             }
         }
     }
@@ -568,12 +573,17 @@ void launch(const void* x_, const float* weight, const float* bias, const void* 
         auto go_step = [&](auto kernel) {
             kernel<<<dim3((unsigned)blocks), dim3(kThreads), 0, stream>>>(x, weight, bias, state_in, u, state_out, handoff, wk);
         };
-        switch (W) {
-        case 1: go_step(k_conv1d_silu_step<T, 1>); break;
-        case 2: go_step(k_conv1d_silu_step<T, 2>); break;
-        case 3: go_step(k_conv1d_silu_step<T, 3>); break;
-        default: go_step(k_conv1d_silu_step<T, 4>); break;
-        }
+        auto taps = [&](auto units) {
+            constexpr int UNITS = decltype(units)::value;
+            switch (W) {
+            case 1: go_step(k_conv1d_silu_step<T, 1, UNITS>); break;
+            case 2: go_step(k_conv1d_silu_step<T, 2, UNITS>); break;
+            case 3: go_step(k_conv1d_silu_step<T, 3, UNITS>); break;
+            default: go_step(k_conv1d_silu_step<T, 4, UNITS>); break;
+            }
+        };
+        if (turns == 1) taps(std::integral_constant<int, 1>{});
+        else taps(std::integral_constant<int, kStepUnits>{});
         return;
     }
     if (L < 2 * V) {

@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
-@pytest.mark.parametrize("B,D,L", [(1, 1, 1), (3, 7, 1), (2, 514, 1), (300, 2500, 1), (7, 163840, 1), (2, 524300, 1), (2, 6, 7), (2, 3, 8), (2, 5, 15), (2, 3, 16), (1, 9, 17),
+@pytest.mark.parametrize("B,D,L", [(1, 1, 1), (3, 7, 1), (2, 514, 1), (300, 2500, 1), (7, 163840, 1), (2, 524300, 1),
+                                   (51, 5120, 1), (52, 5120, 1), (102, 5120, 1), (103, 5120, 1), (700, 5120, 1),      # one sequence a lane, two, seven
+                                   (2, 6, 7), (2, 3, 8), (2, 5, 15), (2, 3, 16), (1, 9, 17),
                                    (3, 2, 23), (1, 3, 511), (2, 3, 512), (1, 3, 513), (5, 1, 1024), (3, 1500, 1500), (2, 1100, 1024)])
 def test_outputs_state_and_range(B, D, L, dtype):
     print(f"[case] conv edges {B} {D} {L} {dtype}", flush=True)
