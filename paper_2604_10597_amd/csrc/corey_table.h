@@ -156,9 +156,10 @@ __device__ __forceinline__ void add(uint32_t* s_tab, Shared& sh, uint32_t p)
     settle(s_tab, sh, p, add_issue(s_tab, sh, p));
 }
 
-// The eight elements of one 16-byte word: all adds first, then one look at the OR of what they returned.  A word without a zero
-// pattern needs no look at each of its elements for one: an element is then its place (two instructions), its half (two) and
-// its add.
+// The eight elements of one 16-byte word: all adds first, then one look at the OR of what they returned.  Words without a zero
+// pattern need no look at each of their elements for one: an element is then its place (two instructions), its half (two) and
+// its add.  The wave takes either form as a whole: with the choice left to the lanes a few zeros made it issue both, sixteen adds
+// for eight values (84 million bf16 values, one in a hundred zero: 45.4 us; the careful form for every word 44.1, as it is 36.4).
 __device__ __forceinline__ void add_word4(uint32_t* s_tab, Shared& sh, const uint32_t (&w)[4])
 {
     typedef uint16_t half2 __attribute__((ext_vector_type(2)));
@@ -166,7 +167,7 @@ __device__ __forceinline__ void add_word4(uint32_t* s_tab, Shared& sh, const uin
     __builtin_memcpy(h, w, 16);
     const half2 least = __builtin_elementwise_min(__builtin_elementwise_min(h[0], h[1]), __builtin_elementwise_min(h[2], h[3]));
     uint32_t old[8], any = 0u;
-    if (least.x != 0 && least.y != 0) {
+    if (!__any(least.x == 0 || least.y == 0)) {                // over the lanes that have a word
         char* tab = reinterpret_cast<char*>(s_tab);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {

@@ -203,3 +203,16 @@ def test_occupied_units(dtype):
         if not small.all():                                # keep the range finite in binary32
             store, val = tensor(np.asarray(bits, dtype=np.uint16)[small.ravel()[:len(bits)]])
         _check(store, val, dtype, 64)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("share", [3e-4, 0.02, 0.5])
+def test_zeros_among_values(share, dtype):
+    """A wave takes the words of a turn in one of two forms, the careful one if any of its words holds a zero: waves with no zero, with
+    one and with many, and a last turn in which not every lane has a word."""
+    rng = np.random.default_rng(int(share * 1e4))
+    x = rng.standard_normal((1, 37, 4104)).astype(np.float32)
+    x[rng.random(x.shape) < share] = 0.0
+    x[rng.random(x.shape) < share / 4] = -0.0
+    store, val = wl.store(x, dtype)
+    _check(store, val, dtype, 256)
