@@ -57,13 +57,18 @@ struct Shared {                         // LDS bookkeeping beside the table
     uint32_t units[kUnits / 32];
 };
 
-template <typename T> struct Pattern;   // values of the storage bit patterns
+// Values of the storage bit patterns.  kDense: a tensor's values are spread over most of the table (binary16: a dozen of its 32
+// exponents, 1024 patterns each), so that a look at every occurring pattern for the range costs more than the way round it below:
+// 1 million N(0,1) values, binary16 10.1 -> 9.1 us, wide ones 14.4 -> 10.1; bfloat16, whose values fill a tenth of the table, 8.1 -> 8.4.
+template <typename T> struct Pattern;
 template <> struct Pattern<uint16_t> {  // bfloat16
     static constexpr uint32_t kInf = 0x7f80u;
+    static constexpr bool kDense = false;
     static __device__ __forceinline__ float value(uint32_t p) { return __uint_as_float(p << 16); }
 };
 template <> struct Pattern<_Float16> {
     static constexpr uint32_t kInf = 0x7c00u;
+    static constexpr bool kDense = true;
     static __device__ __forceinline__ float value(uint32_t p)
     {
         const uint16_t b = (uint16_t)p;
@@ -221,6 +226,17 @@ __device__ __forceinline__ void end(uint32_t* s_tab, Shared& sh, const Workspace
         for (uint32_t i = threadIdx.x; i < n_over; i += kLanes) fold_pattern<T>(sh.over[i], klo, khi, knan);
     }
     for (int off = 32; off > 0; off >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, off);
+    // kDense: a lane meets its 16-byte words in the order of their patterns' magnitudes, so it notes the first and the last of either
+    // sign and looks at the counts in two of them once they are known.
+    constexpr int kInfWord = (int)(Pattern<T>::kInf / 4);      // (infinity is a word's first pattern)
+    int pos_first = -1, pos_last = -1, neg_first = -1, neg_last = -1;
+    auto fold_words = [&](int i, const word4& v, bool pos, bool neg) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (pos && (v[e] & 0xffffu)) fold_pattern<T>(4 * i + e, klo, khi, knan);
+            if (neg && (v[e] >> 16)) fold_pattern<T>((4 * i + e) | 0x8000u, klo, khi, knan);
+        }
+    };
     word4* slab = reinterpret_cast<word4*>(ws.slabs + (size_t)blockIdx.x * kWords);
     for (int i = threadIdx.x; i < kWords / 4; i += kLanes) {
         const word4 v = reinterpret_cast<const word4*>(s_tab)[i];
@@ -229,12 +245,25 @@ __device__ __forceinline__ void end(uint32_t* s_tab, Shared& sh, const Workspace
         const int unit = i / (kUnitWords / 4);
         if ((threadIdx.x & 63) == 0) atomicOr(&sh.units[unit >> 5], 1u << (unit & 31));
         if constexpr (FROM_TABLE) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (v[e] & 0xffffu) fold_pattern<T>(4 * i + e, klo, khi, knan);
-                if (v[e] >> 16) fold_pattern<T>((4 * i + e) | 0x8000u, klo, khi, knan);
+            if (!Pattern<T>::kDense || i >= kInfWord) {        // (beyond: infinity and NaN)
+                fold_words(i, v, true, true);
+            } else {
+                const uint32_t any = v.x | v.y | v.z | v.w;
+                if (any & 0xffffu) {
+                    pos_first = pos_first < 0 ? i : pos_first;
+                    pos_last = i;
+                }
+                if (any >> 16) {
+                    neg_first = neg_first < 0 ? i : neg_first;
+                    neg_last = i;
+                }
             }
         }
+    }
+    if constexpr (FROM_TABLE && Pattern<T>::kDense) {
+        const int lowest = neg_last >= 0 ? neg_last : pos_first, highest = pos_last >= 0 ? pos_last : neg_first;
+        if (lowest >= 0) fold_words(lowest, reinterpret_cast<const word4*>(s_tab)[lowest], neg_last < 0, neg_last >= 0);
+        if (highest >= 0) fold_words(highest, reinterpret_cast<const word4*>(s_tab)[highest], pos_last >= 0, pos_last < 0);
     }
     corey_range::reduce_range_keys<kLanes>(klo, khi, knan);   // holds a barrier: the units are known, all zero counts have been read
     if ((threadIdx.x & 63) == 0) sh.zeros[threadIdx.x >> 6] = zeros;         // the waves' totals

@@ -216,3 +216,26 @@ def test_zeros_among_values(share, dtype):
     x[rng.random(x.shape) < share / 4] = -0.0
     store, val = wl.store(x, dtype)
     _check(store, val, dtype, 256)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+def test_ends_of_the_range(dtype):
+    """The range read off the table: its ends in one 16-byte word, in different words of one lane, of one sign or both, in the words
+    around infinity's; NaN leaves the range to the other values."""
+    inf = 0x7F80 if dtype == wl.BF16 else 0x7C00
+    one = 0x3F80 if dtype == wl.BF16 else 0x3C00
+    sets = [[one], [one | 0x8000], [one, one + 3], [one | 0x8000, one + 3 | 0x8000], [one + 1, one + 2 | 0x8000], [one, one + 4], [one - 1, one],
+            [one, one - 4096], [one | 0x8000, one - 4096 | 0x8000], [one - 8192, one - 4096, one, one - 4096 | 0x8000], [0, one], [0, one | 0x8000],
+            [0x8000, one]]
+    sets += [[one, p] for p in (inf, inf | 0x8000, inf + 1, inf + 3, inf + 4 | 0x8000, 0x7FFF, 0xFFFF)] + [[inf + 1], [inf, inf | 0x8000, one]]
+    for bits in sets:
+        bits = np.array((bits * 16)[:16], dtype=np.uint16).reshape(1, 2, 8)
+        xd = torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16 if dtype == wl.BF16 else torch.float16)
+        out = corey.corey_entropy_hist_onesweep(xd, 64, table_ws=_ws())
+        ref = corey.corey_entropy_hist(xd, 64)
+        torch.cuda.synchronize()
+        v = xd.float().cpu().numpy()
+        left = v[~np.isnan(v)]
+        what = [hex(b) for b in bits[0, 0]]
+        assert out["range"].flatten().tolist() == ([left.min(), left.max()] if left.size else [np.inf, -np.inf]), what
+        assert torch.equal(out["counts"], ref["counts"]) and int(out["counts"].sum()) == (v.size if np.isfinite(v).all() else 0), what
