@@ -97,7 +97,9 @@ __global__ __launch_bounds__(kLanes) void k_table_count(const T* __restrict__ x,
 }
 
 // Grid: (kWords / 1024 blocks of 1024 table words) x kSlabGroups; a workgroup adds up, for its 1024 words (2048
-// patterns), the slabs s = group, group + kSlabGroups, ...: a lane owns 4 consecutive words (8 patterns).
+// patterns), the kGroupSlabs slabs of its group: a lane owns 4 consecutive words (8 patterns).  Groups are filled one after another, so
+// that few slabs are binned and merged few times, and neighbouring patterns that share a bin are one add (small magnitudes crowd one bin):
+// 1 million binary16 values (32 slabs) 9.2 -> 7.1 us, 33.5 million over many exponents 12.9 -> 11.3, bf16 10.2 -> 8.5, N(0,1) 9.3 -> 8.3.
 constexpr int kBinLanes = 256;
 constexpr int kWordBlock = kBinLanes * 4;
 constexpr int kSlabGroups = 16;
@@ -119,11 +121,12 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
     for (int i = threadIdx.x; i < 2 * kWordBlock; i += kBinLanes) s_extra[i] = 0u;
     for (int i = threadIdx.x; i < K; i += kBinLanes) s_bins[i] = 0u;
     corey_table::Head head = {};
-    const int mine = group + (int)threadIdx.x * kSlabGroups;     // one slab of the group per lane
+    const int mine = group * kGroupSlabs + (int)threadIdx.x;     // one slab of the group per lane
     if (threadIdx.x < kGroupSlabs) head = ws.heads[mine];
     static_assert(corey_table::kMaxSlabs == kBinLanes && kGroupSlabs * kSlabGroups == corey_table::kMaxSlabs, "a partial range per lane");
     const RangePart rp = ws.rparts[threadIdx.x];
     const int nslabs = (int)min(*ws.nslabs, (uint32_t)corey_table::kMaxSlabs);
+    if (group * kGroupSlabs >= nslabs) return;                  // uniform: no slab left for this group
     if (threadIdx.x < kGroupSlabs) {
         if (mine >= nslabs) head = corey_table::Head{};
         s_nover[threadIdx.x] = min(head.n_over, (uint32_t)corey_table::kMaxOver);
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
         word4 q[kBinBatch];
 #pragma unroll
         for (int k = 0; k < kBinBatch; ++k) {
-            const int s = group + (left ? __builtin_ctz(left) : 0) * kSlabGroups;
+            const int s = group * kGroupSlabs + (left ? __builtin_ctz(left) : 0);
             q[k] = left ? *reinterpret_cast<const word4*>(ws.slabs + (size_t)s * kWords + my) : word4{0u, 0u, 0u, 0u};
             left &= left - 1u;
         }
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
     if (wb == 0 && head.zeros) atomicAdd(&s_extra[0], head.zeros);      // pattern 0x0000 is the low half of word 0
     for (int t = 0; t < kGroupSlabs; ++t) {                      // uniform
         const uint32_t n = s_nover[t];
-        const corey_table::Tail* tail = ws.tails + (group + t * kSlabGroups);
+        const corey_table::Tail* tail = ws.tails + (group * kGroupSlabs + t);
         for (uint32_t i = threadIdx.x; i < n; i += kBinLanes) {
             const uint32_t p = tail->over[i];
             const uint32_t m = p & 0x7fffu;
@@ -186,19 +189,26 @@ __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
     const float scale = flat ? 0.f : (float)((double)K / ((double)hi - (double)lo));
     const int top = K - 1;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const uint32_t m = (uint32_t)my + e;
-        const uint32_t local = (uint32_t)threadIdx.x * 4 + e;
+    for (int sign = 0; sign < 2; ++sign) {
+        int run_bin = 0;                                         // neighbouring patterns that share a bin are one add
+        uint32_t run = 0u;
 #pragma unroll
-        for (int sign = 0; sign < 2; ++sign) {
-            const uint32_t total = (sign ? tot_hi[e] : tot_lo[e]) + s_extra[local * 2 + sign];
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t m = (uint32_t)my + e;
+            const uint32_t total = (sign ? tot_hi[e] : tot_lo[e]) + s_extra[(threadIdx.x * 4 + e) * 2 + sign];
             if (total == 0u) continue;
             const float v = corey_table::Pattern<T>::value(m | (sign ? 0x8000u : 0u));
             const float qv = __fmul_rn(__fsub_rn(v, lo), scale);          // two separate binary32 roundings
             int k = (int)qv;                                             // truncation; qv >= 0
             k = flat ? 0 : (k > top ? top : (k < 0 ? 0 : k));
-            atomicAdd(&s_bins[k], total);
+            if (k != run_bin && run) {
+                atomicAdd(&s_bins[run_bin], run);
+                run = 0u;
+            }
+            run_bin = k;
+            run += total;
         }
+        if (run) atomicAdd(&s_bins[run_bin], run);
     }
     __syncthreads();
     uint32_t* out = ws.parts + (size_t)(wg % corey_table::kParts) * K;

@@ -239,3 +239,15 @@ def test_ends_of_the_range(dtype):
         what = [hex(b) for b in bits[0, 0]]
         assert out["range"].flatten().tolist() == ([left.min(), left.max()] if left.size else [np.inf, -np.inf]), what
         assert torch.equal(out["counts"], ref["counts"]) and int(out["counts"].sum()) == (v.size if np.isfinite(v).all() else 0), what
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("slabs", [1, 2, 15, 16, 17, 33, 256])
+def test_groups_of_slabs(slabs, dtype):
+    """The binning's groups take 16 slabs each, one after another: groups that are full, partly filled and empty; neighbouring patterns
+    that share a bin (few bins) and that do not (many); patterns that overflow their counter in the last slab."""
+    x = np.random.default_rng(slabs).standard_normal((1, slabs, 32768)).astype(np.float32)
+    x[0, -1, 5:] = 1.0 + 2.0 ** -7
+    store, val = wl.store(x[:, :, :32768], dtype)
+    for K in (2, 256, 4096):
+        _check(store, val, dtype, K)
