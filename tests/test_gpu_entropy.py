@@ -92,7 +92,7 @@ def test_block_sampled_histogram(dtype):
     _check(w.dev["u"], w.val["u"], cfg.dtype, 256, stride=8, block=512)
     # per-sequence histograms over long rows: turns of whole slabs that cross rows, rows with a ragged last slab, and the
     # sampled sweep that skips the vectors of unsampled blocks without fetching them
-    cfg = wl.scaled(wl.CONFIGS["c3_mamba1p4b"], B=3, D=6, L=6144, dtype=dtype, seqlens=(6144, 4096, 2056))
+    cfg = wl.scaled(wl.CONFIGS["c3_mamba1p4b"], B=3, D=7, L=6144, dtype=dtype, seqlens=(6144, 4096, 2056))      # (beyond one launch's values)
     w = wl.make(cfg)
     lens = np.array(cfg.seqlens, np.int32)
     for stride, block in ((1, 1), (8, 512), (2, 8), (4, 2048), (8, 16384), (3, 64), (8, 4)):
@@ -114,12 +114,15 @@ def test_bin_limits_and_eps():
 
 
 @pytest.mark.parametrize("K", [255, 256, 257, 2048, 2049, 2730, 2731, 4095])
-def test_bin_counts_where_the_number_of_counter_copies_changes(K):
-    """32, 16 ... 2 copies of the counters per workgroup, one beyond 2730 bins; whole-tensor and per-sequence sweeps."""
-    _say(f"entropy counter copies K {K}")
-    store, val = wl.store(np.random.default_rng(K).laplace(0, 3, (2, 16, 512)).astype(np.float32), wl.BF16)
+@pytest.mark.parametrize("L", [512, 2560])
+def test_bin_counts_where_the_number_of_counter_copies_changes(K, L):
+    """32, 16 ... 2 copies of the counters per workgroup, one beyond 2730 bins; whole-tensor and per-sequence statistics in one launch
+    (8192 values a sequence) and in sweeps (43520)."""
+    _say(f"entropy counter copies K {K} L {L}")
+    D = 16 if L == 512 else 17
+    store, val = wl.store(np.random.default_rng(K).laplace(0, 3, (2, D, L)).astype(np.float32), wl.BF16)
     _check(store, val, wl.BF16, K)
-    _check(store, val, wl.BF16, K, seqlens=np.array([512, 77], np.int32))
+    _check(store, val, wl.BF16, K, seqlens=np.array([L, 77], np.int32))
 
 
 def test_degenerate_inputs():

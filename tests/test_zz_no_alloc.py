@@ -52,7 +52,9 @@ def test_static_scratch_entry_point_equals_the_workspace_one():
         # (config, D, L, seqlens, K, stride, block): a large call first, then smaller ones on the same built-in buffer
         ("c4_mamba2p8b", 512, 4096, None, 256, 1, 1),
         ("c2_mamba370m", 24, 1000, None, 64, 1, 1),              # fewer bins, fewer values: stale partial counts would show
-        ("c3_mamba1p4b", 16, 1024, (1024, 300), 256, 1, 1),      # per-sequence histograms (the general kernels)
+        ("c3_mamba1p4b", 16, 1024, (1024, 300), 256, 1, 1),      # per-sequence histograms in one launch (no scratch)
+        ("c3_mamba1p4b", 48, 1024, (1024, 300), 256, 1, 1),      # in sweeps over rows of whole words
+        ("c3_mamba1p4b", 48, 1023, (1023, 300), 64, 1, 1),       # and the general kernels
         ("c4_mamba2p8b", 64, 2048, None, 4096, 8, 512),          # most bins, sampled
         ("c1_mamba130m", 3, 7, None, 16, 1, 1),                  # a handful of values, unaligned rows
     ]
