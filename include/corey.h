@@ -218,7 +218,9 @@ int corey_route_device(const void* x, corey_dtype dt, int64_t B, int64_t D, int6
  * it fills *route (HOST, caller-owned, opaque) instead.  selective_scan_fwd_routed is selective_scan_fwd with the
  * reduction and the chunk rule evaluated first: at the start of the kernel that rewrites B and C, or, in launches that read B
  * and C directly (at most 3072 rows B * D, 1024 in COREY_F32; see workspace of selective_scan_fwd), by the reduction's own kernel, as many
- * launches as corey_route_device takes then.  Every result corey_route_device would have written (counts, H, r, range, chunk, chunk counters) is written then, bit for bit the same, and the scan
+ * launches as corey_route_device takes then -- but for few values (stride 1, no range_parts, at most 40960 values a histogram, x and
+ * its rows (seqlens) or its size in whole 16-byte words): there corey_route_device is one launch and the deferred form three, so
+ * corey_route_device is the call to make.  Every result corey_route_device would have written (counts, H, r, range, chunk, chunk counters) is written then, bit for bit the same, and the scan
  * runs with the chunk so selected (per sequence when the statistic was per sequence, else one chunk for all).
  * With range_parts from the producer the whole routed path is: producer, one count sweep, scan.  A refused call has launched
  * nothing and leaves *route as it was.

@@ -49,7 +49,10 @@ using corey_range::reduce_range_keys;
 constexpr int kVecBytes = 16;
 using corey_range::kParts;     // partial histograms per histogram in the workspace
 constexpr int kMaxBlocks = COREY_RANGE_PARTS;  // most workgroups per sweep (four per compute unit) and partial ranges kept
-constexpr int kMostRowHistograms = 64;          // per-sequence flat sweeps: at least 16 workgroups for a histogram
+// Most histograms of the per-sequence flat sweeps: 16 workgroups of the 1024 for each.  64 histograms of 49152 to 3 million values take 27 to
+// 96 % of the general kernels' time; so would 65 to 128 (21 to 96 %; bf16, 96 of 512 x 1024: 172 us there, 42 in sweeps), beyond which a
+// histogram would have fewer than the eight workgroups the general kernels give it.
+constexpr int kMostRowHistograms = 64;
 constexpr int kFlatBlocks = 512;               // workgroups of a flat sweep: two per compute unit measured 4 % (exact) to
                                                // 11 % (sampled) faster than four (fewer LDS clears, merges and range folds)
 
@@ -711,7 +714,9 @@ __global__ __launch_bounds__(kThreads) void k_entropy_count_flat(const word4* __
 // Range, counts, reduction and rule of 64 x 256 binary32 values at K = 16: 8.8 us in three launches, 7.2 in one (with the scan 16.4 and
 // 14.3 a step).  The one compute unit's counts are what grows: the line lies at 40960 values (us, three launches and one: K = 16,
 // binary32, 32768 values 9.4 and 8.4, 49152 9.2 and 9.7; bf16, 32768 9.5 and 8.2, 49152 9.6 and 9.4, 65536 9.6 and 10.5; K = 256 the
-// same within 0.4; K = 4096 24 and 14 at 32768, 23 and 17 at 65536).
+// same within 0.4; K = 4096 24 and 14 at 32768, 23 and 17 at 65536).  Several histograms are counted side by side: bf16, 80 x 512 values
+// each, 8 sequences 12.3 us in sweeps and 11.3 in one launch, 64 13.7 and 11.6; of 250 forms with 1 to 64 sequences the sweeps
+// are faster in five, by 3 to 9 % (40960 values of binary32); from 65, where they end, the one launch takes 0.1 to 0.4 of the time.
 constexpr int kSmallThreads = 1024;
 constexpr int64_t kSmallValues = 40960;
 template <typename T, int MODE>

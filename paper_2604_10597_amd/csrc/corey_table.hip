@@ -7,10 +7,12 @@
 //                   occurs is binned once, with its multiplicity, by the very binary32 expression the two-pass kernels
 //                   apply to every element, so the K counts are bit-identical to theirs
 //   k_entropy_finalise (corey_entropy.hip)  H, r and the chunk rule from the counts
-// Bandwidth and LDS-atomic work: no matrix instructions.  33.5 million bf16 values at K = 256: counting 23.2 -> 18.9 us (bound by the
-// adds, 7 to 8 a clock and compute unit, and six instructions a value), binning 11.4 -> 9.0 (a chain of four trips to memory), the
-// statistic 39.2 -> 32.1: only the parts of a slab that hold counts move, the range is read off the table, a word without a zero
-// needs no look at each value, the slabs of a group are one trip.
+// Bandwidth and LDS-atomic work: no matrix instructions.  33.5 million bf16 values at K = 256: counting 24.9 -> 20.0 us, binning 11.4 ->
+// 8.3, the statistic 39.2 -> 31.1: only the parts of a slab that hold counts move (84 million values: 33.8 -> 4.3 MB written), the
+// range is read off the table, a word without a zero needs no look at each value, the slabs of a group are one trip.  Of the counting some
+// 9 us do not grow (64 thousand values take 8.6: clearing and reading 128 KiB of table, one workgroup a compute unit); the rest
+// goes at the rate memory is read (84 million values 36.0 us: 101 MB more in 16 us, 5 adds a clock and compute unit).  The binning
+// is a chain of four trips to memory.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -102,8 +104,8 @@ __global__ __launch_bounds__(kLanes) void k_table_count(const T* __restrict__ x,
 // 1 million binary16 values (32 slabs) 9.2 -> 7.1 us, 33.5 million over many exponents 12.9 -> 11.3, bf16 10.2 -> 8.5, N(0,1) 9.3 -> 8.3.
 constexpr int kBinLanes = 256;
 constexpr int kWordBlock = kBinLanes * 4;
-constexpr int kSlabGroups = 16;
-constexpr int kBinBatch = 16;       // slab loads a lane keeps in flight: a group's slabs are one trip to memory
+constexpr int kSlabGroups = 16;     // 8: 33.5 million bf16 values 8.9 us against 8.4, binary16 10.2 against 9.3, 1 million 8.9 against 7.1
+constexpr int kBinBatch = 16;       // slab loads a lane keeps in flight: a group's slabs are one trip to memory (8: the same within 0.4 us)
 
 template <typename T>
 __global__ __launch_bounds__(kBinLanes) void k_table_bin(void* workspace, int K)
