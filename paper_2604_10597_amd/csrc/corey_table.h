@@ -164,7 +164,7 @@ __device__ __forceinline__ void add(uint32_t* s_tab, Shared& sh, uint32_t p)
 // The eight elements of one 16-byte word: all adds first, then one look at the OR of what they returned.  Words without a zero
 // pattern need no look at each of their elements for one: an element is then its place (two instructions), its half (two) and
 // its add.  The wave takes either form as a whole: with the choice left to the lanes a few zeros made it issue both, sixteen adds
-// for eight values (84 million bf16 values, one in a hundred zero: 45.4 us; the careful form for every word 44.1, as it is 36.4).
+// for eight values (84 million bf16 values, one in a hundred zero: 45.4 us, as it is 36.4).
 __device__ __forceinline__ void add_word4(uint32_t* s_tab, Shared& sh, const uint32_t (&w)[4])
 {
     typedef uint16_t half2 __attribute__((ext_vector_type(2)));
