@@ -7,9 +7,9 @@
 #include "corey_scan_impl.h"
 
 namespace corey_scan {
-void launch_scan_f32(const ScanArgs& a, const LaunchPlan& p);
-void launch_scan_bf16(const ScanArgs& a, const LaunchPlan& p);
-void launch_scan_f16(const ScanArgs& a, const LaunchPlan& p);
+void launch_scan_f32(ScanArgs& a, const LaunchPlan& p);
+void launch_scan_bf16(ScanArgs& a, const LaunchPlan& p);
+void launch_scan_f16(ScanArgs& a, const LaunchPlan& p);
 }  // namespace corey_scan
 
 namespace {
@@ -93,7 +93,7 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     a.L = L; a.rows_total = B * D; a.D = (int32_t)D; a.N = (int32_t)N; a.chunk = chunk; a.softplus = delta_softplus ? 1 : 0;
     a.allow_structured = (flags & COREY_SCAN_GENERAL_A) ? 0 : 1;
     a.one_chunk = (flags & COREY_SCAN_ONE_CHUNK) ? 1 : 0;
-    a.allow_split = (flags & COREY_SCAN_WHOLE_ROWS) ? 0 : 1;
+    int allow_split = (flags & COREY_SCAN_WHOLE_ROWS) ? 0 : 1;
     // LDS budget for the per-row arrays (carried state and A): at most 32 rows and 8 KiB each, so that the staging
     // buffers and the rows of a workgroup stay below what a compute unit gives four workgroups (chunks below 64,
     // which would put more than 32 rows into a workgroup, run with idle lanes).
@@ -101,12 +101,18 @@ int scan_impl(const char* who, const void* u, const void* delta, const float* A,
     a.rows_cap = rows_cap < 1 ? 1 : (rows_cap > 32 ? 32 : rows_cap);
     const int64_t fit = (((int64_t)1 << 32) - 1) / row_bytes;
     if (a.rows_cap > fit) a.rows_cap = (int)fit;
-    a.d16 = corey_scan::plan_d16(B, D, chunk, a.rows_cap);
-    a.klo = corey_scan::plan_klo(B, D, chunk, a.d16);
-    a.split = corey_scan::plan_split(B, D, (int)N, chunk, a.d16, a.klo, a.allow_split);
-    a.direct = corey_scan::direct_launch(B, D, N, L, dt == COREY_F32, route || chunks_dev, a.d16, a.klo, a.split) ? 1 : 0;
+    a.host = corey_scan::row_plan(B, D, N, chunk, a.rows_cap, allow_split);
+    a.direct = corey_scan::direct_launch(B, D, N, L, dt == COREY_F32, route || chunks_dev, a.host.d16, a.host.klo, a.host.split) ? 1 : 0;
     // the second row of a channel finds its half of the states at a 32-bit byte offset
-    if (a.direct && (double)N * (double)L * (double)esz >= 2147483648.0) a.allow_split = a.split = 0;
+    if (a.direct && (double)N * (double)L * (double)esz >= 2147483648.0) {
+        allow_split = 0;
+        a.host.split = 0;
+    }
+    a.plans = corey_scan::Plans{};
+    if (!route && !chunks_dev) a.plans.set(corey_scan::tile_of(chunk, B * D), a.host);      // the relayout's
+    else
+        for (int c = COREY_MIN_CHUNK; c <= corey_scan::kMaxTile; c *= 2)
+            a.plans.set(c, corey_scan::row_plan(B, D, N, c, a.rows_cap, allow_split));
     a.route = corey_finalise::Args{};
     if (route) {
         a.route = *route;

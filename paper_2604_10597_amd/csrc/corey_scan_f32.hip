@@ -2,5 +2,5 @@
 #include "corey_scan_impl.h"
 
 namespace corey_scan {
-void launch_scan_f32(const ScanArgs& a, const LaunchPlan& p) { launch_scan<float>(a, p); }
+void launch_scan_f32(ScanArgs& a, const LaunchPlan& p) { launch_scan<float>(a, p); }
 }  // namespace corey_scan

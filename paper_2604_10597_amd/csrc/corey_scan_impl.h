@@ -91,7 +91,7 @@ template <int K, int CHUNK> struct Geo {
 // 16-step waves per SIMD plus 1024 rows as one 8-step wave, 10 % faster than either geometry alone).
 // plan_d16 returns d16: channels [0, d16) of every sequence take 16 steps per lane, [d16, D) take 8; 0 and D are the
 // pure launches.  It runs on the host (known chunk) and on the device (chunk read from memory) with the same inputs.
-__host__ __device__ inline int64_t plan_d16(int64_t B, int64_t D, int chunk, int rows_cap)
+inline int64_t plan_d16(int64_t B, int64_t D, int chunk, int rows_cap)
 {
     chunk = tile_of(chunk, B * D);
     if (chunk > 512) return D;                                   // a row of 8-step lanes would no longer fit one wave
@@ -112,7 +112,7 @@ __host__ __device__ inline int64_t plan_d16(int64_t B, int64_t D, int chunk, int
 // 4 steps win by 10 ... 35 % while the 8-step launch has at most about 1500 waves (1.5 per SIMD) and a 4-step row still
 // fits one wave (chunk <= 256); with 2 steps the lane scan costs more than the extra waves bring at chunks of 64 and up.
 constexpr int64_t kFewWaves = 1536;
-__host__ __device__ inline int plan_klo(int64_t B, int64_t D, int chunk, int64_t d16)
+inline int plan_klo(int64_t B, int64_t D, int chunk, int64_t d16)
 {
     if (d16 != 0 || chunk > 256) return 8;
     return B * D * (chunk / 8) / 64 <= kFewWaves ? 4 : 8;
@@ -125,7 +125,7 @@ __host__ __device__ inline int plan_klo(int64_t B, int64_t D, int chunk, int64_t
 // walked: chunk 2048 takes the launch of 1024 (bf16, 64 rows of 4096 steps: one row per channel 37.1 us, two 23.5; 256 of 32768 264
 // and 159; binary32 284 and 175).
 constexpr int64_t kSplitWaves = 1536;
-__host__ __device__ inline int plan_split(int64_t B, int64_t D, int N, int chunk, int64_t d16, int klo, int allow)
+inline int plan_split(int64_t B, int64_t D, int N, int chunk, int64_t d16, int klo, int allow)
 {
     if (!allow || N < 4 || (d16 > 0 && d16 < D)) return 0;    // (fewer than four states: the second row would hold padding only)
     chunk = tile_of(chunk, B * D);
@@ -561,6 +561,44 @@ __device__ __forceinline__ void scan_segments(int jseg, float (&P)[Q], float (&h
 __device__ __forceinline__ void carry_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
 
 // ------------------------------------------------------------------------------------------- kernel arguments
+// How a launch takes one tile.
+struct RowPlan {
+    int32_t d16;            // channels below d16 take 16 steps per lane, the others klo (see plan_d16)
+    int32_t g16;            // workgroups of the launch that take those
+    int32_t klo;            // 8 or 4 (see plan_klo)
+    int32_t split;          // the states of a channel are shared by two rows (see plan_split)
+};
+inline RowPlan row_plan(int64_t B, int64_t D, int64_t N, int chunk, int rows_cap, int allow_split)
+{
+    const int64_t d16 = plan_d16(B, D, chunk, rows_cap);
+    const int klo = plan_klo(B, D, chunk, d16);
+    return RowPlan{(int32_t)d16, 0, klo, plan_split(B, D, (int)N, chunk, d16, klo, allow_split)};
+}
+
+// ... and every tile, for a chunk read from device memory (chunks walked in the same tiles are taken the same way).  Worked out on the
+// host: on the GPU its divisions were 800 scalar instructions between the chunk and the first request for data.  Direct launches read the
+// flags only: what a kernel has to know is in the way of its first request, too.
+constexpr int kPlans = 7;
+static_assert(COREY_MIN_CHUNK == 16 && kMaxTile == 16 << (kPlans - 1), "a plan for every tile");
+__host__ __device__ constexpr int plan_index(int tile) { return 27 - __builtin_clz((unsigned)tile); }
+struct Plans {
+    uint32_t split, four;   // bit plan_index(tile): split; klo is 4
+    int32_t d16[kPlans], g16[kPlans];
+    void set(int tile, const RowPlan& r)
+    {
+        const int i = plan_index(tile);
+        split = (split & ~(1u << i)) | (uint32_t)(r.split != 0) << i;
+        four = (four & ~(1u << i)) | (uint32_t)(r.klo == 4) << i;
+        d16[i] = r.d16;
+        g16[i] = r.g16;
+    }
+    __host__ __device__ RowPlan get(int tile) const
+    {
+        const int i = plan_index(tile);
+        return RowPlan{d16[i], g16[i], four >> i & 1u ? 4 : 8, (int32_t)(split >> i & 1u)};
+    }
+};
+
 struct ScanArgs {
     const void* u;
     const void* delta;
@@ -579,11 +617,9 @@ struct ScanArgs {
     float* ws_C;
     float* ws_B8;           // the same operands in the order of the 8- or 4-step rows of this launch (ws_B / ws_C: the 16-step ones)
     float* ws_C8;
-    int64_t d16;            // channels below d16 take 16 steps per lane, the others klo (host chunk; see plan_d16)
-    int32_t klo;            // 8 or 4 (host chunk; see plan_klo)
-    int32_t split;          // the states of a channel are shared by two rows (host chunk; see plan_split)
+    RowPlan host;           // of the host chunk
+    Plans plans;            // of any chunk read from device memory
     int32_t direct;         // B and C are read as stored (see kDirectRows); the workspace is not used
-    int32_t allow_split;    // 0: every channel keeps one row whatever the size of the launch
     int64_t L, Lpad;
     int64_t rows_total;     // B * D (input of the items-per-lane rule)
     int32_t D, N;
@@ -616,13 +652,11 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_relayout_bc(const T* __restrict__ Bm, const T* __restrict__ Cm, float* __restrict__ ws_B,
                                                      float* __restrict__ ws_C, float* __restrict__ ws_B8, float* __restrict__ ws_C8,
                                                      const int32_t* __restrict__ seqlens, const int32_t* __restrict__ chunks_dev,
-                                                     int one_chunk, int chunk_host, int64_t d16_host, int klo_host, int64_t Bn, int64_t D, int rows_cap,
+                                                     int one_chunk, int chunk_host, const Plans plans, int64_t Bn, int64_t D,
                                                      int Nreal, int N, int64_t L, int64_t Lpad, corey_finalise::Args route)
 {
     const int b = blockIdx.y;
     int chunk = chunk_host;
-    int64_t d16 = d16_host;
-    int klo = klo_host;
     if (route.parts) {
         // the end of the entropy statistic, left to this kernel: every workgroup reduces the partial histograms of its
         // sequence's statistic and applies the chunk rule (all arrive at the same chunk); the first one publishes counts, H,
@@ -632,15 +666,19 @@ __global__ __launch_bounds__(256) void k_relayout_bc(const T* __restrict__ Bm, c
         const bool first = blockIdx.x == 0 && (route.nh > 1 || b == 0);
         const int c = corey_finalise::finalise(route, route.nh > 1 ? b : 0, first);
         if (c >= COREY_MIN_CHUNK && c <= COREY_MAX_CHUNK && (c & (c - 1)) == 0) chunk = c;
-        d16 = plan_d16(Bn, D, chunk, rows_cap);
-        klo = plan_klo(Bn, D, chunk, d16);
     } else if (chunks_dev) {
         const int c = chunks_dev[one_chunk ? 0 : b];
         if (c >= COREY_MIN_CHUNK && c <= COREY_MAX_CHUNK && (c & (c - 1)) == 0) chunk = c;
-        d16 = plan_d16(Bn, D, chunk, rows_cap);
-        klo = plan_klo(Bn, D, chunk, d16);
     }
     chunk = tile_of(chunk, Bn * D);                              // the layout is by the tiles the scan walks
+    const int klo = plans.four >> plan_index(chunk) & 1u ? 4 : 8;
+    int d16 = 0;
+#pragma unroll
+    for (int i = 0; i < kPlans; ++i) {                           // (an index into the argument would have it copied to scratch memory)
+        int di = plans.d16[i];
+        asm("" : "+s"(di));
+        if (plan_index(chunk) == i) d16 = di;
+    }
     int64_t len = L;
     if (seqlens) {
         const int64_t sl = seqlens[b];
@@ -714,6 +752,19 @@ __device__ __forceinline__ void stage_async(const float* __restrict__ srcB, cons
     }
 }
 
+// Whether every lane of the workgroup holds a nonzero value; a barrier.  (Another barrier has to pass before the next call.)
+__device__ __forceinline__ bool all_lanes(int v)
+{
+    __shared__ int s_all[kWaves];
+    const bool wave_all = __all(v);
+    if ((threadIdx.x & 63) == 0) s_all[threadIdx.x >> 6] = wave_all;
+    __syncthreads();
+    int all = 1;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) all &= s_all[w];
+    return __builtin_amdgcn_readfirstlane(all) != 0;
+}
+
 // Floats of dynamic LDS one workgroup of the (K, CHUNK) geometry needs for `rows` rows of N states.
 template <int K, int CHUNK>
 __host__ __device__ constexpr int lds_floats(int rows, int N, bool split, bool direct)
@@ -736,8 +787,67 @@ __host__ __device__ constexpr int lds_floats(int rows, int N, bool split, bool d
 // DIRECT: B and C are read where they are, as stored: every lane loads the K values of its steps (one or two 16-byte words per
 // operand and state, a set of states ahead) and widens them, two instructions per value more than from the fp32 copy.  In
 // return there is no staging, no barrier in the loop, and no launch before this one.  Which launches: see kDirectRows.
+// What a lane has of its first tile before the walk begins, as stored.
+template <typename T, int K> struct FirstTile {
+    Raw<T, K> u, delta;
+    float bias, Dd;
+};
+
+// The start of a group of rows is trips to memory with nothing beside them, so they are made together: the first tile, the rows'
+// parameters, A with what decides its structure, and the carried state.  Returns whether every row has the structured A; the LDS
+// arrays are there.  (Lane numbers are worked out here and again in the walk: kept for it, they would fill its registers.)
+// With the plan of a routed tile from the host instead of the device, against structure, arrays and first tile one after another: scan
+// of 1024 fp16 rows of 4096 steps at chunk 512 29.7 -> 28.6 us; routed layers, bf16, 1536 rows of 2048 steps 39.5 -> 37.4, 2048 of 977
+// 34.9 -> 33.6, steps of 8192 rows of 4096 170.5 -> 167.1, two padded sequences of 4096 rows 207.1 -> 204.3.  A lane of 16 steps asks
+// for its first tile in the walk: 16 registers kept until then spill there (the first of these layers 41.4 us, the second 34.6).
+template <typename T, int K, int CHUNK, bool SPLIT, bool DIRECT>
+__device__ __forceinline__ bool start_group(const ScanArgs& a, float* s_mem, const int rows, const int d0, FirstTile<T, K>& first)
+{
+    constexpr int LPR = Geo<K, CHUNK>::LPR;
+    constexpr int STAGE = DIRECT ? 0 : Geo<K, CHUNK>::STAGE;
+    const int b = blockIdx.y;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int row_local = tid / LPR, j = tid % LPR;
+    const int ch_local = SPLIT ? row_local >> 1 : row_local;
+    const int half = SPLIT ? row_local & 1 : 0;
+    const bool active = ch_local < rows && d0 + ch_local < a.D;
+    const int rl = active ? ch_local : 0;
+    const int N = a.Np, Nreal = a.N;
+    const int64_t L = a.L;
+    if constexpr (DIRECT && K < 16) {
+        // (in a sequence of less than a tile the lanes beyond the row and the one at the end of the tensor read further to the left)
+        int64_t at = (int64_t)j * K;
+        if (at + K > L && (at >= L || (b == (int)gridDim.y - 1 && d0 + rl == a.D - 1))) at = L - K;
+        const int64_t row = ((int64_t)b * a.D + d0 + rl) * L + at;
+        first.u = load_full<T, K>(static_cast<const T*>(a.u) + row);
+        first.delta = load_full<T, K>(static_cast<const T*>(a.delta) + row);
+    }
+    first.bias = (a.dbias && active) ? a.dbias[d0 + ch_local] : 0.f;
+    first.Dd = (a.Dv && active && half == 0) ? a.Dv[d0 + ch_local] : 0.f;      // the skip term enters once per channel
+    float* s_carry = s_mem + 4 * STAGE;
+    float* s_A2 = s_carry + rows * N;
+    float* s_zero = s_A2 + rows * N;
+    int chain = sizeof(T) == 2 && a.allow_structured ? 1 : 0;   // fp32 storage keeps the one-exponential-per-state path
+    const float inv_N = 1.f / (float)N;
+    for (int i = tid; i < rows * N; i += kBlock) {
+        const int r = (int)(((float)i + 0.5f) * inv_N), n = i - r * N;      // (exact: fewer than 2^14 values)
+        const int64_t dd = d0 + r;
+        float Av = 0.f, h = 0.f;
+        if (dd < a.D && n < Nreal) {
+            Av = a.A[dd * Nreal + n];
+            if (a.h0) h = a.h0[((int64_t)b * a.D + dd) * Nreal + n];
+            if (chain) chain = Av == (float)(n + 1) * a.A[dd * Nreal];
+        }
+        s_carry[i] = h;
+        s_A2[i] = Av * kLog2e;
+    }
+    for (int i = tid; i < N; i += kBlock) s_zero[i] = 0.f;
+    return all_lanes(chain);
+}
+
 template <typename T, int K, int CHUNK, bool STRUCT, bool SPLIT, int W, bool DIRECT>
-__device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, const int rows, const int d0)
+__device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, const int rows, const int d0, const FirstTile<T, K>& first)
 {
     using Gm = Geo<K, CHUNK>;
     constexpr int NS = SPLIT ? 2 : 1;                       // rows per channel
@@ -787,16 +897,6 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     float* s_zero = s_A2 + rows * N;                        // [N] zeros: the "carried state" of lanes that are not first in their row
     float* s_sink = s_zero + N;                             // [kMaxGroup * kBlock + N] where lanes that are not last in their row "store" the state
     float* s_ypart = s_sink + kMaxGroup * kBlock + N;       // SPLIT: [K][kBlock / 2] partial y of the second rows
-    for (int i = tid; i < rows * N; i += kBlock) {
-        const int r = i / N, n = i - r * N;
-        const int dd = d0 + r;
-        const bool ok = dd < a.D && n < Nreal;
-        s_carry[i] = (a.h0 && ok) ? a.h0[((int64_t)b * a.D + dd) * Nreal + n] : 0.f;
-        s_A2[i] = ok ? a.A[(int64_t)dd * Nreal + n] * kLog2e : 0.f;
-    }
-    for (int i = tid; i < N; i += kBlock) s_zero[i] = 0.f;
-    __syncthreads();                                        // the first tile reads A before any other barrier (STRUCT)
-
     // u, delta, z and y are addressed as a base that is uniform over the workgroup (the group's first row; it lives in
     // scalar registers and advances by a tile per iteration) plus ONE 32-bit byte offset per lane that never changes
     // (the lane's row inside the group and its sub-block inside a tile): four 64-bit pointers per lane would not fit the
@@ -813,8 +913,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     const bool z_on = z_grp != nullptr;
     const float* wsB = (K < 16 ? a.ws_B8 : a.ws_B) + (int64_t)b * N * a.Lpad;    // each kind of row has its own order of B / C
     const float* wsC = (K < 16 ? a.ws_C8 : a.ws_C) + (int64_t)b * N * a.Lpad;
-    const float bias = (a.dbias && active) ? a.dbias[d] : 0.f;
-    const float Dd = (a.Dv && active && half == 0) ? a.Dv[d] : 0.f;      // the skip term enters once per channel
+    const float bias = first.bias, Dd = first.Dd;
     const bool sp = a.softplus != 0;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // uniform: addresses built from it stay in scalar registers
@@ -866,7 +965,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     // The gate of a partial tile comes with the tile where registers allow: a short sequence is that tile alone, and a request in its
     // last group of states is a trip to memory with little beside it (binary32, 64 rows of 1 step at chunk 16: 10.0 -> 9.3 us).
     constexpr bool kGateFirst = !DIRECT && K < 16;
-    Raw<T, K> u_nx, d_nx;
+    Raw<T, K> u_nx = first.u, d_nx = first.delta;           // (direct launches have the first tile's)
     bool have_nx = false;                                   // uniform over the workgroup
     GHv cin_nx, A2_nx;
     if constexpr (DIRECT) {
@@ -908,7 +1007,14 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         }
         float dl[K], du[K], yv[K];
         Raw<T, K> z_raw;                                    // the gate is fetched with the tile and used after the last state
-        if (FULL && kTileAhead && have_nx) {                // fetched one tile ago
+        if (kTileAhead && (DIRECT || (FULL && have_nx))) {  // fetched one tile ago
+            if constexpr (!FULL) {
+                if (in_last) {
+                    tail.place(u_nx);
+                    tail.place(d_nx);
+                }
+                tail.mask(u_nx);
+            }
             widen<T, K>(d_nx, dl);
             widen<T, K>(u_nx, du);
         } else {
@@ -1145,7 +1251,17 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
         }
     };
     for (int64_t tau = 0; tau < nfull; ++tau) walk_tile(std::true_type{}, tau);
-    if (nfull < ntiles) walk_tile(std::false_type{}, nfull);
+    if (nfull < ntiles) {
+        if constexpr (DIRECT && kTileAhead) {
+            if (nfull > 0) {
+                const int64_t t0 = nfull * CHUNK + (int64_t)j * K;
+                const int64_t back = t0 + K > L && (t0 >= L || (b == (int)gridDim.y - 1 && d0 + rl == a.D - 1)) ? L - K - t0 : 0;
+                u_nx = load_full<T, K>(at(u_grp + nfull * CHUNK) + back);
+                d_nx = load_full<T, K>(at(dl_grp + nfull * CHUNK) + back);
+            }
+        }
+        walk_tile(std::false_type{}, nfull);
+    }
 
     // tiles wholly beyond the sequence: y is written as zero
     if (active && half == 0) {
@@ -1179,20 +1295,10 @@ __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const
     const int rows_full = kChannels < a.rows_cap ? kChannels : a.rows_cap;
     for (int64_t d0 = d_first + wg * rows_full; d0 < d_end; d0 += nwg * rows_full) {   // uniform over the workgroup
         const int rows = d_end - d0 < rows_full ? (int)(d_end - d0) : rows_full;     // the range's last group may be short
-        bool structured = false;
-        if constexpr (sizeof(T) == 2) {                      // fp32 storage keeps the one-exponential-per-state path
-            if (a.allow_structured) {
-                int ok = 1;
-                for (int i = threadIdx.x; i < rows * a.N; i += kBlock) {
-                    const int r = i / a.N, n = i - r * a.N;
-                    const int64_t dd = d0 + r;
-                    if (dd < a.D) ok &= a.A[dd * a.N + n] == (float)(n + 1) * a.A[dd * a.N];
-                }
-                structured = __syncthreads_and(ok) != 0;
-            }
-        }
-        if (structured) scan_group<T, K, CHUNK, true, SPLIT, W, DIRECT>(a, s_mem, rows, (int)d0);
-        else scan_group<T, K, CHUNK, false, SPLIT, W, DIRECT>(a, s_mem, rows, (int)d0);
+        FirstTile<T, K> first;
+        const bool structured = start_group<T, K, CHUNK, SPLIT, DIRECT>(a, s_mem, rows, (int)d0, first);
+        if (sizeof(T) == 2 && structured) scan_group<T, K, CHUNK, true, SPLIT, W, DIRECT>(a, s_mem, rows, (int)d0, first);
+        else scan_group<T, K, CHUNK, false, SPLIT, W, DIRECT>(a, s_mem, rows, (int)d0, first);
         __syncthreads();                                     // the LDS arrays are set up afresh for the next group
     }
 }
@@ -1251,7 +1357,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_ta
     extern __shared__ __align__(16) float s_mem[];
     constexpr int W = waves_target<T, K, CHUNK, DIRECT>();
     if constexpr (split_exists<K, CHUNK, DIRECT>()) {
-        if (a.split) {
+        if (a.host.split) {
             scan_rows<T, K, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
             return;
         }
@@ -1266,13 +1372,22 @@ template <int CHUNK> __host__ __device__ inline int rows_of(int K, int rows_cap,
     return rows < rows_cap ? rows : rows_cap;
 }
 
-// Workgroup `wg` of `nwg` takes its share of one sequence's channels: those below d16 with 16 steps per lane (the first
-// g16 workgroups), the others with 8.  With a grid sized for exactly these two kinds every workgroup has one row group;
-// any other grid is still correct (row groups are taken grid-stride within each kind).
+// A workgroup takes its share of one sequence's channels: the first g16 those below d16 with 16 steps per lane, the others the
+// rest with 8 or 4.  With a grid sized for exactly these two kinds every workgroup has one row group;
+// any other grid is still correct (row groups are taken grid-stride within each kind).  Direct launches have one kind of row, a
+// geometry for each tile.
 template <typename T, int CHUNK, int W, bool DIRECT>
-__device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, const int64_t d16, const int klo, const int split)
+__device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, const RowPlan& plan)
 {
-    if (split) {                                                 // one kind of row, two rows per channel
+    const int d16 = plan.d16, klo = plan.klo;
+    if constexpr (DIRECT) {
+        constexpr int K = CHUNK == 1024 ? 16 : (CHUNK == 512 ? 8 : 4);
+        static_assert(geometry_exists<K, CHUNK, true>() && split_exists<K, CHUNK, true>(), "the geometry of direct launches");
+        if (plan.split) scan_rows<T, K, CHUNK, true, W, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+        else scan_rows<T, K, CHUNK, false, W, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+        return;
+    }
+    if (plan.split) {                                            // one kind of row, two rows per channel
         if (d16 >= a.D) {
             if constexpr (split_exists<16, CHUNK, DIRECT>()) scan_rows<T, 16, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         } else if (klo == 8) {
@@ -1282,17 +1397,7 @@ __device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, co
         }
         return;
     }
-    const int rows16 = rows_of<CHUNK>(16, a.rows_cap);
-    const int64_t n16 = (d16 + rows16 - 1) / rows16;
-    const int64_t nwg = gridDim.x;
-    const int rows8 = rows_of<CHUNK>(klo, a.rows_cap);
-    const int64_t n8 = (a.D - d16 + rows8 - 1) / rows8;
-    int64_t g16 = n16;                                           // workgroups of the 16-step kind
-    if (n16 + n8 != nwg) {                                       // a grid sized for another chunk: share it in proportion
-        g16 = n8 == 0 ? nwg : (n16 == 0 ? 0 : (nwg * n16 + (n16 + n8) / 2) / (n16 + n8));
-        if (n16 > 0 && g16 < 1) g16 = 1;
-        if (n8 > 0 && g16 > nwg - 1) g16 = nwg - 1;
-    }
+    const int64_t nwg = gridDim.x, g16 = plan.g16;
     const int64_t wg = (int64_t)blockIdx.x - g16;
     if ((int64_t)blockIdx.x < g16) {
         if constexpr (geometry_exists<16, CHUNK, DIRECT>()) scan_rows<T, 16, CHUNK, false, W, DIRECT>(a, s_mem, 0, d16, blockIdx.x, g16);
@@ -1308,7 +1413,9 @@ template <typename T, int CHUNK>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_scan_mix(const ScanArgs a)
 {
     extern __shared__ __align__(16) float s_mem[];
-    scan_by_kind<T, CHUNK, 3, false>(a, s_mem, a.d16, a.klo, 0);
+    RowPlan plan = a.host;
+    plan.split = 0;                                              // (two kinds of rows)
+    scan_by_kind<T, CHUNK, 3, false>(a, s_mem, plan);
 }
 
 // Per-sequence chunk read from device memory: every geometry of the launch's kind in one kernel, selected per workgroup.
@@ -1323,12 +1430,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W))) voi
         const int n = a.route.nh * corey_range::kParts * a.route.K;
         for (int i = threadIdx.x; i < n; i += kBlock) a.route.parts[i] = 0u;
     }
-    const int64_t d16 = plan_d16(gridDim.y, a.D, chunk, a.rows_cap);
-    const int klo = plan_klo(gridDim.y, a.D, chunk, d16);
-    const int split = plan_split(gridDim.y, a.D, a.N, chunk, d16, klo, a.allow_split);
 #define COREY_CASE(C)                                                                       \
     case C:                                                                                 \
-        scan_by_kind<T, C, W, DIRECT>(a, s_mem, d16, klo, split);                           \
+        scan_by_kind<T, C, W, DIRECT>(a, s_mem, a.plans.get(C));                           \
         break;
     switch (tile_of(chunk, a.rows_total)) {
         COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
@@ -1370,59 +1474,77 @@ inline void geometry(int64_t nrows, int64_t N, int rows_cap, int split, int64_t&
 
 // Grid and LDS of a launch whose channels below d16 take 16 steps per lane and the others klo.
 template <int CHUNK, bool DIRECT>
-inline void launch_geometry(const LaunchPlan& p, int rows_cap, int64_t d16, int klo, int split, int64_t& gx, size_t& lds)
+inline void launch_geometry(const LaunchPlan& p, int rows_cap, const RowPlan& r, int64_t& gx, size_t& lds)
 {
     gx = 0;
     lds = 0;
     int64_t g = 0;
     size_t l = 0;
-    if (d16 > 0) {
-        geometry<16, CHUNK, DIRECT>(d16, p.N, rows_cap, split, g, l);
+    if (r.d16 > 0) {
+        geometry<16, CHUNK, DIRECT>(r.d16, p.N, rows_cap, r.split, g, l);
         gx += g;
         lds = l > lds ? l : lds;
     }
-    if (d16 < p.D) {
-        if (klo == 8) geometry<8, CHUNK, DIRECT>(p.D - d16, p.N, rows_cap, split, g, l);
-        else geometry<4, CHUNK, DIRECT>(p.D - d16, p.N, rows_cap, split, g, l);
+    if (r.d16 < p.D) {
+        if (r.klo == 8) geometry<8, CHUNK, DIRECT>(p.D - r.d16, p.N, rows_cap, r.split, g, l);
+        else geometry<4, CHUNK, DIRECT>(p.D - r.d16, p.N, rows_cap, r.split, g, l);
         gx += g;
         lds = l > lds ? l : lds;
     }
 }
 
+// Workgroups, of nwg, that take the channels below d16.
+template <int CHUNK> inline int32_t share16(const LaunchPlan& p, int rows_cap, const RowPlan& r, int64_t nwg)
+{
+    const int rows16 = rows_of<CHUNK>(16, rows_cap), rows8 = rows_of<CHUNK>(r.klo, rows_cap);
+    const int64_t n16 = (r.d16 + rows16 - 1) / rows16, n8 = (p.D - r.d16 + rows8 - 1) / rows8;
+    int64_t g16 = n16;
+    if (n16 + n8 != nwg) {                                       // a grid sized for another chunk: share it in proportion
+        g16 = n8 == 0 ? nwg : (n16 == 0 ? 0 : (nwg * n16 + (n16 + n8) / 2) / (n16 + n8));
+        if (n16 > 0 && g16 < 1) g16 = 1;
+        if (n8 > 0 && g16 > nwg - 1) g16 = nwg - 1;
+    }
+    return (int32_t)g16;
+}
+
 template <typename T, bool DIRECT>
-inline void launch_kernels(const ScanArgs& a, const LaunchPlan& p)
+inline void launch_kernels(ScanArgs& a, const LaunchPlan& p)
 {
     int64_t gx = 0, g;
     size_t lds = 0, l;
+#define COREY_TILES(p, c)                                                                   \
+    switch (tile_of(c, (p).B * (p).D)) {                                                    \
+        COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)   \
+    default: break;                                                                         \
+    }
     if (p.routed) {
         // grid from the host's chunk (the caller's hint: workgroups take row groups grid-stride, so any grid is correct),
-        // LDS for the largest need of any geometry the device-side plan can pick
+        // LDS for the largest need of any geometry the plans hold
         for (int c = COREY_MIN_CHUNK; c <= COREY_MAX_CHUNK; c *= 2) {
-            const int64_t d16_c = plan_d16(p.B, p.D, c, a.rows_cap);
-            const int klo_c = plan_klo(p.B, p.D, c, d16_c);
-            const int split_c = plan_split(p.B, p.D, (int)p.N, c, d16_c, klo_c, a.allow_split);
             g = 0;
             l = 0;
 #define COREY_CASE(C)                                                                       \
     case C:                                                                                 \
-        launch_geometry<C, DIRECT>(p, a.rows_cap, d16_c, klo_c, split_c, g, l);             \
+        launch_geometry<C, DIRECT>(p, a.rows_cap, a.plans.get(C), g, l);          \
         break;
-            switch (tile_of(c, p.B * p.D)) {
-                COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
-            default: break;
-            }
+            COREY_TILES(p, c)
 #undef COREY_CASE
             lds = l > lds ? l : lds;
             if (c == p.chunk) gx = g;
         }
-        if (gx < 2) gx = 2;     // two kinds of rows decided on the device need a workgroup for each kind (a surplus one leaves at once)
+        if (gx < 2) gx = 2;     // two kinds of rows chosen by the chunk in memory need a workgroup for each kind (a surplus one leaves at once)
+        if constexpr (!DIRECT) {
+#define COREY_CASE(C) a.plans.g16[plan_index(C)] = share16<C>(p, a.rows_cap, a.plans.get(C), gx);
+            COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
+#undef COREY_CASE
+        }
         const dim3 grid((unsigned)gx, (unsigned)p.B), block(kBlock);
         if constexpr (DIRECT) {
             k_scan_any<T, waves_target<T, 16, 1024, true>(), true><<<grid, block, lds, p.stream>>>(a);
         } else {
             // registers for the long tiles: three waves per SIMD if those give two kinds of rows, or if the sequences' lengths
             // differ (the longest one's waves, a part of the launch, decide: 233 us against 254 for the padded pair); else four
-            const int64_t d16_512 = plan_d16(p.B, p.D, 512, a.rows_cap);
+            const int64_t d16_512 = a.plans.get(512).d16;
             if ((d16_512 > 0 && d16_512 < p.D) || a.seqlens) k_scan_any<T, 3, false><<<grid, block, lds, p.stream>>>(a);
             else k_scan_any<T, 4, false><<<grid, block, lds, p.stream>>>(a);
         }
@@ -1431,26 +1553,26 @@ inline void launch_kernels(const ScanArgs& a, const LaunchPlan& p)
     const dim3 block(kBlock);
 #define COREY_LAUNCH(K, C)                                                                  \
     if constexpr (geometry_exists<K, C, DIRECT>()) k_scan<T, K, C, DIRECT><<<dim3((unsigned)gx, (unsigned)p.B), block, lds, p.stream>>>(a)
+    RowPlan& r = a.host;
 #define COREY_CASE(C)                                                                       \
     case C:                                                                                 \
-        launch_geometry<C, DIRECT>(p, a.rows_cap, a.d16, a.klo, a.split, gx, lds);           \
-        if (a.d16 >= p.D) { COREY_LAUNCH(16, C); }                                          \
-        else if (a.d16 > 0) {                                                               \
+        launch_geometry<C, DIRECT>(p, a.rows_cap, r, gx, lds);                               \
+        r.g16 = share16<C>(p, a.rows_cap, r, gx);                                            \
+        if (r.d16 >= p.D) { COREY_LAUNCH(16, C); }                                          \
+        else if (r.d16 > 0) {                                                               \
             if constexpr (!DIRECT && C <= 512) k_scan_mix<T, C><<<dim3((unsigned)gx, (unsigned)p.B), block, lds, p.stream>>>(a);   \
         }                                                                                   \
-        else if (a.klo == 8) { COREY_LAUNCH(8, C); }                                        \
+        else if (r.klo == 8) { COREY_LAUNCH(8, C); }                                        \
         else { COREY_LAUNCH(4, C); }                                                        \
         break;
-    switch (tile_of(p.chunk, p.B * p.D)) {
-        COREY_CASE(16) COREY_CASE(32) COREY_CASE(64) COREY_CASE(128) COREY_CASE(256) COREY_CASE(512) COREY_CASE(1024)
-    default: break;
-    }
+    COREY_TILES(p, p.chunk)
 #undef COREY_CASE
 #undef COREY_LAUNCH
+#undef COREY_TILES
 }
 
 template <typename T>
-inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
+inline void launch_scan(ScanArgs& a, const LaunchPlan& p)
 {
     if (a.direct) {
         launch_kernels<T, true>(a, p);
@@ -1461,7 +1583,7 @@ inline void launch_scan(const ScanArgs& a, const LaunchPlan& p)
     rb = rb < 1 ? 1 : (rb > 2048 ? 2048 : rb);
     k_relayout_bc<T><<<dim3((unsigned)rb, (unsigned)p.B), dim3(256), 0, p.stream>>>(
         static_cast<const T*>(a.Bm), static_cast<const T*>(a.Cm), a.ws_B, a.ws_C, a.ws_B8, a.ws_C8, a.seqlens, a.chunks_dev,
-        a.one_chunk, p.chunk, a.d16, a.klo, p.B, p.D, a.rows_cap, (int)p.N, a.Np, a.L, a.Lpad, a.route);
+        a.one_chunk, p.chunk, a.plans, p.B, p.D, (int)p.N, a.Np, a.L, a.Lpad, a.route);
     launch_kernels<T, false>(a, p);
 }
 
