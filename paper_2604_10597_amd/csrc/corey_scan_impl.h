@@ -1059,7 +1059,31 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
             decay_burst<K, true, true>(dl, P_base);                      // from here on dl holds the decay of state 0
         }
 
-        for (int n0 = 0; n0 < NH; n0 += GH) {                 // n0: number inside the row of the group's first state
+        // DIRECT, but for long tiles of binary32: the gate and the next tile of a full one are requested a group before the last, behind that
+        // group's request for the next states.  Loads return in order, so requested ahead of those, or in the last group, their trip to
+        // memory stood between a wave and its next states or its gate.  Routed layers, bf16, 1536 rows of 2048 steps 37.2 -> 36.0 us, 2048 of
+        // 977 33.0 -> 32.3, 1024 fp16 rows of 4096 at chunk 512 28.7 -> 28.5; bf16 scans of 64 to 3072 rows at chunks 16 to 64 take 0.90 to
+        // 0.95 of the time, binary32 ones 0.93 to 0.96 (at chunks 256 and 512, where their words are many, up to 1.06: not there).
+        // Unconditional, so that the wait for the states can leave them out: without a gate or a next tile they repeat what is there.
+        auto request_tile = [&] __attribute__((always_inline)) {
+            z_raw = load_full<T, K>(at((z_on ? z_grp : u_grp) + tile));
+            if constexpr (kTileAhead) {
+                const int64_t next = tau + 1 < nfull ? tile + CHUNK : tile;
+                u_nx = load_full<T, K>(at(u_grp + next));
+                d_nx = load_full<T, K>(at(dl_grp + next));
+            }
+        };
+        constexpr bool kAhead = DIRECT && FULL && (sizeof(T) == 2 || CHUNK <= 128);    // (takes the last two groups out of their loop)
+#ifndef COREY_SCAN_STAGED
+        auto groups = [&](auto ask_c, const int n_from, const int n_to) __attribute__((always_inline)) {
+#else
+        // (a unit of staged kernels alone keeps the plain loop: the same code as a function had registers and order another way, routed
+        // binary32 scans of 1536 rows 1 to 4 % slower)
+        const std::false_type ask_c;
+        const int n_from = 0, n_to = NH;
+        {
+#endif
+        for (int n0 = n_from; n0 < n_to; n0 += GH) {          // n0: number inside the row of the group's first state
             const float* s_B = s_stage + buf * 2 * STAGE;
             const float* s_C = s_B + STAGE;
             // A and the carried state of the group's states (the latter was written a tile ago by this wave's own lanes).  Staged:
@@ -1082,7 +1106,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 if (!last_group) stage_group(tau, n0 + GH, s_stage + (buf ^ 1) * 2 * STAGE);
                 else if (tau + 1 < ntiles) stage_group(tau + 1, 0, s_stage + (buf ^ 1) * 2 * STAGE);
             }
-            if (last_group) {                               // the gate, and the next tile if it is a full one, arrive while it is computed
+            if (!kAhead && last_group) {                    // the gate, and the next tile if it is a full one, arrive while it is computed
                 if constexpr (!kGateFirst || FULL)
                     if (z_on) z_raw = load_row(z_grp);
                 if constexpr (kTileAhead) {
@@ -1115,6 +1139,10 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                     // (after the row's last full tile this reads a set nobody uses: cheaper than a branch among the states)
                     const bool more = n0 + nl + Q < NH;
                     fetch(full_c, more ? n0 + nl + Q : 0, FULL ? (more || tau + 1 >= nfull ? tile : tile + CHUNK) : 0);
+                    if (decltype(ask_c)::value && nl == 0) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        request_tile();
+                    }
                 } else {
 #pragma unroll
                     for (int s = 0; s < Q; ++s)
@@ -1220,6 +1248,22 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
                 carry_fence();
             }
         }
+#ifndef COREY_SCAN_STAGED
+        };
+        if constexpr (kAhead) {
+            if (NH > GH) {
+                groups(std::false_type{}, 0, NH - 2 * GH);
+                groups(std::true_type{}, NH - 2 * GH, NH - GH);
+            } else {
+                request_tile();
+            }
+            groups(std::false_type{}, NH - GH, NH);
+        } else {
+            groups(std::false_type{}, 0, NH);
+        }
+#else
+        }
+#endif
 
         if constexpr (SPLIT) {                              // the second row of a channel hands over its part of the sum over states
             // (DIRECT: two buffers in turn, because nothing else separates these reads from the next tile's writes)

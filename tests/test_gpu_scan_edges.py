@@ -107,3 +107,23 @@ def test_the_longest_chunk_is_launched_as_the_tiles_it_is_walked_in(dtype, B, D,
     for dev in (None, torch.full((B,), 2048, dtype=torch.int32, device="cuda")):
         got = _scan(d, 512 if dev is not None else 2048, chunks_dev=dev)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
+@pytest.mark.parametrize("N", [4, 8, 12])
+@pytest.mark.parametrize("gate", [True, False])
+def test_tiles_requested_ahead(N, gate, dtype):
+    """Direct launches ask for the gate and the next tile a group of states before the last: rows of one group, two and three, of one
+    full tile, several and a partial one behind them, with and without a gate."""
+    for L in (64, 128, 512, 1024, 1100):
+        cfg = wl.Config("edges_ahead", 2, 5, N, L, dtype, 16, (), seed=4400 + L + N)
+        w = wl.make(cfg, a_kind="random", with_h0=True)
+        d = upload(w)
+        if not gate:
+            d["z"] = None
+        y_ref, s_ref = oracle_scan(w, use_z=gate)
+        for chunk in (16, 64, 128, 256, 512, 1024):
+            for whole in (False, True):
+                y, s = _scan(d, chunk, whole_rows=whole)
+                check_y(y_to_f64(y), y_ref, cfg, f"y L {L} chunk {chunk}")
+                assert_close(s.cpu().numpy(), s_ref, fp32_rtol(L), f"state L {L} chunk {chunk}")
