@@ -1,6 +1,5 @@
 // k_scan_any for fp32 storage with registers for 3 waves per SIMD.
 #define COREY_SCAN_ANY_HERE
-#define COREY_SCAN_STAGED
 #include "corey_scan_impl.h"
 
 namespace corey_scan {

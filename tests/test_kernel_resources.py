@@ -65,3 +65,14 @@ def test_binary32_staging_begins_at_the_start_of_lds(kernels):
     """The buffers that B and C are copied into are the first words of the dynamic LDS; anything static comes before them."""
     for name, k in _scan_kernels(kernels, "f").items():
         assert k[".group_segment_fixed_size"] == 0, name
+
+
+def test_a_scan_kernel_has_one_body():
+    """The units instantiate parts of the same templates: nothing but where k_scan_any is instantiated may depend on the unit, or one
+    name has two bodies."""
+    for name in sorted(os.listdir(build.CSRC)):
+        if name.startswith("corey_scan"):
+            with open(os.path.join(build.CSRC, name)) as f:
+                text = f.read()
+            used = set(re.findall(r"^#\s*(?:ifdef|ifndef|if|elif)\s+(?:!?defined\W*)?(\w+)", text, re.M))
+            assert used <= {"COREY_SCAN_ANY_HERE", name.upper().replace(".", "_")}, (name, used)
