@@ -1191,9 +1191,9 @@ __device__ __forceinline__ void scan_rows(const ScanArgs& a, float* s_mem, const
 // In binary32 a lane of 8 or 16 steps has twice the bytes in flight: two waves per SIMD fit, and the words of a 16-step lane are 64
 // bytes apart.  Beyond 1024 rows those launches read directly only where they know that all of their waves fit (4096 steps,
 // staged and direct, us: chunk 512, 1536 rows in pairs of rows 50.4 and 58.4, 2048 rows one each 62.3 and 55.0, 2560 rows 67.3 and
-// 81.4; chunk 1024, 1536 rows 46.1 and 64.8, 2048 53.6 and 74.9, 3072 66.1 and 110; chunk 256, lanes of 4 steps, four waves per SIMD,
-// 1536 rows 56 and 52.5, 3072 75.8 and 76.7, 1000 steps 26.9 and 24.8); with the chunk in device memory they are staged (chunk
-// 256 76.5 and 100 at 3072 rows, 1024 60 and 77 at 2048; 512 62.6 and 56 there).
+// 81.4; chunk 1024, 1536 rows 46.1 and 64.8, 2048 53.6 and 74.9, 3072 66.1 and 110; chunk 256, lanes of 4 steps, a wave a row and three
+// waves per SIMD (waves_target), 1536 rows 57.2 and 49.0, 3072 77.6 and 73.8, of 1000 steps 27.9 and 25.1); with the chunk in device
+// memory they are staged (chunk 256 76.5 and 100 at 3072 rows, 1024 60 and 77 at 2048; 512 62.6 and 56 there).
 constexpr int64_t kDirectRows = 3072, kDirectRowsF32 = 1024, kDirectWavesF32 = 2048;
 inline bool direct_launch(int64_t B, int64_t D, int64_t N, int64_t L, bool f32, bool routed, int64_t d16, int klo, int split)
 {
@@ -1223,11 +1223,11 @@ template <int K, int CHUNK, bool DIRECT> constexpr bool split_exists()
 // Plain instructions of two waves pair only across the two halves a SIMD's waves are dealt to, so 4 waves (2 + 2) use the issue
 // slots better than 3, but with 128 registers a 16-step lane cannot hold C ahead of its use.  Measured: 4096 + 1024 rows of
 // 16384 steps at chunk 512 (a mixed launch: 3 waves per SIMD whatever the budget) 329 us with 168 registers, 347 with 128; 8192
-// rows of 4096 (4 waves per SIMD) 143 and 135.  Direct launches have at most 3 waves per SIMD (binary32 runs of 16 steps need 256
-// registers).
+// rows of 4096 (4 waves per SIMD) 143 and 135.  Direct launches have at most 3 waves per SIMD (binary32 runs of 8 and 16 steps need
+// 256 registers, and the dispatch sends them only launches of 2).
 template <typename T, int K, int CHUNK, bool DIRECT> constexpr int waves_target()
 {
-    if (DIRECT) return sizeof(T) == 4 ? 2 : 3;
+    if (DIRECT) return sizeof(T) == 4 && K != 4 ? 2 : 3;
     return K == 16 && CHUNK > 512 ? 3 : 4;
 }
 

@@ -76,3 +76,13 @@ def test_a_scan_kernel_has_one_body():
                 text = f.read()
             used = set(re.findall(r"^#\s*(?:ifdef|ifndef|if|elif)\s+(?:!?defined\W*)?(\w+)", text, re.M))
             assert used <= {"COREY_SCAN_ANY_HERE", name.upper().replace(".", "_")}, (name, used)
+
+
+@pytest.mark.parametrize("storage, steps, waves", [("f", 4, 3), ("f", 8, 2), ("f", 16, 2), ("t", 4, 3), ("t", 8, 3), ("t", 16, 3),
+                                                   ("DF16_", 4, 3), ("DF16_", 8, 3), ("DF16_", 16, 3)])
+def test_direct_kernels_fit_the_waves_they_are_launched_for(kernels, storage, steps, waves):
+    """A SIMD's 512 registers, in blocks of 8 a wave: launches that read B and C directly go out with as many waves as these hold."""
+    mine = [k for n, k in kernels.items() if re.match(rf"_ZN10corey_scan6k_scanI{storage}Li{steps}ELi\d+ELb1E", n)]
+    assert mine
+    for k in mine:
+        assert k[".vgpr_count"] <= 512 // waves // 8 * 8, k[".name"]
