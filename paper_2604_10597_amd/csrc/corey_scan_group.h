@@ -36,7 +36,7 @@ if (!kAhead && last_group) {                    // the gate, and the next tile i
         if (FULL && tau + 1 < nfull) {
             u_nx = load_full<T, K>(at(u_grp + tile + CHUNK));
             d_nx = load_full<T, K>(at(dl_grp + tile + CHUNK));
-            have_nx = true;
+            if constexpr (!DIRECT) have_nx = true;
         }
     }
 }

@@ -90,7 +90,7 @@ template <int K, int CHUNK> struct Geo {
 // eight: the two kinds of workgroups then fill the SIMDs evenly (e.g. 5120 rows at chunk 512: 4096 rows as two
 // 16-step waves per SIMD plus 1024 rows as one 8-step wave, 10 % faster than either geometry alone).
 // plan_d16 returns d16: channels [0, d16) of every sequence take 16 steps per lane, [d16, D) take 8; 0 and D are the
-// pure launches.  It runs on the host (known chunk) and on the device (chunk read from memory) with the same inputs.
+// pure launches.  It runs on the host, for every tile that a chunk read from device memory may ask for (Plans).
 inline int64_t plan_d16(int64_t B, int64_t D, int chunk, int rows_cap)
 {
     chunk = tile_of(chunk, B * D);
@@ -618,7 +618,7 @@ struct ScanArgs {
     float* ws_B8;           // the same operands in the order of the 8- or 4-step rows of this launch (ws_B / ws_C: the 16-step ones)
     float* ws_C8;
     RowPlan host;           // of the host chunk
-    Plans plans;            // of any chunk read from device memory
+    Plans plans;            // of every tile if the chunk is read from device memory, else of the host chunk's (for the relayout)
     int32_t direct;         // B and C are read as stored (see kDirectRows); the workspace is not used
     int64_t L, Lpad;
     int64_t rows_total;     // B * D (input of the items-per-lane rule)
@@ -774,20 +774,7 @@ __host__ __device__ constexpr int lds_floats(int rows, int N, bool split, bool d
 }
 
 // ------------------------------------------------------------------------------------------- the scan
-// The rows d0 .. d0 + rows - 1 of sequence blockIdx.y, start to end.
-//
-// STRUCT: every row of the group has A[d, n] = (n + 1) A[d, 0] (the S4D-real initialisation Mamba starts from, and
-// the benchmark's A = -(n + 1)).  Then exp(dl A[d, n]) = exp(dl A[d, 0])^(n + 1): one exponential per time step
-// instead of one per (time step, state), the decay of state n following from that of state n - 1 by one multiply
-// (likewise the sub-block product P).  The chain adds at most n roundings (about (n + 1) 2^-24 relative) to a decay.
-//
-// SPLIT: a channel has two rows of the workgroup (neighbours), the first with states [0, N/2), the second with
-// [N/2, N); `rows` counts channels.  Both do the per-token work; the second hands its partial y to the first through
-// LDS at the end of every tile, and the first adds the skip term, gates and stores.
-// DIRECT: B and C are read where they are, as stored: every lane loads the K values of its steps (one or two 16-byte words per
-// operand and state, a set of states ahead) and widens them, two instructions per value more than from the fp32 copy.  In
-// return there is no staging, no barrier in the loop, and no launch before this one.  Which launches: see kDirectRows.
-// What a lane has of its first tile before the walk begins, as stored.
+// What a lane has before the walk begins: its parameters, and in direct launches of lanes of up to 8 steps its first tile as stored.
 template <typename T, int K> struct FirstTile {
     Raw<T, K> u, delta;
     float bias, Dd;
@@ -798,8 +785,9 @@ template <typename T, int K> struct FirstTile {
 // arrays are there.  (Lane numbers are worked out here and again in the walk: kept for it, they would fill its registers.)
 // With the plan of a routed tile from the host instead of the device, against structure, arrays and first tile one after another: scan
 // of 1024 fp16 rows of 4096 steps at chunk 512 29.7 -> 28.6 us; routed layers, bf16, 1536 rows of 2048 steps 39.5 -> 37.4, 2048 of 977
-// 34.9 -> 33.6, steps of 8192 rows of 4096 170.5 -> 167.1, two padded sequences of 4096 rows 207.1 -> 204.3.  A lane of 16 steps asks
-// for its first tile in the walk: 16 registers kept until then spill there (the first of these layers 41.4 us, the second 34.6).
+// 34.9 -> 33.6, steps of 8192 rows of 4096 170.5 -> 167.1, two padded sequences of 4096 rows 207.1 -> 204.3.  Staged launches and lanes
+// of 16 steps (the first two of these layers) ask for their first tile in the walk: 16 registers kept until then spill there (41.4 us
+// and 34.6).
 template <typename T, int K, int CHUNK, bool SPLIT, bool DIRECT>
 __device__ __forceinline__ bool start_group(const ScanArgs& a, float* s_mem, const int rows, const int d0, FirstTile<T, K>& first)
 {
@@ -850,6 +838,19 @@ __device__ __forceinline__ bool start_group(const ScanArgs& a, float* s_mem, con
     return false;
 }
 
+// The rows d0 .. d0 + rows - 1 of sequence blockIdx.y, start to end.
+//
+// STRUCT: every row of the group has A[d, n] = (n + 1) A[d, 0] (the S4D-real initialisation Mamba starts from, and
+// the benchmark's A = -(n + 1)).  Then exp(dl A[d, n]) = exp(dl A[d, 0])^(n + 1): one exponential per time step
+// instead of one per (time step, state), the decay of state n following from that of state n - 1 by one multiply
+// (likewise the sub-block product P).  The chain adds at most n roundings (about (n + 1) 2^-24 relative) to a decay.
+//
+// SPLIT: a channel has two rows of the workgroup (neighbours), the first with states [0, N/2), the second with
+// [N/2, N); `rows` counts channels.  Both do the per-token work; the second hands its partial y to the first through
+// LDS at the end of every tile, and the first adds the skip term, gates and stores.
+// DIRECT: B and C are read where they are, as stored: every lane loads the K values of its steps (one or two 16-byte words per
+// operand and state, a set of states ahead) and widens them, two instructions per value more than from the fp32 copy.  In
+// return there is no staging, no barrier in the loop, and no launch before this one.  Which launches: see kDirectRows.
 template <typename T, int K, int CHUNK, bool STRUCT, bool SPLIT, int W, bool DIRECT>
 __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, const int rows, const int d0, const FirstTile<T, K>& first)
 {
@@ -969,8 +970,12 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     // The gate of a partial tile comes with the tile where registers allow: a short sequence is that tile alone, and a request in its
     // last group of states is a trip to memory with little beside it (binary32, 64 rows of 1 step at chunk 16: 10.0 -> 9.3 us).
     constexpr bool kGateFirst = !DIRECT && K < 16;
-    Raw<T, K> u_nx = first.u, d_nx = first.delta;           // (direct launches have the first tile's)
-    bool have_nx = false;                                   // uniform over the workgroup
+    Raw<T, K> u_nx, d_nx;
+    if constexpr (DIRECT && kTileAhead) {                   // the first tile's; in the walk always those of the next
+        u_nx = first.u;
+        d_nx = first.delta;
+    }
+    bool have_nx = false;                                   // staged launches: they hold the next tile's; uniform over the workgroup
     GHv cin_nx, A2_nx;
     if constexpr (DIRECT) {
         cin_nx = *reinterpret_cast<const GHv*>(carry_rd);
@@ -1065,9 +1070,9 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
 
         // DIRECT, but for long tiles of binary32: the gate and the next tile of a full one are requested a group before the last, behind that
         // group's request for the next states.  Loads return in order, so requested ahead of those, or in the last group, their trip to
-        // memory stood between a wave and its next states or its gate.  Routed layers, bf16, 1536 rows of 2048 steps 37.2 -> 36.0 us, 2048 of
-        // 977 33.0 -> 32.3, 1024 fp16 rows of 4096 at chunk 512 28.7 -> 28.5; bf16 scans of 64 to 3072 rows at chunks 16 to 64 take 0.90 to
-        // 0.95 of the time, binary32 ones 0.93 to 0.96 (at chunks 256 and 512, where their words are many, up to 1.06: not there).
+        // memory stood between a wave and its next states or its gate.  Scans of 64 to 3072 rows of 33 to 4096 steps at chunks 16 and 64:
+        // 16 bits 0.96 to 0.97 of the time, binary32 0.92 to 0.96; at 256 and 512 the same (binary32 up to 1.06 there: not done); routed to
+        // 1024, where a lane of 16 steps asks for the gate alone, 0.98 (layer of 1536 bf16 rows of 2048 steps 37.2 -> 36.0 us).
         // Unconditional, so that the wait for the states can leave them out: without a gate or a next tile they repeat what is there.
         auto request_tile = [&] __attribute__((always_inline)) {
             z_raw = load_full<T, K>(at((z_on ? z_grp : u_grp) + tile));
@@ -1214,7 +1219,7 @@ template <int K, int CHUNK, bool DIRECT> constexpr bool geometry_exists()
     if (DIRECT) return (K == 16 && CHUNK == 1024) || (K == 8 && CHUNK == 512) || (K == 4 && CHUNK >= 4 && CHUNK <= 256);
     return CHUNK >= K && (K == 16 || (K == 8 && CHUNK <= 512) || (K == 4 && CHUNK <= 256));
 }
-template <int K, int CHUNK, bool DIRECT> constexpr bool split_exists()
+template <int K, int CHUNK> constexpr bool split_exists()
 {
     return (K == 16 && CHUNK == 1024) || (K == 8 && CHUNK == 512) || (K == 4 && CHUNK >= 4 && CHUNK <= 256);
 }
@@ -1237,7 +1242,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(waves_ta
 {
     extern __shared__ __align__(16) float s_mem[];
     constexpr int W = waves_target<T, K, CHUNK, DIRECT>();
-    if constexpr (split_exists<K, CHUNK, DIRECT>()) {
+    if constexpr (split_exists<K, CHUNK>()) {
         if (a.host.split) {
             scan_rows<T, K, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
             return;
@@ -1260,32 +1265,29 @@ template <int CHUNK> __host__ __device__ inline int rows_of(int K, int rows_cap,
 template <typename T, int CHUNK, int W, bool DIRECT>
 __device__ __forceinline__ void scan_by_kind(const ScanArgs& a, float* s_mem, const RowPlan& plan)
 {
-    const int d16 = plan.d16, klo = plan.klo;
     if constexpr (DIRECT) {
         constexpr int K = CHUNK == 1024 ? 16 : (CHUNK == 512 ? 8 : 4);
-        static_assert(geometry_exists<K, CHUNK, true>() && split_exists<K, CHUNK, true>(), "the geometry of direct launches");
+        static_assert(geometry_exists<K, CHUNK, true>() && split_exists<K, CHUNK>(), "the geometry of direct launches");
         if (plan.split) scan_rows<T, K, CHUNK, true, W, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         else scan_rows<T, K, CHUNK, false, W, true>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
-        return;
-    }
-    if (plan.split) {                                            // one kind of row, two rows per channel
-        if (d16 >= a.D) {
-            if constexpr (split_exists<16, CHUNK, DIRECT>()) scan_rows<T, 16, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
-        } else if (klo == 8) {
-            if constexpr (split_exists<8, CHUNK, DIRECT>()) scan_rows<T, 8, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+    } else if (plan.split) {                                     // one kind of row, two rows per channel
+        if (plan.d16 >= a.D) {
+            if constexpr (split_exists<16, CHUNK>()) scan_rows<T, 16, CHUNK, true, W, false>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+        } else if (plan.klo == 8) {
+            if constexpr (split_exists<8, CHUNK>()) scan_rows<T, 8, CHUNK, true, W, false>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         } else {
-            if constexpr (split_exists<4, CHUNK, DIRECT>()) scan_rows<T, 4, CHUNK, true, W, DIRECT>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
+            if constexpr (split_exists<4, CHUNK>()) scan_rows<T, 4, CHUNK, true, W, false>(a, s_mem, 0, a.D, blockIdx.x, gridDim.x);
         }
-        return;
-    }
-    const int64_t nwg = gridDim.x, g16 = plan.g16;
-    const int64_t wg = (int64_t)blockIdx.x - g16;
-    if ((int64_t)blockIdx.x < g16) {
-        if constexpr (geometry_exists<16, CHUNK, DIRECT>()) scan_rows<T, 16, CHUNK, false, W, DIRECT>(a, s_mem, 0, d16, blockIdx.x, g16);
-    } else if (klo == 8) {
-        if constexpr (geometry_exists<8, CHUNK, DIRECT>()) scan_rows<T, 8, CHUNK, false, W, DIRECT>(a, s_mem, d16, a.D, wg, nwg - g16);
     } else {
-        if constexpr (geometry_exists<4, CHUNK, DIRECT>()) scan_rows<T, 4, CHUNK, false, W, DIRECT>(a, s_mem, d16, a.D, wg, nwg - g16);
+        const int64_t nwg = gridDim.x, g16 = plan.g16;
+        const int64_t wg = (int64_t)blockIdx.x - g16;
+        if ((int64_t)blockIdx.x < g16) {
+            if constexpr (geometry_exists<16, CHUNK, false>()) scan_rows<T, 16, CHUNK, false, W, false>(a, s_mem, 0, plan.d16, blockIdx.x, g16);
+        } else if (plan.klo == 8) {
+            if constexpr (geometry_exists<8, CHUNK, false>()) scan_rows<T, 8, CHUNK, false, W, false>(a, s_mem, plan.d16, a.D, wg, nwg - g16);
+        } else {
+            if constexpr (geometry_exists<4, CHUNK, false>()) scan_rows<T, 4, CHUNK, false, W, false>(a, s_mem, plan.d16, a.D, wg, nwg - g16);
+        }
     }
 }
 
