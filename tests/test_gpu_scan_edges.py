@@ -127,3 +127,29 @@ def test_tiles_requested_ahead(N, gate, dtype):
                 y, s = _scan(d, chunk, whole_rows=whole)
                 check_y(y_to_f64(y), y_ref, cfg, f"y L {L} chunk {chunk}")
                 assert_close(s.cpu().numpy(), s_ref, fp32_rtol(L), f"state L {L} chunk {chunk}")
+
+
+@pytest.mark.parametrize("a_kind", ["mamba", "random"])
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
+@pytest.mark.parametrize("N", [4, 8, 12])
+def test_tiles_requested_ahead_of_routed_and_padded_rows(N, dtype, a_kind):
+    """The same loops with the chunk in device memory (one for all sequences, one each, neither the host's), with the structured A, and
+    with sequences that end inside a tile behind full ones in the middle of their rows; the tensor's last row ends beside a lane's run."""
+    for lens in ((1101, 530, 1024), (530, 1024, 1101), (67, 33, 64)):
+        L = max(lens)
+        cfg = wl.Config("edges_ahead_routed", 3, 5, N, L, dtype, 16, (), seqlens=lens, seed=4500 + L + N)
+        w = wl.make(cfg, a_kind=a_kind, with_h0=True)
+        d = upload(w)
+        for b, n in enumerate(lens):                        # what lies behind a sequence's end is read into no result
+            for name in ("u", "delta", "z", "B", "C"):
+                d[name][b, :, n:] = float("nan")
+        y_ref, s_ref = oracle_scan(w)
+        routes = [(c, None) for c in (16, 64, 256, 512, 1024)]
+        routes += [(512 if c != 512 else 64, (c,) * 3) for c in (16, 64, 256, 512, 1024, 2048)] + [(256, (64, 1024, 512)), (16, (2048, 16, 128))]
+        for chunk, dev in routes:
+            dev_t = None if dev is None else torch.tensor(dev, dtype=torch.int32, device="cuda")
+            for whole in (False, True):
+                y, s = _scan(d, chunk, chunks_dev=dev_t, whole_rows=whole)
+                what = f"lens {lens} chunk {chunk} routed {dev} whole {whole}"
+                check_y(y_to_f64(y), y_ref, cfg, "y " + what)
+                assert_close(s.cpu().numpy(), s_ref, fp32_rtol(L), "state " + what)
