@@ -865,7 +865,7 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     // 128 and two states spill: in binary32, whose stored values take twice the room, inside the loop (4096 rows of 4096 steps at
     // chunk 512: 107.8 us, with one 97.2; at chunk 256 115.4 and 106.7); in 16 bits at tiles of 512, where the spills are at a tile's
     // ends (176 bytes a lane; 4096 rows of 1000 steps 31.4 and 28.3, of 4096 80.5 and 78.7; 2560 rows of 7 steps 20.4 and 17.5), while at 256
-    // two states are worth theirs (96 bytes; 4096 rows of 4096 steps 85.3 and 87.6, of 1000 32.8 and 30.0).
+    // two states are worth theirs (68 to 72 bytes; 4096 rows of 4096 steps 85.3 and 87.6, of 1000 32.8 and 30.0).
     constexpr bool kTight = K == 8 && W == 4 && !DIRECT && (sizeof(T) == 4 || CHUNK == 512);
     constexpr int Q = K < 16 && GH > 1 && !kTight ? 2 : 1;
     static_assert(GH % Q == 0, "whole sets of states");
