@@ -886,15 +886,17 @@ __device__ __forceinline__ void scan_group(const ScanArgs& a, float* s_mem, cons
     const bool active = ch_local < rows && d < a.D;
     const int rl = active ? ch_local : 0;                   // safe LDS row for idle lanes
     int N = a.Np;                                           // padded state count: whole staging groups, no tail group
-    int64_t L = a.L;
-    // The 4-step binary32 kernels: opaque, so that what follows from them for the walk is worked out here.  Worked out ahead of the loop
+    // The 4-step binary32 kernels: opaque, so that what follows from N and L for the walk is worked out here.  Worked out ahead of the loop
     // over the groups of rows, it filled the scalar registers before the start's first request: sequences of one tile, against the start in
     // several trips, took 1.05 times as long at chunk 64 and 1.04 at 128, with this 1.02 and 1.01; of several tiles 0.94 and 0.96, with
     // this 0.93 and 0.94.
-    if constexpr (sizeof(T) == 4 && DIRECT && K == 4 && W == 3) asm volatile("" : "+s"(N), "+s"(L));
+    constexpr bool kOpaque = sizeof(T) == 4 && DIRECT && K == 4 && W == 3;
+    if constexpr (kOpaque) asm volatile("" : "+s"(N));
     const int NH = N / NS;                                  // states per row (N is a multiple of 4: whole half-groups)
     const int n_first = half * NH;                          // first state of this lane's row
     const int Nreal = a.N;
+    int64_t L = a.L;
+    if constexpr (kOpaque) asm volatile("" : "+s"(L));
     int64_t len = L;
     if (a.seqlens) {
         const int64_t s = a.seqlens[b];
